@@ -7,7 +7,7 @@ namespace {
 
 // See the gate+up table for the template parameters; skinny_kernel<JB, gateup, STAGES, SPLITK, packed>.
 const Variant kDown[] = {
-    /*0*/ {256, false, launch_tile<1, false, 3, 1, false, false>, "tile_kernel<1, false, 3, 1, false, false>"},
+    /*0*/ {256, false, launch_rows<1, false, true>, "tile_kernel<1, false>"},
     /*1*/ {32, false, launch_skinny<1, false, 4, 4, false>, "skinny_kernel<1, false, 4, 4, false>"},
     /*2*/ {64, false, launch_skinny<2, false, 4, 4, false>, "skinny_kernel<2, false, 4, 4, false>"},
     /*3*/ {32, true, launch_skinny<1, false, 4, 4, true>, "skinny_kernel<1, false, 4, 4, true>"},
@@ -16,6 +16,8 @@ const Variant kDown[] = {
     /*6*/ {256, true, launch_down_mixed_wide_nt, "tile_kernel_mixed<2, false, true, true, false>"},
     /*7*/ {256, true, launch_down_mixed_wide, "tile_kernel_mixed<2, false, true, false, false>"},
     /*8*/ {128, true, launch_tile_mixed<1, false, true, true, true>, "tile_kernel_mixed<1, false, true, true, true>"},
+    /*9*/ {256, false, launch_down_rows_wide_chunk, "tile_kernel<2, false>"},
+    /*10*/ {256, false, launch_down_rows_wide, "tile_kernel<2, false>"},
 };
 constexpr int kNumDown = sizeof(kDown) / sizeof(kDown[0]);
 
@@ -32,12 +34,15 @@ int pick(int M, bool packed, const moe_config& c) {
     const bool wide = (long long)(c.d / 256) * (active + R / 256) >= 512;
     if (few_rows && M <= 32) return packed ? 3 : 1;
     if (few_rows && M <= 64) return packed ? 4 : 2;
-    if (!packed) return 0;   // row-major lines are consumed by four loads each: cached loads only
-    if (M <= 128 && two_workgroups_per_cu(c)) return 8;
-    // Per-block regime selection (tile_kernel_mixed).  Non-temporal weight loads for single-block
+    if (packed && M <= 128 && two_workgroups_per_cu(c)) return 8;
+    // Per-block regime selection (tile_kernel_mixed, tile_kernel).  Non-temporal weight loads for single-block
     // experts while the token buffers are small; with many rows per expert on average, the
     // two-weight-block form with cached loads throughout.
     const bool once = (double)R / c.E <= 192.0 && (double)R * c.d * 2.0 <= 128e6;
+    // Row-major: the same line; 9 and 10 differ in the launch order only (10 keeps the row tiles of an
+    // expert side by side: Mixtral shape, 4096 tokens 940 against 1210 us; 9 runs a contiguous eighth
+    // of the work per XCD: 0 and 9 at 256 experts, 512 tokens 1330 against 1240 us).
+    if (!packed) return once ? (wide ? 9 : 0) : 10;
     if (once) return wide ? 6 : 5;
     return 7;
 }
@@ -48,7 +53,7 @@ bool down_fuses_combine(const moe_config& c, int32_t M, bool packed) {
     int id = forced_variant(kKnobDownVariant, kNumDown, M, packed, kDown);
     if (id < 0) id = pick(M, packed, c);
     // the per-block-regime kernels (LDS-DMA body) carry the fused epilogue; token * groups + group is an int
-    return id >= 5 && (long long)c.T * combine_groups(c) < (1ll << 31);
+    return kDown[id].packed && id >= 5 && (long long)c.T * combine_groups(c) < (1ll << 31);
 }
 
 const char* down_variant_name(const moe_config& c, int32_t M, bool packed) {
@@ -96,7 +101,7 @@ hipError_t launch_down(const moe_config& c, int32_t M, const uint16_t* h, int32_
         a.deal_always = knob(kKnobInterleave) > 0;
     }
     if (fuse != nullptr) {
-        if (id < 5) return hipErrorInvalidValue;   // only the per-block-regime kernels have the fused epilogue
+        if (id < 5 || !kDown[id].packed) return hipErrorInvalidValue;   // only the per-block-regime kernels have the fused epilogue
         a.comb_src = fuse->src_of;
         a.comb_row_of = fuse->row_of;
         a.comb_w = fuse->topk_w;

@@ -21,13 +21,13 @@
 // wavefront streams one contiguous region.  Both layouts are supported by every kernel.
 //
 // Kernels that share that mapping:
-//   tile_kernel        token tile (up to 256 rows) staged in LDS through registers and shared by
-//                      the four wavefronts; body chosen per block from the rows it holds.
-//   tile_kernel_mixed  the same tile brought global -> LDS by DMA into a ring of buffers, with
-//                      the regime chosen per block: weights streamed
+//   tile_kernel_mixed  token tile (up to 256 rows) brought global -> LDS by DMA into a ring of
+//                      buffers and shared by the four wavefronts; body chosen per block from
+//                      the rows it holds, regime per block from its expert's rows: weights streamed
 //                      once (non-temporal, k rotated) for experts that fit one block, shared
 //                      through L2 (cached, k in step, row tiles side by side) for experts that
-//                      span several (the default for packed weights).
+//                      span several (packed weights).
+//   tile_kernel        the same for row-major weights, which go through LDS too (rows_body).
 //   skinny_kernel      <= 64 token rows, token fragments loaded straight from L2 by each
 //                      wavefront: no LDS, no barrier in the reduction loop; the four wavefronts
 //                      split K (down projection of few-expert models at a handful of tokens,
@@ -47,7 +47,7 @@ struct GemmArgs {
     int src_k;                  // slots per token: row r then lives at X[src[r] / src_k]
     int x_rows;                 // rows of X (T with a source map, else R); x_rows * ldx * 2 bytes < 4 GiB
     int ldx, ldo;               // row strides of X and Out in elements (>= K and >= N)
-    int rot_mul;                // k-loop rotation between workgroups of one XCD, in steps (see tile_body)
+    int rot_mul;                // k-loop rotation between workgroups of one XCD, in steps (see tile_body_dma)
     int rot_mul_multi;          // the same for blocks of experts that span several row tiles (tile_kernel_mixed)
     int slots;                  // workgroups the chip runs at once (one per CU); 0 = do not split the last round
     const uint16_t* W0;         // [E, N, K]  gate (or down)
@@ -82,12 +82,13 @@ typedef hipError_t (*launch_fn)(const GemmArgs&, int, hipStream_t);
 // compiled in a translation unit of their own (ffn_down_wide.hip) to shorten the build.
 hipError_t launch_down_mixed_wide_nt(const GemmArgs& a, int max_blocks, hipStream_t s);
 hipError_t launch_down_mixed_wide(const GemmArgs& a, int max_blocks, hipStream_t s);
+hipError_t launch_down_rows_wide(const GemmArgs& a, int max_blocks, hipStream_t s);
+hipError_t launch_down_rows_wide_chunk(const GemmArgs& a, int max_blocks, hipStream_t s);
 
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kBK = 64;            // reduction elements per pipeline step
-constexpr int kLdsStride = 72;     // bf16 elements per staged token row: 64 + 8 pad (144 B)
 
 
 template <int... Is, class F>
@@ -125,21 +126,11 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
     return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
 
-// Buffer addressing (buffer_load_dwordx4 ... offen): address = descriptor base (scalar) + scalar
-// offset + per-lane 32-bit offset + immediate.  The per-step advance along k is the scalar offset
-// and the per-lane offset never changes, so the loads of the reduction loop need no vector
-// address arithmetic and no 64-bit address registers.  Offsets beyond the descriptor's range
-// read as zero instead of faulting.
+// Buffer descriptor: base and range in bytes.  Offsets beyond the range read as zero and are not written.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 __device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);   // raw, 32-bit data format
 }
-template <bool NT>
-__device__ __forceinline__ uint4 buffer_load16(rsrc_t r, uint32_t lane_off, uint32_t scalar_off) {
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, scalar_off, NT ? 2 : 0);
-    return make_uint4(v[0], v[1], v[2], v[3]);
-}
-
 // Weight fragment addressing.  Unpacked: row-major rows, element (row, k).  Packed: 16-byte
 // units ordered [expert][row block][k step][matrix][s][lane].
 template <bool PACKED, int NM>
@@ -160,15 +151,6 @@ struct WAddr {
             return a.P + ((size_t)e * (a.N / 32) + rb) * (size_t)(a.K / kBK) * kStep + m * 4 * 512;
         else
             return (m == 0 ? a.W0 : a.W1) + ((size_t)e * a.N + rb * 32) * a.K;
-    }
-    // bytes from block() to the end of the rows / packed region it belongs to (buffer range)
-    __device__ static __forceinline__ uint32_t block_bytes(const GemmArgs& a, int row_block, int m) {
-        if constexpr (PACKED) {
-            return (uint32_t)(a.K / kBK) * kStep * 2u - (uint32_t)m * 4096u;
-        } else {
-            const int rows = a.N - clamp_block(a, row_block) * 32;
-            return (uint32_t)(rows < 32 ? rows : 32) * (uint32_t)a.K * 2u;
-        }
     }
     __device__ static __forceinline__ uint32_t lane_bytes(const GemmArgs& a, int row_block, int lane) {
         if constexpr (PACKED) {
@@ -273,167 +255,6 @@ __device__ __forceinline__ void store_block(const f32x16& g, const f32x16& u, ui
             }
         }
     }
-}
-
-// =============================================================================================
-// tile_body: up to 256 token rows (JBE blocks of 32) staged in LDS through registers and shared
-// by the four wavefronts; each wavefront owns IB 32-row weight blocks per matrix and ALL token
-// rows of the tile.
-// =============================================================================================
-template <int JBE, int IB, bool GATEUP, int STAGES, int XD, bool PACKED, bool WNT>
-__device__ __forceinline__ void tile_body(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
-    constexpr int NM = GATEUP ? 2 : 1;
-    constexpr int NI = IB * NM;
-    constexpr int BM = 256;                     // rows one LDS buffer is laid out for
-    constexpr int BN = 4 * IB * 32;
-    constexpr int JW = JBE;                     // 32-row token blocks per wavefront
-    constexpr int XROWS = kThreads / 8;         // token rows staged per pass (8 threads x 16 B per row)
-    constexpr int XP = (JBE * 32) / XROWS;      // passes per step
-    const int tid = threadIdx.x, lane = tid % kWave;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);   // wave-uniform: scalar register
-    const int li = lane & 31, half = lane >> 5;
-    const int K = a.K, N = a.N;
-    const int KT = K / kBK;
-    const int n0w = nt * BN + wave * (IB * 32);
-
-    // Weight fragments: scalar block base per (matrix, row block) + one per-lane byte offset.
-    // Out-of-range rows of a ragged last feature tile are clamped, their stores masked.
-    typedef WAddr<PACKED, NM> WA;
-    rsrc_t wb[NI];
-    uint32_t wl[PACKED ? 1 : IB];
-    static_for<NM>([&](auto m) {
-        static_for<IB>([&](auto ib) {
-            wb[m * IB + ib] = make_rsrc(WA::block(a, t.e, n0w / 32 + ib, m), WA::block_bytes(a, n0w / 32 + ib, m));
-        });
-    });
-    static_for<(PACKED ? 1 : IB)>([&](auto ib) { wl[ib] = WA::lane_bytes(a, n0w / 32 + ib, lane); });
-    auto w_load = [&](auto i, int kc, auto s) {
-        return buffer_load16<WNT>(wb[i], wl[PACKED ? 0 : i % IB] + s * (WA::sStep * 2), (uint32_t)kc * (WA::kStep * 2));
-    };
-    const rsrc_t xb = make_rsrc(a.X, (uint32_t)a.x_rows * (uint32_t)a.ldx * 2u);
-    // token tile: thread -> (row tid/8 + XROWS*p, 16-byte chunk tid%8); rows clamped inside X.
-    // Scalar base a.X + k offset, per-thread 32-bit byte offsets fixed for the whole loop.
-    uint32_t xo[XP];
-    static_for<XP>([&](auto p) {
-        xo[p] = token_row_bytes(a, t.row0 + (tid >> 3) + XROWS * p) + (uint32_t)(tid & 7) * 16u;
-    });
-    const int xs_store = (tid >> 3) * kLdsStride + (tid & 7) * 8;
-    const int xs_read = li * kLdsStride + half * 8;
-
-    f32x16 acc[NI][JW];
-    static_for<NI>([&](auto i) {
-        static_for<JW>([&](auto j) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-        });
-    });
-
-    uint4 wreg[STAGES][NI][4];
-    typedef uint32_t xreg_t __attribute__((ext_vector_type(4 * XP)));
-    xreg_t xreg[XD];   // each set is one SSA vector value (a plain array is not reliably kept in registers)
-
-    // The K loop is rotated per workgroup: logical step i reads physical step (i + rot) mod KT.
-    // All rows of a token tile at one k step are a whole multiple of 4 KiB apart when the row
-    // length is (d = 4096, F = 14336, ...), so they sit in the same L2 channel; workgroups that
-    // run together on an XCD (ids 8 apart) start two steps apart and so spread over the channels
-    // instead of all hammering the same one.  The sum over k does not care about the order.
-    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)a.rot_mul) % (unsigned)KT);
-    auto phys = [&](int i) {
-        int p = (i < KT ? i : KT - 1) + rot;
-        return p >= KT ? p - KT : p;
-    };
-
-    // Software pipeline.  In step kt the wavefront issues the token-tile loads of step kt+XD and
-    // the weight loads of step kt+STAGES-1, runs the MFMAs of step kt from LDS buffer kt%2 and
-    // its weight registers, then writes the token tile of step kt+1 (loaded XD-1 steps ago) into
-    // the other LDS buffer.  Loads complete in issue order, so that last wait leaves everything
-    // issued later in flight.  All loads are unconditional (the step index is clamped to the
-    // last step, which is re-read harmlessly): straight-line code.
-    auto load_w = [&](int kt, auto st) {
-        const int kc = phys(kt);
-        static_for<NI>([&](auto i) {
-            static_for<4>([&](auto s) {
-                wreg[st][i][s] = w_load(i, kc, s);
-            });
-        });
-    };
-    auto load_x = [&](int kt, auto xs_) {
-        const uint32_t kb = (uint32_t)phys(kt) * (kBK * 2);
-        static_for<XP>([&](auto p) {
-            const uint4 v = buffer_load16<false>(xb, xo[p], kb);
-            xreg[xs_][4 * p + 0] = v.x;
-            xreg[xs_][4 * p + 1] = v.y;
-            xreg[xs_][4 * p + 2] = v.z;
-            xreg[xs_][4 * p + 3] = v.w;
-        });
-    };
-    auto store_x = [&](int buf, auto xs_) {
-        static_for<XP>([&](auto p) {
-            *reinterpret_cast<uint4*>(&xs[buf * BM * kLdsStride + xs_store + p * XROWS * kLdsStride]) =
-                make_uint4(xreg[xs_][4 * p + 0], xreg[xs_][4 * p + 1], xreg[xs_][4 * p + 2], xreg[xs_][4 * p + 3]);
-        });
-    };
-    // One step.  Whatever a wavefront does between MFMAs leaves the matrix pipe idle unless it
-    // is issued while an MFMA is still executing (or another wavefront of the SIMD has MFMAs
-    // ready).  The weight loads of the prefetched step and the LDS fragment reads of the next
-    // slot are therefore spread between the MFMA groups (one group = one weight fragment against
-    // all token blocks); sched_barrier pins that order, which the compiler's scheduler would undo.
-    // `u` = kt modulo the unroll factor UNR (a multiple of both STAGES and XD), compile-time.
-    auto step = [&](int kt, auto u) {
-        const int buf = kt & 1;
-        constexpr int wst = (u + STAGES - 1) % STAGES;
-        const int kw = phys(kt + STAGES - 1);
-        load_x(kt + XD, std::integral_constant<int, (u + XD) % XD>{});           // set (kt+XD)%XD == kt%XD
-        bf16x8 xf[2][JW];
-        static_for<JW>([&](auto j) {
-            xf[0][j] = *reinterpret_cast<const bf16x8*>(&xs[buf * BM * kLdsStride + xs_read + j * 32 * kLdsStride]);
-        });
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<4>([&](auto s) {
-            static_for<NI>([&](auto i) {
-                const bf16x8 wf = __builtin_bit_cast(bf16x8, wreg[u % STAGES][i][s]);
-                static_for<JW>([&](auto j) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, xf[s & 1][j], acc[i][j], 0, 0, 0);
-                    constexpr int p = i * JW + j;   // position in the slot: one memory instruction behind each MFMA
-                    if constexpr (j == 0) wreg[wst][i][s] = w_load(i, kw, s);
-                    if constexpr (s < 3 && p % NI == NI - 1) {
-                        constexpr int jj = p / NI;
-                        xf[(s + 1) & 1][jj] = *reinterpret_cast<const bf16x8*>(
-                            &xs[buf * BM * kLdsStride + xs_read + jj * 32 * kLdsStride + (s + 1) * 16]);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                });
-            });
-        });
-        store_x(buf ^ 1, std::integral_constant<int, (u + 1) % XD>{});            // token tile of step kt+1
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-    };
-    // NOTE on register sets: in step kt the set kt%XD is free (its tile, step kt, went to LDS at
-    // the end of step kt-1), so the loads of step kt+XD reuse it; with XD == 1 the single set is
-    // loaded at the top of the step and stored at its end.
-
-    static_for<STAGES - 1>([&](auto st) { load_w(st, st); });
-    load_x(0, std::integral_constant<int, 0>{});
-    store_x(0, std::integral_constant<int, 0>{});
-    static_for<XD - 1>([&](auto q) { load_x(q + 1, std::integral_constant<int, (q + 1) % XD>{}); });
-    __syncthreads();
-
-    constexpr int UNR = (STAGES % XD == 0) ? STAGES : STAGES * XD;
-    int kt = 0;
-    for (; kt + UNR <= KT; kt += UNR) static_for<UNR>([&](auto u) { step(kt + u, u); });
-    static_for<UNR>([&](auto u) {
-        if (kt + u < KT) step(kt + u, u);
-    });
-
-    static_for<IB>([&](auto ib) {
-        static_for<JW>([&](auto j) {
-            const int tr = j * 32 + li;
-            const bool live = tr < t.rows;
-            store_block<GATEUP>(acc[ib][j], acc[GATEUP ? IB + ib : ib][j],
-                                a.Out + (size_t)(t.row0 + (live ? tr : 0)) * a.ldo, n0w + ib * 32, half, N, live);
-        });
-    });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -601,7 +422,12 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
     });
     uint4 wreg[STAGES][NI][4];
 
-    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)a.rot_mul) % (unsigned)KT);   // see tile_body
+    // The k loop is rotated per workgroup: logical step i reads physical step (i + rot) mod KT.  All
+    // rows of a token tile at one k step are a whole multiple of 4 KiB apart when the row length is
+    // (d = 4096, F = 14336, ...), so they sit in the same L2 channel; workgroups that run together on
+    // an XCD (ids 8 apart) start two steps apart and so spread over the channels.  The sum over k
+    // does not care about the order.  Steps past the last are re-reads of it (harmless).
+    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)a.rot_mul) % (unsigned)KT);
     auto phys = [&](int i) {
         int p = (i < KT ? i : KT - 1) + rot;
         return p >= KT ? p - KT : p;
@@ -719,36 +545,198 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
     });
 }
 
-// DYN (256-row tiles only): the body is chosen per tile from the rows it really holds, so one
-// launch serves experts of any size: a 20-row expert runs the 32-row body, a 1000-row expert
-// four 256-row tiles.  This is the "dynamic block-to-expert assignment" the paper leaves as
-// future work (its Sec. 4.7 and limitation 5): Algorithm 1 runs with M = 256 and the tile
-// height inside a block follows n_e.  Empty token blocks cost neither loads, LDS traffic nor
-// MFMA issue slots.  Pipeline depths per body are what the register file allows.
-// Body of the 256-row dynamic-height kernel for a block of t.rows rows (four wavefronts).
-template <int IB, bool GATEUP, int STAGES, int XD, bool PACKED, bool WNT>
-__device__ __forceinline__ void tile_dispatch(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
-    constexpr int NI = IB * (GATEUP ? 2 : 1);
-    constexpr int SD = NI >= 4 ? 3 : 4;          // stages for the small bodies
-    constexpr int S56 = NI >= 4 ? 2 : SD;
-    switch ((t.rows + 31) / 32) {
-        case 1: return tile_body<1, IB, GATEUP, SD, 2, PACKED, WNT>(a, t, nt, xs);
-        case 2: return tile_body<2, IB, GATEUP, SD, 2, PACKED, WNT>(a, t, nt, xs);
-        case 3: return tile_body<3, IB, GATEUP, SD, 2, PACKED, WNT>(a, t, nt, xs);
-        case 4: return tile_body<4, IB, GATEUP, SD, 2, PACKED, WNT>(a, t, nt, xs);
-        case 5: return tile_body<5, IB, GATEUP, S56, 2, PACKED, WNT>(a, t, nt, xs);
-        case 6: return tile_body<6, IB, GATEUP, S56, 2, PACKED, WNT>(a, t, nt, xs);
-        default: return tile_body<8, IB, GATEUP, STAGES, XD, PACKED, WNT>(a, t, nt, xs);
+// =============================================================================================
+// rows_body: ROW-MAJOR weights.  The token tile comes by LDS-DMA as in tile_body_dma, and so do the
+// weights: a fragment read of row-major weights straight into registers touches 32 rows, 16 bytes
+// each, i.e. 64 L1 accesses per instruction, which is what bounds that form (5.0 TB/s at the Mixtral
+// shape, 512 tokens).  A DMA instruction takes 8 rows x 128 bytes instead, whole lines, and the wavefront
+// reads its fragments back from LDS (its own rows only: no other wavefront waits for them).
+// Ring of NB buffers, each one k step: JBE * 4 KiB of tokens and, per wavefront, NI * 4 KiB of
+// weights; the loads of step kt + NB - 1 are issued in step kt and awaited at the end of step
+// kt + NB - 2.  Three buffers where 160 KiB hold them, else two (taller than 160 rows with gate and
+// up, where a step's MFMAs are long enough to cover one step of latency).  LDS traffic per step at
+// 256 rows: 224 KiB = 1792 of the step's 2048 MFMA cycles.
+// Before (weights straight to registers, row-major) and now, us, gate+up / down projection: Mixtral shape 47
+// tokens 401 / 230 -> 307 / 151, 512 tokens 470 / 270 -> 343 / 212 (5.5 TB/s of weights), 4096 tokens
+// 1955 / 1305 -> 1690 / 940; 256 experts of DeepSeek-V3's widths, 512 tokens 3390 / 1790 -> 2188 / 1233 (6.9 TB/s):
+// as fast as the packed layout up to ~160 rows per expert, 6-10 % behind it beyond.
+// =============================================================================================
+constexpr int kLdsBytes = 160 * 1024;
+constexpr int rows_buffer_bytes(int jbe, int ni) { return jbe * 4096 + ni * 16384; }
+constexpr int rows_buffers(int jbe, int ni) {
+    const int n = kLdsBytes / rows_buffer_bytes(jbe, ni);
+    return n > 3 ? 3 : n;   // a fourth measured no gain (row-major, 47 tokens 307 -> 309 us; 256 experts, 512 tokens 2188 -> 2200)
+}
+// LDS that tiles of up to 256 rows need
+constexpr int rows_lds(int ni) {
+    int most = 0;
+    for (int j = 1; j <= 8; ++j) {
+        const int b = rows_buffer_bytes(j, ni) * rows_buffers(j, ni);
+        most = b > most ? b : most;
     }
+    return most;
+}
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// As lds_dma16, from a wave-uniform base plus a 32-bit lane offset; NT: non-temporal.
+template <bool NT>
+__device__ __forceinline__ void lds_dma16_at(const void* base, uint32_t lane_off, uint32_t lds_addr) {
+    const uint64_t b = (uint64_t)(uintptr_t)base;
+    const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr);
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(lane_off), "s"(u), "s"(dst)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(u), "s"(dst)
+                     : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+template <int JBE, int IB, bool GATEUP, bool WNT>
+__device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
+    constexpr int NM = GATEUP ? 2 : 1;
+    constexpr int NI = IB * NM;
+    constexpr int BN = 4 * IB * 32;
+    constexpr int NB = rows_buffers(JBE, NI);
+    constexpr int XD = NB - 1;                          // steps the loads run ahead
+    constexpr int X_BYTES = JBE * 4096;                 // token tile of a step
+    constexpr int BUF = X_BYTES + 4 * NI * 4096;
+    constexpr int LPS = JBE + 4 * NI;                   // loads per wavefront and step
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int li = lane & 31, half = lane >> 5;
+    const int K = a.K, N = a.N;
+    const int KT = K / kBK;
+    const int n0w = nt * BN + wave * (IB * 32);
+
+    // Weights: DMA g of a 32-row block covers rows 8 g .. 8 g + 7: lane -> row 8 g + lane / 8, position
+    // lane % 8 of the LDS row, source chunk position ^ swizzle(row) (the swizzle of the token rows).
+    typedef WAddr<false, NM> WA;
+    const uint16_t* wp[NI];                             // wave-uniform
+    static_for<NM>([&](auto m) {
+        static_for<IB>([&](auto ib) { wp[m * IB + ib] = WA::block(a, t.e, n0w / 32 + ib, m); });
+    });
+    uint32_t wo[4];
+    static_for<4>([&](auto g) {
+        const int chunk = (lane & 7) ^ (((lane >> 3) ^ g) & 7);
+        wo[g] = (uint32_t)(g * 8 + (lane >> 3)) * (uint32_t)K * 2u + (uint32_t)chunk * 16u;
+    });
+    // Tokens: DMA q covers the rows rg * 8 .., rg = 4 q + wave, as in tile_body_dma.
+    uint32_t xo[JBE];
+    static_for<JBE>([&](auto q) {
+        const int rg = q * 4 + wave;
+        const int chunk = (lane & 7) ^ (((lane >> 3) ^ rg) & 7);
+        xo[q] = token_row_bytes(a, t.row0 + rg * 8 + (lane >> 3)) + (uint32_t)chunk * 16u;
+    });
+    const uint32_t lds0 = (uint32_t)(uintptr_t)xs;
+    const uint32_t x_dst = lds0 + wave * 1024;                       // + q * 4096 + buffer * BUF
+    const uint32_t w_dst = lds0 + X_BYTES + wave * (NI * 4096);      // + i * 4096 + g * 1024 + buffer * BUF
+    const int sw0 = (li ^ (li >> 3)) & 7;
+    int rd_off[2][4];   // [j parity][slot] byte offset inside a row; weight rows use parity 0
+    static_for<2>([&](auto pj) {
+        static_for<4>([&](auto s) { rd_off[pj][s] = (((2 * s + half) ^ (sw0 ^ (pj * 4))) & 7) * 16; });
+    });
+    const char* xs_b = reinterpret_cast<const char*>(xs) + li * 128;
+    const char* ws_b = xs_b + X_BYTES + wave * (NI * 4096);
+
+    f32x16 acc[NI][JBE];
+    static_for<NI>([&](auto i) {
+        static_for<JBE>([&](auto j) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+        });
+    });
+    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)a.rot_mul) % (unsigned)KT);   // see tile_body_dma
+    auto phys = [&](int i) {
+        int p = (i < KT ? i : KT - 1) + rot;
+        return p >= KT ? p - KT : p;
+    };
+    // load l of a step: the weight rows first (they come from farthest away), then the token rows
+    auto load = [&](auto l, int kc, uint32_t buf) {
+        const uint32_t kb = (uint32_t)kc * (kBK * 2);
+        if constexpr (l < 4 * NI) {
+            constexpr int i = l / 4, g = l % 4;
+            lds_dma16_at<WNT>(reinterpret_cast<const char*>(wp[i]) + kb, wo[g], w_dst + buf + i * 4096 + g * 1024);
+        } else {
+            constexpr int q = l - 4 * NI;
+            lds_dma16_at<false>(reinterpret_cast<const char*>(a.X) + kb, xo[q], x_dst + buf + q * 4096);
+        }
+    };
+    auto xfrag = [&](int buf, auto j, auto s) {
+        return *reinterpret_cast<const bf16x8*>(xs_b + buf + j * 4096 + rd_off[j & 1][s]);
+    };
+    auto wfrag = [&](int buf, auto i, auto s) {
+        return *reinterpret_cast<const bf16x8*>(ws_b + buf + i * 4096 + rd_off[0][s]);
+    };
+    // The step's loads are dealt singly between its MFMAs (one wavefront per SIMD: a run of memory
+    // instructions would idle the matrix pipe): over the whole step when they have a step to spare,
+    // over its first half when they are awaited at its end.
+    constexpr int MF = 4 * NI * JBE;
+    constexpr int SPREAD = XD > 1 ? MF : (MF + 1) / 2;
+    auto step = [&](int kt) {
+        const int buf = (kt % NB) * BUF;
+        const uint32_t nbuf = (uint32_t)((kt + XD) % NB) * BUF;    // read in step kt - 1: free since that step's barrier
+        const int kc = phys(kt + XD);
+        bf16x8 xf[2][JBE], wf[2][NI];
+        static_for<NI>([&](auto i) { wf[0][i] = wfrag(buf, i, std::integral_constant<int, 0>{}); });
+        static_for<JBE>([&](auto j) { xf[0][j] = xfrag(buf, j, std::integral_constant<int, 0>{}); });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<4>([&](auto s) {
+            static_for<NI>([&](auto i) {
+                static_for<JBE>([&](auto j) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s & 1][i], xf[s & 1][j], acc[i][j], 0, 0, 0);
+                    constexpr int p = i * JBE + j, at = s * NI * JBE + p;
+                    static_for<LPS>([&](auto l) {
+                        if constexpr (l * SPREAD / LPS == at) load(l, kc, nbuf);
+                    });
+                    if constexpr (s < 3) {     // next slot's fragments: the weights behind the first MFMA, the tokens spread
+                        if constexpr (p == 0)
+                            static_for<NI>([&](auto n) { wf[(s + 1) & 1][n] = wfrag(buf, n, std::integral_constant<int, (s + 1) % 4>{}); });
+                        if constexpr (p % NI == NI - 1) {
+                            constexpr int jj = p / NI;
+                            xf[(s + 1) & 1][jj] = xfrag(buf, std::integral_constant<int, jj>{}, std::integral_constant<int, (s + 1) % 4>{});
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            });
+        });
+        wait_vmcnt<(XD - 1) * LPS>();      // everything of step kt + 1 has landed (loads return in issue order)
+        __syncthreads();
+    };
+    static_for<XD>([&](auto q) {
+        const int kc = phys(q);
+        static_for<LPS>([&](auto l) { load(l, kc, (uint32_t)(q % NB) * BUF); });
+    });
+    wait_vmcnt<(XD - 1) * LPS>();
+    __syncthreads();
+    for (int kt = 0; kt < KT; ++kt) step(kt);
+    wait_vmcnt<0>();   // nothing of this workgroup may still be writing LDS when it retires
+
+    static_for<IB>([&](auto ib) {
+        static_for<JBE>([&](auto j) {
+            const int tr = j * 32 + li;
+            const bool live = tr < t.rows;
+            store_block<GATEUP>(acc[ib][j], acc[GATEUP ? IB + ib : ib][j],
+                                a.Out + (size_t)(t.row0 + (live ? tr : 0)) * a.ldo, n0w + ib * 32, half, N, live);
+        });
+    });
 }
 
-template <int IB, bool GATEUP, int STAGES, int XD, bool PACKED, bool WNT>
-__global__ __launch_bounds__(kThreads) void tile_kernel(const GemmArgs a) {
-    extern __shared__ __attribute__((aligned(16))) uint16_t xs[];
-    Tile t;
-    int tile, nt;
-    if (!map_workgroup(a, tile, nt) || !load_tile(a, tile, 256, t)) return;
-    tile_dispatch<IB, GATEUP, STAGES, XD, PACKED, WNT>(a, t, nt, xs);
+template <int IB, bool GATEUP, bool WNT>
+__device__ __forceinline__ void rows_dispatch(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
+    switch ((t.rows + 31) / 32) {
+        case 1: return rows_body<1, IB, GATEUP, WNT>(a, t, nt, xs);
+        case 2: return rows_body<2, IB, GATEUP, WNT>(a, t, nt, xs);
+        case 3: return rows_body<3, IB, GATEUP, WNT>(a, t, nt, xs);
+        case 4: return rows_body<4, IB, GATEUP, WNT>(a, t, nt, xs);
+        case 5: return rows_body<5, IB, GATEUP, WNT>(a, t, nt, xs);
+        case 6: return rows_body<6, IB, GATEUP, WNT>(a, t, nt, xs);
+        case 7: return rows_body<7, IB, GATEUP, WNT>(a, t, nt, xs);
+        default: return rows_body<8, IB, GATEUP, WNT>(a, t, nt, xs);
+    }
 }
 
 // The dynamic-height kernel with the LDS-DMA token tile.  LDS: (XD+1) buffers of up to 32 KiB.
@@ -781,11 +769,7 @@ __device__ __forceinline__ void dma_dispatch(const GemmArgs& a, const Tile& t, i
 // run the LDS-DMA body.  An expert that fits one block streams its weights once: non-temporal
 // weight loads if WNT, k loop rotated against its XCD neighbours.  An expert that spans several
 // row tiles shares its weight panels through L2: cached weight loads, k walked in step, its row
-// tiles launched side by side.  (Packed weights.  The register-staged body of tile_kernel was the
-// single-block choice until the memory instructions of the DMA body were dealt singly between
-// its MFMAs; since then the DMA body wins there too: no staging registers, no ds_write, half the
-// instructions per token-tile byte.  Mixtral shape: T=512 layer -3 %, T=1024 -5 %, T <= 256 and
-// the 64- and 256-expert shapes unchanged.)
+// tiles launched side by side.
 //
 // Last round (IB = 2 only).  The grid runs in rounds of `slots` workgroups, one per CU.  With
 // two weight blocks per wavefront a projection has few, heavy workgroups (Mixtral shape, down
@@ -1001,6 +985,27 @@ __global__ __launch_bounds__(kThreads, HALF ? 2 : 1) void tile_kernel_mixed(cons
     dma_dispatch<IB, GATEUP, PACKED, WNT, HALF>(b, t, nt, xs);
 }
 
+// Row-major weights: the same launch orders and regimes, rows_body.
+template <int IB, bool GATEUP>
+__global__ __launch_bounds__(kThreads) void tile_kernel(const GemmArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) uint16_t xs[];
+    MixedWork m;
+    if (!mixed_assign<IB, GATEUP>(a, (int)blockIdx.x, m)) return;
+    Tile t;
+    t.e = m.e;
+    t.row0 = m.row0;
+    t.rows = m.rows;
+    t.n_e = m.n_e;
+    GemmArgs b = a;
+    const bool multi = t.n_e > a.M && t.rows > a.short_nt;
+    if (multi) b.rot_mul = a.rot_mul_multi;
+    if constexpr (IB == 2 && !GATEUP) {
+        if (m.halves) return rows_dispatch<1, GATEUP, false>(b, t, m.nt, xs);
+    }
+    if (multi || a.no_nt) return rows_dispatch<IB, GATEUP, false>(b, t, m.nt, xs);
+    rows_dispatch<IB, GATEUP, true>(b, t, m.nt, xs);
+}
+
 // =============================================================================================
 // skinny_kernel: JB*32 <= 64 token rows, fragments straight from global memory, no LDS in the
 // reduction loop.  SPLITK == 1: the four wavefronts own four different 32-row weight blocks.
@@ -1127,23 +1132,6 @@ inline int rot_steps(bool dma) {
 }
 
 
-template <int IB, bool GATEUP, int STAGES, int XD, bool PACKED, bool WNT>
-hipError_t launch_tile(const GemmArgs& a, int max_blocks, hipStream_t s) {
-    constexpr int BN = 4 * IB * 32;
-    constexpr int lds = 2 * 256 * kLdsStride * (int)sizeof(uint16_t);   // two buffers of 256 padded rows: 72 KiB
-    auto kern = tile_kernel<IB, GATEUP, STAGES, XD, PACKED, WNT>;
-    // dynamic LDS above 64 KB needs an explicit opt-in; once per process and kernel (not allowed
-    // while a stream is being captured into a graph)
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (attr != hipSuccess) return attr;
-    GemmArgs args = a;
-    args.n_tiles_n = (a.N + BN - 1) / BN;
-    const long long grid = (long long)max_blocks * args.n_tiles_n;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds, s, args);
-    return hipGetLastError();
-}
-
 // Launch order switches, feature-tile count and grid of a tile_kernel_mixed launch (host arithmetic
 // only; `cus` = CUs of the device).  Returns the grid size.
 template <int IB, bool GATEUP, bool WNT>
@@ -1167,6 +1155,16 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     return grid;
 }
 
+inline int device_cus() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return 0;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        return n;
+    }();
+    return cus;
+}
+
 template <int IB, bool GATEUP, bool PACKED, bool WNT, bool HALF = false>
 hipError_t launch_tile_mixed(const GemmArgs& a, int max_blocks, hipStream_t s) {
     constexpr int lds = 4 * (HALF ? 4 : 8) * 32 * 128;   // the DMA ring: XD+1 = 4 buffers of 256 (128) rows x 128 bytes
@@ -1175,14 +1173,23 @@ hipError_t launch_tile_mixed(const GemmArgs& a, int max_blocks, hipStream_t s) {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        return n;
-    }();
     GemmArgs args = a;
-    const long long grid = mixed_launch_shape<IB, GATEUP, WNT>(args, max_blocks, cus);
+    const long long grid = mixed_launch_shape<IB, GATEUP, WNT>(args, max_blocks, device_cus());
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds, s, args);
+    return hipGetLastError();
+}
+
+template <int IB, bool GATEUP, bool CHUNK>
+hipError_t launch_rows(const GemmArgs& a, int max_blocks, hipStream_t s) {
+    constexpr int NI = IB * (GATEUP ? 2 : 1);
+    constexpr int lds = rows_lds(NI);
+    auto kern = tile_kernel<IB, GATEUP>;
+    // once per process and kernel: not allowed while a stream is being captured into a graph
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (attr != hipSuccess) return attr;
+    GemmArgs args = a;
+    const long long grid = mixed_launch_shape<IB, GATEUP, CHUNK>(args, max_blocks, device_cus());
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds, s, args);
     return hipGetLastError();
 }

@@ -1,0 +1,87 @@
+"""GEMM bodies that stage the weights in LDS (every tile of row-major weights; the single-block tiles
+of packed ones): all rows of h and y_perm at the sizes where the body can go wrong - one to eight
+32-row blocks and one row past each, two and three ring buffers, one to five k steps, output
+widths that leave the last feature tile partly empty - through moe_grouped_ffn, with every
+down-projection kernel that holds the body.
+
+Error bounds, per element (u = 2^-24, K the reduction length): an fp32 sum of exact products is off by at
+most K u sum|a||b|; SiLU's exp and reciprocal by a few 1e-7 relative; the result is rounded to bf16
+once, to eight significant bits: half a unit in the last place is at most 2^-8 of the value.  y_perm is compared with the product of the kernel's own h, so it carries one
+rounding only."""
+import os
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+sys.path.insert(0, os.path.dirname(__file__))
+
+pytestmark = pytest.mark.gpu
+
+COUNTS = {
+    "heights": [1, 32, 33, 64, 96, 128, 129, 160, 161, 192, 224, 225, 256],
+    "multi": [257, 0, 300, 31, 520, 160],          # experts of two and three tiles among small ones and an empty one
+    "one_row": [0, 1, 0],
+    "short_round": [200] * 3,                      # few workgroups: a down projection with a split last round
+}
+
+
+def _run(moe, cfg, x, offsets, w, packed, R):
+    dev = x.device
+    h = torch.full((R, cfg.F), float("nan"), dtype=torch.bfloat16, device=dev)
+    y = torch.full((R, cfg.d), float("nan"), dtype=torch.bfloat16, device=dev)
+    ws = torch.empty(moe.ffn_workspace_size(cfg), dtype=torch.uint8, device=dev)
+    if packed is None:
+        moe.moe_grouped_ffn(cfg, x, offsets, *w, h, y, ws)
+    else:
+        moe.moe_grouped_ffn(cfg, x, offsets, None, None, None, h, y, ws, W_packed=packed)
+    torch.cuda.synchronize()
+    return h, y
+
+
+@pytest.mark.parametrize("counts", list(COUNTS))
+@pytest.mark.parametrize("d,F", [(64, 128), (128, 64), (192, 320), (320, 192)])
+def test_all_rows(counts, d, F):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_23911_amd as moe
+    import paper_2605_23911_amd.binding as B
+    moe.lib()
+    dev = "cuda:0"
+    n = COUNTS[counts]
+    E, R = len(n), sum(n)
+    g = torch.Generator().manual_seed(17 * d + F + R)
+    rnd = lambda *s, std=1.0: (torch.randn(*s, generator=g) * std).to(torch.bfloat16).to(dev)
+    x = rnd(R, d)
+    w = rnd(E, F, d, std=d ** -0.5), rnd(E, F, d, std=d ** -0.5), rnd(E, d, F, std=F ** -0.5)
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(n)]), dtype=torch.int32, device=dev)
+    cfg = moe.MoEConfig.of(R, d, F, E, 1)
+    packed = torch.empty(moe.packed_weights_size(cfg), dtype=torch.uint8, device=dev)
+    moe.moe_pack_weights(cfg, *w, packed)
+    u = 2.0 ** -24
+    down = [(None, 0), (None, 9), (None, 10), (packed, 5), (packed, 6), (packed, 7)]
+    try:
+        for p, variant in down:
+            print(f"[weights in LDS] {counts} d={d} F={F} packed={p is not None} down variant {variant}", flush=True)
+            B.test_knob(B.KNOB_DOWN_VARIANT, variant)
+            h, y = _run(moe, cfg, x, offsets, w, p, R)
+            for e in range(E):
+                a, b = sum(n[:e]), sum(n[:e + 1])
+                if a == b:
+                    continue
+                xe, he = x[a:b].double(), h[a:b].double()
+                wg, wu, wd = (t[e].double() for t in w)
+                gate, up = xe @ wg.t(), xe @ wu.t()
+                dg, du = d * u * (xe.abs() @ wg.abs().t()), d * u * (xe.abs() @ wu.abs().t())
+                s = torch.nn.functional.silu(gate)
+                ref = s * up
+                bound = 2.0 ** -8 * ref.abs() + 1.1 * up.abs() * dg + s.abs() * du + 1e-6 * ref.abs() + 1e-30
+                worst = float(((he - ref).abs() / bound).max())
+                assert worst <= 1.0, ("h", e, variant, worst)
+                refy = he @ wd.t()
+                boundy = 2.0 ** -8 * refy.abs() + F * u * (he.abs() @ wd.abs().t()) + 1e-30
+                worst = float(((y[a:b].double() - refy).abs() / boundy).max())
+                assert worst <= 1.0, ("y_perm", e, variant, worst)
+    finally:
+        B.test_knob(B.KNOB_DOWN_VARIANT, -1)
