@@ -546,17 +546,23 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
 }
 
 // =============================================================================================
-// rows_body: ROW-MAJOR weights.  The token tile comes by LDS-DMA as in tile_body_dma, and so do the
-// weights: a fragment read of row-major weights straight into registers touches 32 rows, 16 bytes
-// each, i.e. 64 L1 accesses per instruction, which is what bounds that form (5.0 TB/s at the Mixtral
-// shape, 512 tokens).  A DMA instruction takes 8 rows x 128 bytes instead, whole lines, and the wavefront
+// rows_body: the weights go through LDS as well.  Every tile of row-major weights and the single-block
+// tiles of packed ones.
+// Row-major: a fragment read straight into registers touches 32 rows, 16 bytes each, i.e. 64 L1
+// accesses per instruction, which is what bounded that form (5.0 TB/s at the Mixtral shape, 512
+// tokens).  A DMA instruction takes 8 rows x 128 bytes instead, whole lines, and the wavefront
 // reads its fragments back from LDS (its own rows only: no other wavefront waits for them).
+// Packed: the load instructions are the same 1 KiB each, but no register is held by a load in flight
+// and no MFMA waits for one: weights and tokens are awaited together, once a step.  Bound by HBM; us,
+// tile_body_dma / rows_body: Mixtral shape 512 tokens gate+up 346 / 337, Qwen2-MoE shape 512 tokens 401 / 391
+// and down 244 / 229, 256 experts (DeepSeek-V3 widths) down 1340 / 1286 at 512 tokens (5.8 TB/s), 1632 / 1602
+// at 4096.
 // Ring of NB buffers, each one k step: JBE * 4 KiB of tokens and, per wavefront, NI * 4 KiB of
 // weights; the loads of step kt + NB - 1 are issued in step kt and awaited at the end of step
 // kt + NB - 2.  Three buffers where 160 KiB hold them, else two (taller than 160 rows with gate and
 // up, where a step's MFMAs are long enough to cover one step of latency).  LDS traffic per step at
 // 256 rows: 224 KiB = 1792 of the step's 2048 MFMA cycles.
-// Before (weights straight to registers, row-major) and now, us, gate+up / down projection: Mixtral shape 47
+// Row-major, weights straight to registers and now, us, gate+up / down projection: Mixtral shape 47
 // tokens 401 / 230 -> 307 / 151, 512 tokens 470 / 270 -> 343 / 212 (5.5 TB/s of weights), 4096 tokens
 // 1955 / 1305 -> 1690 / 940; 256 experts of DeepSeek-V3's widths, 512 tokens 3390 / 1790 -> 2188 / 1233 (6.9 TB/s):
 // as fast as the packed layout up to ~160 rows per expert, 6-10 % behind it beyond.
@@ -567,10 +573,14 @@ constexpr int rows_buffers(int jbe, int ni) {
     const int n = kLdsBytes / rows_buffer_bytes(jbe, ni);
     return n > 3 ? 3 : n;   // a fourth measured no gain (row-major, 47 tokens 307 -> 309 us; 256 experts, 512 tokens 2188 -> 2200)
 }
-// LDS that tiles of up to 256 rows need
-constexpr int rows_lds(int ni) {
+// Tallest single-block tile of packed weights (32-row blocks) that takes rows_body: three buffers fit.
+// With two (gate and up, or two weight blocks, beyond 160 rows) the register path of tile_body_dma is
+// the better one (us, rows_body / tile_body_dma: Mixtral shape 1024 tokens, down projection 391 / 316).
+constexpr int rows_max(int ni) { return ni >= 2 ? 5 : 8; }
+// LDS that tiles of up to max_jbe 32-row blocks need
+constexpr int rows_lds(int max_jbe, int ni) {
     int most = 0;
-    for (int j = 1; j <= 8; ++j) {
+    for (int j = 1; j <= max_jbe; ++j) {
         const int b = rows_buffer_bytes(j, ni) * rows_buffers(j, ni);
         most = b > most ? b : most;
     }
@@ -594,7 +604,7 @@ __device__ __forceinline__ void lds_dma16_at(const void* base, uint32_t lane_off
 }
 #pragma clang diagnostic pop
 
-template <int JBE, int IB, bool GATEUP, bool WNT>
+template <int JBE, int IB, bool GATEUP, bool PACKED, bool WNT>
 __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
     constexpr int NM = GATEUP ? 2 : 1;
     constexpr int NI = IB * NM;
@@ -611,9 +621,10 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
     const int KT = K / kBK;
     const int n0w = nt * BN + wave * (IB * 32);
 
-    // Weights: DMA g of a 32-row block covers rows 8 g .. 8 g + 7: lane -> row 8 g + lane / 8, position
+    // Packed weights: DMA g of a 32-row block is slot g of the step, 1 KiB in a row, in fragment order.
+    // Row-major weights: DMA g of a 32-row block covers rows 8 g .. 8 g + 7: lane -> row 8 g + lane / 8, position
     // lane % 8 of the LDS row, source chunk position ^ swizzle(row) (the swizzle of the token rows).
-    typedef WAddr<false, NM> WA;
+    typedef WAddr<PACKED, NM> WA;
     const uint16_t* wp[NI];                             // wave-uniform
     static_for<NM>([&](auto m) {
         static_for<IB>([&](auto ib) { wp[m * IB + ib] = WA::block(a, t.e, n0w / 32 + ib, m); });
@@ -621,7 +632,8 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
     uint32_t wo[4];
     static_for<4>([&](auto g) {
         const int chunk = (lane & 7) ^ (((lane >> 3) ^ g) & 7);
-        wo[g] = (uint32_t)(g * 8 + (lane >> 3)) * (uint32_t)K * 2u + (uint32_t)chunk * 16u;
+        wo[g] = PACKED ? (uint32_t)(g * 1024 + lane * 16)
+                       : (uint32_t)(g * 8 + (lane >> 3)) * (uint32_t)K * 2u + (uint32_t)chunk * 16u;
     });
     // Tokens: DMA q covers the rows rg * 8 .., rg = 4 q + wave, as in tile_body_dma.
     uint32_t xo[JBE];
@@ -639,7 +651,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
         static_for<4>([&](auto s) { rd_off[pj][s] = (((2 * s + half) ^ (sw0 ^ (pj * 4))) & 7) * 16; });
     });
     const char* xs_b = reinterpret_cast<const char*>(xs) + li * 128;
-    const char* ws_b = xs_b + X_BYTES + wave * (NI * 4096);
+    const char* ws_b = reinterpret_cast<const char*>(xs) + X_BYTES + wave * (NI * 4096) + (PACKED ? lane * 16 : li * 128);
 
     f32x16 acc[NI][JBE];
     static_for<NI>([&](auto i) {
@@ -658,7 +670,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
         const uint32_t kb = (uint32_t)kc * (kBK * 2);
         if constexpr (l < 4 * NI) {
             constexpr int i = l / 4, g = l % 4;
-            lds_dma16_at<WNT>(reinterpret_cast<const char*>(wp[i]) + kb, wo[g], w_dst + buf + i * 4096 + g * 1024);
+            lds_dma16_at<WNT>(reinterpret_cast<const char*>(wp[i]) + (PACKED ? (uint32_t)kc * (WA::kStep * 2) : kb), wo[g], w_dst + buf + i * 4096 + g * 1024);
         } else {
             constexpr int q = l - 4 * NI;
             lds_dma16_at<false>(reinterpret_cast<const char*>(a.X) + kb, xo[q], x_dst + buf + q * 4096);
@@ -668,7 +680,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
         return *reinterpret_cast<const bf16x8*>(xs_b + buf + j * 4096 + rd_off[j & 1][s]);
     };
     auto wfrag = [&](int buf, auto i, auto s) {
-        return *reinterpret_cast<const bf16x8*>(ws_b + buf + i * 4096 + rd_off[0][s]);
+        return *reinterpret_cast<const bf16x8*>(ws_b + buf + i * 4096 + (PACKED ? s * 1024 : rd_off[0][s]));
     };
     // The step's loads are dealt singly between its MFMAs (one wavefront per SIMD: a run of memory
     // instructions would idle the matrix pipe): over the whole step when they have a step to spare,
@@ -715,6 +727,19 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
     for (int kt = 0; kt < KT; ++kt) step(kt);
     wait_vmcnt<0>();   // nothing of this workgroup may still be writing LDS when it retires
 
+    if constexpr (!GATEUP && PACKED) {
+        if (a.comb_arrive != nullptr) {
+            static_for<IB>([&](auto ib) {
+                static_for<JBE>([&](auto j) {
+                    const int tr = j * 32 + li;
+                    const bool live = tr < t.rows;
+                    store_block<GATEUP, true>(acc[ib][j], acc[ib][j], a.Out + (size_t)(t.row0 + (live ? tr : 0)) * a.ldo,
+                                              n0w + ib * 32, half, N, live);
+                });
+            });
+            return fused_combine<IB>(a, t, nt, xs);
+        }
+    }
     static_for<IB>([&](auto ib) {
         static_for<JBE>([&](auto j) {
             const int tr = j * 32 + li;
@@ -725,17 +750,18 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
     });
 }
 
-template <int IB, bool GATEUP, bool WNT>
+// MAXJ: tallest tile handed in, in 32-row blocks.
+template <int IB, bool GATEUP, bool PACKED, bool WNT, int MAXJ>
 __device__ __forceinline__ void rows_dispatch(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
     switch ((t.rows + 31) / 32) {
-        case 1: return rows_body<1, IB, GATEUP, WNT>(a, t, nt, xs);
-        case 2: return rows_body<2, IB, GATEUP, WNT>(a, t, nt, xs);
-        case 3: return rows_body<3, IB, GATEUP, WNT>(a, t, nt, xs);
-        case 4: return rows_body<4, IB, GATEUP, WNT>(a, t, nt, xs);
-        case 5: return rows_body<5, IB, GATEUP, WNT>(a, t, nt, xs);
-        case 6: return rows_body<6, IB, GATEUP, WNT>(a, t, nt, xs);
-        case 7: return rows_body<7, IB, GATEUP, WNT>(a, t, nt, xs);
-        default: return rows_body<8, IB, GATEUP, WNT>(a, t, nt, xs);
+        case 1: return rows_body<1, IB, GATEUP, PACKED, WNT>(a, t, nt, xs);
+        case 2: if constexpr (MAXJ >= 2) return rows_body<2, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
+        case 3: if constexpr (MAXJ >= 3) return rows_body<3, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
+        case 4: if constexpr (MAXJ >= 4) return rows_body<4, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
+        case 5: if constexpr (MAXJ >= 5) return rows_body<5, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
+        case 6: if constexpr (MAXJ >= 6) return rows_body<6, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
+        case 7: if constexpr (MAXJ >= 7) return rows_body<7, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
+        default: if constexpr (MAXJ >= 8) return rows_body<8, IB, GATEUP, PACKED, WNT>(a, t, nt, xs);
     }
 }
 
@@ -981,6 +1007,13 @@ __global__ __launch_bounds__(kThreads, HALF ? 2 : 1) void tile_kernel_mixed(cons
             return dma_dispatch<1, GATEUP, PACKED, WNT, HALF>(b, t, nt, xs);
         }
     }
+    // Single-block tiles: weights through LDS where three ring buffers fit (rows_body).  Not in the build
+    // for two workgroups per CU, whose half of LDS holds two (Qwen2-MoE shape, 100 tokens, gate+up 362 -> 384 us).
+    if constexpr (!HALF) {
+        constexpr int RM = rows_max(IB * (GATEUP ? 2 : 1));
+        if (!multi && !(WNT && a.no_nt) && t.rows <= RM * 32)
+            return rows_dispatch<IB, GATEUP, PACKED, WNT, RM>(b, t, nt, xs);
+    }
     if (shared) return dma_dispatch<IB, GATEUP, PACKED, false, HALF>(b, t, nt, xs);
     dma_dispatch<IB, GATEUP, PACKED, WNT, HALF>(b, t, nt, xs);
 }
@@ -1000,10 +1033,10 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const GemmArgs a) {
     const bool multi = t.n_e > a.M && t.rows > a.short_nt;
     if (multi) b.rot_mul = a.rot_mul_multi;
     if constexpr (IB == 2 && !GATEUP) {
-        if (m.halves) return rows_dispatch<1, GATEUP, false>(b, t, m.nt, xs);
+        if (m.halves) return rows_dispatch<1, GATEUP, false, false, 8>(b, t, m.nt, xs);
     }
-    if (multi || a.no_nt) return rows_dispatch<IB, GATEUP, false>(b, t, m.nt, xs);
-    rows_dispatch<IB, GATEUP, true>(b, t, m.nt, xs);
+    if (multi || a.no_nt) return rows_dispatch<IB, GATEUP, false, false, 8>(b, t, m.nt, xs);
+    rows_dispatch<IB, GATEUP, false, true, 8>(b, t, m.nt, xs);
 }
 
 // =============================================================================================
@@ -1167,7 +1200,9 @@ inline int device_cus() {
 
 template <int IB, bool GATEUP, bool PACKED, bool WNT, bool HALF = false>
 hipError_t launch_tile_mixed(const GemmArgs& a, int max_blocks, hipStream_t s) {
-    constexpr int lds = 4 * (HALF ? 4 : 8) * 32 * 128;   // the DMA ring: XD+1 = 4 buffers of 256 (128) rows x 128 bytes
+    // the DMA ring of tile_body_dma: XD+1 = 4 buffers of 256 (128) rows x 128 bytes; that of rows_body
+    constexpr int ni = IB * (GATEUP ? 2 : 1), ring = 4 * (HALF ? 4 : 8) * 32 * 128, rows = HALF ? 0 : rows_lds(rows_max(ni), ni);
+    constexpr int lds = ring > rows ? ring : rows;
     auto kern = tile_kernel_mixed<IB, GATEUP, PACKED, WNT, HALF>;
     // once per process and kernel: not allowed while a stream is being captured into a graph
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -1182,7 +1217,7 @@ hipError_t launch_tile_mixed(const GemmArgs& a, int max_blocks, hipStream_t s) {
 template <int IB, bool GATEUP, bool CHUNK>
 hipError_t launch_rows(const GemmArgs& a, int max_blocks, hipStream_t s) {
     constexpr int NI = IB * (GATEUP ? 2 : 1);
-    constexpr int lds = rows_lds(NI);
+    constexpr int lds = rows_lds(8, NI);
     auto kern = tile_kernel<IB, GATEUP>;
     // once per process and kernel: not allowed while a stream is being captured into a graph
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
