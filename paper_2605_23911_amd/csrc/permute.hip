@@ -132,18 +132,32 @@ __global__ __launch_bounds__(kThreads) void scan_kernel(int32_t* __restrict__ ch
     __shared__ int total;
     __shared__ int first[kThreads], first2[kThreads];
     const int tid = threadIdx.x;
+    // One thread per expert walks the chunks, 16 loads in flight at a time (one by one the loop costs a
+    // memory latency per chunk: 16.5 us at 32 chunks, now 8); up to 16 chunks' values stay in registers.
+    constexpr int kBatch = 16;
     int n_e = 0;
-    if (tid < E)
-        for (int c = 0; c < nchunks; ++c) n_e += chunk_counts[(size_t)c * E + tid];
+    int held[kBatch];
+    for (int c0 = 0; c0 < nchunks; c0 += kBatch) {
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) held[i] = (tid < E && c0 + i < nchunks) ? chunk_counts[(size_t)(c0 + i) * E + tid] : 0;
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) n_e += held[i];
+    }
     const int off = block_exclusive_scan(n_e, wave_tot, &total);
     if (tid < E) {
         counts[tid] = n_e;
         offsets[tid] = off;
         int run = off;
-        for (int c = 0; c < nchunks; ++c) {
-            const int v = chunk_counts[(size_t)c * E + tid];
-            chunk_counts[(size_t)c * E + tid] = run;
-            run += v;
+        for (int c0 = 0; c0 < nchunks; c0 += kBatch) {
+            if (nchunks > kBatch) {
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) held[i] = c0 + i < nchunks ? chunk_counts[(size_t)(c0 + i) * E + tid] : 0;
+            }
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                if (c0 + i < nchunks) chunk_counts[(size_t)(c0 + i) * E + tid] = run;
+                run += held[i];
+            }
         }
     }
     if (tid == 0) offsets[E] = R;
