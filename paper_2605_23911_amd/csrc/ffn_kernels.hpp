@@ -37,6 +37,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "lds_dma.hpp"
 #include "moe_internal.hpp"
 
 namespace moe {
@@ -272,25 +273,6 @@ __device__ __forceinline__ void store_block(const f32x16& g, const f32x16& u, ui
 // outstanding the N later loads are outstanding too, so the counter is above N; extra operations
 // only lengthen the wait.
 // ---------------------------------------------------------------------------------------------
-// M0 is on the clobber list so that the compiler never orders this statement between its own
-// write of M0 and the instruction that consumes it.  M0 is a reserved (non-allocatable)
-// register, for which clang prints a generic "may not be preserved" warning: overwriting it is
-// exactly what is declared here, so the warning is silenced for this one statement.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void lds_dma16(const void* gptr, uint32_t lds_addr) {
-    const uint32_t base = __builtin_amdgcn_readfirstlane(lds_addr);   // wave-uniform: goes through M0
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(base)
-                 : "memory", "m0");
-}
-#pragma clang diagnostic pop
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit field");
-    // gfx9 encoding: vmcnt[3:0] -> bits 3:0, vmcnt[5:4] -> bits 15:14; expcnt (6:4) and lgkmcnt (11:8) = no wait
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
 // Weighted combine (Eq. 3) folded into the down projection: the paper's limitation 1, second
 // half.  The k rows of a token come from k different experts, i.e. from workgroups that run at
 // different times on different XCDs, each with an L2 of its own.  A device-scope fence pair
@@ -586,24 +568,6 @@ constexpr int rows_lds(int max_jbe, int ni) {
     }
     return most;
 }
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-// As lds_dma16, from a wave-uniform base plus a 32-bit lane offset; NT: non-temporal.
-template <bool NT>
-__device__ __forceinline__ void lds_dma16_at(const void* base, uint32_t lane_off, uint32_t lds_addr) {
-    const uint64_t b = (uint64_t)(uintptr_t)base;
-    const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b) |
-                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32;
-    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr);
-    if constexpr (NT)
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(lane_off), "s"(u), "s"(dst)
-                     : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(u), "s"(dst)
-                     : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
 template <int JBE, int IB, bool GATEUP, bool PACKED, bool WNT>
 __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
     constexpr int NM = GATEUP ? 2 : 1;

@@ -24,6 +24,7 @@
 // Kernel 2 (gate + top-k): one wavefront per token sums the slices, applies the gate and
 //   selects k experts.
 // Models with at most 8 experts take a single kernel instead (route_direct_kernel).
+#include "lds_dma.hpp"
 #include "moe_internal.hpp"
 
 namespace moe {
@@ -136,13 +137,15 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
 }
 
 // ---- kernel 1, fast form: all logits on the bf16 matrix cores, with an error bound ----------
-// One wavefront per unit of 32 tokens x NB*32 experts x one slice of d, v_mfma_f32_32x32x16_bf16
-// with the token rows as the first operand: lane l supplies, per MFMA, 8 reduction elements of
-// token row l%32 and of expert row l%32, and receives D[token 8(v/4) + 4(l/32) + v%4][expert l%32].
-// The reduction runs in groups of 64 elements: lane half h = l/32 loads the 32 consecutive
-// elements h*32.. of the group (64 contiguous bytes) and the j-th MFMA of the group takes its
-// j-th 16-byte piece; both operands use the same assignment, so the sum is the same.  The four
-// MFMAs of a group accumulate in fp32; the group's sum is then added to fp64 accumulators.
+// One workgroup per 64 tokens x 128 experts x one slice of d, v_mfma_f32_32x32x16_bf16 with the token
+// rows as the first operand.  Per step of 64 elements the workgroup brings its 64 token rows and
+// each wavefront its own 32 expert rows global -> LDS (whole 128-byte pieces, swizzled source chunks:
+// no bank conflicts), one step ahead into a ring of two buffers; the token rows are shared by the four
+// wavefronts.  A lane supplies 8 reduction elements of one row per MFMA (chunk 2 s + lane / 32 of the
+// step for MFMA s, in both operands) and receives D[token 8(v/4) + 4(lane/32) + v%4][expert lane%32].
+// The four MFMAs of a step accumulate in fp32; the step's sum is added to fp64 accumulators.
+// Bound by the loads (24 KiB per step and workgroup from L2).  256 experts, d = 7168, 4096 tokens: 90 us with
+// each wavefront loading its own 160 rows to registers, now 31 (the router 166 -> 127; 2048 tokens 97 -> 76).
 //
 // Error bound.  bf16 products are exact in fp32.  Taking each MFMA's result (16 products plus
 // the accumulator) to be off by at most 2^-19 of the sum of the magnitudes involved (32 units in
@@ -150,101 +153,107 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
 // four is off by at most 2^-17 * S_g, S_g = sum over the group of |x_k w_k|; the conversions and
 // the fp64 additions add ~1e-16.  So
 //     |z_fast - z| <= 2^-17 * sum_k |x_k w_k| <= 2^-17 * |x_t|_2 * |w_e|_2.
-// The units of the first token tile also leave sum_k w_ek^2 per expert and slice (fp32) for that.
-// part[ks][t][e], t < T32*32, e < E32*32 (fp64); wsq[ks][e] (fp32).
-template <int NB>
+// The workgroups of the first token tile also leave sum_k w_ek^2 per expert and slice (fp32) for that.
+// part[ks][t][e], t < TP (tokens padded to 64), e < EP (experts padded to 32), fp64; wsq[ks][e], fp32.
+constexpr int kFastTokens = 64, kFastExperts = 128;
+constexpr int kFastBuffers = 2;   // 48 KiB: three workgroups per CU (three buffers, two workgroups: 129 -> 136 us at T=3333)
+constexpr int kFastBuf = (kFastTokens + kFastExperts) * 128;
 __global__ __launch_bounds__(kThreads) void fast_logits_kernel(const uint16_t* __restrict__ x,
                                                               const uint16_t* __restrict__ wr,
                                                               double* __restrict__ part, float* __restrict__ wsq,
-                                                              int T, int d, int E, int T32, int E32, int KS,
-                                                              int units) {
-    const int lane = threadIdx.x % kWave;
-    const int unit = blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
-    if (unit >= units) return;
-    const int EG = (E32 + NB - 1) / NB;
-    const int ks = unit % KS;
-    const int eg = (unit / KS) % EG;
-    const int tt = unit / (KS * EG);
-    const int r = lane & 31, h = lane >> 5;
-    const int ngroup = d / 64;
-    const int per = (ngroup + KS - 1) / KS;
-    const int g0 = ks * per;
-    const int g1 = (g0 + per) < ngroup ? (g0 + per) : ngroup;
+                                                              int T, int d, int E, int TP, int EP, int KS) {
+    __shared__ __attribute__((aligned(1024))) char ring[kFastBuffers * kFastBuf];
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int li = lane & 31, half = lane >> 5;
+    const int EG = (EP + kFastExperts - 1) / kFastExperts;
+    const int ks = blockIdx.x % KS, eg = (blockIdx.x / KS) % EG, tt = blockIdx.x / (KS * EG);
+    const int nstep = d / 64, per = (nstep + KS - 1) / KS;
+    const int g0 = ks * per, g1 = g0 + per < nstep ? g0 + per : nstep;
 
-    const int trow = (tt * 32 + r) < T ? (tt * 32 + r) : (T - 1);
-    const uint16_t* xp = x + (size_t)trow * d + h * 32;
-    const uint16_t* wp[NB];
+    uint32_t xo[2], wo[4];   // byte offsets of this lane's source pieces (rows clamped into the tensors)
 #pragma unroll
-    for (int n = 0; n < NB; ++n) {
-        const int erow = ((eg * NB + n) * 32 + r) < E ? ((eg * NB + n) * 32 + r) : (E - 1);
-        wp[n] = wr + (size_t)erow * d + h * 32;
+    for (int q = 0; q < 2; ++q) {
+        const int rg = q * 4 + wave, t = tt * kFastTokens + rg * 8 + (lane >> 3);
+        xo[q] = (uint32_t)((lane & 7) ^ (((lane >> 3) ^ rg) & 7)) * 16u + (uint32_t)(t < T ? t : T - 1) * (uint32_t)d * 2u;
     }
-    double acc[NB][16];
-    float sq[NB];
 #pragma unroll
-    for (int n = 0; n < NB; ++n) {
-        sq[n] = 0.0f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[n][v] = 0.0;
+    for (int g = 0; g < 4; ++g) {
+        const int e = eg * kFastExperts + wave * 32 + g * 8 + (lane >> 3);
+        wo[g] = (uint32_t)((lane & 7) ^ (((lane >> 3) ^ g) & 7)) * 16u + (uint32_t)(e < E ? e : E - 1) * (uint32_t)d * 2u;
     }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)ring;
+    const uint32_t x_dst = lds0 + wave * 1024, w_dst = lds0 + kFastTokens * 128 + wave * 4096;
+    auto load = [&](int g, int buf) {
+        const int gc = g < g1 ? g : g1 - 1;   // steps past the last re-read it (harmless)
+        const char* xb = reinterpret_cast<const char*>(x) + (size_t)gc * 128;
+        const char* wb = reinterpret_cast<const char*>(wr) + (size_t)gc * 128;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) lds_dma16_at<false>(xb, xo[q], x_dst + buf * kFastBuf + q * 4096);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lds_dma16_at<false>(wb, wo[i], w_dst + buf * kFastBuf + i * 1024);
+    };
+    constexpr int LPS = 6;   // loads per wavefront and step
+    const int sw0 = (li ^ (li >> 3)) & 7;
+    const char* xs_b = ring + li * 128;
+    const char* ws_b = ring + kFastTokens * 128 + wave * 4096 + li * 128;
+
+    double acc[2][16];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[b][v] = 0.0;
+    float sq = 0.0f;
     if (g0 < g1) {
-        uint4 xa[4], wb[NB][4];
-        auto load = [&](int g, uint4 (&xo)[4], uint4 (&wo)[NB][4]) {
+        constexpr int XD = kFastBuffers - 1;   // steps the loads run ahead
 #pragma unroll
-            for (int j = 0; j < 4; ++j) xo[j] = *reinterpret_cast<const uint4*>(xp + (size_t)g * 64 + j * 8);
-#pragma unroll
-            for (int n = 0; n < NB; ++n)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) wo[n][j] = *reinterpret_cast<const uint4*>(wp[n] + (size_t)g * 64 + j * 8);
-        };
-        load(g0, xa, wb);
+        for (int q = 0; q < XD; ++q) load(g0 + q, q);
+        wait_vmcnt<(XD - 1) * LPS>();
+        __syncthreads();
         for (int g = g0; g < g1; ++g) {
-            uint4 xn[4], wn[NB][4];
-            load(g + 1 < g1 ? g + 1 : g, xn, wn);   // prefetch (the last group re-reads itself)
+            const int buf = (g - g0) % kFastBuffers;
+            load(g + XD, (g - g0 + XD) % kFastBuffers);   // the buffer read in the step before: free since its barrier
+            f32x16 c[2];
 #pragma unroll
-            for (int n = 0; n < NB; ++n) {
-                f32x16 c;
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) c[v] = 0.0f;
+                for (int v = 0; v < 16; ++v) c[b][v] = 0.0f;
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa[j]),
-                                                                __builtin_bit_cast(bf16x8, wb[n][j]), c, 0, 0, 0);
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[n][v] += (double)c[v];
+            for (int s = 0; s < 4; ++s) {
+                const int at = (2 * s + half) ^ sw0;
+                const uint4 w4 = *reinterpret_cast<const uint4*>(ws_b + buf * kFastBuf + (at & 7) * 16);
+                const bf16x8 x0 = *reinterpret_cast<const bf16x8*>(xs_b + buf * kFastBuf + (at & 7) * 16);
+                const bf16x8 x1 = *reinterpret_cast<const bf16x8*>(xs_b + buf * kFastBuf + 4096 + ((at ^ 4) & 7) * 16);
+                c[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, __builtin_bit_cast(bf16x8, w4), c[0], 0, 0, 0);
+                c[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, __builtin_bit_cast(bf16x8, w4), c[1], 0, 0, 0);
                 if (tt == 0) {
+                    const uint32_t u[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const uint32_t w4[4] = {wb[n][j].x, wb[n][j].y, wb[n][j].z, wb[n][j].w};
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float lo = __uint_as_float(w4[i] << 16), hi = __uint_as_float(w4[i] & 0xffff0000u);
-                            sq[n] = fmaf(lo, lo, fmaf(hi, hi, sq[n]));
-                        }
+                    for (int i = 0; i < 4; ++i) {
+                        const float lo = __uint_as_float(u[i] << 16), hi = __uint_as_float(u[i] & 0xffff0000u);
+                        sq = fmaf(lo, lo, fmaf(hi, hi, sq));
                     }
                 }
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) xa[j] = xn[j];
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int n = 0; n < NB; ++n)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) wb[n][j] = wn[n][j];
+                for (int v = 0; v < 16; ++v) acc[b][v] += (double)c[b][v];
+            wait_vmcnt<(XD - 1) * LPS>();   // everything of step g + 1 has landed
+            __syncthreads();
         }
+        wait_vmcnt<0>();         // nothing of this workgroup may still be writing LDS when it retires
     }
-    const size_t EP = (size_t)E32 * 32;
+    const int e = eg * kFastExperts + wave * 32 + li;
+    if (e >= EP) return;   // a whole wavefront beyond the padded experts
+    double* out = part + ((size_t)ks * TP + (size_t)tt * kFastTokens) * EP + e;
 #pragma unroll
-    for (int n = 0; n < NB; ++n) {
-        const int et = eg * NB + n;
-        if (et < E32) {
-            double* out = part + ((size_t)ks * T32 * 32 + (size_t)tt * 32) * EP + (size_t)et * 32 + r;
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) out[(size_t)(8 * (v / 4) + 4 * h + v % 4) * EP] = acc[n][v];
-            if (tt == 0) {
-                const float both = sq[n] + __shfl_xor(sq[n], 32, kWave);
-                if (h == 0) wsq[(size_t)ks * EP + (size_t)et * 32 + r] = both;
-            }
-        }
+        for (int v = 0; v < 16; ++v) out[(size_t)(b * 32 + 8 * (v / 4) + 4 * half + v % 4) * EP] = acc[b][v];
+    if (tt == 0) {
+        const float both = sq + __shfl_xor(sq, 32, kWave);
+        if (half == 0) wsq[(size_t)ks * EP + e] = both;
     }
 }
 
@@ -261,11 +270,12 @@ __device__ __forceinline__ void zero_token_counters(int32_t* __restrict__ zero, 
     for (int i = lane; i < zero_n; i += kWave) zero[(size_t)t * zero_n + i] = 0;
 }
 
-__device__ __forceinline__ void gate_and_select(double (&z)[kLogitsPerLane], const bool (&ok)[kLogitsPerLane],
+// Q: logits per lane that can exist (E <= 64 Q): the exponentials and compares of the others are left out.
+template <int Q>
+__device__ __forceinline__ void gate_and_select(double (&z)[Q], const bool (&ok)[Q],
                                                 int lane, int wave, int t, int k, int gating,
                                                 double (*wsel)[kMaxExperts], int32_t (*sel_idx)[kMaxExperts],
                                                 int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    constexpr int Q = kLogitsPerLane;
     const double ninf = -__builtin_huge_val();
     double p[Q];
 #pragma unroll
@@ -453,7 +463,7 @@ __device__ __forceinline__ void refine_candidates(double (&z)[kLogitsPerLane], c
 
 // ---- kernel 2: gate + top-k, one wavefront per token ------------------------------------------
 // FAST: `part` holds the fast logits' slices (row tiles of 32, see fast_logits_kernel), refined here.
-template <bool FAST>
+template <bool FAST, int Q>
 __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict__ part,
                                                        const float* __restrict__ bias,
                                                        int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
@@ -468,7 +478,6 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict
     if (t >= T) return;
     zero_token_counters(zero, zero_n, t, lane);
 
-    constexpr int Q = kLogitsPerLane;
     const double ninf = -__builtin_huge_val();
     const size_t EP = (size_t)E16 * 16;   // (FAST: T16 and E16 are passed as twice the 32-tile counts)
     double z[Q];
@@ -508,8 +517,8 @@ __global__ __launch_bounds__(kThreads) void route_direct_kernel(const uint16_t* 
                                                                int32_t* __restrict__ topk_idx,
                                                                float* __restrict__ topk_w, int d, int E, int k,
                                                                int gating, int32_t* __restrict__ zero, int zero_n) {
-    __shared__ double wsel[kWavesPerBlock][kMaxExperts];
-    __shared__ int32_t sel_idx[kWavesPerBlock][kMaxExperts];
+    __shared__ double wsel[1][kMaxExperts];
+    __shared__ int32_t sel_idx[1][kMaxExperts];
     __shared__ double partial[kWavesPerBlock][EB];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int t = blockIdx.x;
@@ -546,22 +555,35 @@ __global__ __launch_bounds__(kThreads) void route_direct_kernel(const uint16_t* 
             acc[e] += two ? a2 : 0.0;
         }
     }
+    // Sums over the wavefront: three halving exchanges leave each lane the sum of expert lane % 8 over its
+    // eight lane groups' first three levels, three butterflies finish it: 10 exchanges instead of 6 per expert.
+    static_assert(EB == 8, "halving exchanges over 8 sums");
+    {
+        double s4[4], s2[2], s1;
+        const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
 #pragma unroll
-    for (int e = 0; e < EB; ++e) {
-        const double tot = wave_sum(acc[e]);
-        if (lane == 0) partial[wave][e] = tot;
+        for (int i = 0; i < 4; ++i) {   // lanes with bit 0 set keep the odd experts
+            const double keep = b0 ? acc[2 * i + 1] : acc[2 * i], give = b0 ? acc[2 * i] : acc[2 * i + 1];
+            s4[i] = keep + __shfl_xor(give, 1, kWave);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {   // s4[i] belongs to expert 2 i + bit 0; bit 1 keeps the odd i
+            const double keep = b1 ? s4[2 * i + 1] : s4[2 * i], give = b1 ? s4[2 * i] : s4[2 * i + 1];
+            s2[i] = keep + __shfl_xor(give, 2, kWave);
+        }
+        {
+            const double keep = b2 ? s2[1] : s2[0], give = b2 ? s2[0] : s2[1];
+            s1 = keep + __shfl_xor(give, 4, kWave);
+        }
+#pragma unroll
+        for (int off = 8; off < kWave; off <<= 1) s1 += __shfl_xor(s1, off, kWave);
+        if (lane < EB) partial[wave][lane] = s1;   // expert = lane % 8
     }
     __syncthreads();
     if (wave != 0) return;
     zero_token_counters(zero, zero_n, t, lane);
-    constexpr int Q = kLogitsPerLane;
-    double z[Q];
-    bool ok[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        ok[q] = q == 0 && lane < E;
-        z[q] = -__builtin_huge_val();
-    }
+    double z[1] = {-__builtin_huge_val()};
+    const bool ok[1] = {lane < E};
     if (ok[0]) {
         double v = bias ? (double)bias[lane] : 0.0;
 #pragma unroll
@@ -573,34 +595,30 @@ __global__ __launch_bounds__(kThreads) void route_direct_kernel(const uint16_t* 
 
 struct RoutePlan {
     int T16, E16, KS, NT;
-    bool fast;          // bf16 logits + exact candidates; then T16/E16 count 16-row units of the 32-padded sizes
-    int T32, E32, NB;
+    bool fast;          // bf16 logits + exact candidates
+    int TP, EP;         // fast: tokens padded to 64, experts padded to 32
 };
 
 // mode: the test knob's value.  -1 the rule, 1 every logit in fp64, 0 the bf16 first pass from 256 tokens on.
 RoutePlan plan(const moe_config& c, int mode) {
-    RoutePlan p;
+    RoutePlan p{};
     // From half a million logits on (DeepSeek-V3 shape: 2048 tokens); below, the exact pass over
     // ~k+1 router rows per token costs more than the fp64 matrix cores need for all of them
     // (measured: Qwen2-MoE shape T=4096 72 -> 104 us, DeepSeek-V3 shape T=512 57 -> 86 us).
-    p.fast = mode != 1 && c.E > 8 && (mode == 0 ? c.T >= 256 : (long long)c.T * c.E >= (1ll << 19));
+    p.fast = mode != 1 && c.E > 8 && (unsigned long long)c.T * c.d * 2ull < (1ull << 32) &&
+             (mode == 0 ? c.T >= 256 : (long long)c.T * c.E >= (1ll << 19));
     if (p.fast) {
-        p.T32 = (c.T + 31) / 32;
-        p.E32 = (c.E + 31) / 32;
-        p.T16 = 2 * p.T32;
-        p.E16 = 2 * p.E32;
-        p.NB = p.E32 >= 4 ? 4 : (p.E32 >= 2 ? 2 : 1);
-        p.NT = 0;
-        const long long tiles = (long long)p.T32 * ((p.E32 + p.NB - 1) / p.NB);
-        const int ngroup = c.d / 64;
-        long long ks = (1024 + tiles - 1) / tiles;          // one wavefront per SIMD or more
-        if (ks > 16) ks = 16;
-        if (ks > ngroup / 2) ks = ngroup / 2;
+        p.TP = (c.T + kFastTokens - 1) / kFastTokens * kFastTokens;
+        p.EP = (c.E + 31) / 32 * 32;
+        const long long tiles = (long long)(p.TP / kFastTokens) * ((p.EP + kFastExperts - 1) / kFastExperts);
+        const int nstep = c.d / 64;
+        long long ks = (512 + tiles - 1) / tiles;           // two workgroups per CU
+        if (ks > 8) ks = 8;                                 // the refining kernel sums the slices
+        if (ks > nstep / 2) ks = nstep / 2;
         if (ks < 1) ks = 1;
         p.KS = (int)ks;
         return p;
     }
-    p.T32 = p.E32 = p.NB = 0;
     p.T16 = (c.T + 15) / 16;
     p.E16 = (c.E + 15) / 16;
     // four expert tiles per wavefront (the converted token fragment is then shared by 64 experts)
@@ -613,6 +631,19 @@ RoutePlan plan(const moe_config& c, int mode) {
     if (ks > 16) ks = 16;                               // the top-k kernel sums the slices serially
     if (ks > nchunk / 2) ks = nchunk / 2;               // at least two chunks per slice
     if (ks < 1) ks = 1;
+    if (p.NT == 4 && tiles * ks > 2048) {
+        // More wavefronts than two per SIMD: a third round for the few left over.  The slice count
+        // whose rounds are shortest: ceil(wavefronts / SIMDs) * chunks per slice.  (256 experts, 1000
+        // tokens: 9 slices of 252 tiles 105 us, 8 slices 85; 160 experts, 1024 tokens 68 -> 55.)
+        long long best = 1ll << 60;
+        for (long long n = 1, most = ks; n <= most; ++n) {
+            const long long cost = ((tiles * n + 1023) / 1024) * ((nchunk + n - 1) / n);
+            if (cost <= best) {
+                best = cost;
+                ks = n;
+            }
+        }
+    }
     p.KS = (int)ks;
     return p;
 }
@@ -625,8 +656,8 @@ size_t route_workspace_bytes(const moe_config& c) {
     size_t need = 0;
     for (int mode = -1; mode <= 1; ++mode) {
         const RoutePlan p = plan(c, mode);
-        size_t bytes = (size_t)p.KS * p.T16 * 16 * p.E16 * 16 * sizeof(double);
-        if (p.fast) bytes += (size_t)p.KS * p.E16 * 16 * sizeof(float);
+        const size_t bytes = p.fast ? (size_t)p.KS * p.EP * ((size_t)p.TP * sizeof(double) + sizeof(float))
+                                    : (size_t)p.KS * p.T16 * 16 * p.E16 * 16 * sizeof(double);
         need = bytes > need ? bytes : need;
     }
     return need;
@@ -642,18 +673,12 @@ hipError_t launch_route(const moe_config& c, const uint16_t* x, const uint16_t* 
     }
     const RoutePlan p = plan(c, knob(kKnobRouteExact));
     if (p.fast) {
-        const int units = p.T32 * ((p.E32 + p.NB - 1) / p.NB) * p.KS;
         double* part = (double*)workspace;
-        float* wsq = (float*)(part + (size_t)p.KS * p.T32 * 32 * p.E32 * 32);
-        const dim3 grid((units + kWavesPerBlock - 1) / kWavesPerBlock);
-        auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, x, wr, part, wsq, c.T, c.d, c.E, p.T32, p.E32, p.KS, units);
-        };
-        if (p.NB == 4) go(fast_logits_kernel<4>);
-        else if (p.NB == 2) go(fast_logits_kernel<2>);
-        else go(fast_logits_kernel<1>);
-        hipLaunchKernelGGL(topk_kernel<true>, dim3((c.T + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kThreads), 0, s,
-                           part, bias, topk_idx, topk_w, c.T, c.E, c.k, c.gating, p.T16, p.E16, p.KS, zero, zero_per_token,
+        float* wsq = (float*)(part + (size_t)p.KS * p.TP * p.EP);
+        hipLaunchKernelGGL(fast_logits_kernel, dim3((p.TP / kFastTokens) * ((p.EP + kFastExperts - 1) / kFastExperts) * p.KS), dim3(kThreads), 0, s, x,
+                           wr, part, wsq, c.T, c.d, c.E, p.TP, p.EP, p.KS);
+        hipLaunchKernelGGL((topk_kernel<true, kLogitsPerLane>), dim3((c.T + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kThreads), 0, s,
+                           part, bias, topk_idx, topk_w, c.T, c.E, c.k, c.gating, p.TP / 16, p.EP / 16, p.KS, zero, zero_per_token,
                            x, wr, c.d, wsq);
         return hipGetLastError();
     }
@@ -666,9 +691,13 @@ hipError_t launch_route(const moe_config& c, const uint16_t* x, const uint16_t* 
     else
         hipLaunchKernelGGL(logits_kernel<1>, grid, dim3(kThreads), 0, s, x, wr, part, c.T, c.d, c.E, p.T16, p.E16,
                            p.KS, units);
-    hipLaunchKernelGGL(topk_kernel<false>, dim3((c.T + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kThreads), 0, s, part,
-                       bias, topk_idx, topk_w, c.T, c.E, c.k, c.gating, p.T16, p.E16, p.KS, zero, zero_per_token,
-                       nullptr, nullptr, 0, nullptr);
+    auto select = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((c.T + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kThreads), 0, s, part, bias, topk_idx,
+                           topk_w, c.T, c.E, c.k, c.gating, p.T16, p.E16, p.KS, zero, zero_per_token, nullptr, nullptr, 0, nullptr);
+    };
+    if (c.E <= 64) select(topk_kernel<false, 1>);
+    else if (c.E <= 128) select(topk_kernel<false, 2>);
+    else select(topk_kernel<false, 4>);
     return hipGetLastError();
 }
 
