@@ -1,4 +1,4 @@
-"""Router kernels at the edges of their tiles, against logits, softmax and top-k in float64 (torch): the bf16
+"""Router, scan and combine kernels at the edges of their tiles; the router against logits, softmax and top-k in float64 (torch): the bf16
 first pass (64 tokens x 128 experts per workgroup, 64 elements of d per step, up to eight slices of d)
 forced on, the all-fp64 form at token counts where the slices of d are chosen by rounds, the one-launch
 form for up to eight experts, and the permutation's scan over more chunks than one batch of loads.
@@ -87,3 +87,23 @@ def test_scan_over_many_chunks(T, E):
     c, o, ro, so, _ = G.run_permute(moe.MoEConfig.of(T, 64, 64, E, 4), idx, torch.zeros((T, 64), dtype=torch.bfloat16, device="cuda:0"))
     for got, want in zip((c, o, ro, so), orc.permutation(idx, E)):
         assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 8, 9, 17])
+def test_combine_row_batches(k):
+    """Every batch width of the combine kernel and its remainders.  An fp32 sum of k products is off by at most
+    (k + 1) 2^-24 sum|w y|, and one rounding to bf16 by half a unit in the last place (2^-8)."""
+    moe = _moe()
+    print(f"[combine] k={k}", flush=True)
+    dev, T, d = "cuda:0", 37, 2112
+    g = torch.Generator().manual_seed(k)
+    yp = torch.randn(T * k, d, generator=g).to(torch.bfloat16).to(dev)
+    w = torch.rand(T, k, generator=g).to(dev)
+    row_of = torch.randperm(T * k, generator=g).to(torch.int32).to(dev)
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device=dev)
+    moe.moe_combine(moe.MoEConfig.of(T, d, 64, 32, k), yp, row_of, w, y)
+    torch.cuda.synchronize()
+    terms = w.double()[:, :, None] * yp.double()[row_of.long().view(T, k)]
+    ref = terms.sum(1)
+    bound = 2.0 ** -8 * ref.abs() + (k + 1) * 2.0 ** -24 * terms.abs().sum(1) + 1e-30
+    assert float(((y.double() - ref).abs() / bound).max()) <= 1.0
