@@ -11,8 +11,8 @@ constexpr int kThreads = 256;
 
 // KB: rows requested before the first is used (2, 4 or 8, by k): one row after the other a piece costs k
 // memory latencies.  The sum runs in slot order whatever KB is.  Bound by HBM (k d * 2 bytes read, d * 2
-// written per token) from a few thousand tokens on; below by latency: k = 8, 100 tokens x 3584 7.6 -> 4.8 us,
-// 512 x 7168 14.9 -> 12.6, 4096 x 7168 108 -> 108 (4.9 TB/s).
+// written per token) from a few thousand tokens on; below by latency: k = 8, stage by events, 100 tokens x 3584 9.8 -> 7.0 us,
+// 512 x 7168 17.3 -> 15.0, 4096 x 7168 111 -> 111 (4.8 TB/s).
 template <int KB>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const uint16_t* __restrict__ y_perm,
                                                           const int32_t* __restrict__ row_of,

@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kThreads) void scan_kernel(int32_t* __restrict__ ch
     __shared__ int first[kThreads], first2[kThreads];
     const int tid = threadIdx.x;
     // One thread per expert walks the chunks, 16 loads in flight at a time (one by one the loop costs a
-    // memory latency per chunk: 16.5 us at 32 chunks, now 8); up to 16 chunks' values stay in registers.
+    // memory latency per chunk: 16.5 us at 32 chunks, now 10); up to 16 chunks' values stay in registers.
     constexpr int kBatch = 16;
     int n_e = 0;
     int held[kBatch];
