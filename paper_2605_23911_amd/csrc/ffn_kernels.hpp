@@ -1008,8 +1008,11 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const GemmArgs a) {
 // reduction loop.  SPLITK == 1: the four wavefronts own four different 32-row weight blocks.
 // SPLITK == 4: they share one weight block and each reduces a quarter of K; partial sums are
 // added in wavefront order through LDS (fixed order: bit-reproducible).
+// Packed weights are loaded non-temporally, row-major ones are not: each of their 128-byte lines is consumed by
+// the four loads of a step (down projection of the Mixtral shape, row-major, non-temporal / cached: 1 token 81 / 40 us,
+// 2 tokens 169 / 93; packed 37 us at one token).
 // =============================================================================================
-template <int JB, bool GATEUP, int STAGES, int SPLITK, bool PACKED, bool WNT = true>
+template <int JB, bool GATEUP, int STAGES, int SPLITK, bool PACKED>
 __global__ __launch_bounds__(kThreads) void skinny_kernel(const GemmArgs a) {
     constexpr int NM = GATEUP ? 2 : 1;
     constexpr int BM = JB * 32;
@@ -1052,7 +1055,7 @@ __global__ __launch_bounds__(kThreads) void skinny_kernel(const GemmArgs a) {
         kc = kc > 0 ? kc : 0;
         static_for<NM>([&](auto i) {
             static_for<4>([&](auto s) {
-                wreg[st][i][s] = load_w16<WNT>(wp[i] + (size_t)kc * WA::kStep + s * WA::sStep);
+                wreg[st][i][s] = load_w16<PACKED>(wp[i] + (size_t)kc * WA::kStep + s * WA::sStep);
             });
         });
         static_for<JB>([&](auto j) {
