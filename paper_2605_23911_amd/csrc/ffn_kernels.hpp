@@ -359,7 +359,7 @@ __device__ __forceinline__ void fused_combine(const GemmArgs& a, const Tile& t, 
     }
 }
 
-template <int JB, int JBE, int IB, bool GATEUP, int STAGES, int XD, bool PACKED, bool WNT = false>
+template <int JBE, int IB, bool GATEUP, int STAGES, int XD, bool WNT>
 __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
     constexpr int NM = GATEUP ? 2 : 1;
     constexpr int NI = IB * NM;
@@ -372,7 +372,7 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
     const int KT = K / kBK;
     const int n0w = nt * BN + wave * (IB * 32);
 
-    typedef WAddr<PACKED, NM> WA;
+    typedef WAddr<true, NM> WA;
     const uint16_t* wp[NI];
     static_for<NM>([&](auto m) {
         static_for<IB>([&](auto ib) { wp[m * IB + ib] = WA::base(a, t.e, n0w / 32 + ib, m, lane); });
@@ -682,6 +682,10 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
         wait_vmcnt<(XD - 1) * LPS>();      // everything of step kt + 1 has landed (loads return in issue order)
         __syncthreads();
     };
+    // Nothing is outstanding here.  The wait tells the compiler so: where it lays this code out behind another body's, it
+    // takes that body's last loads for outstanding and waits for them in the loop, which empties the ring at every
+    // step (down projection, two weight blocks, 160 rows: Qwen2-MoE shape, 1000 tokens 245 -> 267 us).
+    wait_vmcnt<0>();
     static_for<XD>([&](auto q) {
         const int kc = phys(q);
         static_for<LPS>([&](auto l) { load(l, kc, (uint32_t)(q % NB) * BUF); });
@@ -729,28 +733,29 @@ __device__ __forceinline__ void rows_dispatch(const GemmArgs& a, const Tile& t, 
     }
 }
 
-// The dynamic-height kernel with the LDS-DMA token tile.  LDS: (XD+1) buffers of up to 32 KiB.
-template <int IB, bool GATEUP, bool PACKED, bool WNT = false, bool HALF = false>
+// The dynamic-height kernel with the LDS-DMA token tile (packed weights).  LDS: (XD+1) buffers of up to 32 KiB.
+// MINJ: shortest tile handed in, in 32-row blocks (no body is compiled for shorter ones).
+template <int IB, bool GATEUP, bool WNT, bool HALF, int MINJ = 1>
 __device__ __forceinline__ void dma_dispatch(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
     constexpr int NI = IB * (GATEUP ? 2 : 1);
     constexpr int SD = NI >= 4 ? 3 : 4;
     if constexpr (HALF) {   // blocks of at most 128 rows, two workgroups per CU: register budget 256 per wavefront
         switch ((t.rows + 31) / 32) {
-            case 1: return tile_body_dma<8, 1, IB, GATEUP, 3, 3, PACKED, WNT>(a, t, nt, xs);
-            case 2: return tile_body_dma<8, 2, IB, GATEUP, 3, 3, PACKED, WNT>(a, t, nt, xs);
-            case 3: return tile_body_dma<8, 3, IB, GATEUP, 2, 3, PACKED, WNT>(a, t, nt, xs);
-            default: return tile_body_dma<8, 4, IB, GATEUP, 2, 3, PACKED, WNT>(a, t, nt, xs);
+            case 1: return tile_body_dma<1, IB, GATEUP, 3, 3, WNT>(a, t, nt, xs);
+            case 2: return tile_body_dma<2, IB, GATEUP, 3, 3, WNT>(a, t, nt, xs);
+            case 3: return tile_body_dma<3, IB, GATEUP, 2, 3, WNT>(a, t, nt, xs);
+            default: return tile_body_dma<4, IB, GATEUP, 2, 3, WNT>(a, t, nt, xs);
         }
     }
     switch ((t.rows + 31) / 32) {
-        case 1: return tile_body_dma<8, 1, IB, GATEUP, SD, 3, PACKED, WNT>(a, t, nt, xs);
-        case 2: return tile_body_dma<8, 2, IB, GATEUP, SD, 3, PACKED, WNT>(a, t, nt, xs);
-        case 3: return tile_body_dma<8, 3, IB, GATEUP, SD, 3, PACKED, WNT>(a, t, nt, xs);
-        case 4: return tile_body_dma<8, 4, IB, GATEUP, SD, 3, PACKED, WNT>(a, t, nt, xs);
-        case 5: return tile_body_dma<8, 5, IB, GATEUP, NI >= 4 ? 2 : SD, 3, PACKED, WNT>(a, t, nt, xs);
-        case 6: return tile_body_dma<8, 6, IB, GATEUP, NI >= 4 ? 2 : SD, 3, PACKED, WNT>(a, t, nt, xs);
-        case 7: return tile_body_dma<8, 7, IB, GATEUP, 3, 3, PACKED, WNT>(a, t, nt, xs);
-        default: return tile_body_dma<8, 8, IB, GATEUP, 3, 3, PACKED, WNT>(a, t, nt, xs);
+        case 1: if constexpr (MINJ <= 1) return tile_body_dma<1, IB, GATEUP, SD, 3, WNT>(a, t, nt, xs); break;
+        case 2: if constexpr (MINJ <= 2) return tile_body_dma<2, IB, GATEUP, SD, 3, WNT>(a, t, nt, xs); break;
+        case 3: if constexpr (MINJ <= 3) return tile_body_dma<3, IB, GATEUP, SD, 3, WNT>(a, t, nt, xs); break;
+        case 4: if constexpr (MINJ <= 4) return tile_body_dma<4, IB, GATEUP, SD, 3, WNT>(a, t, nt, xs); break;
+        case 5: if constexpr (MINJ <= 5) return tile_body_dma<5, IB, GATEUP, NI >= 4 ? 2 : SD, 3, WNT>(a, t, nt, xs); break;
+        case 6: if constexpr (MINJ <= 6) return tile_body_dma<6, IB, GATEUP, NI >= 4 ? 2 : SD, 3, WNT>(a, t, nt, xs); break;
+        case 7: return tile_body_dma<7, IB, GATEUP, 3, 3, WNT>(a, t, nt, xs);
+        default: return tile_body_dma<8, IB, GATEUP, 3, 3, WNT>(a, t, nt, xs);
     }
 }
 
@@ -945,8 +950,10 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
 }
 
 // The kernel: what to work on from mixed_assign, the regime from the expert's rows, the body from the block's.
+// PACKED: always true (kept because it is part of the kernel's name, which the library reports); row-major weights: tile_kernel.
 template <int IB, bool GATEUP, bool PACKED, bool WNT, bool HALF = false>
 __global__ __launch_bounds__(kThreads, HALF ? 2 : 1) void tile_kernel_mixed(const GemmArgs a) {
+    static_assert(PACKED, "row-major weights: tile_kernel");
     extern __shared__ __attribute__((aligned(1024))) uint16_t xs[];
     MixedWork m;
     if (!mixed_assign<IB, GATEUP>(a, (int)blockIdx.x, m)) return;
@@ -967,19 +974,20 @@ __global__ __launch_bounds__(kThreads, HALF ? 2 : 1) void tile_kernel_mixed(cons
     const bool shared = multi || a.no_nt;
     if constexpr (IB == 2 && !GATEUP) {
         if (halves) {
-            if (shared) return dma_dispatch<1, GATEUP, PACKED, false, HALF>(b, t, nt, xs);
-            return dma_dispatch<1, GATEUP, PACKED, WNT, HALF>(b, t, nt, xs);
+            if (shared || !WNT) return dma_dispatch<1, GATEUP, false, HALF>(b, t, nt, xs);
+            return dma_dispatch<1, GATEUP, WNT, HALF>(b, t, nt, xs);
         }
     }
-    // Single-block tiles: weights through LDS where three ring buffers fit (rows_body).  Not in the build
-    // for two workgroups per CU, whose half of LDS holds two (Qwen2-MoE shape, 100 tokens, gate+up 362 -> 384 us).
-    if constexpr (!HALF) {
-        constexpr int RM = rows_max(IB * (GATEUP ? 2 : 1));
+    // Single-block tiles: weights through LDS where three ring buffers fit (rows_body); only taller ones are left
+    // for the bodies below.  Not in the build for two workgroups per CU, whose half of LDS holds two buffers
+    // (Qwen2-MoE shape, 100 tokens, gate+up 362 -> 384 us).
+    constexpr int RM = HALF ? 0 : rows_max(IB * (GATEUP ? 2 : 1));
+    if constexpr (RM > 0) {
         if (!multi && !(WNT && a.no_nt) && t.rows <= RM * 32)
-            return rows_dispatch<IB, GATEUP, PACKED, WNT, RM>(b, t, nt, xs);
+            return rows_dispatch<IB, GATEUP, true, WNT, RM>(b, t, nt, xs);
     }
-    if (shared) return dma_dispatch<IB, GATEUP, PACKED, false, HALF>(b, t, nt, xs);
-    dma_dispatch<IB, GATEUP, PACKED, WNT, HALF>(b, t, nt, xs);
+    if (shared || !WNT) return dma_dispatch<IB, GATEUP, false, HALF>(b, t, nt, xs);
+    if constexpr (WNT && RM < 8) dma_dispatch<IB, GATEUP, true, HALF, RM + 1>(b, t, nt, xs);
 }
 
 // Row-major weights: the same launch orders and regimes, rows_body.
