@@ -605,8 +605,8 @@ RoutePlan plan(const moe_config& c, int mode) {
     // From half a million logits on (DeepSeek-V3 shape: 2048 tokens); below, the exact pass over
     // ~k+1 router rows per token costs more than the fp64 matrix cores need for all of them
     // (measured: Qwen2-MoE shape T=4096 72 -> 104 us, DeepSeek-V3 shape T=512 57 -> 86 us).
-    p.fast = mode != 1 && c.E > 8 && (unsigned long long)c.T * c.d * 2ull < (1ull << 32) &&
-             (mode == 0 ? c.T >= 256 : (long long)c.T * c.E >= (1ll << 19));
+    // Its 32-bit byte offsets hold: every entry point refuses T d 2 >= 2^32 bytes, and here E <= 256 <= T.
+    p.fast = mode != 1 && c.E > 8 && (mode == 0 ? c.T >= 256 : (long long)c.T * c.E >= (1ll << 19));
     if (p.fast) {
         p.TP = (c.T + kFastTokens - 1) / kFastTokens * kFastTokens;
         p.EP = (c.E + 31) / 32 * 32;
