@@ -85,3 +85,62 @@ def test_all_rows(counts, d, F):
                 assert worst <= 1.0, ("y_perm", e, variant, worst)
     finally:
         B.test_knob(B.KNOB_DOWN_VARIANT, -1)
+
+
+@pytest.mark.parametrize("k", [1, 2])
+@pytest.mark.parametrize("layout", ["row-major", "packed"])
+def test_rows_through_the_source_map(layout, k):
+    """moe_forward reads expert-contiguous row r from token src_of[r] / k: experts of 161 to 256 rows (two and three ring
+    buffers) and just beyond one block.  The router's matrix picks features that the tokens carry their experts in, so every
+    expert holds the rows asked for; h and y_perm are compared row by row with the bounds above."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_23911_amd as moe
+    moe.lib()
+    print(f"[weights in LDS] source map, {layout}, k={k}", flush=True)
+    dev, d, F = "cuda:0", 192, 320
+    n = [161, 192, 193, 224, 225, 256, 257, 300]
+    E, R = len(n), sum(n)
+    T = R // k
+    assert T * k == R and max(n) <= T
+    g = torch.Generator().manual_seed(91 + k)
+    rnd = lambda *s, std=1.0: (torch.randn(*s, generator=g) * std).to(torch.bfloat16).to(dev)
+    want = torch.repeat_interleave(torch.arange(E), torch.tensor(n)).view(k, T).t()    # [T, k], the experts of a token differ
+    want = want[torch.randperm(T, generator=g)]
+    x = rnd(T, d)
+    x[:, :E] *= 0.125
+    for j in range(k):
+        x[torch.arange(T, device=dev), want[:, j].to(dev)] = 16.0 - 4.0 * j
+    wr = torch.eye(E, d, dtype=torch.bfloat16, device=dev)
+    w = rnd(E, F, d, std=d ** -0.5), rnd(E, F, d, std=d ** -0.5), rnd(E, d, F, std=F ** -0.5)
+    cfg = moe.MoEConfig.of(T, d, F, E, k, moe.GATE_SOFTMAX_RENORM)
+    packed = None
+    if layout == "packed":
+        packed = torch.empty(moe.packed_weights_size(cfg), dtype=torch.uint8, device=dev)
+        moe.moe_pack_weights(cfg, *w, packed)
+    lay = moe.forward_workspace_layout(cfg)
+    ws = torch.full((lay.total,), 0xFF, dtype=torch.uint8, device=dev)                 # bf16 NaN where nothing is written
+    y = torch.empty((T, d), dtype=torch.bfloat16, device=dev)
+    moe.moe_forward(cfg, x, wr, None, *(w if packed is None else (None, None, None)), y, ws, W_packed=packed)
+    torch.cuda.synchronize()
+    src = ws[lay.src_of: lay.src_of + 4 * R].view(torch.int32).long()
+    h = ws[lay.h: lay.h + 2 * R * F].view(torch.bfloat16).view(R, F)
+    yp = ws[lay.y_perm: lay.y_perm + 2 * R * d].view(torch.bfloat16).view(R, d)
+    counts = ws[lay.counts: lay.counts + 4 * E].view(torch.int32).tolist()
+    assert counts == n
+    u, a = 2.0 ** -24, 0
+    for e in range(E):
+        b = a + n[e]
+        assert bool((want.reshape(-1).to(dev)[src[a:b]] == e).all())
+        xe, he = x[src[a:b] // k].double(), h[a:b].double()
+        wg, wu, wd = (t[e].double() for t in w)
+        gate, up = xe @ wg.t(), xe @ wu.t()
+        dg, du = d * u * (xe.abs() @ wg.abs().t()), d * u * (xe.abs() @ wu.abs().t())
+        s = torch.nn.functional.silu(gate)
+        ref = s * up
+        bound = 2.0 ** -8 * ref.abs() + 1.1 * up.abs() * dg + s.abs() * du + 1e-6 * ref.abs() + 1e-30
+        assert float(((he - ref).abs() / bound).max()) <= 1.0, ("h", e)
+        refy = he @ wd.t()
+        boundy = 2.0 ** -8 * refy.abs() + F * u * (he.abs() @ wd.abs().t()) + 1e-30
+        assert float(((yp[a:b].double() - refy).abs() / boundy).max()) <= 1.0, ("y_perm", e)
+        a = b
