@@ -39,9 +39,14 @@ int pick(int M, bool packed, const moe_config& c) {
     // experts while the token buffers are small; with many rows per expert on average, the
     // two-weight-block form with cached loads throughout.
     const bool once = (double)R / c.E <= 192.0 && (double)R * c.d * 2.0 <= 128e6;
-    // Row-major: the same line; 9 and 10 differ in the launch order only (10 keeps the row tiles of an
+    // Row-major: the same line.  9 and 10 differ in the launch order only (10 keeps the row tiles of an
     // expert side by side: Mixtral shape, 4096 tokens 940 against 1210 us; 9 runs a contiguous eighth
-    // of the work per XCD: 0 and 9 at 256 experts, 512 tokens 1330 against 1240 us).
+    // of the work per XCD: 0 and 9 at 256 experts, 512 tokens 1330 against 1240 us).  Beyond the line, one weight block
+    // (0, three ring buffers at any height) against two (10): from 256 rows per expert on 10 is ahead (Mixtral shape 256 rows
+    // 423 / 397 us, 320 448 / 371, 512 691 / 547; Qwen2-MoE shape 256 rows 449 / 427).  At 200-248 rows with near-uniform routing
+    // 0 is 3-9 % ahead on some shapes (Mixtral 243 / 262, 32 experts 151 / 161) and 0-8 % behind on others (Qwen2-MoE 361 / 341,
+    // 16 experts of 6144 x 4096 249 / 233), but under routing skew, which the host cannot see, it is up to 1.55x behind
+    // (8 experts of 6144 x 16384, 200-240 rows: 617-739 / 452-482), so the line stays.
     if (!packed) return once ? (wide ? 9 : 0) : 10;
     if (once) return wide ? 6 : 5;
     return 7;

@@ -6,8 +6,9 @@
 // What differs from the paper's A100 design: the MFMA computes the TRANSPOSED tile
 //     C^T[f, row] = sum_k W[f, k] * X[row, k]
 // with the weight rows as the first MFMA operand.  The stored weight layout ([out, in], the
-// reduction dim contiguous) is then exactly the per-lane operand layout, so weights go
-// HBM -> VGPR with 16-byte loads and never touch LDS.  The MFMA sums over k, so which k a
+// reduction dim contiguous) is then exactly the per-lane operand layout: a weight fragment is 16
+// bytes per lane, loaded straight to registers or, in rows_body, brought to LDS by DMA and read back
+// by the wavefront it belongs to.  The MFMA sums over k, so which k a
 // fragment slot carries is free as long as both operands agree: MFMA s of a 64-wide step takes
 // k = 16 s + 8 (lane / 32) + 0..7, which makes the two lanes of a weight row read 32 contiguous
 // bytes per load instruction (one 64-byte L1 access instead of two).  Each wavefront owns its own weight rows
@@ -18,7 +19,8 @@
 // which costs one L1 access per lane.  moe_pack_weights re-orders the weights once (weights are
 // static at inference) into the order the loads consume them, [expert][32-row block][64-k step]
 // [matrix][s][lane] x 16 bytes, so that one load instruction reads 1 KiB contiguous and a
-// wavefront streams one contiguous region.  Both layouts are supported by every kernel.
+// wavefront streams one contiguous region.  Row-major weights have kernels of their own (tile_kernel,
+// skinny_kernel<.., false>).
 //
 // Kernels that share that mapping:
 //   tile_kernel_mixed  token tile (up to 256 rows) brought global -> LDS by DMA into a ring of
@@ -107,8 +109,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 // once per launch (one load instruction consumes whole 128-byte lines), and loading it with the
 // non-temporal hint keeps the streamed weights from evicting the re-used token tiles from L2
 // (+5..10 % at T <= 512).  When an expert spans several row blocks they share the weight panel
-// through L2 and the hint would defeat that; so it would for row-major weights, where a line is
-// consumed by four load instructions.
+// through L2 and the hint would defeat that; so it would for row-major weights loaded to registers,
+// where a line is consumed by four load instructions (skinny_kernel).  By DMA (rows_body) a
+// row-major load takes whole lines too.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <bool NT>
 __device__ __forceinline__ uint4 load_w16(const uint16_t* p) {
@@ -546,8 +549,9 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
 // 256 rows: 224 KiB = 1792 of the step's 2048 MFMA cycles.
 // Row-major, weights straight to registers and now, us, gate+up / down projection: Mixtral shape 47
 // tokens 401 / 230 -> 307 / 151, 512 tokens 470 / 270 -> 343 / 212 (5.5 TB/s of weights), 4096 tokens
-// 1955 / 1305 -> 1690 / 940; 256 experts of DeepSeek-V3's widths, 512 tokens 3390 / 1790 -> 2188 / 1233 (6.9 TB/s):
-// as fast as the packed layout up to ~160 rows per expert, 6-10 % behind it beyond.
+// 1955 / 1305 -> 1690 / 940; 256 experts of DeepSeek-V3's widths, 512 tokens 3390 / 1790 -> 2188 / 1233 (6.9 TB/s).
+// Against the packed layout: 1.00-1.05x its time up to 128 rows per expert on the Mixtral shape, most behind where a tile
+// has two buffers here and registers there: gate+up 1.14x at 192 rows per expert, down projection 1.24x at 256, 1.10x at 1024.
 // =============================================================================================
 constexpr int kLdsBytes = 160 * 1024;
 constexpr int rows_buffer_bytes(int jbe, int ni) { return jbe * 4096 + ni * 16384; }

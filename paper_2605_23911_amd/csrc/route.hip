@@ -145,7 +145,8 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
 // step for MFMA s, in both operands) and receives D[token 8(v/4) + 4(lane/32) + v%4][expert lane%32].
 // The four MFMAs of a step accumulate in fp32; the step's sum is added to fp64 accumulators.
 // Bound by the loads (24 KiB per step and workgroup from L2).  256 experts, d = 7168, 4096 tokens: 90 us with
-// each wavefront loading its own 160 rows to registers, now 31 (the router 166 -> 127; 2048 tokens 97 -> 76).
+// each wavefront loading its own 160 rows to registers, now 31 (the router 167 -> 129; 2048 tokens 97 -> 77); as part of
+// a layer, whose other kernels leave nothing of x in L2, 94 -> 41.
 //
 // Error bound.  bf16 products are exact in fp32.  Taking each MFMA's result (16 products plus
 // the accumulator) to be off by at most 2^-19 of the sum of the magnitudes involved (32 units in
@@ -462,7 +463,8 @@ __device__ __forceinline__ void refine_candidates(double (&z)[kLogitsPerLane], c
 }
 
 // ---- kernel 2: gate + top-k, one wavefront per token ------------------------------------------
-// FAST: `part` holds the fast logits' slices (row tiles of 32, see fast_logits_kernel), refined here.
+// FAST: `part` holds the fast logits' slices (see fast_logits_kernel), refined here.
+// T16, E16: padded tokens and experts in units of 16 (FAST pads tokens to 64 and experts to 32, else both to 16).
 template <bool FAST, int Q>
 __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict__ part,
                                                        const float* __restrict__ bias,
@@ -479,7 +481,7 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict
     zero_token_counters(zero, zero_n, t, lane);
 
     const double ninf = -__builtin_huge_val();
-    const size_t EP = (size_t)E16 * 16;   // (FAST: T16 and E16 are passed as twice the 32-tile counts)
+    const size_t EP = (size_t)E16 * 16;
     double z[Q];
     bool ok[Q];
 #pragma unroll
@@ -602,9 +604,13 @@ struct RoutePlan {
 // mode: the test knob's value.  -1 the rule, 1 every logit in fp64, 0 the bf16 first pass from 256 tokens on.
 RoutePlan plan(const moe_config& c, int mode) {
     RoutePlan p{};
-    // From half a million logits on (DeepSeek-V3 shape: 2048 tokens); below, the exact pass over
-    // ~k+1 router rows per token costs more than the fp64 matrix cores need for all of them
-    // (measured: Qwen2-MoE shape T=4096 72 -> 104 us, DeepSeek-V3 shape T=512 57 -> 86 us).
+    // From half a million logits on (256 experts: 2048 tokens).  Measured, us, all in fp64 / first pass and candidates:
+    // 256 experts (d 7168) 512 tokens 57 / 63, 1024 86 / 67, 2048 152 / 77, 4096 289 / 129; 160 experts (d 5120) 1024 tokens
+    // 55 / 48, 2048 92 / 55, 4096 208 / 93; 128 experts (d 4096) 2048 tokens 53 / 41, 4096 92 / 69; 64 experts (d 3584) 4096
+    // tokens 53 / 78, 8192 93 / 139.  By time alone the line would be at about 2^18 for more than 64 experts and nowhere up to
+    // 64 (the candidates, ~k + 1 rows per token, are then too large a part of all).  It lies higher because below it the softmax
+    // weights keep the last 0.5-1.4 % of precision that the non-candidates' share of the denominator takes (relative error
+    // 2.51e-8 / 2.53e-8 at 256 experts, 1024 tokens; with the other two gates the two forms agree).
     // Its 32-bit byte offsets hold: every entry point refuses T d 2 >= 2^32 bytes, and here E <= 256 <= T.
     p.fast = mode != 1 && c.E > 8 && (mode == 0 ? c.T >= 256 : (long long)c.T * c.E >= (1ll << 19));
     if (p.fast) {
