@@ -44,9 +44,9 @@ int pick(int M, bool packed, const moe_config& c) {
     // of the work per XCD: 0 and 9 at 256 experts, 512 tokens 1330 against 1240 us).  Beyond the line, one weight block
     // (0, three ring buffers at any height) against two (10): from 256 rows per expert on 10 is ahead (Mixtral shape 256 rows
     // 423 / 397 us, 320 448 / 371, 512 691 / 547; Qwen2-MoE shape 256 rows 449 / 427).  At 200-248 rows with near-uniform routing
-    // 0 is 3-9 % ahead on some shapes (Mixtral 243 / 262, 32 experts 151 / 161) and 0-8 % behind on others (Qwen2-MoE 361 / 341,
-    // 16 experts of 6144 x 4096 249 / 233), but under routing skew, which the host cannot see, it is up to 1.55x behind
-    // (8 experts of 6144 x 16384, 200-240 rows: 617-739 / 452-482), so the line stays.
+    // 0 is 3-17 % ahead on some shapes (Mixtral 243 / 262, 32 experts of 2880 x 2880 151 / 182) and 0-18 % behind on others
+    // (Qwen2-MoE 361 / 341, 4 experts of 2048 x 8192 93 / 79), but under routing skew, which the host cannot
+    // see, it is up to 1.55x behind (8 experts of 6144 x 16384, 200-240 rows: 617-739 / 452-482), so the line stays.
     if (!packed) return once ? (wide ? 9 : 0) : 10;
     if (once) return wide ? 6 : 5;
     return 7;
