@@ -9,42 +9,55 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// KB: rows requested before the first is used (2, 4 or 8, by k): one row after the other a piece costs k
-// memory latencies.  The sum runs in slot order whatever KB is.  Bound by HBM (k d * 2 bytes read, d * 2
-// written per token) from a few thousand tokens on; below by latency: k = 8, stage by events, 100 tokens x 3584 9.8 -> 7.0 us,
-// 512 x 7168 17.3 -> 15.0, 4096 x 7168 111 -> 111 (4.8 TB/s).
-template <int KB>
+// N rows, of slots i .. i + N - 1: requested before the first is used (one row after the other a piece costs a memory
+// latency per row), added in slot order.
+template <int N>
+__device__ __forceinline__ void add_rows(const uint16_t* __restrict__ y_perm, const int32_t* __restrict__ rows,
+                                         const float* __restrict__ w, int i, int d, int c, float (&acc)[8]) {
+    uint4 v[N];
+    float wi[N];
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+        v[b] = *reinterpret_cast<const uint4*>(y_perm + (size_t)rows[i + b] * d + c);
+        wi[b] = w[i + b];
+    }
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+        const uint32_t u[4] = {v[b].x, v[b].y, v[b].z, v[b].w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            acc[2 * q] = fmaf(wi[b], __uint_as_float(u[q] << 16), acc[2 * q]);
+            acc[2 * q + 1] = fmaf(wi[b], __uint_as_float(u[q] & 0xffff0000u), acc[2 * q + 1]);
+        }
+    }
+}
+
+// K: experts per token where that is up to 8, else 0: batches of eight rows, then of 4, 2 and 1.  No row is requested that is not
+// used: batches of 2, 4 or 8 that repeated the last row cost 3-7 % at 3, 5, 6 and 7 experts per token.
+// Bound by HBM and the Infinity Cache (k d * 2 bytes read, d * 2 written per token) from about a thousand tokens on; below by
+// latency.  Stage inside a layer by events, us, row by row / repeating batches / now: 6 experts, 900 tokens x 2048 8.0 / 8.6 /
+// 7.9, 1200 x 3584 12.5 / 12.8 / 12.4, 4096 x 4096 39.6 / 40.4 / 40.2; 8 experts, 100 tokens x 3584 9.8 / 7.1 / 6.1, 512 x 7168
+// 17.4 / 15.0 / 13.4, 4096 x 7168 110 / 109 / 105 (5.0 TB/s), 1024 x 4096 (64 MiB of rows) 15.3 / 17.8 / 17.6.
+template <int K>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const uint16_t* __restrict__ y_perm,
                                                           const int32_t* __restrict__ row_of,
                                                           const float* __restrict__ topk_w, int k, int d,
                                                           uint16_t* __restrict__ y) {
     const int t = blockIdx.x;
-    const int32_t* rows = row_of + (size_t)t * k;
-    const float* w = topk_w + (size_t)t * k;
+    const int32_t* rows = row_of + (size_t)t * (K ? K : k);
+    const float* w = topk_w + (size_t)t * (K ? K : k);
     for (int c = threadIdx.x * 8; c < d; c += kThreads * 8) {
         float acc[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
-        for (int i0 = 0; i0 < k; i0 += KB) {
-            uint4 v[KB];
-            float wi[KB];
-#pragma unroll
-            for (int b = 0; b < KB; ++b) {
-                const int i = i0 + b < k ? i0 + b : k - 1;   // past the last slot: the last row again, not used
-                v[b] = *reinterpret_cast<const uint4*>(y_perm + (size_t)rows[i] * d + c);
-                wi[b] = w[i];
-            }
-#pragma unroll
-            for (int b = 0; b < KB; ++b) {
-                if (i0 + b < k) {
-                    const uint32_t u[4] = {v[b].x, v[b].y, v[b].z, v[b].w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        acc[2 * q] = fmaf(wi[b], __uint_as_float(u[q] << 16), acc[2 * q]);
-                        acc[2 * q + 1] = fmaf(wi[b], __uint_as_float(u[q] & 0xffff0000u), acc[2 * q + 1]);
-                    }
-                }
-            }
+        if constexpr (K > 0) {
+            add_rows<K>(y_perm, rows, w, 0, d, c, acc);
+        } else {
+            int i = 0;
+            for (; i + 8 <= k; i += 8) add_rows<8>(y_perm, rows, w, i, d, c, acc);
+            if (k & 4) add_rows<4>(y_perm, rows, w, i, d, c, acc), i += 4;
+            if (k & 2) add_rows<2>(y_perm, rows, w, i, d, c, acc), i += 2;
+            if (k & 1) add_rows<1>(y_perm, rows, w, i, d, c, acc);
         }
         uint4 o;
         o.x = pack2_bf16(acc[0], acc[1]);
@@ -62,9 +75,17 @@ hipError_t launch_combine(const moe_config& c, const uint16_t* y_perm, const int
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(c.T), dim3(kThreads), 0, s, y_perm, row_of, topk_w, c.k, c.d, y);
     };
-    if (c.k <= 2) go(combine_kernel<2>);
-    else if (c.k <= 4) go(combine_kernel<4>);
-    else go(combine_kernel<8>);
+    switch (c.k) {
+        case 1: go(combine_kernel<1>); break;
+        case 2: go(combine_kernel<2>); break;
+        case 3: go(combine_kernel<3>); break;
+        case 4: go(combine_kernel<4>); break;
+        case 5: go(combine_kernel<5>); break;
+        case 6: go(combine_kernel<6>); break;
+        case 7: go(combine_kernel<7>); break;
+        case 8: go(combine_kernel<8>); break;
+        default: go(combine_kernel<0>);
+    }
     return hipGetLastError();
 }
 

@@ -107,3 +107,9 @@ def test_combine_row_batches(k):
     ref = terms.sum(1)
     bound = 2.0 ** -8 * ref.abs() + (k + 1) * 2.0 ** -24 * terms.abs().sum(1) + 1e-30
     assert float(((y.double() - ref).abs() / bound).max()) <= 1.0
+
+
+@pytest.mark.parametrize("k", [6, 7, 10, 12, 15, 23, 32])
+def test_combine_exact_batches(k):
+    """The remaining exact batch widths, and eight-row batches with each remainder; the bound above."""
+    test_combine_row_batches(k)
