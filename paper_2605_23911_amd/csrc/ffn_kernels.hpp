@@ -53,6 +53,7 @@ struct GemmArgs {
     int rot_mul;                // k-loop rotation between workgroups of one XCD, in steps (see tile_body_dma)
     int rot_mul_multi;          // the same for blocks of experts that span several row tiles (tile_kernel_mixed)
     int slots;                  // workgroups the chip runs at once (one per CU); 0 = do not split the last round
+    int cus;                    // CUs of the device (0: not known)
     const uint16_t* W0;         // [E, N, K]  gate (or down)
     const uint16_t* W1;         // [E, N, K]  up   (unused for down)
     const uint16_t* P;          // packed weights of this projection (PACKED kernels), else unused
@@ -543,10 +544,19 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
 // and down 244 / 229, 256 experts (DeepSeek-V3 widths) down 1340 / 1286 at 512 tokens (5.8 TB/s), 1632 / 1602
 // at 4096.
 // Ring of NB buffers, each one k step: JBE * 4 KiB of tokens and, per wavefront, NI * 4 KiB of
-// weights; the loads of step kt + NB - 1 are issued in step kt and awaited at the end of step
-// kt + NB - 2.  Three buffers where 160 KiB hold them, else two (taller than 160 rows with gate and
-// up, where a step's MFMAs are long enough to cover one step of latency).  LDS traffic per step at
+// weights; the loads of step kt + 2 are issued in step kt and awaited at the end of step kt + 1, with
+// two buffers those of step kt + 1 (taller than 160 rows with two weight blocks in all, where a step's
+// MFMAs are long enough to cover one step of latency).  LDS traffic per step at
 // 256 rows: 224 KiB = 1792 of the step's 2048 MFMA cycles.
+// `deep`: three steps ahead where 160 KiB hold four buffers (up to 192 rows with one weight block, 64 with two).
+// Two steps of one weight block are 32 KiB of weights in flight per CU.  That is enough while every CU streams; where the
+// last round of a launch leaves CUs idle the rest could take more from HBM, and it is not: down projection, us, weights to
+// registers (48 KiB ahead) / two steps / three: Mixtral shape 4 tokens 101 / 119 / 100, 7 tokens under skew 1.6 98 / 120 / 97;
+// 8 experts of 6144 x 16384, 8 tokens 243 / 265 / 242, 200 tokens 311 / 320 / 310; DeepSeek-V3 widths 2 tokens 83 / 87 / 82;
+// Qwen2-MoE shape 2 tokens 50 / 54 / 49.  At whole rounds three steps are 0-2 % behind two (Mixtral shape, 16 tokens,
+// 141 / 144 with three throughout), and with two weight blocks too (Qwen2-MoE shape, 150 tokens, down 210 / 212; 60 experts
+// of 2048 x 1408, 40 tokens, gate+up 116 / 117), except where half of the CUs or fewer have work (8 experts of 4096 x 1024,
+// 8 tokens, gate+up: registers 45.6, two steps 47.0, three 45.9).
 // Row-major, weights straight to registers and now, us, gate+up / down projection: Mixtral shape 47
 // tokens 401 / 230 -> 307 / 151, 512 tokens 470 / 270 -> 343 / 212 (5.5 TB/s of weights), 4096 tokens
 // 1955 / 1305 -> 1690 / 940; 256 experts of DeepSeek-V3's widths, 512 tokens 3390 / 1790 -> 2188 / 1233 (6.9 TB/s).
@@ -557,7 +567,7 @@ constexpr int kLdsBytes = 160 * 1024;
 constexpr int rows_buffer_bytes(int jbe, int ni) { return jbe * 4096 + ni * 16384; }
 constexpr int rows_buffers(int jbe, int ni) {
     const int n = kLdsBytes / rows_buffer_bytes(jbe, ni);
-    return n > 3 ? 3 : n;   // a fourth measured no gain (row-major, 47 tokens 307 -> 309 us; 256 experts, 512 tokens 2188 -> 2200)
+    return n > 4 ? 4 : n;
 }
 // Tallest single-block tile of packed weights (32-row blocks) that takes rows_body: three buffers fit.
 // With two (gate and up, or two weight blocks, beyond 160 rows) the register path of tile_body_dma is
@@ -573,12 +583,14 @@ constexpr int rows_lds(int max_jbe, int ni) {
     return most;
 }
 template <int JBE, int IB, bool GATEUP, bool PACKED, bool WNT>
-__device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
+__device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int nt, bool deep, uint16_t* xs) {
     constexpr int NM = GATEUP ? 2 : 1;
     constexpr int NI = IB * NM;
     constexpr int BN = 4 * IB * 32;
     constexpr int NB = rows_buffers(JBE, NI);
-    constexpr int XD = NB - 1;                          // steps the loads run ahead
+    constexpr int XM = NB - 1;                          // steps the loads can run ahead
+    constexpr int XD = XM > 2 ? 2 : XM;                 // steps they do, unless `deep`
+    const int ahead = deep ? XM : XD;
     constexpr int X_BYTES = JBE * 4096;                 // token tile of a step
     constexpr int BUF = X_BYTES + 4 * NI * 4096;
     constexpr int LPS = JBE + 4 * NI;                   // loads per wavefront and step
@@ -655,10 +667,17 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
     // over its first half when they are awaited at its end.
     constexpr int MF = 4 * NI * JBE;
     constexpr int SPREAD = XD > 1 ? MF : (MF + 1) / 2;
+    // All but the last `ahead` - 1 steps' loads have landed (they return in issue order).
+    auto landed = [&] {
+        if (XM > XD && deep)
+            wait_vmcnt<(XM - 1) * LPS>();
+        else
+            wait_vmcnt<(XD - 1) * LPS>();
+    };
     auto step = [&](int kt) {
         const int buf = (kt % NB) * BUF;
-        const uint32_t nbuf = (uint32_t)((kt + XD) % NB) * BUF;    // read in step kt - 1: free since that step's barrier
-        const int kc = phys(kt + XD);
+        const uint32_t nbuf = (uint32_t)((kt + ahead) % NB) * BUF;    // read in step kt - 1 or before: free since that step's barrier
+        const int kc = phys(kt + ahead);
         bf16x8 xf[2][JBE], wf[2][NI];
         static_for<NI>([&](auto i) { wf[0][i] = wfrag(buf, i, std::integral_constant<int, 0>{}); });
         static_for<JBE>([&](auto j) { xf[0][j] = xfrag(buf, j, std::integral_constant<int, 0>{}); });
@@ -683,18 +702,20 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
                 });
             });
         });
-        wait_vmcnt<(XD - 1) * LPS>();      // everything of step kt + 1 has landed (loads return in issue order)
+        landed();      // everything of step kt + 1
         __syncthreads();
     };
     // Nothing is outstanding here.  The wait tells the compiler so: where it lays this code out behind another body's, it
     // takes that body's last loads for outstanding and waits for them in the loop, which empties the ring at every
     // step (down projection, two weight blocks, 160 rows: Qwen2-MoE shape, 1000 tokens 245 -> 267 us).
     wait_vmcnt<0>();
-    static_for<XD>([&](auto q) {
-        const int kc = phys(q);
-        static_for<LPS>([&](auto l) { load(l, kc, (uint32_t)(q % NB) * BUF); });
+    static_for<XM>([&](auto q) {
+        if (q < XD || deep) {
+            const int kc = phys(q);
+            static_for<LPS>([&](auto l) { load(l, kc, (uint32_t)(q % NB) * BUF); });
+        }
     });
-    wait_vmcnt<(XD - 1) * LPS>();
+    landed();
     __syncthreads();
     for (int kt = 0; kt < KT; ++kt) step(kt);
     wait_vmcnt<0>();   // nothing of this workgroup may still be writing LDS when it retires
@@ -724,16 +745,16 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
 
 // MAXJ: tallest tile handed in, in 32-row blocks.
 template <int IB, bool GATEUP, bool PACKED, bool WNT, int MAXJ>
-__device__ __forceinline__ void rows_dispatch(const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
+__device__ __forceinline__ void rows_dispatch(const GemmArgs& a, const Tile& t, int nt, bool deep, uint16_t* xs) {
     switch ((t.rows + 31) / 32) {
-        case 1: return rows_body<1, IB, GATEUP, PACKED, WNT>(a, t, nt, xs);
-        case 2: if constexpr (MAXJ >= 2) return rows_body<2, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
-        case 3: if constexpr (MAXJ >= 3) return rows_body<3, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
-        case 4: if constexpr (MAXJ >= 4) return rows_body<4, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
-        case 5: if constexpr (MAXJ >= 5) return rows_body<5, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
-        case 6: if constexpr (MAXJ >= 6) return rows_body<6, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
-        case 7: if constexpr (MAXJ >= 7) return rows_body<7, IB, GATEUP, PACKED, WNT>(a, t, nt, xs); break;
-        default: if constexpr (MAXJ >= 8) return rows_body<8, IB, GATEUP, PACKED, WNT>(a, t, nt, xs);
+        case 1: return rows_body<1, IB, GATEUP, PACKED, WNT>(a, t, nt, deep, xs);
+        case 2: if constexpr (MAXJ >= 2) return rows_body<2, IB, GATEUP, PACKED, WNT>(a, t, nt, deep, xs); break;
+        case 3: if constexpr (MAXJ >= 3) return rows_body<3, IB, GATEUP, PACKED, WNT>(a, t, nt, deep, xs); break;
+        case 4: if constexpr (MAXJ >= 4) return rows_body<4, IB, GATEUP, PACKED, WNT>(a, t, nt, deep, xs); break;
+        case 5: if constexpr (MAXJ >= 5) return rows_body<5, IB, GATEUP, PACKED, WNT>(a, t, nt, deep, xs); break;
+        case 6: if constexpr (MAXJ >= 6) return rows_body<6, IB, GATEUP, PACKED, WNT>(a, t, nt, deep, xs); break;
+        case 7: if constexpr (MAXJ >= 7) return rows_body<7, IB, GATEUP, PACKED, WNT>(a, t, nt, deep, xs); break;
+        default: if constexpr (MAXJ >= 8) return rows_body<8, IB, GATEUP, PACKED, WNT>(a, t, nt, deep, xs);
     }
 }
 
@@ -787,6 +808,7 @@ struct MixedWork {
     int e, row0, rows, n_e;   // expert, first expert-contiguous row, rows of this workgroup, rows of the expert
     int nt;                   // feature tile: of IB * 128 features, or of 128 when `halves`
     bool halves;              // IB == 2 down projection: one 128-feature half of a tile of the split last round (IB = 1 body)
+    bool deep;                // loads run three steps ahead where the LDS ring holds four (rows_body)
 };
 template <int IB, bool GATEUP>
 __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, MixedWork& m) {
@@ -950,6 +972,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
     m.n_e = n_e;
     m.nt = nt;
     m.halves = halves;
+    m.deep = a.cus > 0 && (IB * (GATEUP ? 2 : 1) == 1 ? total % a.cus != 0 : 2 * total <= a.cus);   // see rows_body
     return true;
 }
 
@@ -988,7 +1011,7 @@ __global__ __launch_bounds__(kThreads, HALF ? 2 : 1) void tile_kernel_mixed(cons
     constexpr int RM = HALF ? 0 : rows_max(IB * (GATEUP ? 2 : 1));
     if constexpr (RM > 0) {
         if (!multi && !(WNT && a.no_nt) && t.rows <= RM * 32)
-            return rows_dispatch<IB, GATEUP, true, WNT, RM>(b, t, nt, xs);
+            return rows_dispatch<IB, GATEUP, true, WNT, RM>(b, t, nt, m.deep, xs);
     }
     if (shared || !WNT) return dma_dispatch<IB, GATEUP, false, HALF>(b, t, nt, xs);
     if constexpr (WNT && RM < 8) dma_dispatch<IB, GATEUP, true, HALF, RM + 1>(b, t, nt, xs);
@@ -1009,10 +1032,10 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const GemmArgs a) {
     const bool multi = t.n_e > a.M && t.rows > a.short_nt;
     if (multi) b.rot_mul = a.rot_mul_multi;
     if constexpr (IB == 2 && !GATEUP) {
-        if (m.halves) return rows_dispatch<1, GATEUP, false, false, 8>(b, t, m.nt, xs);
+        if (m.halves) return rows_dispatch<1, GATEUP, false, false, 8>(b, t, m.nt, m.deep, xs);
     }
-    if (multi || a.no_nt) return rows_dispatch<IB, GATEUP, false, false, 8>(b, t, m.nt, xs);
-    rows_dispatch<IB, GATEUP, false, true, 8>(b, t, m.nt, xs);
+    if (multi || a.no_nt) return rows_dispatch<IB, GATEUP, false, false, 8>(b, t, m.nt, m.deep, xs);
+    rows_dispatch<IB, GATEUP, false, true, 8>(b, t, m.nt, m.deep, xs);
 }
 
 // =============================================================================================
@@ -1160,6 +1183,7 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     args.rot_mul_multi = rot_steps(true);
     long long grid = ((long long)max_blocks * args.n_tiles_n + 7) / 8 * 8;   // whole eighths for the per-XCD chunking
     args.slots = 0;
+    args.cus = cus;
     if constexpr (IB == 2 && !GATEUP) {
         args.slots = cus;
         grid += cus / 2;     // a split last round has up to slots/2 extra workgroups

@@ -144,3 +144,15 @@ def test_rows_through_the_source_map(layout, k):
         boundy = 2.0 ** -8 * refy.abs() + F * u * (he.abs() @ wd.abs().t()) + 1e-30
         assert float(((yp[a:b].double() - refy).abs() / boundy).max()) <= 1.0, ("y_perm", e)
         a = b
+
+
+# 4096 output features are 32 feature tiles: eight blocks are one whole round of 256 workgroups (loads two steps ahead), seven are
+# not (three steps where the ring holds four buffers)
+ROUNDS = {"whole_round": [1, 33, 64, 65, 128, 160, 192, 256], "part_round": [1, 33, 65, 128, 160, 192, 193]}
+
+
+@pytest.mark.parametrize("counts", list(ROUNDS))
+@pytest.mark.parametrize("F", [64, 128, 320])
+def test_steps_ahead(counts, F):
+    COUNTS.update(ROUNDS)
+    test_all_rows(counts, 4096, F)
