@@ -169,7 +169,7 @@ moe_status moe_block_schedule(const moe_config* cfg, const int32_t* offsets, int
  * should pack once at load time and pass W_packed from then on.  The row-major tensors of
  * Sec. 3.2 are accepted by every entry point as the interchange layout (same integers, floats
  * within the stated tolerance); the layer then takes up to 9 % longer, from one token to 1024 rows
- * per expert (single projections up to 24 %: the down projection at 256 rows per expert).
+ * per expert (single projections up to 25 %: the down projection at 256 rows per expert).
  * Sec. 3.2 stores each projection as a flattened E*N x K matrix; the GEMM kernels read it
  * through per-lane 16-byte loads whose lanes touch 32 different rows.  moe_pack_weights
  * re-orders the same bf16 values into the order those loads consume them, so that every load

@@ -42,11 +42,11 @@ int pick(int M, bool packed, const moe_config& c) {
     // Row-major: the same line.  9 and 10 differ in the launch order only (10 keeps the row tiles of an
     // expert side by side: Mixtral shape, 4096 tokens 940 against 1210 us; 9 runs a contiguous eighth
     // of the work per XCD: 0 and 9 at 256 experts, 512 tokens 1330 against 1240 us).  Beyond the line, one weight block
-    // (0, three ring buffers at any height) against two (10): from 256 rows per expert on 10 is ahead (Mixtral shape 256 rows
-    // 423 / 397 us, 320 448 / 371, 512 691 / 547; Qwen2-MoE shape 256 rows 449 / 427).  At 200-248 rows with near-uniform routing
-    // 0 is 3-17 % ahead on some shapes (Mixtral 243 / 262, 32 experts of 2880 x 2880 151 / 182) and 0-18 % behind on others
-    // (Qwen2-MoE 361 / 341, 4 experts of 2048 x 8192 93 / 79), but under routing skew, which the host cannot
-    // see, it is up to 1.55x behind (8 experts of 6144 x 16384, 200-240 rows: 617-739 / 452-482), so the line stays.
+    // (0, three ring buffers or more at any height) against two (10): from 256 rows per expert on 10 is ahead (Mixtral shape 256
+    // rows 432 / 396 us, 320 450 / 370, 512 694 / 545; Qwen2-MoE shape 256 rows 440 / 426).  At 200-248 rows with near-uniform
+    // routing 0 is 3-15 % ahead on some shapes (Mixtral 246 / 263, 32 experts of 2880 x 2880 154 / 181) and 0-18 % behind on
+    // others (16 experts of 6144 x 4096 247 / 230, 4 of 2048 x 8192 94 / 80), but under routing skew, which the host cannot
+    // see, it is up to 1.58x behind (8 experts of 6144 x 16384, 200-240 rows: 611-755 / 455-505), so the line stays.
     if (!packed) return once ? (wide ? 9 : 0) : 10;
     if (once) return wide ? 6 : 5;
     return 7;

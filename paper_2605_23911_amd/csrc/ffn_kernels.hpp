@@ -560,8 +560,8 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
 // Row-major, weights straight to registers and now, us, gate+up / down projection: Mixtral shape 47
 // tokens 401 / 230 -> 307 / 151, 512 tokens 470 / 270 -> 343 / 212 (5.5 TB/s of weights), 4096 tokens
 // 1955 / 1305 -> 1690 / 940; 256 experts of DeepSeek-V3's widths, 512 tokens 3390 / 1790 -> 2188 / 1233 (6.9 TB/s).
-// Against the packed layout: 1.00-1.05x its time up to 128 rows per expert on the Mixtral shape, most behind where a tile
-// has two buffers here and registers there: gate+up 1.14x at 192 rows per expert, down projection 1.24x at 256, 1.10x at 1024.
+// Against the packed layout: 0.99-1.08x its time up to 128 rows per expert on the Mixtral shape, most behind where a tile
+// has two buffers here and registers there: gate+up 1.12x at 192 rows per expert, down projection 1.25x at 256, 1.13x at 1024.
 // =============================================================================================
 constexpr int kLdsBytes = 160 * 1024;
 constexpr int rows_buffer_bytes(int jbe, int ni) { return jbe * 4096 + ni * 16384; }
