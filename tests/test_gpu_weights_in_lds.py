@@ -1,6 +1,6 @@
 """GEMM bodies that stage the weights in LDS (every tile of row-major weights; the single-block tiles
 of packed ones): all rows of h and y_perm at the sizes where the body can go wrong - one to eight
-32-row blocks and one row past each, two and three ring buffers, one to five k steps, output
+32-row blocks and one row past each, two to four ring buffers, one to five k steps, output
 widths that leave the last feature tile partly empty - through moe_grouped_ffn, with every
 down-projection kernel that holds the body.
 
