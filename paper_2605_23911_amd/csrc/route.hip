@@ -11,12 +11,10 @@
 // operands convert exactly to fp64 and their products are exact there, so the fp64 MFMA
 // (v_mfma_f64_16x16x4) gives logits good to ~1e-15 at the fp64 matrix rate.
 //
-// From half a million logits on (and more than 8 experts) the fp64 work is cut down to the experts that can
-// be among the k largest: a first pass computes every logit on the bf16 matrix cores with a
-// proven error bound, the top-k pass takes the experts within twice that bound of the k-th
-// largest value as candidates (k of them plus, rarely, one or two) and recomputes their logits
-// exactly in fp64 before it selects.  Same indices, same order, same weights to ~1e-7 as the
-// all-fp64 path at a third of its time (DeepSeek-V3 shape, T=4096); see fast_logits_kernel.
+// Larger calls take the logits from the int8 matrix cores instead (64 times the fp64 rate): rows are cut
+// into four 8-bit digits, the digits' products are summed exactly in integers, and what the digits leave out is bounded per
+// token; the few tokens whose k + 1 largest logits stand closer together than that bound get the logits in question again in
+// fp64.  Same indices, same order, same weights to the last bit but one as the all-fp64 form (digit_logits_kernel, digits_pay).
 //
 // Kernel 1 (logits): one wavefront per work unit (16 tokens x 16 experts x one slice of d).
 //   The reduction is cut into enough slices to put >= ~2000 wavefronts on the chip even for
@@ -24,6 +22,8 @@
 // Kernel 2 (gate + top-k): one wavefront per token sums the slices, applies the gate and
 //   selects k experts.
 // Models with at most 8 experts take a single kernel instead (route_direct_kernel).
+#include <type_traits>
+
 #include "lds_dma.hpp"
 #include "moe_internal.hpp"
 
@@ -136,125 +136,272 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
     }
 }
 
-// ---- kernel 1, fast form: all logits on the bf16 matrix cores, with an error bound ----------
-// One workgroup per 64 tokens x 128 experts x one slice of d, v_mfma_f32_32x32x16_bf16 with the token
-// rows as the first operand.  Per step of 64 elements the workgroup brings its 64 token rows and
-// each wavefront its own 32 expert rows global -> LDS (whole 128-byte pieces, swizzled source chunks:
-// no bank conflicts), one step ahead into a ring of two buffers; the token rows are shared by the four
-// wavefronts.  A lane supplies 8 reduction elements of one row per MFMA (chunk 2 s + lane / 32 of the
-// step for MFMA s, in both operands) and receives D[token 8(v/4) + 4(lane/32) + v%4][expert lane%32].
-// The four MFMAs of a step accumulate in fp32; the step's sum is added to fp64 accumulators.
-// Bound by the loads (24 KiB per step and workgroup from L2).  256 experts, d = 7168, 4096 tokens: 90 us with
-// each wavefront loading its own 160 rows to registers, now 31 (the router 167 -> 129; 2048 tokens 97 -> 77); as part of
-// a layer, whose other kernels leave nothing of x in L2, 94 -> 41.
+// ---- kernel 1 on the int8 matrix cores: every logit from exact integer sums ------------------
+// A row v (a token or an expert) with 2^E <= max|v_k| < 2^(E+1) is written in fixed point as
+//     v_k = 2^(E-29) (q0 2^24 + q1 2^16 + q2 2^8 + q3) + residual,   q0 in [-65, 65], q1..q3 in [-128, 127].
+// bf16 has 8 significant bits, so the residual is zero unless |v_k| < 2^(E-22).  The products q_i q_j are summed over k
+// by v_mfma_i32_32x32x32_i8, which is exact, one int32 accumulator per order i + j = 0..4; orders 5 and 6 (2^-40 and less of
+// the largest possible term) are left out.  The five sums meet in fp64.
 //
-// Error bound.  bf16 products are exact in fp32.  Taking each MFMA's result (16 products plus
-// the accumulator) to be off by at most 2^-19 of the sum of the magnitudes involved (32 units in
-// the last place of the largest term: room for truncation and for a multi-stage adder), a group of
-// four is off by at most 2^-17 * S_g, S_g = sum over the group of |x_k w_k|; the conversions and
-// the fp64 additions add ~1e-16.  So
-//     |z_fast - z| <= 2^-17 * sum_k |x_k w_k| <= 2^-17 * |x_t|_2 * |w_e|_2.
-// The workgroups of the first token tile also leave sum_k w_ek^2 per expert and slice (fp32) for that.
-// part[ks][t][e], t < TP (tokens padded to 64), e < EP (experts padded to 32), fp64; wsq[ks][e], fp32.
-constexpr int kFastTokens = 64, kFastExperts = 128;
-constexpr int kFastBuffers = 2;   // 48 KiB: three workgroups per CU (three buffers, two workgroups: 129 -> 136 us at T=3333)
-constexpr int kFastBuf = (kFastTokens + kFastExperts) * 128;
-__global__ __launch_bounds__(kThreads) void fast_logits_kernel(const uint16_t* __restrict__ x,
-                                                              const uint16_t* __restrict__ wr,
-                                                              double* __restrict__ part, float* __restrict__ wsq,
-                                                              int T, int d, int E, int TP, int EP, int KS) {
-    __shared__ __attribute__((aligned(1024))) char ring[kFastBuffers * kFastBuf];
+// Error bound.  Let N0 be the 2-norm of a row, N2 and N3 those of its parts q2, q3 and q3 alone, Nr the residual's, as
+// bounded by digits_kernel from how many elements have such a part.  The pairs left out are (2,3), (3,2), (3,3) and
+// whatever a residual meets:
+//     |z_digits - z| <= N2(x) N3(w) + N3(x) N2(w) + Nr(x) N0(w) + N0(x) Nr(w)      (Cauchy-Schwarz)
+// plus the fp64 roundings.  For normally distributed rows of 7168 that is about 1e-8, the error itself 1e-11: an exact
+// evaluation for the purpose of the weights, and topk_kernel recomputes in fp64 what stands closer together than the bound.
+//
+// What bounds it: the int8 matrix rate, 13 products (256 experts, 1024 tokens, d = 7168: 49 GOP, 10 us at 5 POP/s).
+// A wavefront takes 64 experts (two 32-expert operands) and 32 JT tokens, the experts' digits straight from memory in operand
+// order (digits_kernel lays them out), one 32-element step ahead in registers; the tokens come as bf16 by DMA
+// through LDS, shared by the wavefronts that take other experts, and are cut into digits in registers between the matrix
+// instructions (7 vector instructions per element, about half of the issue slots that 13 products of 64 experts leave).
+constexpr int kMinExp = -90;         // smallest E: keeps every scale a normal fp32 number
+constexpr int kMaxDigitDim = 32768;  // 4 pairs x 2^14 x this many elements fill an int32
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ float exp2i(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }   // -126 <= e <= 127
+
+// Digits of four bf16 values (two words, low half first): out[p] holds digit p of all four, one byte each.
+__device__ __forceinline__ void four_digits(uint32_t w0, uint32_t w1, float scale, uint32_t (&out)[4]) {
+    // v + 0x808080 has the bytes q0, q1 + 128, q2 + 128, q3 + 128
+    const uint32_t u0 = (uint32_t)(int)(__uint_as_float(w0 << 16) * scale) + 0x808080u;
+    const uint32_t u1 = (uint32_t)(int)(__uint_as_float(w0 & 0xffff0000u) * scale) + 0x808080u;
+    const uint32_t u2 = (uint32_t)(int)(__uint_as_float(w1 << 16) * scale) + 0x808080u;
+    const uint32_t u3 = (uint32_t)(int)(__uint_as_float(w1 & 0xffff0000u) * scale) + 0x808080u;
+    const uint32_t a = __builtin_amdgcn_perm(u1, u0, 0x05010400u), b = __builtin_amdgcn_perm(u1, u0, 0x07030602u);
+    const uint32_t c = __builtin_amdgcn_perm(u3, u2, 0x05010400u), e = __builtin_amdgcn_perm(u3, u2, 0x07030602u);
+    out[0] = __builtin_amdgcn_perm(e, b, 0x07060302u);
+    out[1] = __builtin_amdgcn_perm(e, b, 0x05040100u) ^ 0x80808080u;
+    out[2] = __builtin_amdgcn_perm(c, a, 0x07060302u) ^ 0x80808080u;
+    out[3] = __builtin_amdgcn_perm(c, a, 0x05040100u) ^ 0x80808080u;
+}
+
+// One wavefront per row: rows 0 .. EP-1 are the experts' (their digits are written, in the order in which
+// digit_logits_kernel loads them: [32-expert block][32-element step][digit][lane] x 16 bytes), then the tokens'.
+// exps[row] = E, norms[row] = N0, N2, N3, Nr (all infinite for a row that holds an infinity or a NaN).
+// Bound by latency up to a thousand tokens, then by reading x and the counting (about ten vector instructions per
+// element).  Rows past the last expert or token repeat it.  (A workgroup per row: 24 instead of 21 us at 4096 tokens x 7168.)
+__global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wr,
+                                                         uint8_t* __restrict__ wdig, int32_t* __restrict__ exps,
+                                                         float4* __restrict__ norms, int T, int d, int E, int EP) {
+    const int lane = threadIdx.x % kWave;
+    const int row = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave));
+    const int t = row - EP;
+    const bool expert = row < EP;
+    const uint16_t* v = expert ? wr + (size_t)(row < E ? row : E - 1) * d : x + (size_t)(t < T ? t : T - 1) * d;
+    // A unit is 16 elements: one lane's 16 bytes of every digit.  A lane holds eight at a time (all loads in flight at
+    // once); rows of up to 8192 elements are read once, longer ones twice.
+    constexpr int kHeld = 8;
+    const int units = d / 16, chunks = (units + kHeld * kWave - 1) / (kHeld * kWave);
+    uint32_t held[kHeld][8];
+    auto load = [&](int c) {
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i) {
+            const int p0 = (c * kHeld + i) * kWave, p = p0 + lane;
+            uint4 a = make_uint4(0, 0, 0, 0), b = a;
+            if (p0 < units) {                 // uniform; past the end: the first unit again
+                const uint4* src = reinterpret_cast<const uint4*>(v + (size_t)(p < units ? p : 0) * 16);
+                a = src[0], b = src[1];
+            }
+            held[i][0] = a.x, held[i][1] = a.y, held[i][2] = a.z, held[i][3] = a.w;
+            held[i][4] = b.x, held[i][5] = b.y, held[i][6] = b.z, held[i][7] = b.w;
+        }
+    };
+    uint32_t top = 0;
+    for (int c = 0; c < chunks; ++c) {
+        load(c);
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const uint32_t lo = held[i][q] & 0x7fffu, hi = (held[i][q] >> 16) & 0x7fffu;
+                const uint32_t m = lo > hi ? lo : hi;
+                top = m > top ? m : top;
+            }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)top, off, kWave);
+        top = o > top ? o : top;
+    }
+    const bool finite = top < 0x7f80u;
+    int ex = finite ? (int)(top >> 7) - 127 : 0;
+    ex = ex < kMinExp ? kMinExp : ex;
+    const float scale = exp2i(29 - ex);
+    float sq = 0.0f;
+    int n2 = 0, n3 = 0, nr = 0;
+    uint8_t* dst = wdig + ((size_t)(row >> 5) * (d / 32) * 4) * 1024 + (row & 31) * 16;
+    for (int c = 0; c < chunks; ++c) {
+        if (chunks > 1) load(c);
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i) {
+            const int p0 = (c * kHeld + i) * kWave, p = p0 + lane;
+            if (p0 >= units) continue;        // uniform
+            const bool live = p < units;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const uint32_t w = live ? held[i][q / 2] : 0u;
+                const float f = __uint_as_float(q & 1 ? w & 0xffff0000u : w << 16) * scale;
+                const int n = (int)f;
+                sq = fmaf(f, f, sq);
+                n2 += __popcll(__ballot((n & 0xffff) != 0));      // wavefront totals, in scalar registers
+                n3 += __popcll(__ballot((n & 0xff) != 0));
+                nr += __popcll(__ballot((float)n != f));
+            }
+            if (expert && live) {
+                uint32_t g[4][4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) four_digits(held[i][2 * q], held[i][2 * q + 1], scale, g[q]);
+                uint8_t* out = dst + (size_t)(p >> 1) * 4096 + (p & 1) * 512;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) *reinterpret_cast<uint4*>(out + j * 1024) = make_uint4(g[0][j], g[1][j], g[2][j], g[3][j]);
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, kWave);
+    if (lane == 0) {
+        const float unit = exp2i(ex - 29), inf = __builtin_huge_valf();
+        exps[row] = ex;
+        // parts q2, q3 and q3 alone are at most 2^15 + 2^7 and 2^7 units, a residual is less than one
+        norms[row] = finite ? make_float4(1.001f * unit * sqrtf(sq), 33000.0f * unit * sqrtf((float)n2), 128.2f * unit * sqrtf((float)n3),
+                                          1.001f * unit * sqrtf((float)nr))
+                            : make_float4(inf, inf, inf, inf);
+    }
+}
+
+// part[ks][t][e], t < TP, e < EP = 64 EGW, fp64.  EGW wavefronts of the four take 64 experts each, 4 / EGW take other
+// tokens.  A lane supplies 16 consecutive k of one row per operand (row lane % 32, half lane / 32 of the 32-element step) and
+// receives D[token 8(v/4) + 4(lane/32) + v%4][expert lane%32].  Workgroup b takes slice b % KS of d: with 8 slices (or 4, 16)
+// the experts' digits of a slice are read by one XCD (two, two) only and stay in its L2.
+// One wavefront per SIMD, software-pipelined by hand: while the 26 matrix instructions of a 32-element step run, the next
+// step's tokens are cut into digits (four vector instructions behind each) and its experts' digits are on their way.
+template <int EGW>
+__global__ __launch_bounds__(kThreads) void digit_logits_kernel(const uint16_t* __restrict__ x, const uint8_t* __restrict__ wdig,
+                                                               const int32_t* __restrict__ exps, double* __restrict__ part,
+                                                               int T, int d, int TP, int KS) {
+    constexpr int TW = 4 / EGW, RT = TW * 32, BUF = RT * 128, EP = EGW * 64, NB = 3;
+    __shared__ __attribute__((aligned(1024))) char ring[NB * BUF];
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int li = lane & 31, half = lane >> 5;
-    const int EG = (EP + kFastExperts - 1) / kFastExperts;
-    const int ks = blockIdx.x % KS, eg = (blockIdx.x / KS) % EG, tt = blockIdx.x / (KS * EG);
+    const int we = wave % EGW, wt = wave / EGW;
+    const int ks = blockIdx.x % KS, t0 = blockIdx.x / KS * RT;
     const int nstep = d / 64, per = (nstep + KS - 1) / KS;
     const int g0 = ks * per, g1 = g0 + per < nstep ? g0 + per : nstep;
 
-    uint32_t xo[2], wo[4];   // byte offsets of this lane's source pieces (rows clamped into the tensors)
+    uint32_t xo[TW];   // byte offsets of this lane's pieces: 8 rows x 128 bytes per load, source chunk swizzled
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int rg = q * 4 + wave, t = tt * kFastTokens + rg * 8 + (lane >> 3);
+    for (int q = 0; q < TW; ++q) {
+        const int rg = q * 4 + wave, t = t0 + rg * 8 + (lane >> 3);
         xo[q] = (uint32_t)((lane & 7) ^ (((lane >> 3) ^ rg) & 7)) * 16u + (uint32_t)(t < T ? t : T - 1) * (uint32_t)d * 2u;
     }
+    const uint32_t x_dst = (uint32_t)(uintptr_t)ring + wave * 1024;
+    auto load_x = [&](int g) {   // steps past the last re-read it (harmless)
+        const char* xb = reinterpret_cast<const char*>(x) + (size_t)(g < g1 ? g : g1 - 1) * 128;
+        const uint32_t buf = (uint32_t)((g - g0) % NB) * BUF;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int e = eg * kFastExperts + wave * 32 + g * 8 + (lane >> 3);
-        wo[g] = (uint32_t)((lane & 7) ^ (((lane >> 3) ^ g) & 7)) * 16u + (uint32_t)(e < E ? e : E - 1) * (uint32_t)d * 2u;
-    }
-    const uint32_t lds0 = (uint32_t)(uintptr_t)ring;
-    const uint32_t x_dst = lds0 + wave * 1024, w_dst = lds0 + kFastTokens * 128 + wave * 4096;
-    auto load = [&](int g, int buf) {
-        const int gc = g < g1 ? g : g1 - 1;   // steps past the last re-read it (harmless)
-        const char* xb = reinterpret_cast<const char*>(x) + (size_t)gc * 128;
-        const char* wb = reinterpret_cast<const char*>(wr) + (size_t)gc * 128;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) lds_dma16_at<false>(xb, xo[q], x_dst + buf * kFastBuf + q * 4096);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) lds_dma16_at<false>(wb, wo[i], w_dst + buf * kFastBuf + i * 1024);
+        for (int q = 0; q < TW; ++q) lds_dma16_at<false>(xb, xo[q], x_dst + buf + q * 4096);
     };
-    constexpr int LPS = 6;   // loads per wavefront and step
-    const int sw0 = (li ^ (li >> 3)) & 7;
-    const char* xs_b = ring + li * 128;
-    const char* ws_b = ring + kFastTokens * 128 + wave * 4096 + li * 128;
+    const uint32_t eb_bytes = (uint32_t)(d / 32) * 4096u;
+    const uint8_t* wp = wdig + (size_t)we * 2 * eb_bytes;        // wave-uniform
+    const uint32_t wl[2] = {(uint32_t)lane * 16u, eb_bytes + (uint32_t)lane * 16u};
+    const int r = wt * 32 + li, xsw = (r ^ (r >> 3)) & 7;
+    const char* xrow = ring + r * 128;
+    const float xscale = exp2i(29 - exps[EP + t0 + r]);
 
-    double acc[2][16];
+    i32x16 acc[5][2];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int o = 0; o < 5; ++o)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[b][v] = 0.0;
-    float sq = 0.0f;
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[o][b][v] = 0;
     if (g0 < g1) {
-        constexpr int XD = kFastBuffers - 1;   // steps the loads run ahead
-#pragma unroll
-        for (int q = 0; q < XD; ++q) load(g0 + q, q);
-        wait_vmcnt<(XD - 1) * LPS>();
-        __syncthreads();
-        for (int g = g0; g < g1; ++g) {
-            const int buf = (g - g0) % kFastBuffers;
-            load(g + XD, (g - g0 + XD) % kFastBuffers);   // the buffer read in the step before: free since its barrier
-            f32x16 c[2];
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) c[b][v] = 0.0f;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int at = (2 * s + half) ^ sw0;
-                const uint4 w4 = *reinterpret_cast<const uint4*>(ws_b + buf * kFastBuf + (at & 7) * 16);
-                const bf16x8 x0 = *reinterpret_cast<const bf16x8*>(xs_b + buf * kFastBuf + (at & 7) * 16);
-                const bf16x8 x1 = *reinterpret_cast<const bf16x8*>(xs_b + buf * kFastBuf + 4096 + ((at ^ 4) & 7) * 16);
-                c[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x0, __builtin_bit_cast(bf16x8, w4), c[0], 0, 0, 0);
-                c[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x1, __builtin_bit_cast(bf16x8, w4), c[1], 0, 0, 0);
-                if (tt == 0) {
-                    const uint32_t u[4] = {w4.x, w4.y, w4.z, w4.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float lo = __uint_as_float(u[i] << 16), hi = __uint_as_float(u[i] & 0xffff0000u);
-                        sq = fmaf(lo, lo, fmaf(hi, hi, sq));
-                    }
-                }
+        i32x4 wq[2][2][4], xq[2][4];   // [parity of the 32-element step][expert block][digit]
+        uint32_t raw[8], u[4];
+        auto load_w = [&](int step, int par, int i) {
+            const uint8_t* base = wp + (size_t)(step < 2 * g1 ? step : 2 * g1 - 1) * 4096;
+            wq[par][i / 4][i % 4] = *reinterpret_cast<const i32x4*>(base + wl[i / 4] + i % 4 * 1024);
+        };
+        auto read_x = [&](int g, int s, int i) {   // half s of step g: 32 bytes of this lane's row, in two pieces
+            const uint4 v = *reinterpret_cast<const uint4*>(xrow + (g - g0) % NB * BUF + ((4 * s + 2 * half + i) ^ xsw) * 16);
+            raw[4 * i] = v.x, raw[4 * i + 1] = v.y, raw[4 * i + 2] = v.z, raw[4 * i + 3] = v.w;
+        };
+        // Sixteenth n of cutting `raw` into digits (four_digits, in pieces that fit behind one matrix instruction).
+        auto cut = [&](int n, int par) {
+            const int i = n / 4;
+            if (n % 4 < 2) {
+                const uint32_t w = raw[2 * i + n % 4];
+                u[2 * (n % 4)] = (uint32_t)(int)(__uint_as_float(w << 16) * xscale) + 0x808080u;
+                u[2 * (n % 4) + 1] = (uint32_t)(int)(__uint_as_float(w & 0xffff0000u) * xscale) + 0x808080u;
+            } else if (n % 4 == 2) {
+                const uint32_t b = __builtin_amdgcn_perm(u[1], u[0], 0x07030602u), e = __builtin_amdgcn_perm(u[3], u[2], 0x07030602u);
+                xq[par][0][i] = (int)__builtin_amdgcn_perm(e, b, 0x07060302u);
+                xq[par][1][i] = (int)(__builtin_amdgcn_perm(e, b, 0x05040100u) ^ 0x80808080u);
+            } else {
+                const uint32_t a = __builtin_amdgcn_perm(u[1], u[0], 0x05010400u), c = __builtin_amdgcn_perm(u[3], u[2], 0x05010400u);
+                xq[par][2][i] = (int)(__builtin_amdgcn_perm(c, a, 0x07060302u) ^ 0x80808080u);
+                xq[par][3][i] = (int)(__builtin_amdgcn_perm(c, a, 0x05040100u) ^ 0x80808080u);
             }
+        };
+        // The 26 matrix instructions of half s of step g; behind each its share of what the next half needs.
+        auto half_step = [&](int g, int s) {
+            constexpr int P[13] = {0, 1, 0, 1, 2, 0, 1, 2, 3, 0, 1, 2, 3}, O[13] = {3, 3, 2, 2, 2, 1, 1, 1, 1, 0, 0, 0, 0};
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
+            for (int i = 0; i < 26; ++i) {
+                const int p = P[i / 2], q = O[i / 2], b = i % 2;
+                acc[p + q][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xq[s][p], wq[s][b][q], acc[p + q][b], 0, 0, 0);
+                // an expert digit's registers take the digit of two halves on as soon as their last product is issued
+                if (b == 1 && (i == 25 || O[i / 2 + 1 < 13 ? i / 2 + 1 : 12] != q)) {
+                    load_w(2 * g + s + 2, s, q);
+                    load_w(2 * g + s + 2, s, 4 + q);
+                }
+                if (i < 2) read_x(g + s, s ^ 1, i);      // (the step past the last: a copy of the last, its digits are not used)
+                if (i >= 5 && i < 21) cut(i - 5, s ^ 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        load_x(g0);
+        load_x(g0 + 1);
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[b][v] += (double)c[b][v];
-            wait_vmcnt<(XD - 1) * LPS>();   // everything of step g + 1 has landed
+        for (int i = 0; i < 8; ++i) load_w(2 * g0, 0, i), load_w(2 * g0 + 1, 1, i);
+        wait_vmcnt<0>();
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) read_x(g0, 0, i);
+#pragma unroll
+        for (int n = 0; n < 16; ++n) cut(n, 0);
+        for (int g = g0; g < g1; ++g) {
+            __builtin_amdgcn_sched_barrier(0);
+            half_step(g, 0);
+            load_x(g + 2);           // its buffer was last read in step g - 1
+            __builtin_amdgcn_sched_barrier(0);
+            half_step(g, 1);
+            // The tokens of step g + 1, requested in step g - 1, are older than this step's 16 + TW loads (and than eight of the
+            // step before).
+            wait_vmcnt<16 + TW>();
             __syncthreads();
         }
-        wait_vmcnt<0>();         // nothing of this workgroup may still be writing LDS when it retires
+        wait_vmcnt<0>();             // nothing of this workgroup may still be writing LDS when it retires
     }
-    const int e = eg * kFastExperts + wave * 32 + li;
-    if (e >= EP) return;   // a whole wavefront beyond the padded experts
-    double* out = part + ((size_t)ks * TP + (size_t)tt * kFastTokens) * EP + e;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b) {
+        const int e = (we * 2 + b) * 32 + li;
+        const int ew = exps[e];
+        const int tr = t0 + wt * 32 + 4 * half;
+        double* out = part + ((size_t)ks * TP + tr) * EP + e;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) out[(size_t)(b * 32 + 8 * (v / 4) + 4 * half + v % 4) * EP] = acc[b][v];
-    if (tt == 0) {
-        const float both = sq + __shfl_xor(sq, 32, kWave);
-        if (half == 0) wsq[(size_t)ks * EP + e] = both;
+        for (int v = 0; v < 16; ++v) {
+            const int row = 8 * (v / 4) + v % 4;
+            const long long e2 = 1023 + exps[EP + tr + row] + ew - 42;     // 2^(Ex-29) 2^(Ew-29) 2^16
+            double z = (double)acc[0][b][v];
+#pragma unroll
+            for (int o = 1; o < 5; ++o) z = fma(z, 256.0, (double)acc[o][b][v]);
+            out[(size_t)row * EP] = z * __longlong_as_double(e2 << 52);
+        }
     }
 }
 
@@ -262,7 +409,6 @@ __global__ __launch_bounds__(kThreads) void fast_logits_kernel(const uint16_t* _
 // Lane l holds the logits of experts l, l+64, ... in z[] (ok[] = expert exists).  Eq. 1-2,
 // Sec. 3.4: max-subtracted softmax (or sigmoid), k rounds of arg-max over the logits with the
 // winners masked, ties to the lower index.
-constexpr int kLogitsPerLane = kMaxExperts / kWave;
 // moe_forward's down projection counts, per (token, 128-feature group), how many of the token's
 // k expert rows have been written (see ffn_kernels.hpp, fused_combine).  The counters of token t
 // are cleared here by the wavefront that routes t, so the layer needs no clearing launch.
@@ -271,21 +417,82 @@ __device__ __forceinline__ void zero_token_counters(int32_t* __restrict__ zero, 
     for (int i = lane; i < zero_n; i += kWave) zero[(size_t)t * zero_n + i] = 0;
 }
 
-// Q: logits per lane that can exist (E <= 64 Q): the exponentials and compares of the others are left out.
+// Largest value over the wavefront, the same in every lane: four exchanges inside rows of 16 lanes (DPP, no LDS
+// crossbar), then the four rows' values through scalar registers.
+__device__ __forceinline__ double wave_max_uniform(double v) {
+    auto exchanged = [](double a, auto ctrl) {
+        const uint64_t u = (uint64_t)__double_as_longlong(a);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, decltype(ctrl)::value, 0xf, 0xf, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+        return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+    };
+    v = fmax(v, exchanged(v, std::integral_constant<int, 0xB1>{}));     // quad_perm 1,0,3,2
+    v = fmax(v, exchanged(v, std::integral_constant<int, 0x4E>{}));     // quad_perm 2,3,0,1
+    v = fmax(v, exchanged(v, std::integral_constant<int, 0x141>{}));    // row_half_mirror
+    v = fmax(v, exchanged(v, std::integral_constant<int, 0x140>{}));    // row_mirror
+    auto lane_value = [&](int l) {
+        const uint64_t u = (uint64_t)__double_as_longlong(v);
+        return __longlong_as_double((long long)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l) << 32 |
+                                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l)));
+    };
+    return fmax(fmax(lane_value(0), lane_value(16)), fmax(lane_value(32), lane_value(48)));
+}
+
+// The largest logit of those not taken and its expert (ties to the lower index); expert -1 if every expert is taken.
+// Uniform over the wavefront.
 template <int Q>
-__device__ __forceinline__ void gate_and_select(double (&z)[Q], const bool (&ok)[Q],
-                                                int lane, int wave, int t, int k, int gating,
-                                                double (*wsel)[kMaxExperts], int32_t (*sel_idx)[kMaxExperts],
-                                                int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    const double ninf = -__builtin_huge_val();
-    double p[Q];
+__device__ __forceinline__ double next_best(const double (&z)[Q], const bool (&ok)[Q], unsigned taken, int lane, int& expert) {
+    double bv = -__builtin_huge_val();
+    int be = -1;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) z[q] = (z[q] != z[q]) ? ninf : z[q];   // a NaN logit can never win and never breaks the index range
+    for (int q = 0; q < Q; ++q) {
+        if (ok[q] && !((taken >> q) & 1u) && (be < 0 || z[q] > bv)) {
+            bv = z[q];
+            be = lane + kWave * q;
+        }
+    }
+    const double m = wave_max_uniform(bv);
+    unsigned long long tied = __ballot(be >= 0 && bv == m);
+    expert = -1;
+    while (tied != 0) {                  // one lane, unless logits are equal
+        const int l = __builtin_ctzll(tied);
+        const int o = __builtin_amdgcn_readlane(be, l);
+        expert = (expert < 0 || o < expert) ? o : expert;
+        tied &= tied - 1;
+    }
+    return m;
+}
+
+// Gate and selection of one token.  Q: logits per lane that can exist (E <= 64 Q): the exponentials and compares of the others
+// are left out.  `suspect` is called with (k-th largest logit, smallest distance between two neighbours among the k + 1
+// largest); if it returns true it has replaced logits in z and the selection starts over (once).
+template <int Q, class Suspect>
+__device__ __forceinline__ void gate_and_select(double (&z)[Q], const bool (&ok)[Q],
+                                                int lane, int wave, int t, int k, int E, int gating,
+                                                double (*wsel)[kMaxExperts], int32_t (*sel_idx)[kMaxExperts],
+                                                int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, Suspect&& suspect) {
+    const double ninf = -__builtin_huge_val();
+    for (bool again = true; again;) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) z[q] = (z[q] != z[q]) ? ninf : z[q];   // a NaN logit can never win and never breaks the index range
+        unsigned taken = 0;   // bit q set: this lane's q-th expert already selected
+        double last = __builtin_huge_val(), gap = __builtin_huge_val();
+        for (int r = 0; r < k; ++r) {
+            int be;
+            const double m = next_best(z, ok, taken, lane, be);
+            const double step = last - m;
+            if (r > 0 && !(step >= gap) && gap == gap) gap = step;      // a NaN (two infinities) stays
+            last = m;
+            if (lane == be % kWave) taken |= 1u << (be / kWave);
+            if (lane == 0) sel_idx[wave][r] = be;
+        }
+        again = suspect(last, gap, taken);
+    }
     double m = ninf;
 #pragma unroll
     for (int q = 0; q < Q; ++q) m = fmax(m, z[q]);
-    m = wave_max(m);
-    double psum = 0.0;
+    m = wave_max_uniform(m);
+    double p[Q], psum = 0.0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         if (gating == MOE_GATE_SIGMOID_NORM)
@@ -294,46 +501,24 @@ __device__ __forceinline__ void gate_and_select(double (&z)[Q], const bool (&ok)
             p[q] = ok[q] ? exp(z[q] - m) : 0.0;
         psum += p[q];
     }
-    psum = wave_sum(psum);
     if (gating != MOE_GATE_SIGMOID_NORM) {
-        const double inv = 1.0 / psum;
+        const double inv = 1.0 / wave_sum(psum);
 #pragma unroll
         for (int q = 0; q < Q; ++q) p[q] = ok[q] ? p[q] * inv : 0.0;   // softmax scores, Eq. 1
     }
-
-    unsigned taken = 0;   // bit q set: this lane's q-th expert already selected
+    __builtin_amdgcn_wave_barrier();
     double wsum = 0.0;
     for (int r = 0; r < k; ++r) {
-        double bv = ninf;
-        int be = -1;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            if (ok[q] && !((taken >> q) & 1u) && (be < 0 || z[q] > bv)) {
-                bv = z[q];
-                be = lane + kWave * q;
-            }
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double ov = __shfl_xor(bv, off, kWave);
-            const int oe = __shfl_xor(be, off, kWave);
-            if (oe >= 0 && (be < 0 || ov > bv || (ov == bv && oe < be))) {
-                bv = ov;
-                be = oe;
-            }
-        }
-        // every lane now holds the same winner `be` (ties resolved to the lower index)
+        const int be = __builtin_amdgcn_readfirstlane(*(volatile int32_t*)&sel_idx[wave][r]);
         const int oq = be / kWave, ol = be % kWave;
         double mine = 0.0;
 #pragma unroll
         for (int q = 0; q < Q; ++q) mine = (q == oq) ? p[q] : mine;
-        const double wv = __shfl(mine, ol, kWave);
-        if (lane == ol) taken |= 1u << oq;
+        const uint64_t u = (uint64_t)__double_as_longlong(mine);
+        const double wv = __longlong_as_double((long long)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), ol) << 32 |
+                                                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, ol)));
         wsum += wv;
-        if (lane == 0) {
-            sel_idx[wave][r] = be;
-            wsel[wave][r] = wv;
-        }
+        if (lane == 0) wsel[wave][r] = wv;
     }
     const double scale = (gating == MOE_GATE_SOFTMAX) ? 1.0 : 1.0 / wsum;
     __builtin_amdgcn_wave_barrier();
@@ -343,78 +528,22 @@ __device__ __forceinline__ void gate_and_select(double (&z)[Q], const bool (&ok)
     }
 }
 
-// The logits of the experts that can be among the k largest, recomputed exactly (see
-// fast_logits_kernel for the bound).  z holds the fast logits (bias included); on return the
-// candidates' entries are exact: dot product in fp64 (bf16 operands and their products are
-// exact there; the order of the additions moves the sum by ~1e-15), plus the bias.
-// Why this is enough: let b = 2^-17 |x_t| max_e |w_e| >= every |z_fast - z|, and v_k the k-th
-// largest fast value.  The k experts with the largest fast values have true logits >= v_k - b, so
-// the true k-th largest logit is >= v_k - b, every expert of the true top-k has z >= v_k - b and
-// therefore z_fast >= v_k - 2b: it is a candidate.  Every non-candidate has z <= z_fast + b <
-// v_k - b, i.e. lies below k candidates' exact values, also when it keeps its fast value: the
-// selection over the mixed array picks the same experts in the same order as over exact logits.
-// The softmax denominator takes the non-candidates' fast values (relative error of a weight
-// ~1e-7 at most: their scores weigh in with the error bound times their share).
+// The logits of the experts that can be among the k largest, recomputed in fp64 (bf16 operands and their products are
+// exact there; the order of the additions moves the sum by ~1e-15), plus the bias: for tokens whose k + 1 largest logits
+// hold neighbours closer than the error of digit_logits_kernel can rule on.  vk: the k-th largest value in z; margin: twice
+// the error bound b of z, or infinity (or NaN) to recompute every expert.
+// Why this is enough: the k experts with the largest z have true logits >= vk - b, so the true k-th largest logit is
+// >= vk - b, every expert of the true top-k has z >= vk - 2b: it is a candidate.  Every non-candidate's value is < vk - 2b,
+// i.e. lies below k candidates' exact values, also when it keeps its place in z: the selection over the mixed
+// array picks the same experts in the same order as over exact logits.
 // cand_list: LDS, kMaxExperts ints per wavefront.
-__device__ __forceinline__ void refine_candidates(double (&z)[kLogitsPerLane], const bool (&ok)[kLogitsPerLane],
-                                                  int lane, int t, int k, int E, int d, int KS, size_t EP,
+template <int Q>
+__device__ __forceinline__ void refine_candidates(double (&z)[Q], const bool (&ok)[Q],
+                                                  int lane, int t, double vk, double margin, int d,
                                                   const uint16_t* __restrict__ x, const uint16_t* __restrict__ wr,
-                                                  const float* __restrict__ bias, const float* __restrict__ wsq,
-                                                  int32_t* cand_list) {
-    constexpr int Q = kLogitsPerLane;
-    constexpr int CB = 12;  // candidates recomputed per pass over the token row (k = 8 gives 8, 9, rarely 10)
-    const double ninf = -__builtin_huge_val();
+                                                  const float* __restrict__ bias, int32_t* cand_list) {
+    constexpr int CB = 4;   // candidates recomputed per pass over the token row
     const uint16_t* xr = x + (size_t)t * d;
-    // |x_t|^2 (fp32: squares of bf16 are exact, the sum is good to 1e-6 relative) and max_e |w_e|^2
-    float xs = 0.0f;
-    for (int p = lane; p < d / 8; p += kWave) {
-        const uint4 v = *reinterpret_cast<const uint4*>(xr + (size_t)p * 8);
-        const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float lo = __uint_as_float(w4[i] << 16), hi = __uint_as_float(w4[i] & 0xffff0000u);
-            xs = fmaf(lo, lo, fmaf(hi, hi, xs));
-        }
-    }
-    float wm = 0.0f;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int e = lane + kWave * q;
-        if (ok[q]) {
-            float sum = 0.0f;
-            for (int s0 = 0; s0 < KS; ++s0) sum += wsq[(size_t)s0 * EP + e];
-            wm = fmaxf(wm, sum);
-        }
-    }
-    const double x2 = wave_sum((double)xs), w2 = wave_max((double)wm);
-    // twice the bound, with 1 % for the rounding of the two norms; NaN or inf makes every expert a candidate
-    const double margin = 2.02 * 0x1p-17 * sqrt(x2 * w2);
-    // k-th largest fast value
-    unsigned taken = 0;
-    double vk = ninf;
-    for (int r = 0; r < k; ++r) {
-        double bv = ninf;
-        int bq = -1;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            if (ok[q] && !((taken >> q) & 1u) && (bq < 0 || z[q] > bv)) {
-                bv = z[q];
-                bq = q;
-            }
-        }
-        int be = bq < 0 ? -1 : lane + kWave * bq;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double ov = __shfl_xor(bv, off, kWave);
-            const int oe = __shfl_xor(be, off, kWave);
-            if (oe >= 0 && (be < 0 || ov > bv || (ov == bv && oe < be))) {
-                bv = ov;
-                be = oe;
-            }
-        }
-        if (be >= 0 && lane == be % kWave) taken |= 1u << (be / kWave);
-        vk = bv;
-    }
     // candidate list (ascending expert index inside each q; the order does not matter)
     int n_cand = 0;
 #pragma unroll
@@ -463,16 +592,16 @@ __device__ __forceinline__ void refine_candidates(double (&z)[kLogitsPerLane], c
 }
 
 // ---- kernel 2: gate + top-k, one wavefront per token ------------------------------------------
-// FAST: `part` holds the fast logits' slices (see fast_logits_kernel), refined here.
-// T16, E16: padded tokens and experts in units of 16 (FAST pads tokens to 64 and experts to 32, else both to 16).
-template <bool FAST, int Q>
+// DIGITS: `part` holds the slices of digit_logits_kernel, with the rows' norms for their error bound.
+// T16, E16: padded tokens and experts in units of 16.
+template <bool DIGITS, int Q>
 __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict__ part,
                                                        const float* __restrict__ bias,
                                                        int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
                                                        int T, int E, int k, int gating, int T16, int E16, int KS,
                                                        int32_t* __restrict__ zero, int zero_n,
                                                        const uint16_t* __restrict__ x, const uint16_t* __restrict__ wr,
-                                                       int d, const float* __restrict__ wsq) {
+                                                       int d, const float4* __restrict__ norms) {
     __shared__ double wsel[kWavesPerBlock][kMaxExperts];
     __shared__ int32_t sel_idx[kWavesPerBlock][kMaxExperts];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -488,22 +617,55 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict
     for (int q = 0; q < Q; ++q) {
         const int e = lane + kWave * q;
         ok[q] = e < E;
-        double v = ninf;
-        if (ok[q]) {
-            v = bias ? (double)bias[e] : 0.0;
-            for (int s0 = 0; s0 < KS; s0 += 8) {   // slices in fixed order; 8 independent loads at a time
-                double tmp[8];
+        z[q] = (ok[q] && bias) ? (double)bias[e] : 0.0;
+    }
+    for (int s0 = 0; s0 < KS; s0 += 8) {   // slices in fixed order; 8 Q independent loads at a time
+        double tmp[Q][8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    tmp[u] = (s0 + u < KS) ? part[((size_t)(s0 + u) * T16 * 16 + t) * EP + e] : 0.0;
+        for (int q = 0; q < Q; ++q)
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v += tmp[u];
+            for (int u = 0; u < 8; ++u)
+                tmp[q][u] = (ok[q] && s0 + u < KS) ? part[((size_t)(s0 + u) * T16 * 16 + t) * EP + lane + kWave * q] : 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) z[q] += tmp[q][u];
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) z[q] = ok[q] ? z[q] : ninf;
+    bool refined = !DIGITS;
+    gate_and_select(z, ok, lane, wave, t, k, E, gating, wsel, sel_idx, topk_idx, topk_w, [&](double vk, double gap, unsigned taken) {
+        if (refined) return false;
+        refined = true;
+        float4 w = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (ok[q]) {
+                const float4 n = norms[lane + kWave * q];
+                w = make_float4(fmaxf(w.x, n.x), fmaxf(w.y, n.y), fmaxf(w.z, n.z), fmaxf(w.w, n.w));
             }
         }
-        z[q] = v;
-    }
-    if constexpr (FAST) refine_candidates(z, ok, lane, t, k, E, d, KS, EP, x, wr, bias, wsq, sel_idx[wave]);
-    gate_and_select(z, ok, lane, wave, t, k, gating, wsel, sel_idx, topk_idx, topk_w);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1)
+            w = make_float4(fmaxf(w.x, __shfl_xor(w.x, off, kWave)), fmaxf(w.y, __shfl_xor(w.y, off, kWave)),
+                            fmaxf(w.z, __shfl_xor(w.z, off, kWave)), fmaxf(w.w, __shfl_xor(w.w, off, kWave)));
+        const float4 n = norms[EP + t];
+        // the bound of digit_logits_kernel, and 2^-40 of |x| |w| for the fp64 sums on either side
+        const double b = (double)n.y * w.z + (double)n.z * w.y + (double)n.w * w.x + (double)n.x * w.w + 0x1p-40 * n.x * w.x;
+        double margin = 2.02 * b;
+        if (k < E) {
+            int be;
+            const double step = vk - next_best(z, ok, taken, lane, be);
+            if (!(step >= gap) && gap == gap) gap = step;
+        }
+        // A looser bound (an element hundreds of times the others) says too little about the weights' last bits: the
+        // selected experts' logits are recomputed, and all of them where the weights depend on all.
+        const bool loose = !(b <= 0x1p-21);
+        if (loose && gating == MOE_GATE_SOFTMAX) margin = __builtin_huge_val();
+        if (!loose && gap > margin) return false;    // written so that a NaN anywhere recomputes
+        refine_candidates(z, ok, lane, t, vk, margin, d, x, wr, bias, sel_idx[wave]);
+        return true;
+    });
 }
 
 // ---- few experts (E <= 8): the whole router in one kernel, one workgroup per token ----------
@@ -592,37 +754,53 @@ __global__ __launch_bounds__(kThreads) void route_direct_kernel(const uint16_t* 
         for (int w = 0; w < kWavesPerBlock; ++w) v += partial[w][lane];
         z[0] = v;
     }
-    gate_and_select(z, ok, lane, 0, t, k, gating, wsel, sel_idx, topk_idx, topk_w);
+    gate_and_select(z, ok, lane, 0, t, k, E, gating, wsel, sel_idx, topk_idx, topk_w, [](double, double, unsigned) { return false; });
 }
+
+// Where the int8 form pays: from about 6e8 multiply-adds on, for at least 32 experts (it pads them to 64, 128 or 256).  Router
+// alone, us, fp64 / int8: 256 experts (d 7168) 256 tokens (4.7e8) 36 / 38, 512 52 / 42, 1024 82 / 49, 2048 149 / 67, 4096
+// 286 / 113; 160 (5120) 1024 tokens 52 / 40; 128 (4096) 1024 tokens (5.4e8) 34 / 35, 1500 44 / 34, 4096 89 / 50; 64 (3584)
+// 2048 tokens (4.7e8) 33 / 34, 3000 44 / 37, 4096 49 / 42; 32 (4096) 4096 tokens (5.4e8) 38 / 40, 8192 69 / 61; 16 (4096)
+// 8192 tokens 40 / 62.  Error of the weights against float64 in every one of these: the same four digits (2.5e-8) in both forms.
+// The three launches of the int8 form take about 13 us (digits), 5 + 0.9 a step (products) and 12 (selection), of which 5 each
+// are a launch's own.
+bool digits_pay(const moe_config& c) { return c.E >= 32 && (double)c.T * c.E * c.d > 6e8; }
 
 struct RoutePlan {
     int T16, E16, KS, NT;
-    bool fast;          // bf16 logits + exact candidates
-    int TP, EP;         // fast: tokens padded to 64, experts padded to 32
+    bool digits;        // logits on the int8 matrix cores
+    int EGW;            // digits: 64-expert groups
+    int TP, EP;         // digits: padded tokens and experts
 };
 
-// mode: the test knob's value.  -1 the rule, 1 every logit in fp64, 0 the bf16 first pass from 256 tokens on.
+size_t digit_bytes(const RoutePlan& p, int d) {
+    return (size_t)p.KS * p.TP * p.EP * sizeof(double) + (size_t)p.EP * d * 4 + (size_t)(p.EP + p.TP) * (sizeof(float4) + sizeof(int32_t));
+}
+
+// mode: the test knob's value.  -1 the rule, 1 every logit in fp64, 0 the int8 form from 256 tokens on.
 RoutePlan plan(const moe_config& c, int mode) {
     RoutePlan p{};
-    // From half a million logits on (256 experts: 2048 tokens).  Measured, us, all in fp64 / first pass and candidates:
-    // 256 experts (d 7168) 512 tokens 57 / 63, 1024 86 / 67, 2048 152 / 77, 4096 289 / 129; 160 experts (d 5120) 1024 tokens
-    // 55 / 48, 2048 92 / 55, 4096 208 / 93; 128 experts (d 4096) 2048 tokens 53 / 41, 4096 92 / 69; 64 experts (d 3584) 4096
-    // tokens 53 / 78, 8192 93 / 139.  By time alone the line would be at about 2^18 for more than 64 experts and nowhere up to
-    // 64 (the candidates, ~k + 1 rows per token, are then too large a part of all).  It lies higher because below it the softmax
-    // weights keep the last 0.5-1.4 % of precision that the non-candidates' share of the denominator takes (relative error
-    // 2.51e-8 / 2.53e-8 at 256 experts, 1024 tokens; with the other two gates the two forms agree).
-    // Its 32-bit byte offsets hold: every entry point refuses T d 2 >= 2^32 bytes, and here E <= 256 <= T.
-    p.fast = mode != 1 && c.E > 8 && (mode == 0 ? c.T >= 256 : (long long)c.T * c.E >= (1ll << 19));
-    if (p.fast) {
-        p.TP = (c.T + kFastTokens - 1) / kFastTokens * kFastTokens;
-        p.EP = (c.E + 31) / 32 * 32;
-        const long long tiles = (long long)(p.TP / kFastTokens) * ((p.EP + kFastExperts - 1) / kFastExperts);
+    // 32-bit byte offsets hold: every entry point refuses T d 2 >= 2^32 bytes.
+    p.digits = mode != 1 && c.E > 8 && c.d <= kMaxDigitDim && (mode == 0 ? c.T >= 256 : digits_pay(c));
+    if (p.digits) {
+        p.EGW = c.E <= 64 ? 1 : c.E <= 128 ? 2 : 4;
+        p.EP = 64 * p.EGW;
         const int nstep = c.d / 64;
-        long long ks = (512 + tiles - 1) / tiles;           // two workgroups per CU
-        if (ks > 8) ks = 8;                                 // the refining kernel sums the slices
-        if (ks > nstep / 2) ks = nstep / 2;
-        if (ks < 1) ks = 1;
-        p.KS = (int)ks;
+        const int rt = 4 / p.EGW * 32;
+        const long long tiles = ((long long)c.T + rt - 1) / rt;
+        p.TP = (int)(tiles * rt);
+        // Slices: rounds of workgroups x steps of each (a quarter more where a slice of the experts' digits fills an XCD's L2),
+        // a workgroup's start and end worth eight steps, and the slices' sum.
+        double best = 1e30;
+        for (int ks = 1; ks <= 16 && ks <= nstep; ks *= 2) {
+            const int steps = (nstep + ks - 1) / ks;
+            const double slow = (double)p.EP * 256 * steps > 2e6 ? 1.25 : 1.0;
+            const double cost = (double)((tiles * ks + 255) / 256) * (slow * steps + 8.0) + 0.3 * ks;
+            if (cost < best) {
+                best = cost;
+                p.KS = ks;
+            }
+        }
         return p;
     }
     p.T16 = (c.T + 15) / 16;
@@ -662,8 +840,8 @@ size_t route_workspace_bytes(const moe_config& c) {
     size_t need = 0;
     for (int mode = -1; mode <= 1; ++mode) {
         const RoutePlan p = plan(c, mode);
-        const size_t bytes = p.fast ? (size_t)p.KS * p.EP * ((size_t)p.TP * sizeof(double) + sizeof(float))
-                                    : (size_t)p.KS * p.T16 * 16 * p.E16 * 16 * sizeof(double);
+        const size_t bytes = p.digits ? digit_bytes(p, c.d)
+                                      : (size_t)p.KS * p.T16 * 16 * p.E16 * 16 * sizeof(double);
         need = bytes > need ? bytes : need;
     }
     return need;
@@ -678,14 +856,30 @@ hipError_t launch_route(const moe_config& c, const uint16_t* x, const uint16_t* 
         return hipGetLastError();
     }
     const RoutePlan p = plan(c, knob(kKnobRouteExact));
-    if (p.fast) {
+    const dim3 topk_grid((c.T + kWavesPerBlock - 1) / kWavesPerBlock);
+    if (p.digits) {
         double* part = (double*)workspace;
-        float* wsq = (float*)(part + (size_t)p.KS * p.TP * p.EP);
-        hipLaunchKernelGGL(fast_logits_kernel, dim3((p.TP / kFastTokens) * ((p.EP + kFastExperts - 1) / kFastExperts) * p.KS), dim3(kThreads), 0, s, x,
-                           wr, part, wsq, c.T, c.d, c.E, p.TP, p.EP, p.KS);
-        hipLaunchKernelGGL((topk_kernel<true, kLogitsPerLane>), dim3((c.T + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kThreads), 0, s,
-                           part, bias, topk_idx, topk_w, c.T, c.E, c.k, c.gating, p.TP / 16, p.EP / 16, p.KS, zero, zero_per_token,
-                           x, wr, c.d, wsq);
+        float4* norms = (float4*)(part + (size_t)p.KS * p.TP * p.EP);
+        int32_t* exps = (int32_t*)(norms + p.EP + p.TP);
+        uint8_t* wdig = (uint8_t*)(exps + p.EP + p.TP);      // 16-byte aligned: EP and TP are multiples of 32
+        hipLaunchKernelGGL(digits_kernel, dim3((p.EP + p.TP) / kWavesPerBlock), dim3(kThreads), 0, s, x, wr, wdig, exps, norms, c.T, c.d, c.E, p.EP);
+        auto logits = [&](auto kern, int rt) {
+            hipLaunchKernelGGL(kern, dim3(p.TP / rt * p.KS), dim3(kThreads), 0, s, x, wdig, exps, part, c.T, c.d, p.TP, p.KS);
+        };
+        auto select = [&](auto kern) {
+            hipLaunchKernelGGL(kern, topk_grid, dim3(kThreads), 0, s, part, bias, topk_idx, topk_w, c.T, c.E, c.k, c.gating, p.TP / 16,
+                               p.EP / 16, p.KS, zero, zero_per_token, x, wr, c.d, norms);
+        };
+        if (p.EGW == 1) {
+            logits(digit_logits_kernel<1>, 128);
+            select(topk_kernel<true, 1>);
+        } else if (p.EGW == 2) {
+            logits(digit_logits_kernel<2>, 64);
+            select(topk_kernel<true, 2>);
+        } else {
+            logits(digit_logits_kernel<4>, 32);
+            select(topk_kernel<true, 4>);
+        }
         return hipGetLastError();
     }
     const int units = p.T16 * ((p.E16 + p.NT - 1) / p.NT) * p.KS;
@@ -698,7 +892,7 @@ hipError_t launch_route(const moe_config& c, const uint16_t* x, const uint16_t* 
         hipLaunchKernelGGL(logits_kernel<1>, grid, dim3(kThreads), 0, s, x, wr, part, c.T, c.d, c.E, p.T16, p.E16,
                            p.KS, units);
     auto select = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3((c.T + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kThreads), 0, s, part, bias, topk_idx,
+        hipLaunchKernelGGL(kern, topk_grid, dim3(kThreads), 0, s, part, bias, topk_idx,
                            topk_w, c.T, c.E, c.k, c.gating, p.T16, p.E16, p.KS, zero, zero_per_token, nullptr, nullptr, 0, nullptr);
     };
     if (c.E <= 64) select(topk_kernel<false, 1>);
