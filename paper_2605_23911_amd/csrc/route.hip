@@ -151,9 +151,9 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
 // evaluation for the purpose of the weights, and topk_kernel recomputes in fp64 what stands closer together than the bound.
 //
 // What bounds it: the int8 matrix rate, 13 products (256 experts, 1024 tokens, d = 7168: 49 GOP, 10 us at 5 POP/s).
-// A wavefront takes 64 experts (two 32-expert operands) and 32 JT tokens, the experts' digits straight from memory in operand
+// A wavefront takes 64 experts (two 32-expert operands) and 32 tokens, the experts' digits straight from memory in operand
 // order (digits_kernel lays them out), one 32-element step ahead in registers; the tokens come as bf16 by DMA
-// through LDS, shared by the wavefronts that take other experts, and are cut into digits in registers between the matrix
+// through LDS and are cut into digits in registers between the matrix
 // instructions (7 vector instructions per element, about half of the issue slots that 13 products of 64 experts leave).
 constexpr int kMinExp = -90;         // smallest E: keeps every scale a normal fp32 number
 constexpr int kMaxDigitDim = 32768;  // 4 pairs x 2^14 x this many elements fill an int32
@@ -272,23 +272,25 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __rest
     }
 }
 
-// part[ks][t][e], t < TP, e < EP = 64 EGW, fp64.  EGW wavefronts of the four take 64 experts each, 4 / EGW take other
-// tokens.  A lane supplies 16 consecutive k of one row per operand (row lane % 32, half lane / 32 of the 32-element step) and
+// part[ks][t][e], t < TP, e < EP, fp64.  A workgroup takes 128 tokens x 64 experts, 32 tokens a wavefront: the four read the
+// same digits of the experts, three of them from L1 (256 experts side by side on 32 tokens: every wavefront's from L2).
+// A lane supplies 16 consecutive k of one row per operand (row lane % 32, half lane / 32 of the 32-element step) and
 // receives D[token 8(v/4) + 4(lane/32) + v%4][expert lane%32].  Workgroup b takes slice b % KS of d: with 8 slices (or 4, 16)
 // the experts' digits of a slice are read by one XCD (two, two) only and stay in its L2.
 // One wavefront per SIMD, software-pipelined by hand: while the 26 matrix instructions of a 32-element step run, the next
-// step's tokens are cut into digits (four vector instructions behind each) and its experts' digits are on their way.
-template <int EGW>
+// step's tokens are cut into digits (four vector instructions behind each) and the experts' digits of the step after that
+// are on their way.
+constexpr int kDigitTokens = 128, kDigitExperts = 64;
 __global__ __launch_bounds__(kThreads) void digit_logits_kernel(const uint16_t* __restrict__ x, const uint8_t* __restrict__ wdig,
                                                                const int32_t* __restrict__ exps, double* __restrict__ part,
-                                                               int T, int d, int TP, int KS) {
-    constexpr int TW = 4 / EGW, RT = TW * 32, BUF = RT * 128, EP = EGW * 64, NB = 3;
+                                                               int T, int d, int TP, int EP, int KS) {
+    constexpr int RT = kDigitTokens, TW = RT / 32, BUF = RT * 128, NB = 3;
     __shared__ __attribute__((aligned(1024))) char ring[NB * BUF];
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int li = lane & 31, half = lane >> 5;
-    const int we = wave % EGW, wt = wave / EGW;
-    const int ks = blockIdx.x % KS, t0 = blockIdx.x / KS * RT;
+    const int EG = EP / kDigitExperts;
+    const int ks = blockIdx.x % KS, eg = blockIdx.x / KS % EG, t0 = blockIdx.x / (KS * EG) * RT;
     const int nstep = d / 64, per = (nstep + KS - 1) / KS;
     const int g0 = ks * per, g1 = g0 + per < nstep ? g0 + per : nstep;
 
@@ -306,9 +308,9 @@ __global__ __launch_bounds__(kThreads) void digit_logits_kernel(const uint16_t* 
         for (int q = 0; q < TW; ++q) lds_dma16_at<false>(xb, xo[q], x_dst + buf + q * 4096);
     };
     const uint32_t eb_bytes = (uint32_t)(d / 32) * 4096u;
-    const uint8_t* wp = wdig + (size_t)we * 2 * eb_bytes;        // wave-uniform
+    const uint8_t* wp = wdig + (size_t)eg * 2 * eb_bytes;        // uniform
     const uint32_t wl[2] = {(uint32_t)lane * 16u, eb_bytes + (uint32_t)lane * 16u};
-    const int r = wt * 32 + li, xsw = (r ^ (r >> 3)) & 7;
+    const int r = wave * 32 + li, xsw = (r ^ (r >> 3)) & 7;
     const char* xrow = ring + r * 128;
     const float xscale = exp2i(29 - exps[EP + t0 + r]);
 
@@ -389,9 +391,9 @@ __global__ __launch_bounds__(kThreads) void digit_logits_kernel(const uint16_t* 
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-        const int e = (we * 2 + b) * 32 + li;
+        const int e = (eg * 2 + b) * 32 + li;
         const int ew = exps[e];
-        const int tr = t0 + wt * 32 + 4 * half;
+        const int tr = t0 + wave * 32 + 4 * half;
         double* out = part + ((size_t)ks * TP + tr) * EP + e;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -769,7 +771,6 @@ bool digits_pay(const moe_config& c) { return c.E >= 32 && (double)c.T * c.E * c
 struct RoutePlan {
     int T16, E16, KS, NT;
     bool digits;        // logits on the int8 matrix cores
-    int EGW;            // digits: 64-expert groups
     int TP, EP;         // digits: padded tokens and experts
 };
 
@@ -783,12 +784,10 @@ RoutePlan plan(const moe_config& c, int mode) {
     // 32-bit byte offsets hold: every entry point refuses T d 2 >= 2^32 bytes.
     p.digits = mode != 1 && c.E > 8 && c.d <= kMaxDigitDim && (mode == 0 ? c.T >= 256 : digits_pay(c));
     if (p.digits) {
-        p.EGW = c.E <= 64 ? 1 : c.E <= 128 ? 2 : 4;
-        p.EP = 64 * p.EGW;
+        p.EP = (c.E + kDigitExperts - 1) / kDigitExperts * kDigitExperts;
+        p.TP = (c.T + kDigitTokens - 1) / kDigitTokens * kDigitTokens;
         const int nstep = c.d / 64;
-        const int rt = 4 / p.EGW * 32;
-        const long long tiles = ((long long)c.T + rt - 1) / rt;
-        p.TP = (int)(tiles * rt);
+        const long long tiles = (long long)(p.TP / kDigitTokens) * (p.EP / kDigitExperts);
         // Slices: rounds of workgroups x steps of each (a quarter more where a slice of the experts' digits fills an XCD's L2),
         // a workgroup's start and end worth eight steps, and the slices' sum.
         double best = 1e30;
@@ -863,23 +862,15 @@ hipError_t launch_route(const moe_config& c, const uint16_t* x, const uint16_t* 
         int32_t* exps = (int32_t*)(norms + p.EP + p.TP);
         uint8_t* wdig = (uint8_t*)(exps + p.EP + p.TP);      // 16-byte aligned: EP and TP are multiples of 32
         hipLaunchKernelGGL(digits_kernel, dim3((p.EP + p.TP) / kWavesPerBlock), dim3(kThreads), 0, s, x, wr, wdig, exps, norms, c.T, c.d, c.E, p.EP);
-        auto logits = [&](auto kern, int rt) {
-            hipLaunchKernelGGL(kern, dim3(p.TP / rt * p.KS), dim3(kThreads), 0, s, x, wdig, exps, part, c.T, c.d, p.TP, p.KS);
-        };
+        hipLaunchKernelGGL(digit_logits_kernel, dim3(p.TP / kDigitTokens * (p.EP / kDigitExperts) * p.KS), dim3(kThreads), 0, s, x, wdig, exps,
+                           part, c.T, c.d, p.TP, p.EP, p.KS);
         auto select = [&](auto kern) {
             hipLaunchKernelGGL(kern, topk_grid, dim3(kThreads), 0, s, part, bias, topk_idx, topk_w, c.T, c.E, c.k, c.gating, p.TP / 16,
                                p.EP / 16, p.KS, zero, zero_per_token, x, wr, c.d, norms);
         };
-        if (p.EGW == 1) {
-            logits(digit_logits_kernel<1>, 128);
-            select(topk_kernel<true, 1>);
-        } else if (p.EGW == 2) {
-            logits(digit_logits_kernel<2>, 64);
-            select(topk_kernel<true, 2>);
-        } else {
-            logits(digit_logits_kernel<4>, 32);
-            select(topk_kernel<true, 4>);
-        }
+        if (c.E <= 64) select(topk_kernel<true, 1>);
+        else if (c.E <= 128) select(topk_kernel<true, 2>);
+        else select(topk_kernel<true, 4>);
         return hipGetLastError();
     }
     const int units = p.T16 * ((p.E16 + p.NT - 1) / p.NT) * p.KS;
