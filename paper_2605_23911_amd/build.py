@@ -13,7 +13,7 @@ LIB_NAME = "libmoe_mi355x.so"
 LIB_PATH = os.path.join(PKG_DIR, LIB_NAME)
 PROBE_SRC = "mfma_ceiling_probe.hip"   # stand-alone measurement program, not linked into the library
 PROBE_PATH = os.path.join(PKG_DIR, "mfma_ceiling_probe")
-SOURCES = ["ffn_down_wide.hip", "ffn_gate_up.hip", "ffn_down.hip", "api.hip", "route.hip", "permute.hip", "pack.hip", "combine.hip"]
+SOURCES = ["ffn_down_wide.hip", "ffn_gate_up.hip", "ffn_gate_up_routed.hip", "ffn_down.hip", "api.hip", "route.hip", "permute.hip", "pack.hip", "combine.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

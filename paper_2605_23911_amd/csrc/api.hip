@@ -323,14 +323,18 @@ moe_status moe_forward_staged(const moe_config* c, const void* x, const void* W_
         e = launch_route(*c, (const uint16_t*)x, (const uint16_t*)W_r, bias, topk_idx, topk_w, route_ws,
                          fuse ? arrive : nullptr, combine_groups(*c), s);
     mark(1);
-    if (e == hipSuccess)
+    // A few rows are permuted by the gate+up launch itself, which saves a launch (see permute_inside in ffn_kernels.hpp).
+    const bool inside = permutes_inside(*c, pgu != nullptr) && !down_deals(*c, M, pdn != nullptr);
+    if (e == hipSuccess && !inside)
         e = launch_permute_index(*c, topk_idx, counts, offsets, row_of, src_of, hist, M, blocks, num_blocks, blocks_mix, num_heavy, s);
     mark(2);
     // The row gather of the permutation is folded into the gate+up tile loads (row r is read from
     // x[src_of[r] / k]); the permuted copy of x that moe_permute can write is not needed here.
     if (e == hipSuccess)
-        e = launch_gate_up(*c, M, (const uint16_t*)x, c->d, src_of, c->F, offsets, blocks, num_blocks,
-                           (const uint16_t*)W_gate, (const uint16_t*)W_up, pgu, h, s);
+        e = inside ? launch_routed_gate_up(*c, M, (const uint16_t*)x, topk_idx, {counts, offsets, row_of, src_of, blocks, num_blocks},
+                                           (const uint16_t*)W_gate, (const uint16_t*)W_up, pgu, h, s)
+                   : launch_gate_up(*c, M, (const uint16_t*)x, c->d, src_of, c->F, offsets, blocks, num_blocks,
+                                    (const uint16_t*)W_gate, (const uint16_t*)W_up, pgu, h, s);
     mark(3);
     if (e == hipSuccess)
         e = launch_down(*c, M, h, c->F, offsets, blocks, num_blocks, blocks_mix, num_heavy, (const uint16_t*)W_down, pdn, y_perm,

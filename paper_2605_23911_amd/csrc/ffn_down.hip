@@ -54,6 +54,12 @@ int pick(int M, bool packed, const moe_config& c) {
 
 }  // namespace
 
+bool down_deals(const moe_config& c, int32_t M, bool packed) {
+    int id = forced_variant(kKnobDownVariant, kNumDown, M, packed, kDown);
+    if (id < 0) id = pick(M, packed, c);
+    return id == 7;
+}
+
 bool down_fuses_combine(const moe_config& c, int32_t M, bool packed) {
     int id = forced_variant(kKnobDownVariant, kNumDown, M, packed, kDown);
     if (id < 0) id = pick(M, packed, c);

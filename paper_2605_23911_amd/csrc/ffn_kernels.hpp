@@ -78,12 +78,20 @@ struct GemmArgs {
     int32_t* comb_arrive;       // [T, comb_groups] rows of the token written so far per 128-feature group (zero at launch)
     uint16_t* comb_y;           // [T, N] layer output
     int comb_k, comb_groups;    // experts per token; ceil(N / 128)
+    // Permutation done by the gate+up launch itself (permute_inside; all null / 0 when it is a launch of its own):
+    const int32_t* topk_idx;    // [R] the router's choice
+    PermuteOut perm;            // what the later stages read, written by workgroup 0
+    int E;
+    int tables_in_lds;          // src, offsets and blocks are in the LDS that the token ring will use
 };
 
 typedef hipError_t (*launch_fn)(const GemmArgs&, int, hipStream_t);
 
 // The down projection's per-block-regime kernels with two weight blocks per wavefront are
 // compiled in a translation unit of their own (ffn_down_wide.hip) to shorten the build.
+// (So are, in ffn_gate_up_routed.hip, the gate+up kernels with the permutation inside.)
+hipError_t launch_routed_mixed(const GemmArgs& a, int max_blocks, hipStream_t s);
+hipError_t launch_routed_mixed_half(const GemmArgs& a, int max_blocks, hipStream_t s);
 hipError_t launch_down_mixed_wide_nt(const GemmArgs& a, int max_blocks, hipStream_t s);
 hipError_t launch_down_mixed_wide(const GemmArgs& a, int max_blocks, hipStream_t s);
 hipError_t launch_down_rows_wide(const GemmArgs& a, int max_blocks, hipStream_t s);
@@ -262,6 +270,114 @@ __device__ __forceinline__ void store_block(const f32x16& g, const f32x16& u, ui
     }
 }
 
+// Up to 1024 rows (permutes_inside): every workgroup of the gate+up launch sorts the router's choice by itself, up to four
+// slots per thread, and reads its own place in the schedule from LDS: same counting sort, same tables as permute.hip's.
+// It takes the place of a launch (5-8 us) and, in each workgroup, of the chain of loads from the tables that the launch
+// wrote.  Workgroup 0 leaves the tables in memory for the later stages.  Costs and gains: permutes_inside.
+constexpr int kSmallGroups = kSmallRows / kThreads;
+constexpr int kSmallBlocks = kSmallRows / 32 + kMaxExperts;   // schedule entries: R / M + min(R, E), M >= 32
+__device__ __forceinline__ void permute_inside(const GemmArgs& a, GemmArgs& b, int32_t* lds) {
+    int32_t* off = lds;                            // [E + 1]
+    int32_t* blk = off + kMaxExperts + 4;          // [kSmallBlocks, 2]
+    int32_t* src = blk + 2 * kSmallBlocks;         // [R]
+    int32_t* nblk = src + kSmallRows;              // the number of entries, and the wavefronts' sums
+    int32_t(*wc)[kMaxExperts] = reinterpret_cast<int32_t(*)[kMaxExperts]>(nblk + 16);
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    constexpr int W = kThreads / kWave;
+    static_assert(kThreads == kMaxExperts, "one expert per thread");
+    const int G = (a.R + kThreads - 1) / kThreads; // 64-slot groups per wavefront, in slot order
+#pragma unroll
+    for (int w = 0; w < W; ++w) wc[w][tid] = 0;
+    int e_of[kSmallGroups];
+#pragma unroll
+    for (int g = 0; g < kSmallGroups; ++g) {
+        const int j = (wave * G + g) * kWave + lane;
+        e_of[g] = -1;
+        if (g < G && j < a.R) {
+            const int e = a.topk_idx[j];
+            e_of[g] = e < 0 ? 0 : (e >= a.E ? a.E - 1 : e);   // as in permute.hip: an id outside the experts never leaves the buffers
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < kSmallGroups; ++g)
+        if (e_of[g] >= 0) atomicAdd(&wc[wave][e_of[g]], 1);
+    __syncthreads();
+    int n = 0;                                     // rows of expert tid
+#pragma unroll
+    for (int w = 0; w < W; ++w) n += wc[w][tid];
+    const int nb = (n + a.M - 1) / a.M;
+    const int v = n | nb << 16;                    // both at most 1024 in all: one scan for the two
+    int inc = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int up = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += up;
+    }
+    if (lane == kWave - 1) nblk[4 + wave] = inc;
+    __syncthreads();
+    int base = inc - v;
+#pragma unroll
+    for (int w = 0; w < W; ++w) base += w < wave ? nblk[4 + w] : 0;
+    const int row0 = base & 0xffff, block0 = base >> 16;
+    if (tid < a.E) {
+        off[tid] = row0;
+        if (tid == a.E - 1) off[a.E] = row0 + n, nblk[0] = block0 + nb;
+        int run = row0;                            // counts per wavefront -> first row per wavefront
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const int c = wc[w][tid];
+            wc[w][tid] = run;
+            run += c;
+        }
+    }
+    for (int q = 0; q < nb; ++q) {
+        blk[2 * (block0 + q)] = tid;
+        blk[2 * (block0 + q) + 1] = q * a.M;
+    }
+    __syncthreads();
+    volatile int32_t* next = wc[wave];
+#pragma unroll
+    for (int g = 0; g < kSmallGroups; ++g) {
+        if (g < G) {                               // uniform over the workgroup
+            const int e = e_of[g];
+            // lanes holding the same expert: AND over the 8 id bits of agreeing ballots
+            unsigned long long same = __ballot(e >= 0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const unsigned long long bal = __ballot((e >> i) & 1);
+                same &= ((e >> i) & 1) ? bal : ~bal;
+            }
+            if (e >= 0) {
+                const unsigned long long below = same & ((1ull << lane) - 1ull);
+                const int first = next[e], pos = first + __popcll(below), j = (wave * G + g) * kWave + lane;
+                src[pos] = j;
+                if (below == 0) next[e] = first + __popcll(same);   // lowest lane of the set advances it
+                if (blockIdx.x == 0) {
+                    a.perm.row_of[j] = pos;
+                    a.perm.src_of[pos] = j;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+    if (blockIdx.x == 0) {
+        if (tid < a.E) {
+            a.perm.counts[tid] = n;
+            a.perm.offsets[tid] = row0;
+            if (tid == a.E - 1) a.perm.offsets[a.E] = row0 + n;
+        }
+        for (int i = tid; i < 2 * nblk[0]; i += kThreads) a.perm.blocks[i] = blk[i];
+        if (tid == 0) *a.perm.num_blocks = nblk[0];
+    }
+    b.offsets = off;
+    b.blocks = blk;
+    b.num_blocks = nblk;
+    b.src = src;
+    b.tables_in_lds = 1;
+}
+
 // ---------------------------------------------------------------------------------------------
 // tile_body_dma: same tile, but the token tile goes global -> LDS with the gfx950 LDS-DMA load
 // (global_load_lds_dwordx4: each lane supplies its own global address, the 64 x 16 bytes land
@@ -398,6 +514,7 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
         static_for<4>([&](auto s) { rd_off[pj][s] = (((2 * s + half) ^ (sw0 ^ (pj * 4))) & 7) * 16; });
     });
     const char* xs_b = reinterpret_cast<const char*>(xs) + li * 128;
+    if (GATEUP && a.tables_in_lds) __syncthreads();   // the last look at tables that the ring is about to overwrite
 
     f32x16 acc[NI][JBE];
     static_for<NI>([&](auto i) {
@@ -632,6 +749,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
     });
     const char* xs_b = reinterpret_cast<const char*>(xs) + li * 128;
     const char* ws_b = reinterpret_cast<const char*>(xs) + X_BYTES + wave * (NI * 4096) + (PACKED ? lane * 16 : li * 128);
+    if (GATEUP && PACKED && a.tables_in_lds) __syncthreads();   // the last look at tables that the ring is about to overwrite
 
     f32x16 acc[NI][JBE];
     static_for<NI>([&](auto i) {
@@ -978,10 +1096,8 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
 
 // The kernel: what to work on from mixed_assign, the regime from the expert's rows, the body from the block's.
 // PACKED: always true (kept because it is part of the kernel's name, which the library reports); row-major weights: tile_kernel.
-template <int IB, bool GATEUP, bool PACKED, bool WNT, bool HALF = false>
-__global__ __launch_bounds__(kThreads, HALF ? 2 : 1) void tile_kernel_mixed(const GemmArgs a) {
-    static_assert(PACKED, "row-major weights: tile_kernel");
-    extern __shared__ __attribute__((aligned(1024))) uint16_t xs[];
+template <int IB, bool GATEUP, bool WNT, bool HALF>
+__device__ __forceinline__ void tile_mixed(const GemmArgs& a, uint16_t* xs) {
     MixedWork m;
     if (!mixed_assign<IB, GATEUP>(a, (int)blockIdx.x, m)) return;
     Tile t;
@@ -1015,6 +1131,22 @@ __global__ __launch_bounds__(kThreads, HALF ? 2 : 1) void tile_kernel_mixed(cons
     }
     if (shared || !WNT) return dma_dispatch<IB, GATEUP, false, HALF>(b, t, nt, xs);
     if constexpr (WNT && RM < 8) dma_dispatch<IB, GATEUP, true, HALF, RM + 1>(b, t, nt, xs);
+}
+
+template <int IB, bool GATEUP, bool PACKED, bool WNT, bool HALF = false>
+__global__ __launch_bounds__(kThreads, HALF ? 2 : 1) void tile_kernel_mixed(const GemmArgs a) {
+    static_assert(PACKED, "row-major weights: tile_kernel");
+    extern __shared__ __attribute__((aligned(1024))) uint16_t xs[];
+    tile_mixed<IB, GATEUP, WNT, HALF>(a, xs);
+}
+
+// The gate+up projection with the permutation inside (permute_inside).
+template <bool HALF>
+__global__ __launch_bounds__(kThreads, HALF ? 2 : 1) void routed_tile_kernel_mixed(const GemmArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) uint16_t xs[];
+    GemmArgs b = a;
+    permute_inside(a, b, reinterpret_cast<int32_t*>(xs));
+    tile_mixed<1, true, true, HALF>(b, xs);
 }
 
 // Row-major weights: the same launch orders and regimes, rows_body.
@@ -1201,12 +1333,16 @@ inline int device_cus() {
     return cus;
 }
 
-template <int IB, bool GATEUP, bool PACKED, bool WNT, bool HALF = false>
+template <int IB, bool GATEUP, bool PACKED, bool WNT, bool HALF = false, bool ROUTED = false>
 hipError_t launch_tile_mixed(const GemmArgs& a, int max_blocks, hipStream_t s) {
     // the DMA ring of tile_body_dma: XD+1 = 4 buffers of 256 (128) rows x 128 bytes; that of rows_body
     constexpr int ni = IB * (GATEUP ? 2 : 1), ring = 4 * (HALF ? 4 : 8) * 32 * 128, rows = HALF ? 0 : rows_lds(rows_max(ni), ni);
     constexpr int lds = ring > rows ? ring : rows;
-    auto kern = tile_kernel_mixed<IB, GATEUP, PACKED, WNT, HALF>;
+    static_assert(!ROUTED || (GATEUP && IB == 1 && PACKED && WNT), "permute_inside is part of the gate+up kernels");
+    auto kern = [] {
+        if constexpr (ROUTED) return routed_tile_kernel_mixed<HALF>;
+        else return tile_kernel_mixed<IB, GATEUP, PACKED, WNT, HALF>;
+    }();
     // once per process and kernel: not allowed while a stream is being captured into a graph
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);

@@ -52,6 +52,7 @@ enum {
     kKnobInterleave = 8,      // 0: launch order = block order (no dealing of heavy and light blocks over the launch), 1: dealt whatever the classes' proportion
     kKnobNoNt = 9,            // 1: cached weight loads for single-block experts too
     kKnobRouteExact = 10,     // 1: every logit in fp64 at any size; 0: int8 digits from 256 tokens on
+    kKnobSmallPermute = 11,   // 0: the permutation is a launch of its own at any size, 1: part of the gate+up launch up to 1024 rows
     kNumKnobs = 12
 };
 extern int g_knobs[kNumKnobs];
@@ -92,6 +93,16 @@ hipError_t launch_gate_up(const moe_config& c, int32_t M, const uint16_t* x_rows
                           int32_t ldh, const int32_t* offsets,
                           const int32_t* blocks, const int32_t* num_blocks, const uint16_t* wg,
                           const uint16_t* wu, const uint16_t* packed_gu, uint16_t* h, hipStream_t s);
+// Tables of the permutation and Algorithm 1's block list, as launch_permute_index writes them.
+struct PermuteOut {
+    int32_t *counts, *offsets, *row_of, *src_of, *blocks, *num_blocks;
+};
+// The same from the un-permuted x[T, d] and the router's choice: the launch permutes by itself and writes the tables.
+// For permutes_inside(c, packed) and a down projection that does not read the second block list (down_deals).
+hipError_t launch_routed_gate_up(const moe_config& c, int32_t M, const uint16_t* x, const int32_t* topk_idx, const PermuteOut& out,
+                                 const uint16_t* wg, const uint16_t* wu, const uint16_t* packed_gu, uint16_t* h, hipStream_t s);
+constexpr int kSmallRows = 1024;      // four slots per thread of a GEMM workgroup
+bool permutes_inside(const moe_config& c, bool packed);
 // Buffers of the weighted combine when it is folded into the down projection (Eq. 3 computed by
 // the workgroup that writes the last of a token's k rows); nullptr = separate combine launch.
 struct CombineFusion {
@@ -102,6 +113,8 @@ struct CombineFusion {
     uint16_t* y;             // [T, d]
 };
 inline int combine_groups(const moe_config& c) { return (c.d + 127) / 128; }
+// whether the down projection deals heavy and light blocks over its launch, i.e. reads blocks_mix and num_heavy
+bool down_deals(const moe_config& c, int32_t M, bool packed);
 // whether the down-projection kernel chosen for this configuration can fold the combine in
 bool down_fuses_combine(const moe_config& c, int32_t M, bool packed);
 hipError_t launch_down(const moe_config& c, int32_t M, const uint16_t* h, int32_t ldh, const int32_t* offsets,
