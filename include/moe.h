@@ -113,7 +113,8 @@ size_t moe_workspace_size(const moe_config* cfg);
 moe_status moe_forward_workspace_layout(const moe_config* cfg, moe_workspace_layout* out);
 /* Name of the GEMM kernel instance the library launches for this config (stage 0: fused
  * gate+up, 1: down; packed != 0: with moe_pack_weights' layout), e.g. for matching profiler
- * output.  Returns a static string, NULL for an invalid config or stage. */
+ * output.  (moe_forward with few rows of packed weights launches gate+up's form that permutes by itself,
+ * routed_tile_kernel_mixed.)  Returns a static string, NULL for an invalid config or stage. */
 const char* moe_ffn_kernel_name(const moe_config* cfg, int32_t stage, int32_t packed);
 /* Upper bound on Alg. 1's block count for tile height M: floor(R/M) + min(E, R); 0 for an
  * invalid config or M outside [1, 2^30]. */

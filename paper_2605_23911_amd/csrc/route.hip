@@ -155,6 +155,7 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
 // order (digits_kernel lays them out), one 32-element step ahead in registers; the tokens come as bf16 by DMA
 // through LDS and are cut into digits in registers between the matrix
 // instructions (7 vector instructions per element, about half of the issue slots that 13 products of 64 experts leave).
+constexpr int kShortRows = 2200;     // rows up to which digits_kernel gives each a workgroup
 constexpr int kMinExp = -90;         // smallest E: keeps every scale a normal fp32 number
 constexpr int kMaxDigitDim = 32768;  // 4 pairs x 2^14 x this many elements fill an int32
 
@@ -178,28 +179,36 @@ __device__ __forceinline__ void four_digits(uint32_t w0, uint32_t w1, float scal
     out[3] = __builtin_amdgcn_perm(c, a, 0x05040100u) ^ 0x80808080u;
 }
 
-// One wavefront per row: rows 0 .. EP-1 are the experts' (their digits are written, in the order in which
+// WPR wavefronts per row: rows 0 .. EP-1 are the experts' (their digits are written, in the order in which
 // digit_logits_kernel loads them: [32-expert block][32-element step][digit][lane] x 16 bytes), then the tokens'.
 // exps[row] = E, norms[row] = N0, N2, N3, Nr (all infinite for a row that holds an infinity or a NaN).
-// Bound by latency up to a thousand tokens, then by reading x and the counting (about ten vector instructions per
-// element).  Rows past the last expert or token repeat it.  (A workgroup per row: 24 instead of 21 us at 4096 tokens x 7168.)
+// Rows past the last expert or token repeat it.
+// Four wavefronts per row up to kShortRows: bound by the latency of one row's chain (256 experts, d = 7168, one / four per row: 512
+// tokens 13.4 / 10.5 us, 1024 13.4 / 10.7; 128 experts, d = 4096, 2048 tokens 11.5 / 10.4).  Beyond, one: bound by reading x and
+// the counting, about ten vector instructions per element (256 experts, 4096 tokens 21 / 24 us).
+template <int WPR>
 __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wr,
                                                          uint8_t* __restrict__ wdig, int32_t* __restrict__ exps,
                                                          float4* __restrict__ norms, int T, int d, int E, int EP) {
-    const int lane = threadIdx.x % kWave;
-    const int row = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave));
+    static_assert(WPR == 1 || WPR == kWavesPerBlock, "a row is one wavefront's or the workgroup's");
+    __shared__ uint32_t tops[kWavesPerBlock];
+    __shared__ float sqs[kWavesPerBlock];
+    __shared__ int cnts[kWavesPerBlock][3];
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int row = WPR == 1 ? (int)blockIdx.x * kWavesPerBlock + wave : (int)blockIdx.x;
+    const int sub = WPR == 1 ? 0 : wave;
     const int t = row - EP;
     const bool expert = row < EP;
     const uint16_t* v = expert ? wr + (size_t)(row < E ? row : E - 1) * d : x + (size_t)(t < T ? t : T - 1) * d;
-    // A unit is 16 elements: one lane's 16 bytes of every digit.  A lane holds eight at a time (all loads in flight at
+    // A unit is 16 elements: one lane's 16 bytes of every digit.  A lane holds 8 / WPR at a time (all loads in flight at
     // once); rows of up to 8192 elements are read once, longer ones twice.
-    constexpr int kHeld = 8;
-    const int units = d / 16, chunks = (units + kHeld * kWave - 1) / (kHeld * kWave);
+    constexpr int kHeld = 8 / WPR, kSpan = kWave * WPR;
+    const int units = d / 16, chunks = (units + kHeld * kSpan - 1) / (kHeld * kSpan);
     uint32_t held[kHeld][8];
     auto load = [&](int c) {
 #pragma unroll
         for (int i = 0; i < kHeld; ++i) {
-            const int p0 = (c * kHeld + i) * kWave, p = p0 + lane;
+            const int p0 = (c * kHeld + i) * kSpan + sub * kWave, p = p0 + lane;
             uint4 a = make_uint4(0, 0, 0, 0), b = a;
             if (p0 < units) {                 // uniform; past the end: the first unit again
                 const uint4* src = reinterpret_cast<const uint4*>(v + (size_t)(p < units ? p : 0) * 16);
@@ -226,6 +235,12 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __rest
         const uint32_t o = (uint32_t)__shfl_xor((int)top, off, kWave);
         top = o > top ? o : top;
     }
+    if constexpr (WPR > 1) {
+        if (lane == 0) tops[wave] = top;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WPR; ++w) top = tops[w] > top ? tops[w] : top;
+    }
     const bool finite = top < 0x7f80u;
     int ex = finite ? (int)(top >> 7) - 127 : 0;
     ex = ex < kMinExp ? kMinExp : ex;
@@ -237,7 +252,7 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __rest
         if (chunks > 1) load(c);
 #pragma unroll
         for (int i = 0; i < kHeld; ++i) {
-            const int p0 = (c * kHeld + i) * kWave, p = p0 + lane;
+            const int p0 = (c * kHeld + i) * kSpan + sub * kWave, p = p0 + lane;
             if (p0 >= units) continue;        // uniform
             const bool live = p < units;
 #pragma unroll
@@ -262,7 +277,14 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __rest
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, kWave);
-    if (lane == 0) {
+    if constexpr (WPR > 1) {
+        if (lane == 0) sqs[wave] = sq, cnts[wave][0] = n2, cnts[wave][1] = n3, cnts[wave][2] = nr;
+        __syncthreads();
+        sq = 0.0f, n2 = n3 = nr = 0;
+#pragma unroll
+        for (int w = 0; w < WPR; ++w) sq += sqs[w], n2 += cnts[w][0], n3 += cnts[w][1], nr += cnts[w][2];
+    }
+    if (lane == 0 && sub == 0) {
         const float unit = exp2i(ex - 29), inf = __builtin_huge_valf();
         exps[row] = ex;
         // parts q2, q3 and q3 alone are at most 2^15 + 2^7 and 2^7 units, a residual is less than one
@@ -764,7 +786,7 @@ __global__ __launch_bounds__(kThreads) void route_direct_kernel(const uint16_t* 
 // 286 / 113; 160 (5120) 1024 tokens 52 / 40; 128 (4096) 1024 tokens (5.4e8) 34 / 35, 1500 44 / 34, 4096 89 / 50; 64 (3584)
 // 2048 tokens (4.7e8) 33 / 34, 3000 44 / 37, 4096 49 / 42; 32 (4096) 4096 tokens (5.4e8) 38 / 40, 8192 69 / 61; 16 (4096)
 // 8192 tokens 40 / 62.  Error of the weights against float64 in every one of these: the same four digits (2.5e-8) in both forms.
-// The three launches of the int8 form take about 13 us (digits), 5 + 0.9 a step (products) and 12 (selection), of which 5 each
+// The three launches of the int8 form take about 11 us (digits), 11 + 1 a step (products) and 12 (selection), of which 5 each
 // are a launch's own.
 bool digits_pay(const moe_config& c) { return c.E >= 32 && (double)c.T * c.E * c.d > 6e8; }
 
@@ -861,7 +883,11 @@ hipError_t launch_route(const moe_config& c, const uint16_t* x, const uint16_t* 
         float4* norms = (float4*)(part + (size_t)p.KS * p.TP * p.EP);
         int32_t* exps = (int32_t*)(norms + p.EP + p.TP);
         uint8_t* wdig = (uint8_t*)(exps + p.EP + p.TP);      // 16-byte aligned: EP and TP are multiples of 32
-        hipLaunchKernelGGL(digits_kernel, dim3((p.EP + p.TP) / kWavesPerBlock), dim3(kThreads), 0, s, x, wr, wdig, exps, norms, c.T, c.d, c.E, p.EP);
+        const int rows = p.EP + p.TP;
+        if (rows <= kShortRows)
+            hipLaunchKernelGGL(digits_kernel<kWavesPerBlock>, dim3(rows), dim3(kThreads), 0, s, x, wr, wdig, exps, norms, c.T, c.d, c.E, p.EP);
+        else
+            hipLaunchKernelGGL(digits_kernel<1>, dim3(rows / kWavesPerBlock), dim3(kThreads), 0, s, x, wr, wdig, exps, norms, c.T, c.d, c.E, p.EP);
         hipLaunchKernelGGL(digit_logits_kernel, dim3(p.TP / kDigitTokens * (p.EP / kDigitExperts) * p.KS), dim3(kThreads), 0, s, x, wdig, exps,
                            part, c.T, c.d, p.TP, p.EP, p.KS);
         auto select = [&](auto kern) {
