@@ -401,13 +401,13 @@ __global__ __launch_bounds__(kThreads) void digit_logits_kernel(const uint16_t* 
         for (int g = g0; g < g1; ++g) {
             __builtin_amdgcn_sched_barrier(0);
             half_step(g, 0);
-            load_x(g + 2);           // its buffer was last read in step g - 1
+            // The next half reads step g + 1's tokens, which all four wavefronts brought in: each waits for its own (requested a whole
+            // step ago, newer are the eight digit loads of each of two halves), then for the others.
+            wait_vmcnt<16>();
+            __syncthreads();
+            load_x(g + 2);           // its buffer was last read in the first half of step g - 1, a barrier ago
             __builtin_amdgcn_sched_barrier(0);
             half_step(g, 1);
-            // The tokens of step g + 1, requested in step g - 1, are older than this step's 16 + TW loads (and than eight of the
-            // step before).
-            wait_vmcnt<16 + TW>();
-            __syncthreads();
         }
         wait_vmcnt<0>();             // nothing of this workgroup may still be writing LDS when it retires
     }
