@@ -505,7 +505,7 @@ __device__ __forceinline__ void gate_and_select(double (&z)[Q], const bool (&ok)
             int be;
             const double m = next_best(z, ok, taken, lane, be);
             const double step = last - m;
-            if (r > 0 && !(step >= gap) && gap == gap) gap = step;      // a NaN (two infinities) stays
+            if (r > 0 && step < gap) gap = step;      // not for two infinities (a NaN): only a bias makes them, they are equal
             last = m;
             if (lane == be % kWave) taken |= 1u << (be / kWave);
             if (lane == 0) sel_idx[wave][r] = be;
@@ -572,7 +572,8 @@ __device__ __forceinline__ void refine_candidates(double (&z)[Q], const bool (&o
     int n_cand = 0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        const bool c = ok[q] && !(z[q] < vk - margin);   // written so that a NaN anywhere keeps the expert in
+        // written so that a NaN anywhere keeps the expert in; -infinity is a bias's, it stays
+        const bool c = ok[q] && !(z[q] < vk - margin) && z[q] != -__builtin_huge_val();
         const unsigned long long bal = __ballot(c);
         if (c) cand_list[n_cand + __popcll(bal & ((1ull << lane) - 1ull))] = lane + kWave * q;
         n_cand += __popcll(bal);
@@ -674,13 +675,15 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict
             w = make_float4(fmaxf(w.x, __shfl_xor(w.x, off, kWave)), fmaxf(w.y, __shfl_xor(w.y, off, kWave)),
                             fmaxf(w.z, __shfl_xor(w.z, off, kWave)), fmaxf(w.w, __shfl_xor(w.w, off, kWave)));
         const float4 n = norms[EP + t];
-        // the bound of digit_logits_kernel, and 2^-40 of |x| |w| for the fp64 sums on either side
-        const double b = (double)n.y * w.z + (double)n.z * w.y + (double)n.w * w.x + (double)n.x * w.w + 0x1p-40 * n.x * w.x;
+        // the bound of digit_logits_kernel
+        const double cut = (double)n.y * w.z + (double)n.z * w.y + (double)n.w * w.x + (double)n.x * w.w;
+        if (cut == 0.0) return false;    // nothing was left out (a row of zeros, of few bits): equal logits are equal
+        const double b = cut + 0x1p-40 * n.x * w.x;       // the fp64 sums on either side
         double margin = 2.02 * b;
         if (k < E) {
             int be;
             const double step = vk - next_best(z, ok, taken, lane, be);
-            if (!(step >= gap) && gap == gap) gap = step;
+            if (step < gap) gap = step;
         }
         // A looser bound (an element hundreds of times the others) says too little about the weights' last bits: the
         // selected experts' logits are recomputed, and all of them where the weights depend on all.
