@@ -476,13 +476,15 @@ __device__ __forceinline__ double next_best(const double (&z)[Q], const bool (&o
         }
     }
     const double m = wave_max_uniform(bv);
-    unsigned long long tied = __ballot(be >= 0 && bv == m);
-    expert = -1;
-    while (tied != 0) {                  // one lane, unless logits are equal
-        const int l = __builtin_ctzll(tied);
-        const int o = __builtin_amdgcn_readlane(be, l);
-        expert = (expert < 0 || o < expert) ? o : expert;
-        tied &= tied - 1;
+    const unsigned long long tied = __ballot(be >= 0 && bv == m);
+    expert = tied != 0 ? __builtin_amdgcn_readlane(be, __builtin_ctzll(tied)) : -1;
+    if ((tied & (tied - 1)) != 0) {      // equal logits: a lane holds the first of its own, the lowest row of 64 goes first
+        expert = -1;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const unsigned long long row = __ballot(be >= 0 && bv == m && be / kWave == q);
+            if (expert < 0 && row != 0) expert = kWave * q + __builtin_ctzll(row);
+        }
     }
     return m;
 }
