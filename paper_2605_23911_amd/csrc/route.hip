@@ -43,12 +43,6 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-
 __device__ __forceinline__ void unpack8(const uint4& v, double* out) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -64,6 +58,45 @@ __device__ __forceinline__ void unpack8(const uint4& v, double* out) {
 // B[k = l/16][j = l%16]; it receives D[i = l/16 + 4v][j = l%16], v = 0..3.  The MFMA sums over
 // k, so which k a slot carries is free as long as A and B agree: lane group g = l/16 loads 8
 // consecutive k (one 16-byte load) and the q-th MFMA of a chunk takes element q of every lane.
+// MT, NT: 16-token and 16-expert tiles per wavefront.  xp, wp: this lane's rows.  Chunks c0 .. c1 - 1 of kChunk elements.
+template <int MT, int NT>
+__device__ __forceinline__ void fp64_tiles(const uint16_t* const (&xp)[MT], const uint16_t* const (&wp)[NT], int c0, int c1, f64x4 (&acc)[MT][NT]) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[m][n] = f64x4{0.0, 0.0, 0.0, 0.0};
+    if (c0 >= c1) return;
+    uint4 xr[MT], wv[NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) xr[m] = *reinterpret_cast<const uint4*>(xp[m] + (size_t)c0 * kChunk);
+#pragma unroll
+    for (int n = 0; n < NT; ++n) wv[n] = *reinterpret_cast<const uint4*>(wp[n] + (size_t)c0 * kChunk);
+    for (int c = c0; c < c1; ++c) {
+        const int cn = (c + 1 < c1) ? c + 1 : c;   // prefetch (the last chunk re-reads itself)
+        uint4 xn[MT], wn[NT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) xn[m] = *reinterpret_cast<const uint4*>(xp[m] + (size_t)cn * kChunk);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) wn[n] = *reinterpret_cast<const uint4*>(wp[n] + (size_t)cn * kChunk);
+        double a8[MT][8];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) unpack8(xr[m], a8[m]);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            double b8[8];
+            unpack8(wv[n], b8);
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a8[m][q], b8[q], acc[m][n], 0, 0, 0);
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m) xr[m] = xn[m];
+#pragma unroll
+        for (int n = 0; n < NT; ++n) wv[n] = wn[n];
+    }
+}
+
 // NT: 16-expert tiles per wavefront (1 or 4).  With 4 the token fragment is loaded and
 // converted once per chunk for 64 experts (used when there are enough tiles to fill the chip
 // without cutting the reduction).
@@ -87,43 +120,15 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
     const int c1 = (c0 + per) < nchunk ? (c0 + per) : nchunk;
 
     const int trow = (tt * 16 + i) < T ? (tt * 16 + i) : (T - 1);
-    const uint16_t* xp = x + (size_t)trow * d + g * 8;
+    const uint16_t* xp[1] = {x + (size_t)trow * d + g * 8};
     const uint16_t* wp[NT];
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
         const int erow = ((eg * NT + n) * 16 + i) < E ? ((eg * NT + n) * 16 + i) : (E - 1);
         wp[n] = wr + (size_t)erow * d + g * 8;
     }
-
-    f64x4 acc[NT];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) acc[n] = f64x4{0.0, 0.0, 0.0, 0.0};
-    if (c0 < c1) {
-        uint4 xr = *reinterpret_cast<const uint4*>(xp + (size_t)c0 * kChunk);
-        uint4 wv[NT];
-#pragma unroll
-        for (int n = 0; n < NT; ++n) wv[n] = *reinterpret_cast<const uint4*>(wp[n] + (size_t)c0 * kChunk);
-        for (int c = c0; c < c1; ++c) {
-            const int cn = (c + 1 < c1) ? c + 1 : c;   // prefetch (the last chunk re-reads itself)
-            const uint4 xn = *reinterpret_cast<const uint4*>(xp + (size_t)cn * kChunk);
-            uint4 wn[NT];
-#pragma unroll
-            for (int n = 0; n < NT; ++n) wn[n] = *reinterpret_cast<const uint4*>(wp[n] + (size_t)cn * kChunk);
-            double a8[8];
-            unpack8(xr, a8);
-#pragma unroll
-            for (int n = 0; n < NT; ++n) {
-                double b8[8];
-                unpack8(wv[n], b8);
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    acc[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a8[q], b8[q], acc[n], 0, 0, 0);
-            }
-            xr = xn;
-#pragma unroll
-            for (int n = 0; n < NT; ++n) wv[n] = wn[n];
-        }
-    }
+    f64x4 acc[1][NT];
+    fp64_tiles(xp, wp, c0, c1, acc);
     const size_t EP = (size_t)E16 * 16;
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
@@ -131,7 +136,7 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
         if (et < E16) {
             double* out = part + ((size_t)ks * T16 * 16 + (size_t)tt * 16) * EP + (size_t)et * 16 + i;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) out[(size_t)(g + 4 * v) * EP] = acc[n][v];
+            for (int v = 0; v < 4; ++v) out[(size_t)(g + 4 * v) * EP] = acc[0][n][v];
         }
     }
 }
@@ -143,12 +148,14 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
 // by v_mfma_i32_32x32x32_i8, which is exact, one int32 accumulator per order i + j = 0..4; orders 5 and 6 (2^-40 and less of
 // the largest possible term) are left out.  The five sums meet in fp64.
 //
-// Error bound.  Let N0 be the 2-norm of a row, N2 and N3 those of its parts q2, q3 and q3 alone, Nr the residual's, as
-// bounded by digits_kernel from how many elements have such a part.  The pairs left out are (2,3), (3,2), (3,3) and
-// whatever a residual meets:
-//     |z_digits - z| <= N2(x) N3(w) + N3(x) N2(w) + Nr(x) N0(w) + N0(x) Nr(w)      (Cauchy-Schwarz)
-// plus the fp64 roundings.  For normally distributed rows of 7168 that is about 1e-8, the error itself 1e-11: an exact
+// Error bound.  Let A be the largest magnitude in a row, N2 and N3 the 2-norms of its parts q2, q3 and q3 alone, R the sum of
+// the residuals' magnitudes, as bounded by digits_kernel from how many elements have such a part.  The pairs left out are
+// (2,3), (3,2), (3,3) (Cauchy-Schwarz) and whatever a residual meets:
+//     |z_digits - z| <= N2(x) N3(w) + N3(x) N2(w) + R(x) A(w) + A(x) R(w)
+// plus the fp64 roundings.  For normally distributed rows of 7168 that is about 1e-9, the error itself 1e-11: an exact
 // evaluation for the purpose of the weights, and topk_kernel recomputes in fp64 what stands closer together than the bound.
+// Where the bound over a tile of 128 tokens x 64 experts says too little (elements hundreds of times the others', infinities,
+// NaN), the workgroups of that tile take their logits from the fp64 matrix cores instead: tile_limit.
 //
 // What bounds it: the int8 matrix rate, 13 products (256 experts, 1024 tokens, d = 7168: 49 GOP, 10 us at 5 POP/s).
 // A wavefront takes 64 experts (two 32-expert operands) and 32 tokens, the experts' digits straight from memory in operand
@@ -181,7 +188,7 @@ __device__ __forceinline__ void four_digits(uint32_t w0, uint32_t w1, float scal
 
 // WPR wavefronts per row: rows 0 .. EP-1 are the experts' (their digits are written, in the order in which
 // digit_logits_kernel loads them: [32-expert block][32-element step][digit][lane] x 16 bytes), then the tokens'.
-// exps[row] = E, norms[row] = N0, N2, N3, Nr (all infinite for a row that holds an infinity or a NaN).
+// exps[row] = E, parts[row] = A, N2, N3, R (all infinite for a row that holds an infinity or a NaN).
 // Rows past the last expert or token repeat it.
 // Four wavefronts per row up to kShortRows: bound by the latency of one row's chain (256 experts, d = 7168, one / four per row: 512
 // tokens 13.4 / 10.5 us, 1024 13.4 / 10.7; 128 experts, d = 4096, 2048 tokens 11.5 / 10.4).  Beyond, one: bound by reading x and
@@ -189,10 +196,9 @@ __device__ __forceinline__ void four_digits(uint32_t w0, uint32_t w1, float scal
 template <int WPR>
 __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wr,
                                                          uint8_t* __restrict__ wdig, int32_t* __restrict__ exps,
-                                                         float4* __restrict__ norms, int T, int d, int E, int EP) {
+                                                         float4* __restrict__ parts, int T, int d, int E, int EP) {
     static_assert(WPR == 1 || WPR == kWavesPerBlock, "a row is one wavefront's or the workgroup's");
     __shared__ uint32_t tops[kWavesPerBlock];
-    __shared__ float sqs[kWavesPerBlock];
     __shared__ int cnts[kWavesPerBlock][3];
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int row = WPR == 1 ? (int)blockIdx.x * kWavesPerBlock + wave : (int)blockIdx.x;
@@ -245,7 +251,6 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __rest
     int ex = finite ? (int)(top >> 7) - 127 : 0;
     ex = ex < kMinExp ? kMinExp : ex;
     const float scale = exp2i(29 - ex);
-    float sq = 0.0f;
     int n2 = 0, n3 = 0, nr = 0;
     uint8_t* dst = wdig + ((size_t)(row >> 5) * (d / 32) * 4) * 1024 + (row & 31) * 16;
     for (int c = 0; c < chunks; ++c) {
@@ -260,7 +265,6 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __rest
                 const uint32_t w = live ? held[i][q / 2] : 0u;
                 const float f = __uint_as_float(q & 1 ? w & 0xffff0000u : w << 16) * scale;
                 const int n = (int)f;
-                sq = fmaf(f, f, sq);
                 n2 += __popcll(__ballot((n & 0xffff) != 0));      // wavefront totals, in scalar registers
                 n3 += __popcll(__ballot((n & 0xff) != 0));
                 nr += __popcll(__ballot((float)n != f));
@@ -275,23 +279,26 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __rest
             }
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, kWave);
     if constexpr (WPR > 1) {
-        if (lane == 0) sqs[wave] = sq, cnts[wave][0] = n2, cnts[wave][1] = n3, cnts[wave][2] = nr;
+        if (lane == 0) cnts[wave][0] = n2, cnts[wave][1] = n3, cnts[wave][2] = nr;
         __syncthreads();
-        sq = 0.0f, n2 = n3 = nr = 0;
+        n2 = n3 = nr = 0;
 #pragma unroll
-        for (int w = 0; w < WPR; ++w) sq += sqs[w], n2 += cnts[w][0], n3 += cnts[w][1], nr += cnts[w][2];
+        for (int w = 0; w < WPR; ++w) n2 += cnts[w][0], n3 += cnts[w][1], nr += cnts[w][2];
     }
     if (lane == 0 && sub == 0) {
         const float unit = exp2i(ex - 29), inf = __builtin_huge_valf();
         exps[row] = ex;
         // parts q2, q3 and q3 alone are at most 2^15 + 2^7 and 2^7 units, a residual is less than one
-        norms[row] = finite ? make_float4(1.001f * unit * sqrtf(sq), 33000.0f * unit * sqrtf((float)n2), 128.2f * unit * sqrtf((float)n3),
-                                          1.001f * unit * sqrtf((float)nr))
+        parts[row] = finite ? make_float4(__uint_as_float(top << 16), 33000.0f * unit * sqrtf((float)n2), 128.2f * unit * sqrtf((float)n3), unit * (float)nr)
                             : make_float4(inf, inf, inf, inf);
     }
+}
+
+// The bound above for a token's and an expert's parts, or for the largest parts of several.
+template <class F>
+__device__ __forceinline__ F digit_bound(const float4& x, const float4& w) {
+    return (F)x.y * (F)w.z + (F)x.z * (F)w.y + (F)x.w * (F)w.x + (F)x.x * (F)w.w;
 }
 
 // part[ks][t][e], t < TP, e < EP, fp64.  A workgroup takes 128 tokens x 64 experts, 32 tokens a wavefront: the four read the
@@ -303,11 +310,25 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(const uint16_t* __rest
 // step's tokens are cut into digits (four vector instructions behind each) and the experts' digits of the step after that
 // are on their way.
 constexpr int kDigitTokens = 128, kDigitExperts = 64;
+// A bound up to which a logit is as good as exact for the weights.  Beyond, the selected experts' logits are recomputed in fp64
+// token by token, which serves the two gates whose weights hang on them alone.  The softmax over all experts hangs on every logit:
+// there a tile beyond the bound is formed in fp64, but only below 2^19 logits, the calls that are all in fp64 without the int8
+// form.  Above, the experts that are not selected may carry the digits' error (less than 2^-19 |x| |w|) into the denominator.
+// Router alone, 256 experts, d = 7168, us, normal rows / one channel 1000 times the others / lognormal magnitudes (sigma 1.5): 1024 tokens
+// softmax 50 / 95 / 94 (all in fp64 87), renormalised 50 / 72 / 72; 4096 tokens 118 / 146 / 143 (all in fp64 286).  One token of such an
+// element among 1024 costs nothing, a router row with a large element, an infinity or a NaN 91 (4096 tokens: 161 and 295).
+constexpr double kCertain = 0x1p-21;
+float tile_limit(const moe_config& c) {
+    return c.gating == MOE_GATE_SOFTMAX && (long long)c.T * c.E < (1 << 19) ? (float)kCertain : 3e38f;
+}
 __global__ __launch_bounds__(kThreads) void digit_logits_kernel(const uint16_t* __restrict__ x, const uint8_t* __restrict__ wdig,
                                                                const int32_t* __restrict__ exps, double* __restrict__ part,
-                                                               int T, int d, int TP, int EP, int KS) {
+                                                               int T, int d, int TP, int EP, int KS, const uint16_t* __restrict__ wr, int E,
+                                                               const float4* __restrict__ parts, float4* __restrict__ wmax,
+                                                               int32_t* __restrict__ in_fp64, float limit) {
     constexpr int RT = kDigitTokens, TW = RT / 32, BUF = RT * 128, NB = 3;
     __shared__ __attribute__((aligned(1024))) char ring[NB * BUF];
+    __shared__ float4 tops[kWavesPerBlock];
     const int tid = threadIdx.x, lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int li = lane & 31, half = lane >> 5;
@@ -315,6 +336,41 @@ __global__ __launch_bounds__(kThreads) void digit_logits_kernel(const uint16_t* 
     const int ks = blockIdx.x % KS, eg = blockIdx.x / KS % EG, t0 = blockIdx.x / (KS * EG) * RT;
     const int nstep = d / 64, per = (nstep + KS - 1) / KS;
     const int g0 = ks * per, g1 = g0 + per < nstep ? g0 + per : nstep;
+
+    // The largest parts of the tile's tokens (wavefronts 0 and 1) and experts (wavefront 2) decide how its logits are formed.
+    static_assert(RT == 2 * kWave && kDigitExperts == kWave, "rows of the tile per wavefront");
+    float4 most = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (wave < 3) most = parts[wave < 2 ? EP + t0 + tid : eg * kDigitExperts + lane];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+        most = make_float4(fmaxf(most.x, __shfl_xor(most.x, off, kWave)), fmaxf(most.y, __shfl_xor(most.y, off, kWave)),
+                           fmaxf(most.z, __shfl_xor(most.z, off, kWave)), fmaxf(most.w, __shfl_xor(most.w, off, kWave)));
+    if (lane == 0) tops[wave] = most;
+    __syncthreads();
+    const float4 a = tops[0], c = tops[1], w = tops[2];
+    const float4 xm = make_float4(fmaxf(a.x, c.x), fmaxf(a.y, c.y), fmaxf(a.z, c.z), fmaxf(a.w, c.w));
+    const bool fp64 = !(digit_bound<float>(xm, w) <= limit);     // written so that a NaN (infinity times zero) counts
+    if (ks == 0 && tid == 0) {
+        in_fp64[t0 / RT * EG + eg] = fp64;
+        if (t0 == 0) wmax[eg] = w;
+    }
+    if (fp64) {
+        const int i = lane & 15, g = lane >> 4, tw = t0 + wave * 32;
+        const uint16_t *xp[2], *ep[4];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) xp[m] = x + (size_t)(tw + m * 16 + i < T ? tw + m * 16 + i : T - 1) * d + g * 8;
+#pragma unroll
+        for (int n = 0; n < 4; ++n) ep[n] = wr + (size_t)((eg * 4 + n) * 16 + i < E ? (eg * 4 + n) * 16 + i : E - 1) * d + g * 8;
+        f64x4 z[2][4];
+        fp64_tiles(xp, ep, g0 * (64 / kChunk), g1 * (64 / kChunk), z);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) part[((size_t)ks * TP + tw + m * 16 + g + 4 * v) * EP + (eg * 4 + n) * 16 + i] = z[m][n][v];
+        return;
+    }
 
     uint32_t xo[TW];   // byte offsets of this lane's pieces: 8 rows x 128 bytes per load, source chunk swizzled
 #pragma unroll
@@ -556,16 +612,16 @@ __device__ __forceinline__ void gate_and_select(double (&z)[Q], const bool (&ok)
 
 // The logits of the experts that can be among the k largest, recomputed in fp64 (bf16 operands and their products are
 // exact there; the order of the additions moves the sum by ~1e-15), plus the bias: for tokens whose k + 1 largest logits
-// hold neighbours closer than the error of digit_logits_kernel can rule on.  vk: the k-th largest value in z; margin: twice
-// the error bound b of z, or infinity (or NaN) to recompute every expert.
+// hold neighbours closer than the error of digit_logits_kernel can rule on.  vk: the k-th largest value in z; margin[q]: the
+// largest error bound b of z plus the bound b_q of the lane's q-th logit, or less than zero if that one is not off at all.
 // Why this is enough: the k experts with the largest z have true logits >= vk - b, so the true k-th largest logit is
-// >= vk - b, every expert of the true top-k has z >= vk - 2b: it is a candidate.  Every non-candidate's value is < vk - 2b,
-// i.e. lies below k candidates' exact values, also when it keeps its place in z: the selection over the mixed
+// >= vk - b, every expert of the true top-k has z >= vk - b - b_q: it is a candidate, or z is its true logit.  Every other
+// expert's value is < vk - b, i.e. lies below those k, also when it keeps its place in z: the selection over the mixed
 // array picks the same experts in the same order as over exact logits.
 // cand_list: LDS, kMaxExperts ints per wavefront.
 template <int Q>
 __device__ __forceinline__ void refine_candidates(double (&z)[Q], const bool (&ok)[Q],
-                                                  int lane, int t, double vk, double margin, int d,
+                                                  int lane, int t, double vk, const double (&margin)[Q], int d,
                                                   const uint16_t* __restrict__ x, const uint16_t* __restrict__ wr,
                                                   const float* __restrict__ bias, int32_t* cand_list) {
     constexpr int CB = 4;   // candidates recomputed per pass over the token row
@@ -574,8 +630,8 @@ __device__ __forceinline__ void refine_candidates(double (&z)[Q], const bool (&o
     int n_cand = 0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        // written so that a NaN anywhere keeps the expert in; -infinity is a bias's, it stays
-        const bool c = ok[q] && !(z[q] < vk - margin) && z[q] != -__builtin_huge_val();
+        // -infinity is a bias's, it stays
+        const bool c = ok[q] && margin[q] >= 0.0 && z[q] >= vk - margin[q] && z[q] != -__builtin_huge_val();
         const unsigned long long bal = __ballot(c);
         if (c) cand_list[n_cand + __popcll(bal & ((1ull << lane) - 1ull))] = lane + kWave * q;
         n_cand += __popcll(bal);
@@ -619,7 +675,7 @@ __device__ __forceinline__ void refine_candidates(double (&z)[Q], const bool (&o
 }
 
 // ---- kernel 2: gate + top-k, one wavefront per token ------------------------------------------
-// DIGITS: `part` holds the slices of digit_logits_kernel, with the rows' norms for their error bound.
+// DIGITS: `part` holds the slices of digit_logits_kernel; parts, wmax and in_fp64 say how far off they can be.
 // T16, E16: padded tokens and experts in units of 16.
 template <bool DIGITS, int Q>
 __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict__ part,
@@ -628,7 +684,8 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict
                                                        int T, int E, int k, int gating, int T16, int E16, int KS,
                                                        int32_t* __restrict__ zero, int zero_n,
                                                        const uint16_t* __restrict__ x, const uint16_t* __restrict__ wr,
-                                                       int d, const float4* __restrict__ norms) {
+                                                       int d, const float4* __restrict__ parts, const float4* __restrict__ wmax,
+                                                       const int32_t* __restrict__ in_fp64) {
     __shared__ double wsel[kWavesPerBlock][kMaxExperts];
     __shared__ int32_t sel_idx[kWavesPerBlock][kMaxExperts];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -664,34 +721,30 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(const double* __restrict
     gate_and_select(z, ok, lane, wave, t, k, E, gating, wsel, sel_idx, topk_idx, topk_w, [&](double vk, double gap, unsigned taken) {
         if (refined) return false;
         refined = true;
-        float4 w = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const float4 n = parts[EP + t];
+        const int EG = (int)(EP / kDigitExperts);
+        static_assert(kDigitExperts == kWave, "a lane's q-th logit is of the q-th group of experts");
+        double b = 0.0, margin[Q], round = 0.0;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            if (ok[q]) {
-                const float4 n = norms[lane + kWave * q];
-                w = make_float4(fmaxf(w.x, n.x), fmaxf(w.y, n.y), fmaxf(w.z, n.z), fmaxf(w.w, n.w));
+            margin[q] = -1.0;
+            if (q < EG && !in_fp64[t / kDigitTokens * EG + q]) {
+                const float4 w = wmax[q];
+                margin[q] = digit_bound<double>(n, w);
+                b = fmax(b, margin[q]);
+                round = fmax(round, (double)n.x * w.x);
             }
         }
+        if (b == 0.0) return false;    // nothing was left out (a row of zeros, of few bits): equal logits are equal
+        round *= 0x1p-53 * d * (d / 64 + 32);        // of the fp64 sums on either side
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-            w = make_float4(fmaxf(w.x, __shfl_xor(w.x, off, kWave)), fmaxf(w.y, __shfl_xor(w.y, off, kWave)),
-                            fmaxf(w.z, __shfl_xor(w.z, off, kWave)), fmaxf(w.w, __shfl_xor(w.w, off, kWave)));
-        const float4 n = norms[EP + t];
-        // the bound of digit_logits_kernel
-        const double cut = (double)n.y * w.z + (double)n.z * w.y + (double)n.w * w.x + (double)n.x * w.w;
-        if (cut == 0.0) return false;    // nothing was left out (a row of zeros, of few bits): equal logits are equal
-        const double b = cut + 0x1p-40 * n.x * w.x;       // the fp64 sums on either side
-        double margin = 2.02 * b;
+        for (int q = 0; q < Q; ++q) margin[q] = margin[q] > 0.0 ? 1.01 * (b + margin[q]) + 2.0 * round : -1.0;
         if (k < E) {
             int be;
             const double step = vk - next_best(z, ok, taken, lane, be);
             if (step < gap) gap = step;
         }
-        // A looser bound (an element hundreds of times the others) says too little about the weights' last bits: the
-        // selected experts' logits are recomputed, and all of them where the weights depend on all.
-        const bool loose = !(b <= 0x1p-21);
-        if (loose && gating == MOE_GATE_SOFTMAX) margin = __builtin_huge_val();
-        if (!loose && gap > margin) return false;    // written so that a NaN anywhere recomputes
+        if (b <= kCertain && gap > 2.02 * b + 2.0 * round) return false;
         refine_candidates(z, ok, lane, t, vk, margin, d, x, wr, bias, sel_idx[wave]);
         return true;
     });
@@ -802,7 +855,9 @@ struct RoutePlan {
 };
 
 size_t digit_bytes(const RoutePlan& p, int d) {
-    return (size_t)p.KS * p.TP * p.EP * sizeof(double) + (size_t)p.EP * d * 4 + (size_t)(p.EP + p.TP) * (sizeof(float4) + sizeof(int32_t));
+    const size_t groups = p.EP / kDigitExperts;
+    return (size_t)p.KS * p.TP * p.EP * sizeof(double) + (size_t)p.EP * d * 4 + (size_t)(p.EP + p.TP) * (sizeof(float4) + sizeof(int32_t)) +
+           groups * (sizeof(float4) + p.TP / kDigitTokens * sizeof(int32_t));
 }
 
 // mode: the test knob's value.  -1 the rule, 1 every logit in fp64, 0 the int8 form from 256 tokens on.
@@ -885,19 +940,21 @@ hipError_t launch_route(const moe_config& c, const uint16_t* x, const uint16_t* 
     const dim3 topk_grid((c.T + kWavesPerBlock - 1) / kWavesPerBlock);
     if (p.digits) {
         double* part = (double*)workspace;
-        float4* norms = (float4*)(part + (size_t)p.KS * p.TP * p.EP);
-        int32_t* exps = (int32_t*)(norms + p.EP + p.TP);
+        float4* parts = (float4*)(part + (size_t)p.KS * p.TP * p.EP);
+        float4* wmax = parts + p.EP + p.TP;
+        int32_t* exps = (int32_t*)(wmax + p.EP / kDigitExperts);
         uint8_t* wdig = (uint8_t*)(exps + p.EP + p.TP);      // 16-byte aligned: EP and TP are multiples of 32
+        int32_t* in_fp64 = (int32_t*)(wdig + (size_t)p.EP * c.d * 4);
         const int rows = p.EP + p.TP;
         if (rows <= kShortRows)
-            hipLaunchKernelGGL(digits_kernel<kWavesPerBlock>, dim3(rows), dim3(kThreads), 0, s, x, wr, wdig, exps, norms, c.T, c.d, c.E, p.EP);
+            hipLaunchKernelGGL(digits_kernel<kWavesPerBlock>, dim3(rows), dim3(kThreads), 0, s, x, wr, wdig, exps, parts, c.T, c.d, c.E, p.EP);
         else
-            hipLaunchKernelGGL(digits_kernel<1>, dim3(rows / kWavesPerBlock), dim3(kThreads), 0, s, x, wr, wdig, exps, norms, c.T, c.d, c.E, p.EP);
+            hipLaunchKernelGGL(digits_kernel<1>, dim3(rows / kWavesPerBlock), dim3(kThreads), 0, s, x, wr, wdig, exps, parts, c.T, c.d, c.E, p.EP);
         hipLaunchKernelGGL(digit_logits_kernel, dim3(p.TP / kDigitTokens * (p.EP / kDigitExperts) * p.KS), dim3(kThreads), 0, s, x, wdig, exps,
-                           part, c.T, c.d, p.TP, p.EP, p.KS);
+                           part, c.T, c.d, p.TP, p.EP, p.KS, wr, c.E, parts, wmax, in_fp64, tile_limit(c));
         auto select = [&](auto kern) {
             hipLaunchKernelGGL(kern, topk_grid, dim3(kThreads), 0, s, part, bias, topk_idx, topk_w, c.T, c.E, c.k, c.gating, p.TP / 16,
-                               p.EP / 16, p.KS, zero, zero_per_token, x, wr, c.d, norms);
+                               p.EP / 16, p.KS, zero, zero_per_token, x, wr, c.d, parts, wmax, in_fp64);
         };
         if (c.E <= 64) select(topk_kernel<true, 1>);
         else if (c.E <= 128) select(topk_kernel<true, 2>);
@@ -915,7 +972,7 @@ hipError_t launch_route(const moe_config& c, const uint16_t* x, const uint16_t* 
                            p.KS, units);
     auto select = [&](auto kern) {
         hipLaunchKernelGGL(kern, topk_grid, dim3(kThreads), 0, s, part, bias, topk_idx,
-                           topk_w, c.T, c.E, c.k, c.gating, p.T16, p.E16, p.KS, zero, zero_per_token, nullptr, nullptr, 0, nullptr);
+                           topk_w, c.T, c.E, c.k, c.gating, p.T16, p.E16, p.KS, zero, zero_per_token, nullptr, nullptr, 0, nullptr, nullptr, nullptr);
     };
     if (c.E <= 64) select(topk_kernel<false, 1>);
     else if (c.E <= 128) select(topk_kernel<false, 2>);

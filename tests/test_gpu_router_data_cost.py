@@ -25,6 +25,26 @@ def _few_experts_left(x, wr, bias):
     bias[3:] = -float("inf")      # fewer than k
 
 
+def _channel_of_thousands(x, wr, bias):
+    x[:, 17] *= 1000.0
+
+
+def _heavy_tails(x, wr, bias):
+    x *= torch.exp(1.5 * torch.randn(x.shape, generator=torch.Generator(device=DEV).manual_seed(2), device=DEV))
+
+
+def _one_large_element(x, wr, bias):
+    x[5, 17] = 1000.0
+
+
+def _large_router_element(x, wr, bias):
+    wr[3, 5] = 1000.0
+
+
+def _infinity_and_nan(x, wr, bias):
+    x[700, 3], wr[3, 5] = float("inf"), float("nan")
+
+
 def _time(moe, cfg, x, wr, bias):
     idx, w = torch.empty((T, K), dtype=torch.int32, device=DEV), torch.empty((T, K), device=DEV)
     ws = torch.empty(moe.route_workspace_size(cfg), dtype=torch.uint8, device=DEV)
@@ -42,7 +62,9 @@ def _time(moe, cfg, x, wr, bias):
     return once
 
 
-@pytest.mark.parametrize("change,gating,most", [(_zero_tokens, 0, 1.2), (_padded_half, 0, 1.2), (_zero_router, 0, 1.2), (_few_experts_left, 0, 1.2)])
+@pytest.mark.parametrize("change,gating,most", [(_zero_tokens, 0, 1.2), (_padded_half, 0, 1.2), (_zero_router, 0, 1.2), (_few_experts_left, 0, 1.2),
+                                                (_channel_of_thousands, 0, 2.2), (_channel_of_thousands, 1, 2.2), (_heavy_tails, 0, 2.2), (_heavy_tails, 2, 2.2),
+                                                (_one_large_element, 0, 2.2), (_large_router_element, 0, 2.2), (_infinity_and_nan, 1, 2.2)])
 def test_cost(change, gating, most):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -17,15 +17,16 @@ def _kernel(asm, name):
     for line in asm.splitlines():
         if re.match(r"_ZN\S*%s\S*:" % name, line):
             inside = True
+        if inside and line.startswith(".Lfunc_end"):
+            return body
         if inside:
             body.append(line.split(";")[0].strip())
-            if body[-1] == "s_endpgm":
-                return body
     raise AssertionError(f"no kernel {name}")
 
 
 def split_loop(lines):
-    """Instructions in front of the loop over the steps (the one with the matrix instructions), and those of one trip."""
+    """Instructions in front of the loop over the steps (the one with the matrix instructions), from the block on that holds the first
+    load into LDS, and those of one trip."""
     for end, line in enumerate(lines):
         m = re.match(r"s_cbranch_\w+ (\S+)", line)
         if m and lines.index(m[1] + ":") < end:
@@ -33,7 +34,9 @@ def split_loop(lines):
             trip = lines[start + 1: end]
             if any(l.startswith("v_mfma_i32") for l in trip):
                 assert not any(re.match(r"s_c?branch|\S+:$", l) for l in trip), "the trip is one straight line"
-                return lines[:start], trip
+                first = next(i for i, l in enumerate(lines) if "global_load_lds" in l)
+                block = max(i for i, l in enumerate(lines[:first]) if l.endswith(":"))
+                return lines[block:start], trip
     raise AssertionError("no loop")
 
 
