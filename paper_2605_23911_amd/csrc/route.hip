@@ -14,7 +14,7 @@
 // Larger calls take the logits from the int8 matrix cores instead (64 times the fp64 rate): rows are cut
 // into four 8-bit digits, the digits' products are summed exactly in integers, and what the digits leave out is bounded per
 // token; the few tokens whose k + 1 largest logits stand closer together than that bound get the logits in question again in
-// fp64.  Same indices, same order, same weights to the last bit but one as the all-fp64 form (digit_logits_kernel, digits_pay).
+// fp64.  Same indices, same order, same weights to the last bit but one as the all-fp64 form (digit_logits_kernel, kCertain, digits_pay).
 //
 // Kernel 1 (logits): one wavefront per work unit (16 tokens x 16 experts x one slice of d).
 //   The reduction is cut into enough slices to put >= ~2000 wavefronts on the chip even for
@@ -314,10 +314,11 @@ constexpr int kDigitTokens = 128, kDigitExperts = 64;
 // token by token, which serves the two gates whose weights hang on them alone.  The softmax over all experts hangs on every logit:
 // there a tile beyond the bound is formed in fp64, but only below 2^19 logits, the calls that are all in fp64 without the int8
 // form.  Above, the experts that are not selected may carry the digits' error (less than 2^-19 |x| |w|) into the denominator.
+// 2^-25: a weight is then off by at most one rounding to fp32 more (2^-24); normal rows stay below 2^-29.
 // Router alone, 256 experts, d = 7168, us, normal rows / one channel 1000 times the others / lognormal magnitudes (sigma 1.5): 1024 tokens
-// softmax 50 / 95 / 94 (all in fp64 87), renormalised 50 / 72 / 72; 4096 tokens 118 / 146 / 143 (all in fp64 286).  One token of such an
-// element among 1024 costs nothing, a router row with a large element, an infinity or a NaN 91 (4096 tokens: 161 and 295).
-constexpr double kCertain = 0x1p-21;
+// softmax 50 / 95 / 95 (all in fp64 87), renormalised 50 / 72 / 71; 4096 tokens 118 / 160 / 161 (all in fp64 286).  One token of such an
+// element among 1024, a router row with a large element, an infinity or a NaN 91 to 95 (4096 tokens: 134, 169 and 295).
+constexpr double kCertain = 0x1p-25;
 float tile_limit(const moe_config& c) {
     return c.gating == MOE_GATE_SOFTMAX && (long long)c.T * c.E < (1 << 19) ? (float)kCertain : 3e38f;
 }
