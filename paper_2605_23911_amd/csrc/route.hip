@@ -164,7 +164,9 @@ __global__ __launch_bounds__(kThreads) void logits_kernel(const uint16_t* __rest
 // instructions (7 vector instructions per element, about half of the issue slots that 13 products of 64 experts leave).
 constexpr int kShortRows = 2200;     // rows up to which digits_kernel gives each a workgroup
 constexpr int kMinExp = -90;         // smallest E: keeps every scale a normal fp32 number
-constexpr int kMaxDigitDim = 32768;  // 4 pairs x 2^14 x this many elements fill an int32
+constexpr int kMaxDigitSlice = 32768;                // 4 pairs x 2^14 x this many elements fill an int32
+constexpr int kMaxDigitSlices = 16;                  // topk_kernel sums the slices
+constexpr int kMaxDigitDim = kMaxDigitSlice * kMaxDigitSlices;
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
@@ -874,8 +876,9 @@ RoutePlan plan(const moe_config& c, int mode) {
         // Slices: rounds of workgroups x steps of each (a quarter more where a slice of the experts' digits fills an XCD's L2),
         // a workgroup's start and end worth eight steps, and the slices' sum.
         double best = 1e30;
-        for (int ks = 1; ks <= 16 && ks <= nstep; ks *= 2) {
+        for (int ks = 1; ks <= kMaxDigitSlices && ks <= nstep; ks *= 2) {
             const int steps = (nstep + ks - 1) / ks;
+            if (steps > kMaxDigitSlice / 64) continue;
             const double slow = (double)p.EP * 256 * steps > 2e6 ? 1.25 : 1.0;
             const double cost = (double)((tiles * ks + 255) / 256) * (slow * steps + 8.0) + 0.3 * ks;
             if (cost < best) {

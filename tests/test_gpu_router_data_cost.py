@@ -1,6 +1,7 @@
-"""What the router costs does not hang on the data: calls on which the int8 form's digits say less than usual, or logits are equal, against
+"""What the router costs hangs neither on the data nor on the row length: calls on which the int8 form's digits say less than usual, or logits are equal, against
 the same call on normal activations.  The bound is on the ratio of the two (medians of interleaved rounds in one process): a
-token whose E logits are all computed again by one wavefront takes 13 times as long as the whole call."""
+token whose E logits are all computed again by one wavefront takes 13 times as long as the whole call.  And calls on long rows
+against the all-fp64 form of the same call."""
 import pytest
 import torch
 
@@ -46,7 +47,7 @@ def _infinity_and_nan(x, wr, bias):
 
 
 def _time(moe, cfg, x, wr, bias):
-    idx, w = torch.empty((T, K), dtype=torch.int32, device=DEV), torch.empty((T, K), device=DEV)
+    idx, w = torch.empty((cfg.T, cfg.k), dtype=torch.int32, device=DEV), torch.empty((cfg.T, cfg.k), device=DEV)
     ws = torch.empty(moe.route_workspace_size(cfg), dtype=torch.uint8, device=DEV)
 
     def once():
@@ -60,6 +61,11 @@ def _time(moe, cfg, x, wr, bias):
 
     once()
     return once
+
+
+def _medians(runs):
+    rounds = [[f() for f in runs] for _ in range(9)]
+    return [sorted(r[i] for r in rounds)[4] for i in range(len(runs))]
 
 
 @pytest.mark.parametrize("change,gating,most", [(_zero_tokens, 0, 1.2), (_padded_half, 0, 1.2), (_zero_router, 0, 1.2), (_few_experts_left, 0, 1.2),
@@ -77,7 +83,31 @@ def test_cost(change, gating, most):
     x1, wr1, bias1 = x.clone(), wr.clone(), bias.clone()
     change(x1, wr1, bias1)
     runs = [_time(moe, cfg, a.to(torch.bfloat16), b.to(torch.bfloat16), c) for a, b, c in ((x, wr, bias), (x1, wr1, bias1))]
-    rounds = [[f() for f in runs] for _ in range(9)]
-    usual, changed = (sorted(r[i] for r in rounds)[4] for i in (0, 1))
+    usual, changed = _medians(runs)
     print(f"  {usual * 200:.1f} us, changed {changed * 200:.1f} us", flush=True)
     assert changed <= most * usual
+
+
+@pytest.mark.parametrize("T,d,E,k,most", [(8192, 32832, 64, 4, 0.8), (2048, 32832, 256, 8, 0.6)])
+def test_long_rows(T, d, E, k, most):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_23911_amd as moe
+    import paper_2605_23911_amd.binding as B
+    moe.lib()
+    print(f"[router cost] T={T} d={d} E={E}", flush=True)
+    cfg = moe.MoEConfig.of(T, d, 64, E, k, 0)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    x, wr = ((torch.randn(n, d, generator=g, device=DEV) * std).to(torch.bfloat16) for n, std in ((T, 1.0), (E, d ** -0.5)))
+    run = _time(moe, cfg, x, wr, None)
+
+    def in_fp64():
+        B.test_knob(B.KNOB_ROUTE_EXACT, 1)
+        try:
+            return run()
+        finally:
+            B.test_knob(B.KNOB_ROUTE_EXACT, -1)
+
+    ruled, fp64 = _medians([run, in_fp64])
+    print(f"  {ruled * 200:.1f} us, all in fp64 {fp64 * 200:.1f} us", flush=True)
+    assert ruled <= most * fp64

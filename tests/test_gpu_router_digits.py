@@ -56,7 +56,7 @@ def _check(moe, x, wr, k, gating, gap_min, tol=2.0 ** -23, scale=1.0):
 
 
 @pytest.mark.parametrize("T,d,E,k", [(256, 64, 9, 2), (257, 128, 64, 8), (300, 192, 65, 4), (511, 2112, 128, 1), (289, 1088, 129, 8),
-                                     (256, 8256, 256, 8), (383, 16448, 40, 3)])
+                                     (256, 8256, 256, 8), (383, 16448, 40, 3), (256, 32832, 65, 4), (300, 65600, 33, 2)])
 @pytest.mark.parametrize("gating", [0, 1, 2])
 def test_remainders(moe, T, d, E, k, gating):
     print(f"[digits] T={T} d={d} E={E} k={k} gating={gating}", flush=True)
@@ -80,6 +80,18 @@ def test_every_pair_of_digits(moe, i, j, shift, gating):
     x[:, 128: 128 + n] = c0[i] * 2.0 ** (-5 - 8 * i)
     wr[1::2, 128: 128 + n] = c0[j] * 2.0 ** (-5 - 8 * j)
     _check(moe, x * 2.0 ** shift, wr, k, gating, 1e-9, tol=2.0 ** -24 if i + j < 5 else 2.0 ** -23)
+
+
+def test_sums_of_long_rows(moe):
+    """147456 products of 127 x 127 of one order: more than an int32 holds, a slice of d has to stay below."""
+    print("[digits] long rows", flush=True)
+    T, d, E, n = 256, 147584, 33, 147456
+    x, wr = torch.zeros(T, d, dtype=torch.bfloat16), torch.zeros(E, d, dtype=torch.bfloat16)
+    x[:, 0], wr[:, 1] = 1.0, 1.0
+    x[:, 2], wr[:, 2] = 0.5, (3 * torch.arange(E) / 128.0).to(torch.bfloat16)
+    x[:, 128:] = 127 * 2.0 ** -13
+    wr[1::2, 128:] = 127 * 2.0 ** -21
+    _check(moe, x, wr, 4, 0, 1e-9, tol=2.0 ** -24)
 
 
 @pytest.mark.parametrize("outlier", [30.0, 300.0, 3000.0, 1e6])
