@@ -842,14 +842,23 @@ __global__ __launch_bounds__(kThreads) void route_direct_kernel(const uint16_t* 
     gate_and_select(z, ok, lane, 0, t, k, E, gating, wsel, sel_idx, topk_idx, topk_w, [](double, double, unsigned) { return false; });
 }
 
-// Where the int8 form pays: from about 6e8 multiply-adds on, for at least 32 experts (it pads them to 64, 128 or 256).  Router
-// alone, us, fp64 / int8: 256 experts (d 7168) 256 tokens (4.7e8) 36 / 38, 512 52 / 42, 1024 82 / 49, 2048 149 / 67, 4096
-// 286 / 113; 160 (5120) 1024 tokens 52 / 40; 128 (4096) 1024 tokens (5.4e8) 34 / 35, 1500 44 / 34, 4096 89 / 50; 64 (3584)
+// Where the int8 form pays: from about 6e8 multiply-adds on, for at least 32 experts (it pads them to a multiple of 64).  Router
+// alone, us, fp64 / int8: 256 experts (d 7168) 256 tokens (4.7e8) 36 / 38, 512 52 / 42, 1024 82 / 50, 2048 149 / 68, 4096
+// 286 / 118; 160 (5120) 1024 tokens 52 / 40; 128 (4096) 1024 tokens (5.4e8) 34 / 35, 1500 44 / 34, 4096 89 / 50; 64 (3584)
 // 2048 tokens (4.7e8) 33 / 34, 3000 44 / 37, 4096 49 / 42; 32 (4096) 4096 tokens (5.4e8) 38 / 40, 8192 69 / 61; 16 (4096)
-// 8192 tokens 40 / 62.  Error of the weights against float64 in every one of these: the same four digits (2.5e-8) in both forms.
+// 8192 tokens 40 / 62.  The line is a mean: the fp64 form's time goes in steps, with the rounds of its wavefronts and its groups of 64
+// experts, and where one is just begun the int8 form is ahead earlier (160 experts (5120) 384 tokens, 3.1e8, 38 / 31; 65 (2048) 4096
+// tokens, 5.5e8, 50 / 37; 48 (4096) 2048 tokens, 4.0e8, 33 / 30).
+// And from 36000 logits on, which tells from d = 16384 up: on longer rows the experts' digits, written at 6 bytes an element, are the
+// larger part.  d = 32768, fp64 / int8: 256 experts 128 tokens (32768) 69 / 84, 192 118 / 88; 160 129 tokens 64 / 75, 256 100 / 77; 128
+// 256 tokens 66 / 68, 384 115 / 71; 64 512 tokens 67 / 68, 800 115 / 76; 32 1000 tokens 67 / 81, 2000 137 / 105.
+// Error of the weights against float64 in every one of these: the same four digits (2.5e-8) in both forms.
 // The three launches of the int8 form take about 11 us (digits), 11 + 1 a step (products) and 12 (selection), of which 5 each
 // are a launch's own.
-bool digits_pay(const moe_config& c) { return c.E >= 32 && (double)c.T * c.E * c.d > 6e8; }
+bool digits_pay(const moe_config& c) {
+    const double logits = (double)c.T * c.E;
+    return c.E >= 32 && logits * c.d > 6e8 && logits > 36000.0;
+}
 
 struct RoutePlan {
     int T16, E16, KS, NT;

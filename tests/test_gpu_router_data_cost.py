@@ -88,7 +88,7 @@ def test_cost(change, gating, most):
     assert changed <= most * usual
 
 
-@pytest.mark.parametrize("T,d,E,k,most", [(8192, 32832, 64, 4, 0.8), (2048, 32832, 256, 8, 0.6)])
+@pytest.mark.parametrize("T,d,E,k,most", [(8192, 32832, 64, 4, 0.8), (2048, 32832, 256, 8, 0.6), (128, 32768, 256, 8, 1.1), (129, 32768, 160, 4, 1.1)])
 def test_long_rows(T, d, E, k, most):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
