@@ -930,9 +930,9 @@ RoutePlan plan(const moe_config& c, int mode) {
 
 size_t route_workspace_bytes(const moe_config& c) {
     if (c.T == 0) return 0;
-    // sized for whichever form a test knob may switch to
+    // for the rule's form and, if the test knob forces one, for that
     size_t need = 0;
-    for (int mode = -1; mode <= 1; ++mode) {
+    for (const int mode : {-1, knob(kKnobRouteExact)}) {
         const RoutePlan p = plan(c, mode);
         const size_t bytes = p.digits ? digit_bytes(p, c.d)
                                       : (size_t)p.KS * p.T16 * 16 * p.E16 * 16 * sizeof(double);

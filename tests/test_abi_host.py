@@ -95,6 +95,19 @@ def test_null_alignment_and_workspace_errors_need_no_gpu(L):
     assert L.moe_combine(C.byref(z), p, p, p, p, None) == 0
 
 
+@pytest.mark.parametrize("T,d,E,slices", [(32768, 4096, 16, 1), (32768, 4096, 9, 1), (400, 512, 64, 16), (300, 7168, 256, 16)])
+def test_router_workspace_holds_one_form(L, T, d, E, slices):
+    """A call whose logits are formed in fp64 needs the partial tiles only, not what the int8 form would: that one is forced by the test knob here."""
+    c = moe.MoEConfig.of(T, d, 64, E, 2)
+    tiles = -(-T // 16) * 16 * (-(-E // 16) * 16) * 8
+    assert tiles <= moe.route_workspace_size(c) <= slices * tiles + 256
+    binding.test_knob(binding.KNOB_ROUTE_EXACT, 0)
+    try:
+        assert moe.route_workspace_size(c) >= 4 * E * d
+    finally:
+        binding.test_knob(binding.KNOB_ROUTE_EXACT, -1)
+
+
 def test_workspace_layout_is_ordered_and_sized(L):
     for T, d, F, E, k in [(64, 256, 512, 8, 2), (512, 4096, 14336, 8, 2), (4096, 7168, 2048, 256, 8), (1, 64, 64, 1, 1)]:
         c = moe.MoEConfig.of(T, d, F, E, k)
