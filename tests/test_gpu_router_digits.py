@@ -1,6 +1,7 @@
 """The router's int8 form (rows cut into four 8-bit digits, products summed in integers) forced on, against float64 by torch: tiles and
 slices with remainders, rows longer than one pass of the digit kernel, ranges at which the fixed point loses elements, logits
-that differ by less than the digits resolve, and values that are not finite.
+that differ by less than the digits resolve, and values that are not finite.  The digits' kernel gives a row a workgroup up to 2200 padded rows and
+a wavefront beyond: the cases of 2305 tokens (a padded tile of one token) are there for the second.
 
 Bound on a weight, relative: one rounding to fp32 (2^-24) plus twice the logits' error (the weight's own logit and the sum below it),
 which is at most 2^-25 (beyond, they are formed in fp64): 2^-23."""
@@ -56,7 +57,8 @@ def _check(moe, x, wr, k, gating, gap_min, tol=2.0 ** -23, scale=1.0):
 
 
 @pytest.mark.parametrize("T,d,E,k", [(256, 64, 9, 2), (257, 128, 64, 8), (300, 192, 65, 4), (511, 2112, 128, 1), (289, 1088, 129, 8),
-                                     (256, 8256, 256, 8), (383, 16448, 40, 3), (256, 32832, 65, 4), (300, 65600, 33, 2)])
+                                     (256, 8256, 256, 8), (383, 16448, 40, 3), (256, 32832, 65, 4), (300, 65600, 33, 2),
+                                     (2305, 64, 9, 2), (2305, 192, 40, 8), (2305, 8256, 40, 4), (2305, 16448, 129, 2)])
 @pytest.mark.parametrize("gating", [0, 1, 2])
 def test_remainders(moe, T, d, E, k, gating):
     print(f"[digits] T={T} d={d} E={E} k={k} gating={gating}", flush=True)
@@ -82,6 +84,39 @@ def test_every_pair_of_digits(moe, i, j, shift, gating):
     _check(moe, x * 2.0 ** shift, wr, k, gating, 1e-9, tol=2.0 ** -24 if i + j < 5 else 2.0 ** -23)
 
 
+@pytest.mark.parametrize("k", [5, 6])
+@pytest.mark.parametrize("ahead", [2.0 ** -26, 2.0 ** -25, 2.0 ** -24])
+def test_order_within_and_beyond_the_bound(moe, ahead, k):
+    """Pairs of experts of which the second is larger by a sum of left-out products, 2.6e-8, and the first by `ahead`: in the digits'
+    sums the first leads, in truth the second where `ahead` is 1.5e-8.  Beyond twice the bound, 5.3e-8, nothing is recomputed; inside the selection and
+    across its boundary."""
+    print(f"[digits] order, ahead {ahead} k={k}", flush=True)
+    T, d, E, n = 300, 2048, 40, 1792
+    x, wr = torch.zeros(T, d), torch.zeros(E, d)
+    x[:, 0], wr[:, 1] = 1.0, 1.0
+    x[:, 2], wr[:, 2] = 0.5, 3 * (torch.arange(E) // 2) / 128.0
+    x[:, 3], wr[::2, 3] = 1.0, ahead
+    x[:, 128: 128 + n], wr[1::2, 128: 128 + n] = 127 * 2.0 ** -21, 127 * 2.0 ** -29
+    _check(moe, x, wr, k, 1, 1e-9)
+
+
+@pytest.mark.parametrize("gating", [0, 1])
+@pytest.mark.parametrize("tokens", [True, False])
+@pytest.mark.parametrize("shift", [0, 4])
+def test_residuals(moe, tokens, shift, gating):
+    """Elements just below the fixed point's unit, of one sign, against the other side's largest: 15 units of 2^-29 are lost, 2.8e-8, and the
+    bound is just under 2^-25; with shift 4 it is 4.5e-7, to be formed in fp64."""
+    print(f"[digits] residuals of the {'tokens' if tokens else 'experts'} shift={shift} gating={gating}", flush=True)
+    T, d, E, k = 300, 256, 40, 6
+    x, wr = torch.zeros(T, d), torch.zeros(E, d)
+    x[:, 0], wr[:, 1] = 1.0, 1.0
+    x[:, 2], wr[:, 2] = 0.5, 3 * torch.arange(E) / 128.0
+    small = 255 * 2.0 ** -37
+    x[:, 128: 143] = small if tokens else 1.0
+    wr[1::2, 128: 143] = 1.0 if tokens else small
+    _check(moe, x * 2.0 ** shift, wr, k, gating, 1e-9)
+
+
 def test_sums_of_long_rows(moe):
     """147456 products of 127 x 127 of one order: more than an int32 holds, a slice of d has to stay below."""
     print("[digits] long rows", flush=True)
@@ -96,10 +131,12 @@ def test_sums_of_long_rows(moe):
 
 @pytest.mark.parametrize("outlier", [30.0, 300.0, 3000.0, 1e6])
 @pytest.mark.parametrize("gating", [0, 1])
-def test_outliers(moe, outlier, gating):
-    """One element far above the others takes digits away from its row; at the larger ones the softmax recomputes every logit."""
-    print(f"[digits] outlier {outlier} gating={gating}", flush=True)
-    x, wr = _rows(260, 1024, 100, 3)
+@pytest.mark.parametrize("T", [260, 2305])
+def test_outliers(moe, outlier, gating, T):
+    """One element far above the others takes digits away from its row; at the larger ones the softmax has its tiles formed in fp64, the
+    renormalised one its candidates."""
+    print(f"[digits] outlier {outlier} T={T} gating={gating}", flush=True)
+    x, wr = _rows(T, 1024, 100, 3)
     x[::2, 17] = outlier
     wr[:, 17] *= 1.0 / outlier
     wr[5, 400] = outlier * 1024 ** -0.5
@@ -108,9 +145,10 @@ def test_outliers(moe, outlier, gating):
 
 
 @pytest.mark.parametrize("sx,sw", [(2.0 ** -100, 2.0 ** 100), (2.0 ** 90, 2.0 ** -90), (2.0 ** -60, 1.0), (2.0 ** -120, 2.0 ** 118)])
-def test_range_of_exponents(moe, sx, sw):
-    print(f"[digits] scales {sx} {sw}", flush=True)
-    x, wr = _rows(256, 512, 70, 7)
+@pytest.mark.parametrize("T", [256, 2305])
+def test_range_of_exponents(moe, sx, sw, T):
+    print(f"[digits] scales {sx} {sw} T={T}", flush=True)
+    x, wr = _rows(T, 512, 70, 7)
     _check(moe, x * sx, wr * sw, 4, 1, 1e-9, scale=sx * sw)
 
 
@@ -128,14 +166,16 @@ def test_logits_closer_than_the_digits_resolve(moe):
     _check(moe, x, wr, 5, 0, 1e-13)
 
 
-def test_infinities_and_nans(moe):
-    """A NaN logit never wins; tokens and experts without one are as without its neighbours'."""
-    print("[digits] infinities and NaN", flush=True)
-    x, wr = _rows(300, 320, 50, 13)
+@pytest.mark.parametrize("T", [300, 2305])
+def test_infinities_and_nans(moe, T):
+    """A NaN logit never wins; tokens and experts without one are as without its neighbours' (whose tile is then formed in fp64:
+    on normal rows the digits leave nothing that shows in a weight)."""
+    print(f"[digits] infinities and NaN T={T}", flush=True)
+    x, wr = _rows(T, 320, 50, 13)
     x, wr = x.to(torch.bfloat16), wr.to(torch.bfloat16)
     bad = x.clone()
     bad[3, 5], bad[4, 6], bad[5] = float("nan"), float("inf"), float("-inf")
-    ok = torch.ones(300, dtype=torch.bool)
+    ok = torch.ones(T, dtype=torch.bool)
     ok[3:6] = False
     idx0, w0 = _route(moe, x.to(DEV), wr.to(DEV), 6, 0)
     idx, w = _route(moe, bad.to(DEV), wr.to(DEV), 6, 0)
