@@ -266,7 +266,9 @@ def main():
             roofline["traffic_source"] = rec.get("source", "profiles/traffic.json")
     except (OSError, ValueError, KeyError):
         pass
-    roofline.update({"kernel": kname, "kernel_ms": gate_up_ms,
+    # the forward's gate+up of few rows permutes by itself (the library's rule, see moe_ffn_kernel_name in moe.h)
+    inside = packed is not None and (R <= 512 or (R <= 1024 and (kname.endswith("true>") or -(-s.F // 128) * min(R, s.E) <= 256)))
+    roofline.update({"kernel": f"routed_tile_kernel_mixed ({kname} with the permutation inside)" if inside else kname, "kernel_ms": gate_up_ms,
                      "algorithmic_bytes": gate_up_bytes, "algorithmic_flops": gate_up_flops,
                      "active_experts": e_active})
 

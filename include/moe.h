@@ -88,7 +88,7 @@ typedef struct {
     size_t x_perm;    /* zero-length: moe_forward reads x rows through src_of and writes no permuted copy */
     size_t h;         /* bf16  [R,F] */
     size_t y_perm;    /* bf16  [R,d] */
-    size_t scratch;   /* internal: partial logit tiles, chunk histograms, block schedule */
+    size_t scratch;   /* internal: the router's, chunk histograms, block schedule */
     size_t total;     /* bytes needed */
 } moe_workspace_layout;
 
@@ -111,10 +111,10 @@ size_t moe_forward_workspace_size(const moe_config* cfg);
 size_t moe_workspace_size(const moe_config* cfg);
 /* Fills *out with the layout moe_forward uses; returns MOE_OK or the config error. */
 moe_status moe_forward_workspace_layout(const moe_config* cfg, moe_workspace_layout* out);
-/* Name of the GEMM kernel instance the library launches for this config (stage 0: fused
+/* Name of the GEMM kernel instance moe_grouped_ffn launches for this config (stage 0: fused
  * gate+up, 1: down; packed != 0: with moe_pack_weights' layout), e.g. for matching profiler
- * output.  (moe_forward with few rows of packed weights launches gate+up's form that permutes by itself,
- * routed_tile_kernel_mixed.)  Returns a static string, NULL for an invalid config or stage. */
+ * output.  moe_forward launches the same, except that with few rows of packed weights (up to 512, or 1024) its gate+up is
+ * routed_tile_kernel_mixed, which permutes by itself.  Returns a static string, NULL for an invalid config or stage. */
 const char* moe_ffn_kernel_name(const moe_config* cfg, int32_t stage, int32_t packed);
 /* Upper bound on Alg. 1's block count for tile height M: floor(R/M) + min(E, R); 0 for an
  * invalid config or M outside [1, 2^30]. */
@@ -123,10 +123,15 @@ int32_t moe_max_blocks(const moe_config* cfg, int32_t M);
 /* Stage 1, router (Eq. 1-2, Sec. 3.4).
  *   x [T,d] bf16, W_r [E,d] bf16, bias [E] fp32 or NULL (added to the logits)
  *   -> topk_idx [T,k] int32, topk_w [T,k] fp32.
- * Logits z = W_r x + bias are accumulated in fp64 (exact products of the bf16 operands).  The
+ * Logits z = W_r x + bias: exact products of the bf16 operands, accumulated in fp64.  Calls of many
+ * logits sum them in integers instead, 30 bits below each row's largest element, with a proven bound on what is
+ * left out, and go back to fp64 for what the bound cannot rule on: the choice, its order and its ties are those of the
+ * fp64 logits in every case.  Weights are off by one rounding to fp32 (2^-24, relative) and, in those calls, by
+ * 2^-24 more at most; only MOE_GATE_SOFTMAX on 2^19 logits (T*E) or more and rows with elements hundreds
+ * of times the others' lets the experts that are not chosen carry up to 2^-19 |x| |w| in their logits.  The
  * k experts are chosen by k rounds of arg-max over z with the winner masked; a tie goes to the
  * lower expert index; outputs are in selection order (descending score).  Weights follow
- * cfg->gating.  workspace: moe_route_workspace_size(cfg) bytes (partial logit tiles). */
+ * cfg->gating.  workspace: moe_route_workspace_size(cfg) bytes (partial logit tiles, integer digits of W_r). */
 moe_status moe_route(const moe_config* cfg, const void* x, const void* W_r, const float* bias,
                      int32_t* topk_idx, float* topk_w, void* workspace, size_t ws_bytes, void* stream);
 
@@ -215,7 +220,8 @@ moe_status moe_forward(const moe_config* cfg, const void* x, const void* W_r, co
 
 /* moe_forward with timing hooks: `events` is an array of n_events hipEvent_t handles (as void*,
  * entries may be NULL, the array itself may be NULL when n_events == 0) recorded on `stream`
- *   [0] before the router, [1] after it, [2] after the permutation (index arrays; the row gather runs inside gate+up),
+ *   [0] before the router, [1] after it, [2] after the permutation (index arrays; the row gather runs inside gate+up; with
+ *   few rows of packed weights the whole permutation does: then nothing lies between [1] and [2], its time is in [2]-[3]),
  *   [3] after the fused gate+up GEMM, [4] after the down GEMM, [5] after the combine.
  * Entries beyond index 5 are ignored.  Everything else is exactly moe_forward (Sec. 3.1's
  * five stages; the per-stage breakdown mirrors the paper's Table 6). */

@@ -59,7 +59,7 @@ extern int g_knobs[kNumKnobs];
 inline int knob(int i) { return g_knobs[i]; }
 
 // ---- launchers (each enqueues on `s` and returns hipGetLastError()) ----------------------
-// workspace: route_workspace_bytes(c) bytes of fp64 partial logit tiles
+// workspace: route_workspace_bytes(c) bytes: fp64 partial logit tiles and, in the int8 form, the experts' digits and what bounds their error
 size_t route_workspace_bytes(const moe_config& c);
 // zero / zero_per_token: if zero != nullptr the wavefront that routes token t also clears
 // zero[t * zero_per_token .. + zero_per_token) (the fused combine's arrival counters).

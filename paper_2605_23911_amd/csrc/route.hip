@@ -12,9 +12,14 @@
 // (v_mfma_f64_16x16x4) gives logits good to ~1e-15 at the fp64 matrix rate.
 //
 // Larger calls take the logits from the int8 matrix cores instead (64 times the fp64 rate): rows are cut
-// into four 8-bit digits, the digits' products are summed exactly in integers, and what the digits leave out is bounded per
-// token; the few tokens whose k + 1 largest logits stand closer together than that bound get the logits in question again in
-// fp64.  Same indices, same order, same weights to the last bit but one as the all-fp64 form (digit_logits_kernel, kCertain, digits_pay).
+// into four 8-bit digits, the digits' products are summed exactly in integers, and what the digits leave out is bounded.
+// Tiles where the bound says too little for a softmax over all experts are formed in fp64 as above; tokens whose k + 1 largest
+// logits stand closer together than the bound, or whose selected experts' bound is too loose, get the logits in question again in
+// fp64.  Same indices, same order, same weights to the last bit but one as the all-fp64 form (digit_logits_kernel, kCertain with
+// the exception from 2^19 logits on, digits_pay).  After the splitting of operands into digits with exact products of K. Ozaki, T. Ogita,
+// S. Oishi and S. M. Rump, "Error-free transformations of matrix multiplication by using fast routines of matrix
+// multiplication and its applications", Numer. Algorithms 59 (2012), and its use on integer matrix units by H. Ootomo, K. Ozaki and
+// R. Yokota, "DGEMM on integer matrix multiplication unit" (2023).
 //
 // Kernel 1 (logits): one wavefront per work unit (16 tokens x 16 experts x one slice of d).
 //   The reduction is cut into enough slices to put >= ~2000 wavefronts on the chip even for
@@ -318,7 +323,7 @@ constexpr int kDigitTokens = 128, kDigitExperts = 64;
 // form.  Above, the experts that are not selected may carry the digits' error (less than 2^-19 |x| |w|) into the denominator.
 // 2^-25: a weight is then off by at most one rounding to fp32 more (2^-24); normal rows stay below 2^-29.
 // Router alone, 256 experts, d = 7168, us, normal rows / one channel 1000 times the others / lognormal magnitudes (sigma 1.5): 1024 tokens
-// softmax 50 / 95 / 95 (all in fp64 87), renormalised 50 / 72 / 71; 4096 tokens 118 / 160 / 161 (all in fp64 286).  One token of such an
+// softmax 50 / 95 / 95 (all in fp64 84), renormalised 50 / 72 / 71; 4096 tokens 118 / 160 / 161 (all in fp64 288).  One token of such an
 // element among 1024, a router row with a large element, an infinity or a NaN 91 to 95 (4096 tokens: 134, 169 and 295).
 constexpr double kCertain = 0x1p-25;
 float tile_limit(const moe_config& c) {
@@ -627,7 +632,9 @@ __device__ __forceinline__ void refine_candidates(double (&z)[Q], const bool (&o
                                                   int lane, int t, double vk, const double (&margin)[Q], int d,
                                                   const uint16_t* __restrict__ x, const uint16_t* __restrict__ wr,
                                                   const float* __restrict__ bias, int32_t* cand_list) {
-    constexpr int CB = 4;   // candidates recomputed per pass over the token row
+    // Candidates recomputed per pass over the token row.  8 or 12 where there are more than four save passes, but take 160 or 200
+    // registers instead of 126 (256 experts, d = 7168, 4096 tokens, rows of heavy tails 161 / 166 / 172 us, normal rows 118 / 122 / 122).
+    constexpr int CB = 4;
     const uint16_t* xr = x + (size_t)t * d;
     // candidate list (ascending expert index inside each q; the order does not matter)
     int n_cand = 0;
@@ -843,8 +850,8 @@ __global__ __launch_bounds__(kThreads) void route_direct_kernel(const uint16_t* 
 }
 
 // Where the int8 form pays: from about 6e8 multiply-adds on, for at least 32 experts (it pads them to a multiple of 64).  Router
-// alone, us, fp64 / int8: 256 experts (d 7168) 256 tokens (4.7e8) 36 / 38, 512 52 / 42, 1024 82 / 50, 2048 149 / 68, 4096
-// 286 / 118; 160 (5120) 1024 tokens 52 / 40; 128 (4096) 1024 tokens (5.4e8) 34 / 35, 1500 44 / 34, 4096 89 / 50; 64 (3584)
+// alone, us, fp64 / int8: 256 experts (d 7168) 256 tokens (4.7e8) 35 / 38, 512 51 / 43, 1024 83 / 48, 2048 149 / 68, 4096
+// 286 / 117; 160 (5120) 1024 tokens 52 / 40; 128 (4096) 1024 tokens (5.4e8) 34 / 35, 1500 44 / 34, 4096 89 / 50; 64 (3584)
 // 2048 tokens (4.7e8) 33 / 34, 3000 44 / 37, 4096 49 / 42; 32 (4096) 4096 tokens (5.4e8) 38 / 40, 8192 69 / 61; 16 (4096)
 // 8192 tokens 40 / 62.  The line is a mean: the fp64 form's time goes in steps, with the rounds of its wavefronts and its groups of 64
 // experts, and where one is just begun the int8 form is ahead earlier (160 experts (5120) 384 tokens, 3.1e8, 38 / 31; 65 (2048) 4096
@@ -853,7 +860,7 @@ __global__ __launch_bounds__(kThreads) void route_direct_kernel(const uint16_t* 
 // larger part.  d = 32768, fp64 / int8: 256 experts 128 tokens (32768) 69 / 84, 192 118 / 88; 160 129 tokens 64 / 75, 256 100 / 77; 128
 // 256 tokens 66 / 68, 384 115 / 71; 64 512 tokens 67 / 68, 800 115 / 76; 32 1000 tokens 67 / 81, 2000 137 / 105.
 // Error of the weights against float64 in every one of these: the same four digits (2.5e-8) in both forms.
-// The three launches of the int8 form take about 11 us (digits), 11 + 1 a step (products) and 12 (selection), of which 5 each
+// The three launches of the int8 form take about 10 us (digits), 14 + 1 a step (products) and 11 (selection), of which 5 each
 // are a launch's own.
 bool digits_pay(const moe_config& c) {
     const double logits = (double)c.T * c.E;
