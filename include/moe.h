@@ -127,8 +127,9 @@ int32_t moe_max_blocks(const moe_config* cfg, int32_t M);
  * logits sum them in integers instead, 30 bits below each row's largest element, with a proven bound on what is
  * left out, and go back to fp64 for what the bound cannot rule on: the choice, its order and its ties are those of the
  * fp64 logits in every case.  Weights are off by one rounding to fp32 (2^-24, relative) and, in those calls, by
- * 2^-24 more at most; only MOE_GATE_SOFTMAX on 2^19 logits (T*E) or more and rows with elements hundreds
- * of times the others' lets the experts that are not chosen carry up to 2^-19 |x| |w| in their logits.  The
+ * 2^-24 more at most; only MOE_GATE_SOFTMAX on 2^19 logits (T*E) or more lets, on rows where the bound is looser
+ * (elements a hundred times the others', logits in the hundreds), the experts that are not chosen carry up to
+ * 2^-19 |x| |w| in their logits.  The
  * k experts are chosen by k rounds of arg-max over z with the winner masked; a tie goes to the
  * lower expert index; outputs are in selection order (descending score).  Weights follow
  * cfg->gating.  workspace: moe_route_workspace_size(cfg) bytes (partial logit tiles, integer digits of W_r). */
