@@ -270,6 +270,60 @@ __device__ __forceinline__ void store_block(const f32x16& g, const f32x16& u, ui
     }
 }
 
+// Epilogue of a whole tile (JBE * 32 rows x 128 * IB features): the bf16 results are staged in LDS, which the reduction loop no
+// longer needs, and every row is stored in one piece of 256 * IB bytes, non-temporally.  store_block writes the same row in
+// pieces of 32 bytes, IB * 8 of them; the write path takes the pieces one by one, and while they wait the workgroup holds its
+// CU.  Whole lines that go straight through L2 also leave it to the weight panels and token rows.  Cached stores of whole rows
+// gain a fifth of that, non-temporal pieces lose.  Projection alone, us, store_block / staged and cached / staged and non-temporal:
+// down, 64 experts of 128 rows, 2048 -> 7168, 371 / 366 / 332, 144 rows 384 / 376 / 342, 16 rows 317 / 317 / 310; gate+up,
+// 8 experts of 144 rows, 4096 -> 14336, 350 / 348 / 336.
+// Every wavefront must call this, with none of its loads into LDS outstanding.
+template <bool GATEUP, int IB, int JBE, int NI>
+__device__ __forceinline__ void store_tile(const f32x16 (&acc)[NI][JBE], const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
+    constexpr int BN = 128 * IB;
+    constexpr int LD = BN * 2 + 16;              // bytes of a staged row: 16 more, so that the 32 rows a wavefront writes spread over the banks
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int li = lane & 31, half = lane >> 5;
+    char* lds = reinterpret_cast<char*>(xs);
+    __syncthreads();                             // nobody reads the ring any more, nothing is landing in it
+    static_for<IB>([&](auto ib) {
+        static_for<JBE>([&](auto j) {
+            char* row = lds + (j * 32 + li) * LD + (wave * IB + ib) * 64 + half * 8;   // the lane's features: q * 8 + 4 * half + 0..3
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float o[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float g = acc[ib][j][q * 4 + v];
+                    o[v] = GATEUP ? silu_mul(g, acc[GATEUP ? IB + ib : ib][j][q * 4 + v]) : g;
+                }
+                *reinterpret_cast<uint2*>(row + q * 16) = make_uint2(pack2_bf16(o[0], o[1]), pack2_bf16(o[2], o[3]));
+            }
+        });
+    });
+    __syncthreads();
+    constexpr int LANES = BN / 8, ROWS = kThreads / LANES;   // lanes per row, rows per pass of the workgroup
+    const int r0 = tid / LANES, c = tid % LANES, f = nt * BN + c * 8;
+    if (f >= a.N) return;
+    uint16_t* out = a.Out + (size_t)t.row0 * a.ldo + f;
+    auto rows = [&](auto stream) {
+#pragma unroll
+        for (int p = 0; p < JBE * 32 / ROWS; ++p) {
+            const int r = p * ROWS + r0;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(lds + r * LD + c * 16);
+            u32x4* dst = reinterpret_cast<u32x4*>(out + (size_t)r * a.ldo);
+            if (r < t.rows) {
+                if constexpr (decltype(stream)::value) __builtin_nontemporal_store(v, dst);
+                else *dst = v;
+            }
+        }
+    };
+    if (t.n_e <= a.M) rows(std::true_type{});
+    else rows(std::false_type{});
+}
+// LDS that store_tile needs
+constexpr int store_lds(int jbe, int ib) { return jbe * 32 * (256 * ib + 16); }
+
 // Up to 1024 rows (permutes_inside): every workgroup of the gate+up launch sorts the router's choice by itself, up to four
 // slots per thread, and reads its own place in the schedule from LDS: same counting sort, same tables as permute.hip's.
 // It takes the place of a launch (5-8 us) and, in each workgroup, of the chain of loads from the tables that the launch
@@ -638,14 +692,7 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
             return fused_combine<IB>(a, t, nt, xs);
         }
     }
-    static_for<IB>([&](auto ib) {
-        static_for<JBE>([&](auto j) {
-            const int tr = j * 32 + li;
-            const bool live = tr < t.rows;
-            store_block<GATEUP>(acc[ib][j], acc[GATEUP ? IB + ib : ib][j],
-                                a.Out + (size_t)(t.row0 + (live ? tr : 0)) * a.ldo, n0w + ib * 32, half, N, live);
-        });
-    });
+    store_tile<GATEUP, IB, JBE, NI>(acc, a, t, nt, xs);
 }
 
 // =============================================================================================
@@ -851,14 +898,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
             return fused_combine<IB>(a, t, nt, xs);
         }
     }
-    static_for<IB>([&](auto ib) {
-        static_for<JBE>([&](auto j) {
-            const int tr = j * 32 + li;
-            const bool live = tr < t.rows;
-            store_block<GATEUP>(acc[ib][j], acc[GATEUP ? IB + ib : ib][j],
-                                a.Out + (size_t)(t.row0 + (live ? tr : 0)) * a.ldo, n0w + ib * 32, half, N, live);
-        });
-    });
+    store_tile<GATEUP, IB, JBE, NI>(acc, a, t, nt, xs);
 }
 
 // MAXJ: tallest tile handed in, in 32-row blocks.
@@ -1337,7 +1377,7 @@ template <int IB, bool GATEUP, bool PACKED, bool WNT, bool HALF = false, bool RO
 hipError_t launch_tile_mixed(const GemmArgs& a, int max_blocks, hipStream_t s) {
     // the DMA ring of tile_body_dma: XD+1 = 4 buffers of 256 (128) rows x 128 bytes; that of rows_body
     constexpr int ni = IB * (GATEUP ? 2 : 1), ring = 4 * (HALF ? 4 : 8) * 32 * 128, rows = HALF ? 0 : rows_lds(rows_max(ni), ni);
-    constexpr int lds = ring > rows ? ring : rows;
+    constexpr int staged = store_lds(HALF ? 4 : 8, IB), loop = ring > rows ? ring : rows, lds = loop > staged ? loop : staged;
     static_assert(!ROUTED || (GATEUP && IB == 1 && PACKED && WNT), "permute_inside is part of the gate+up kernels");
     auto kern = [] {
         if constexpr (ROUTED) return routed_tile_kernel_mixed<HALF>;
@@ -1356,7 +1396,7 @@ hipError_t launch_tile_mixed(const GemmArgs& a, int max_blocks, hipStream_t s) {
 template <int IB, bool GATEUP, bool CHUNK>
 hipError_t launch_rows(const GemmArgs& a, int max_blocks, hipStream_t s) {
     constexpr int NI = IB * (GATEUP ? 2 : 1);
-    constexpr int lds = rows_lds(8, NI);
+    constexpr int loop = rows_lds(8, NI), staged = store_lds(8, IB), lds = loop > staged ? loop : staged;
     auto kern = tile_kernel<IB, GATEUP>;
     // once per process and kernel: not allowed while a stream is being captured into a graph
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
