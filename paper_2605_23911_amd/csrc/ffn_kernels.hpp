@@ -271,12 +271,16 @@ __device__ __forceinline__ void store_block(const f32x16& g, const f32x16& u, ui
 }
 
 // Epilogue of a whole tile (JBE * 32 rows x 128 * IB features): the bf16 results are staged in LDS, which the reduction loop no
-// longer needs, and every row is stored in one piece of 256 * IB bytes, non-temporally.  store_block writes the same row in
-// pieces of 32 bytes, IB * 8 of them; the write path takes the pieces one by one, and while they wait the workgroup holds its
-// CU.  Whole lines that go straight through L2 also leave it to the weight panels and token rows.  Cached stores of whole rows
-// gain a fifth of that, non-temporal pieces lose.  Projection alone, us, store_block / staged and cached / staged and non-temporal:
-// down, 64 experts of 128 rows, 2048 -> 7168, 371 / 366 / 332, 144 rows 384 / 376 / 342, 16 rows 317 / 317 / 310; gate+up,
-// 8 experts of 144 rows, 4096 -> 14336, 350 / 348 / 336.
+// longer needs, and every row is stored in one piece of 256 * IB bytes.  store_block writes the same row in pieces of 32 bytes,
+// IB * 8 of them; the write path takes the pieces one by one, and while they wait the workgroup holds its CU.
+// Non-temporally where the launch writes 2 MiB or more and the expert is one block: whole lines that go straight through L2 leave it
+// to the weights and token rows.  Cached stores of whole rows gain a fifth of that there, non-temporal pieces lose.  Projection alone,
+// us, store_block / staged and cached / staged and non-temporal: down, 64 experts of 128 rows, 2048 -> 7168, 371 / 366 / 332,
+// 144 rows 384 / 376 / 342, 16 rows 317 / 317 / 310; gate+up, 8 experts of 144 rows, 4096 -> 14336, 350 / 348 / 336.  Cached below
+// that size, where the next kernel still finds the results near (layer of 8 experts of 256 x 512, 1000 tokens, 41.3 / 40.7 / 42.9), and
+// for experts of several blocks (32 experts of 2880 x 2880, 1001 tokens at skew 1, down projection 134 / 134 / 139).
+// A single 32-row block with cached stores takes store_block: nothing there pays for two barriers (8 experts of 256 x 512, 64 tokens,
+// layer 20.5 / 20.7; 60 of 2048 x 1408, 64 tokens, 186.4 / 187.2).
 // Every wavefront must call this, with none of its loads into LDS outstanding.
 template <bool GATEUP, int IB, int JBE, int NI>
 __device__ __forceinline__ void store_tile(const f32x16 (&acc)[NI][JBE], const GemmArgs& a, const Tile& t, int nt, uint16_t* xs) {
@@ -285,6 +289,17 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[NI][JBE], const G
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const int li = lane & 31, half = lane >> 5;
     char* lds = reinterpret_cast<char*>(xs);
+    const bool stream = t.n_e <= a.M && (long long)a.R * a.N >= (1ll << 20);
+    if constexpr (JBE == 1) {
+        if (!stream) {
+            const bool live = li < t.rows;
+            static_for<IB>([&](auto ib) {
+                store_block<GATEUP>(acc[ib][0], acc[GATEUP ? IB + ib : ib][0], a.Out + (size_t)(t.row0 + (live ? li : 0)) * a.ldo,
+                                    nt * BN + (wave * IB + ib) * 32, half, a.N, live);
+            });
+            return;
+        }
+    }
     __syncthreads();                             // nobody reads the ring any more, nothing is landing in it
     static_for<IB>([&](auto ib) {
         static_for<JBE>([&](auto j) {
@@ -318,7 +333,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[NI][JBE], const G
             }
         }
     };
-    if (t.n_e <= a.M) rows(std::true_type{});
+    if (stream) rows(std::true_type{});
     else rows(std::false_type{});
 }
 // LDS that store_tile needs
