@@ -250,7 +250,7 @@ moe_status moe_grouped_ffn(const moe_config* c, const void* x_perm, const int32_
     const uint16_t* pdn = pgu ? pgu + packed_gate_up_bytes(*c) / sizeof(uint16_t) : nullptr;
     hipError_t e = launch_block_schedule(*c, offsets, M, blocks, num_blocks, blocks_mix, num_heavy, s);
     if (e == hipSuccess)
-        e = launch_gate_up(*c, M, (const uint16_t*)x_perm, c->d, nullptr, c->F, offsets, blocks, num_blocks, (const uint16_t*)W_gate,
+        e = launch_gate_up(*c, M, (const uint16_t*)x_perm, c->d, nullptr, c->F, offsets, blocks, num_blocks, num_heavy, (const uint16_t*)W_gate,
                            (const uint16_t*)W_up, pgu, (uint16_t*)h, s);
     if (e == hipSuccess)
         e = launch_down(*c, M, (const uint16_t*)h, c->F, offsets, blocks, num_blocks, blocks_mix, num_heavy, (const uint16_t*)W_down, pdn,
@@ -331,9 +331,9 @@ moe_status moe_forward_staged(const moe_config* c, const void* x, const void* W_
     // The row gather of the permutation is folded into the gate+up tile loads (row r is read from
     // x[src_of[r] / k]); the permuted copy of x that moe_permute can write is not needed here.
     if (e == hipSuccess)
-        e = inside ? launch_routed_gate_up(*c, M, (const uint16_t*)x, topk_idx, {counts, offsets, row_of, src_of, blocks, num_blocks},
+        e = inside ? launch_routed_gate_up(*c, M, (const uint16_t*)x, topk_idx, {counts, offsets, row_of, src_of, blocks, num_blocks, num_heavy},
                                            (const uint16_t*)W_gate, (const uint16_t*)W_up, pgu, h, s)
-                   : launch_gate_up(*c, M, (const uint16_t*)x, c->d, src_of, c->F, offsets, blocks, num_blocks,
+                   : launch_gate_up(*c, M, (const uint16_t*)x, c->d, src_of, c->F, offsets, blocks, num_blocks, num_heavy,
                                     (const uint16_t*)W_gate, (const uint16_t*)W_up, pgu, h, s);
     mark(3);
     if (e == hipSuccess)

@@ -92,6 +92,7 @@ hipError_t launch_down(const moe_config& c, int32_t M, const uint16_t* h, int32_
     a.offsets = offsets;
     a.blocks = blocks;
     a.num_blocks = num_blocks;
+    a.num_multi = num_heavy;
     a.R = c.T * c.k;
     a.N = c.d;
     a.K = c.F;
@@ -142,6 +143,9 @@ extern "C" __attribute__((visibility("default"))) int32_t moe_test_map_launch(
     a.offsets = offsets;
     a.blocks = blocks;
     a.num_blocks = &num_blocks;
+    int32_t multi = 0;
+    for (int i = 0; i < num_blocks; ++i) multi |= blocks[2 * i + 1] > 0;
+    a.num_multi = &multi;
     if (blocks_mix != nullptr && knob(kKnobInterleave) != 0) {
         a.blocks_mix = blocks_mix;
         a.num_heavy = &num_heavy;

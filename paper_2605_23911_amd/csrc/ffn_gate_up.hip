@@ -51,7 +51,7 @@ const char* gate_up_variant_name(const moe_config& c, int32_t M, bool packed) {
 namespace {
 
 hipError_t launch(GemmArgs& a, const moe_config& c, int32_t M, const uint16_t* x_rows, int32_t ldx, const int32_t* src_of, int32_t ldh,
-                  const int32_t* offsets, const int32_t* blocks, const int32_t* num_blocks, const uint16_t* wg, const uint16_t* wu,
+                  const int32_t* offsets, const int32_t* blocks, const int32_t* num_blocks, const int32_t* num_heavy, const uint16_t* wg, const uint16_t* wu,
                   const uint16_t* packed_gu, uint16_t* h, hipStream_t s) {
     a.X = x_rows;
     a.src = src_of;
@@ -68,6 +68,7 @@ hipError_t launch(GemmArgs& a, const moe_config& c, int32_t M, const uint16_t* x
     a.offsets = offsets;
     a.blocks = blocks;
     a.num_blocks = num_blocks;
+    a.num_multi = num_heavy;
     a.R = c.T * c.k;
     a.N = c.F;
     a.K = c.d;
@@ -85,10 +86,10 @@ hipError_t launch(GemmArgs& a, const moe_config& c, int32_t M, const uint16_t* x
 
 hipError_t launch_gate_up(const moe_config& c, int32_t M, const uint16_t* x_rows, int32_t ldx, const int32_t* src_of,
                           int32_t ldh, const int32_t* offsets,
-                          const int32_t* blocks, const int32_t* num_blocks, const uint16_t* wg,
+                          const int32_t* blocks, const int32_t* num_blocks, const int32_t* num_heavy, const uint16_t* wg,
                           const uint16_t* wu, const uint16_t* packed_gu, uint16_t* h, hipStream_t s) {
     GemmArgs a{};
-    return launch(a, c, M, x_rows, ldx, src_of, ldh, offsets, blocks, num_blocks, wg, wu, packed_gu, h, s);
+    return launch(a, c, M, x_rows, ldx, src_of, ldh, offsets, blocks, num_blocks, num_heavy, wg, wu, packed_gu, h, s);
 }
 
 hipError_t launch_routed_gate_up(const moe_config& c, int32_t M, const uint16_t* x, const int32_t* topk_idx, const PermuteOut& out,
@@ -98,7 +99,7 @@ hipError_t launch_routed_gate_up(const moe_config& c, int32_t M, const uint16_t*
     a.topk_idx = topk_idx;
     a.perm = out;
     a.E = c.E;
-    return launch(a, c, M, x, c.d, out.src_of, c.F, out.offsets, out.blocks, out.num_blocks, wg, wu, packed_gu, h, s);
+    return launch(a, c, M, x, c.d, out.src_of, c.F, out.offsets, out.blocks, out.num_blocks, out.num_heavy, wg, wu, packed_gu, h, s);
 }
 
 }  // namespace moe

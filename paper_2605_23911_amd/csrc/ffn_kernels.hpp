@@ -62,10 +62,12 @@ struct GemmArgs {
     const int32_t* blocks;      // [*, 2] (expert, row offset inside the expert)
     const int32_t* num_blocks;  // device scalar
     const int32_t* num_heavy;   // device scalar or null: the first *num_heavy blocks belong to multi-block experts (tile_kernel_mixed)
+    const int32_t* num_multi;   // device scalar or null: 0 if no expert has more than one block
     int R, N, K, n_tiles_n;
     int M;                      // tile height of the block schedule (rows per block <= M)
     int sib;                    // tile_kernel_mixed: launch the row tiles of one expert side by side (see there)
-    int chunk;                  // tile_kernel_mixed: one contiguous eighth of the work per XCD (see there)
+    int chunk;                  // tile_kernel_mixed: one contiguous eighth of the work per XCD (see there): 0 never, 1 always, 2 if no expert has more than one block
+    int rot_mul_chunk;          // the k-loop rotation of a launch whose work is cut into eighths
     const int32_t* blocks_mix;  // with num_heavy: the same blocks, those of multi-block experts first (the list the dealt order reads)
     int deal_always;            // tile_kernel_mixed with num_heavy: deal the two classes whatever their proportion (tests)
     int even;                   // tile_kernel_mixed: rows of a multi-tile expert dealt evenly over its schedule entries
@@ -200,7 +202,8 @@ __device__ __forceinline__ uint32_t token_row_bytes(const GemmArgs& a, int row) 
 // Block schedule entry -> tile geometry (Alg. 1: block = (expert, row offset)).
 struct Tile {
     int e, row0, rows;
-    int n_e;   // rows of the whole expert
+    int n_e;       // rows of the whole expert
+    int rot_mul;   // k-loop rotation between workgroups of one XCD, in steps (tile bodies)
 };
 __device__ __forceinline__ bool load_tile(const GemmArgs& a, int tile, int BM, Tile& t) {
     BM = a.M < BM ? a.M : BM;   // a kernel may serve a schedule with shorter blocks than it can hold
@@ -404,7 +407,10 @@ __device__ __forceinline__ void permute_inside(const GemmArgs& a, GemmArgs& b, i
         blk[2 * (block0 + q)] = tid;
         blk[2 * (block0 + q) + 1] = q * a.M;
     }
+    const int several = __any(nb > 1);             // an expert of this wavefront with more than one block
+    if (lane == 0) nblk[8 + wave] = several;
     __syncthreads();
+    if (tid == 0) nblk[1] = nblk[8] | nblk[9] | nblk[10] | nblk[11];
     volatile int32_t* next = wc[wave];
 #pragma unroll
     for (int g = 0; g < kSmallGroups; ++g) {
@@ -438,11 +444,12 @@ __device__ __forceinline__ void permute_inside(const GemmArgs& a, GemmArgs& b, i
             if (tid == a.E - 1) a.perm.offsets[a.E] = row0 + n;
         }
         for (int i = tid; i < 2 * nblk[0]; i += kThreads) a.perm.blocks[i] = blk[i];
-        if (tid == 0) *a.perm.num_blocks = nblk[0];
+        if (tid == 0) a.perm.num_blocks[0] = nblk[0], a.perm.num_heavy[0] = nblk[1];
     }
     b.offsets = off;
     b.blocks = blk;
     b.num_blocks = nblk;
+    b.num_multi = nblk + 1;
     b.src = src;
     b.tables_in_lds = 1;
 }
@@ -599,7 +606,7 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
     // (d = 4096, F = 14336, ...), so they sit in the same L2 channel; workgroups that run together on
     // an XCD (ids 8 apart) start two steps apart and so spread over the channels.  The sum over k
     // does not care about the order.  Steps past the last are re-reads of it (harmless).
-    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)a.rot_mul) % (unsigned)KT);
+    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)t.rot_mul) % (unsigned)KT);
     auto phys = [&](int i) {
         int p = (i < KT ? i : KT - 1) + rot;
         return p >= KT ? p - KT : p;
@@ -820,7 +827,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
         });
     });
-    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)a.rot_mul) % (unsigned)KT);   // see tile_body_dma
+    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)t.rot_mul) % (unsigned)KT);   // see tile_body_dma
     auto phys = [&](int i) {
         int p = (i < KT ? i : KT - 1) + rot;
         return p >= KT ? p - KT : p;
@@ -981,6 +988,7 @@ struct MixedWork {
     int e, row0, rows, n_e;   // expert, first expert-contiguous row, rows of this workgroup, rows of the expert
     int nt;                   // feature tile: of IB * 128 features, or of 128 when `halves`
     bool halves;              // IB == 2 down projection: one 128-feature half of a tile of the split last round (IB = 1 body)
+    bool chunked;             // the launch's work is cut into one contiguous eighth per XCD
     bool deep;                // loads run three steps ahead where the LDS ring holds four (rows_body)
 };
 template <int IB, bool GATEUP>
@@ -1011,7 +1019,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
         // then run on one XCD and its token tile is fetched into one L2 instead of eight (down
         // projection, single-block experts: the h tile of an expert is read by d/128 workgroups
         // and makes up half of what a CU loads).
-        if (a.chunk && !split_round) {
+        if ((a.chunk == 1 || (a.chunk == 2 && a.num_multi != nullptr && *a.num_multi == 0)) && !split_round) {
             const int per = (total + 7) >> 3;
             const int q = w >> 3;
             if (q >= per) return false;
@@ -1145,8 +1153,14 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
     m.n_e = n_e;
     m.nt = nt;
     m.halves = halves;
+    m.chunked = chunked;
     m.deep = a.cus > 0 && (IB * (GATEUP ? 2 : 1) == 1 ? total % a.cus != 0 : 2 * total <= a.cus);   // see rows_body
     return true;
+}
+
+__device__ __forceinline__ int rotation(const GemmArgs& a, const MixedWork& m, bool multi) {
+    const int apart = a.rot_mul, in_step = a.rot_mul_multi, chunk = a.rot_mul_chunk;   // values first: a choice between the fields' addresses puts the whole argument block in scratch memory
+    return multi ? in_step : m.chunked ? chunk : apart;
 }
 
 // The kernel: what to work on from mixed_assign, the regime from the expert's rows, the body from the block's.
@@ -1162,18 +1176,17 @@ __device__ __forceinline__ void tile_mixed(const GemmArgs& a, uint16_t* xs) {
     t.row0 = m.row0;
     t.rows = m.rows;
     t.n_e = m.n_e;
-    GemmArgs b = a;
     // A short last tile of a multi-tile expert runs through k several times faster than its
     // siblings and shares nothing with them in time: it streams the panel like a single-block
     // expert does (non-temporal, k rotated), so that its stream does not evict the panels the
     // full tiles share.
     const bool multi = t.n_e > a.M && t.rows > a.short_nt;
-    if (multi) b.rot_mul = a.rot_mul_multi;
+    t.rot_mul = rotation(a, m, multi);
     const bool shared = multi || a.no_nt;
     if constexpr (IB == 2 && !GATEUP) {
         if (halves) {
-            if (shared || !WNT) return dma_dispatch<1, GATEUP, false, HALF>(b, t, nt, xs);
-            return dma_dispatch<1, GATEUP, WNT, HALF>(b, t, nt, xs);
+            if (shared || !WNT) return dma_dispatch<1, GATEUP, false, HALF>(a, t, nt, xs);
+            return dma_dispatch<1, GATEUP, WNT, HALF>(a, t, nt, xs);
         }
     }
     // Single-block tiles: weights through LDS where three ring buffers fit (rows_body); only taller ones are left
@@ -1182,10 +1195,10 @@ __device__ __forceinline__ void tile_mixed(const GemmArgs& a, uint16_t* xs) {
     constexpr int RM = HALF ? 0 : rows_max(IB * (GATEUP ? 2 : 1));
     if constexpr (RM > 0) {
         if (!multi && !(WNT && a.no_nt) && t.rows <= RM * 32)
-            return rows_dispatch<IB, GATEUP, true, WNT, RM>(b, t, nt, m.deep, xs);
+            return rows_dispatch<IB, GATEUP, true, WNT, RM>(a, t, nt, m.deep, xs);
     }
-    if (shared || !WNT) return dma_dispatch<IB, GATEUP, false, HALF>(b, t, nt, xs);
-    if constexpr (WNT && RM < 8) dma_dispatch<IB, GATEUP, true, HALF, RM + 1>(b, t, nt, xs);
+    if (shared || !WNT) return dma_dispatch<IB, GATEUP, false, HALF>(a, t, nt, xs);
+    if constexpr (WNT && RM < 8) dma_dispatch<IB, GATEUP, true, HALF, RM + 1>(a, t, nt, xs);
 }
 
 template <int IB, bool GATEUP, bool PACKED, bool WNT, bool HALF = false>
@@ -1215,14 +1228,13 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const GemmArgs a) {
     t.row0 = m.row0;
     t.rows = m.rows;
     t.n_e = m.n_e;
-    GemmArgs b = a;
     const bool multi = t.n_e > a.M && t.rows > a.short_nt;
-    if (multi) b.rot_mul = a.rot_mul_multi;
+    t.rot_mul = rotation(a, m, multi);
     if constexpr (IB == 2 && !GATEUP) {
-        if (m.halves) return rows_dispatch<1, GATEUP, false, false, 8>(b, t, m.nt, m.deep, xs);
+        if (m.halves) return rows_dispatch<1, GATEUP, false, false, 8>(a, t, m.nt, m.deep, xs);
     }
-    if (multi || a.no_nt) return rows_dispatch<IB, GATEUP, false, false, 8>(b, t, m.nt, m.deep, xs);
-    rows_dispatch<IB, GATEUP, false, true, 8>(b, t, m.nt, m.deep, xs);
+    if (multi || a.no_nt) return rows_dispatch<IB, GATEUP, false, false, 8>(a, t, m.nt, m.deep, xs);
+    rows_dispatch<IB, GATEUP, false, true, 8>(a, t, m.nt, m.deep, xs);
 }
 
 // =============================================================================================
@@ -1364,10 +1376,20 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     // Test knobs (see moe_internal.hpp) can override the three launch-order choices; -1 = the rule.
     args.sib = knob(kKnobSideBySide) >= 0 ? knob(kKnobSideBySide) : 1;
     args.even = knob(kKnobEvenRows) >= 0 ? knob(kKnobEvenRows) : (GATEUP ? 1 : 2);
-    args.chunk = knob(kKnobXcdChunk) >= 0 ? knob(kKnobXcdChunk) : (!GATEUP && WNT ? 1 : 0);
+    // One contiguous eighth of the work per XCD.  The token tile of an expert then comes from beyond L2 once, not once per XCD;
+    // with 128 rows of a 256-expert layer that was a fifth of all bytes that the gate+up launch moved.
+    //   Gate+up: where the workgroups of a block fit the 32 CUs of an XCD (up to 32 feature tiles) and no expert has more than one
+    // block: those of several go side by side, which eighths would take apart, and XCDs with heavy experts would end last.  k loops one
+    // step apart.  us, all XCDs / eighths: 128 experts of 4096 x 1536, 2048 tokens 629 / 544; 256 of 7168 x 2048, 4096 tokens 2553 / 2353,
+    // 512 tokens 2192 / 2173; Qwen2-MoE shape 1024 tokens 419 / 400; 16 experts of 6144 x 4096, 1000 tokens 275 / 268; at 112 and 128
+    // feature tiles (Mixtral shapes) 335 / 345 and 500 / 517; 32 experts of 2880 x 2880 at skew 1 (several blocks) 224 / 234.
+    //   Down: always while weights are streamed (d/128 or d/256 tiles of an h tile that is as many bytes as their weights); with
+    // cached loads under the same condition as gate+up, k in step: 128 experts 385 / 337, 256 experts 2048 tokens 1465 / 1391.
+    args.chunk = knob(kKnobXcdChunk) >= 0 ? knob(kKnobXcdChunk) : (GATEUP ? (args.n_tiles_n <= 32 ? 2 : 0) : WNT ? 1 : 2);
     args.no_nt = knob(kKnobNoNt) > 0;
     args.short_nt = knob(kKnobShortNt) >= 0 ? knob(kKnobShortNt) : (GATEUP ? 64 : 0);
     args.rot_mul_multi = rot_steps(true);
+    args.rot_mul_chunk = knob(kKnobRot) >= 0 ? knob(kKnobRot) : (GATEUP ? 1 : WNT ? 2 : 0);
     long long grid = ((long long)max_blocks * args.n_tiles_n + 7) / 8 * 8;   // whole eighths for the per-XCD chunking
     args.slots = 0;
     args.cus = cus;

@@ -91,11 +91,12 @@ hipError_t launch_block_schedule(const moe_config& c, const int32_t* offsets, in
 // ldx / ldh: row strides (elements) of x_rows and of h.
 hipError_t launch_gate_up(const moe_config& c, int32_t M, const uint16_t* x_rows, int32_t ldx, const int32_t* src_of,
                           int32_t ldh, const int32_t* offsets,
-                          const int32_t* blocks, const int32_t* num_blocks, const uint16_t* wg,
+                          const int32_t* blocks, const int32_t* num_blocks, const int32_t* num_heavy, const uint16_t* wg,
                           const uint16_t* wu, const uint16_t* packed_gu, uint16_t* h, hipStream_t s);
-// Tables of the permutation and Algorithm 1's block list, as launch_permute_index writes them.
+// Tables of the permutation and Algorithm 1's block list, as launch_permute_index writes them, except that num_heavy says
+// only whether an expert has more than one block.
 struct PermuteOut {
-    int32_t *counts, *offsets, *row_of, *src_of, *blocks, *num_blocks;
+    int32_t *counts, *offsets, *row_of, *src_of, *blocks, *num_blocks, *num_heavy;
 };
 // The same from the un-permuted x[T, d] and the router's choice: the launch permutes by itself and writes the tables.
 // For permutes_inside(c, packed) and a down projection that does not read the second block list (down_deals).
