@@ -96,6 +96,7 @@ hipError_t launch_down(const moe_config& c, int32_t M, const uint16_t* h, int32_
     a.R = c.T * c.k;
     a.N = c.d;
     a.K = c.F;
+    a.E = c.E;
     a.M = M;
     // token rows are addressed with 32-bit byte offsets from the buffer's base
     if ((unsigned long long)a.x_rows * (unsigned long long)ldh * 2ull >= (1ull << 32)) return hipErrorInvalidValue;

@@ -72,6 +72,7 @@ hipError_t launch(GemmArgs& a, const moe_config& c, int32_t M, const uint16_t* x
     a.R = c.T * c.k;
     a.N = c.F;
     a.K = c.d;
+    a.E = c.E;
     a.M = M;
     // token rows are addressed with 32-bit byte offsets from the buffer's base
     if ((unsigned long long)a.x_rows * (unsigned long long)ldx * 2ull >= (1ull << 32)) return hipErrorInvalidValue;
@@ -98,7 +99,6 @@ hipError_t launch_routed_gate_up(const moe_config& c, int32_t M, const uint16_t*
     GemmArgs a{};
     a.topk_idx = topk_idx;
     a.perm = out;
-    a.E = c.E;
     return launch(a, c, M, x, c.d, out.src_of, c.F, out.offsets, out.blocks, out.num_blocks, out.num_heavy, wg, wu, packed_gu, h, s);
 }
 

@@ -66,8 +66,9 @@ struct GemmArgs {
     int R, N, K, n_tiles_n;
     int M;                      // tile height of the block schedule (rows per block <= M)
     int sib;                    // tile_kernel_mixed: launch the row tiles of one expert side by side (see there)
-    int chunk;                  // tile_kernel_mixed: one contiguous eighth of the work per XCD (see there): 0 never, 1 always, 2 if no expert has more than one block
-    int rot_mul_chunk;          // the k-loop rotation of a launch whose work is cut into eighths
+    int chunk;                  // tile_kernel_mixed: runs of `unit` positions per XCD: 0 never, 1 always, 2 by the rule (see there)
+    int unit;                   // length of a run: half of the workgroups that an XCD runs at once
+    int rot_mul_chunk;          // the k-loop rotation of blocks whose feature tiles run on one XCD
     const int32_t* blocks_mix;  // with num_heavy: the same blocks, those of multi-block experts first (the list the dealt order reads)
     int deal_always;            // tile_kernel_mixed with num_heavy: deal the two classes whatever their proportion (tests)
     int even;                   // tile_kernel_mixed: rows of a multi-tile expert dealt evenly over its schedule entries
@@ -83,7 +84,7 @@ struct GemmArgs {
     // Permutation done by the gate+up launch itself (permute_inside; all null / 0 when it is a launch of its own):
     const int32_t* topk_idx;    // [R] the router's choice
     PermuteOut perm;            // what the later stages read, written by workgroup 0
-    int E;
+    int E;                      // experts
     int tables_in_lds;          // src, offsets and blocks are in the LDS that the token ring will use
 };
 
@@ -988,13 +989,13 @@ struct MixedWork {
     int e, row0, rows, n_e;   // expert, first expert-contiguous row, rows of this workgroup, rows of the expert
     int nt;                   // feature tile: of IB * 128 features, or of 128 when `halves`
     bool halves;              // IB == 2 down projection: one 128-feature half of a tile of the split last round (IB = 1 body)
-    bool chunked;             // the launch's work is cut into one contiguous eighth per XCD
+    bool chunked;             // the launch is dealt to the XCDs in runs of consecutive positions
     bool deep;                // loads run three steps ahead where the LDS ring holds four (rows_body)
 };
 template <int IB, bool GATEUP>
 __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, MixedWork& m) {
     int tile, nt;
-    bool halves = false, chunked = false, dealt = false;
+    bool halves = false, dealt = false, units = false;
     const int32_t* blist = a.blocks;   // Algorithm 1's order unless the two classes are dealt (below)
     const int total = *a.num_blocks * a.n_tiles_n;
     int split_from = total;            // first position (in two-block tiles) of a split last round
@@ -1014,19 +1015,6 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
                 }
             }
         }
-        // One contiguous eighth of the (tile-major) work per XCD: the hardware deals workgroup id
-        // to XCD id % 8, so XCD x takes ids x*per .. x*per+per-1.  All feature tiles of a block
-        // then run on one XCD and its token tile is fetched into one L2 instead of eight (down
-        // projection, single-block experts: the h tile of an expert is read by d/128 workgroups
-        // and makes up half of what a CU loads).
-        if ((a.chunk == 1 || (a.chunk == 2 && a.num_multi != nullptr && *a.num_multi == 0)) && !split_round) {
-            const int per = (total + 7) >> 3;
-            const int q = w >> 3;
-            if (q >= per) return false;
-            w = (w & 7) * per + q;
-            chunked = true;
-        }
-        if (w >= total) return false;
         // Heavy and light blocks dealt evenly over the launch.  With a.num_heavy the block list
         // holds the blocks of multi-block experts first (their workgroups are bound by the matrix
         // cores and leave HBM mostly alone), then the single-block experts (bound by the weight
@@ -1045,19 +1033,58 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
         // when the single-block experts number at least 2/5 of the multi-block experts' blocks
         // (measured at T=4096: DeepSeek-V3 shape, 173 / 65 / 31 light against ~130 heavy blocks:
         // -9.6 %, -5.6 %, -1.8 %; Qwen2-MoE shape, 40 / 45 / 32 against ~130: +2.6 %, +2.8 %, +5.5 %).
-        if (a.num_heavy != nullptr && !chunked && !split_round) {
-            const int U = (a.n_tiles_n & 7) == 0 ? 8 : a.n_tiles_n;
+        bool deal = false;
+        int dealU = 1, hu = 0, tu = 0;
+        if (a.num_heavy != nullptr && !split_round) {
             const int hb = *a.num_heavy, lb = *a.num_blocks - hb;
-            const int hu = hb * a.n_tiles_n / U, tu = total / U, lu = tu - hu;
-            if (hu > 0 && lu > 0 && (a.deal_always || 5 * lb >= 2 * hb)) {
-                blist = a.blocks_mix;
-                const int p = w / U, r = w - p * U;
-                // heavy units among positions [0, p): floor(p * hu / tu); position p is heavy iff that count steps at p
-                const long long before = (long long)p * hu / tu, upto = (long long)(p + 1) * hu / tu;
-                const int unit = upto > before ? (int)before : hu + (p - (int)before);
-                w = unit * U + r;
-                dealt = U != 8;   // whole units of 8 ids keep an expert's workgroups on the XCDs the order below assumes
+            dealU = (a.n_tiles_n & 7) == 0 ? 8 : a.n_tiles_n;
+            hu = hb * a.n_tiles_n / dealU;
+            tu = total / dealU;
+            deal = hu > 0 && tu > hu && (a.deal_always || 5 * lb >= 2 * hb);
+        }
+        // Runs of consecutive positions per XCD.  The hardware deals workgroup id to XCD id % 8, so the q-th workgroup of an XCD takes
+        // position q % unit of that XCD's next run, and the XCDs take the runs in turn: at any time the chip works on about the same
+        // stretch of the launch as without them, but what runs on an XCD at once belongs together.  The feature tiles of a
+        // single-block expert then fetch its token tile into one L2 instead of eight (down projection: the h tile of an expert is read
+        // by d/128 workgroups and makes up half of what a CU loads), and the row tiles and panels of a multi-block expert meet
+        // there whatever the feature-tile count (the order further down needs a multiple of 8).  The positions after the last eight
+        // whole runs are cut into eight others.
+        //   By the rule: if no expert has more than one block; with multi-block experts where the feature-tile count is no multiple of 8
+        // or no more than 8, and the launch is four rounds or more, three in the down projection (an XCD's runs may hold more full tiles than another's; in few
+        // rounds that shows: 32 experts of 2880 x 2880, 1001 tokens at skew 1, gate+up 3.6 rounds 219 / 233 us; Mixtral shape, 4096 tokens, down
+        // projection 2.2 rounds 814 / 927, gate+up with 112 tiles 1540 / 1600).
+        // Not when heavy and light blocks are dealt (below).  us, without / with: gate+up 60 experts of 2048 x 1408, 4000 tokens
+        // (11 tiles) 334 / 296, 128 of 4096 x 1536, 4096 tokens (12) 867 / 823, Qwen2-MoE shape 4096 tokens (20) 1066 / 1023; down
+        // projection of the first (8) 193 / 157, 32 experts of 2880 x 2880, 4000 tokens (12) 310 / 286, Qwen2-MoE shape at skew 1 (14) 620 / 596.
+        // A run is half of what an XCD runs at once.  Whole ones share no more (Qwen2-MoE shape, 1024 tokens, down projection 240 / 238 with half;
+        // 256 experts, 4096 tokens 1452 / 1415), and under skew tall tiles of one expert crowd an XCD for longer (Qwen2-MoE shape, skew 2,
+        // 200 tokens, down projection without runs 122 / whole 132 / half 122; 4096 tokens at skew 1, gate+up 1145 / 1155 / 1114).  One contiguous
+        // eighth of the launch per XCD: the same for single-block experts, 6-17 % behind no runs at all where one XCD gets the heavy ones.
+        bool runs = !split_round && !deal && a.chunk != 0;
+        if (runs && a.chunk == 2)
+            runs = (a.num_multi != nullptr && *a.num_multi == 0) ||
+                   (((a.n_tiles_n & 7) != 0 || a.n_tiles_n <= 8) && total >= (GATEUP ? 64 : 48) * a.unit);
+        if (runs) {
+            const int U = a.unit, q = w >> 3, x = w & 7, group = q / U;
+            const int groups = total <= 16 * U ? 0 : total / (8 * U);   // one round: an eighth each
+            if (group < groups) {
+                w = (group * 8 + x) * U + (q - group * U);
+            } else {
+                const int done = groups * 8 * U, rest = total - done, per = (rest + 7) >> 3, r = q - groups * U;
+                if (r >= per || x * per + r >= rest) return false;
+                w = done + x * per + r;
             }
+            units = true;
+        }
+        if (w >= total) return false;
+        if (deal) {
+            blist = a.blocks_mix;
+            const int p = w / dealU, r = w - p * dealU;
+            // heavy units among positions [0, p): floor(p * hu / tu); position p is heavy iff that count steps at p
+            const long long before = (long long)p * hu / tu, upto = (long long)(p + 1) * hu / tu;
+            const int unit = upto > before ? (int)before : hu + (p - (int)before);
+            w = unit * dealU + r;
+            dealt = dealU != 8;   // whole units of 8 ids keep an expert's workgroups on the XCDs the order below assumes
         }
         tile = w / a.n_tiles_n;
         nt = w - tile * a.n_tiles_n;
@@ -1094,7 +1121,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
     // workgroups, the halves and the whole tiles before them alike: the two orders number the
     // positions of a span differently, so one span must use one of them throughout.
     const bool in_split = (tile - ti + n) * a.n_tiles_n > split_from;
-    if (a.sib && !in_split && !chunked && !dealt && n >= 2) {
+    if (a.sib && !in_split && !dealt && n >= 2) {
         auto body = [](int rows) { const int c = (rows + 31) >> 5; return c > 7 ? 8 : c; };
         // tiles that run the same body as the first one (all of them when the rows are dealt evenly)
         const int nf = (even || body(n_e - (n - 1) * bm) == body(bm)) ? n : n - 1;
@@ -1103,6 +1130,9 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
         if (l >= span) {
             ti = n - 1;
             nt = l - span;
+        } else if (units) {
+            nt = l / nf;
+            ti = l - nt * nf;
         } else {
             const int cls = l & 7, j = l >> 3;         // class of the position, index inside the class
             int left_before = 0, whole = 0, mine = 0;
@@ -1153,7 +1183,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
     m.n_e = n_e;
     m.nt = nt;
     m.halves = halves;
-    m.chunked = chunked;
+    m.chunked = units;
     m.deep = a.cus > 0 && (IB * (GATEUP ? 2 : 1) == 1 ? total % a.cus != 0 : 2 * total <= a.cus);   // see rows_body
     return true;
 }
@@ -1368,7 +1398,7 @@ inline int rot_steps(bool dma) {
 
 // Launch order switches, feature-tile count and grid of a tile_kernel_mixed launch (host arithmetic
 // only; `cus` = CUs of the device).  Returns the grid size.
-template <int IB, bool GATEUP, bool WNT>
+template <int IB, bool GATEUP, bool WNT, bool HALF = false>
 inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     constexpr int BN = 4 * IB * 32;
     args.n_tiles_n = (args.N + BN - 1) / BN;
@@ -1376,20 +1406,25 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     // Test knobs (see moe_internal.hpp) can override the three launch-order choices; -1 = the rule.
     args.sib = knob(kKnobSideBySide) >= 0 ? knob(kKnobSideBySide) : 1;
     args.even = knob(kKnobEvenRows) >= 0 ? knob(kKnobEvenRows) : (GATEUP ? 1 : 2);
-    // One contiguous eighth of the work per XCD.  The token tile of an expert then comes from beyond L2 once, not once per XCD;
-    // with 128 rows of a 256-expert layer that was a fifth of all bytes that the gate+up launch moved.
-    //   Gate+up: where the workgroups of a block fit the 32 CUs of an XCD (up to 32 feature tiles) and no expert has more than one
-    // block: those of several go side by side, which eighths would take apart, and XCDs with heavy experts would end last.  k loops one
-    // step apart.  us, all XCDs / eighths: 128 experts of 4096 x 1536, 2048 tokens 629 / 544; 256 of 7168 x 2048, 4096 tokens 2553 / 2353,
-    // 512 tokens 2192 / 2173; Qwen2-MoE shape 1024 tokens 419 / 400; 16 experts of 6144 x 4096, 1000 tokens 275 / 268; at 112 and 128
-    // feature tiles (Mixtral shapes) 335 / 345 and 500 / 517; 32 experts of 2880 x 2880 at skew 1 (several blocks) 224 / 234.
-    //   Down: always while weights are streamed (d/128 or d/256 tiles of an h tile that is as many bytes as their weights); with
-    // cached loads under the same condition as gate+up, k in step: 128 experts 385 / 337, 256 experts 2048 tokens 1465 / 1391.
-    args.chunk = knob(kKnobXcdChunk) >= 0 ? knob(kKnobXcdChunk) : (GATEUP ? (args.n_tiles_n <= 32 ? 2 : 0) : WNT ? 1 : 2);
+    // Runs of consecutive positions per XCD (mixed_assign).  The token tile of an expert then comes from beyond L2 once, not once per
+    // XCD; with 128 rows of a 256-expert layer that was a fifth of all bytes that the gate+up launch moved.
+    //   Gate+up: where the workgroups of a block fit the CUs of an XCD (up to 32 feature tiles).  us, without / with: 128 experts of
+    // 4096 x 1536, 2048 tokens 628 / 540; 256 of 7168 x 2048, 4096 tokens 2567 / 2320, 512 tokens 2165 / 2149; Qwen2-MoE shape 1024
+    // tokens 419 / 398; 16 experts of 6144 x 4096, 1000 tokens 270 / 264; at 112 and 128 feature tiles (Mixtral shapes) 325 / 328 and
+    // 500 / 517.
+    //   Down: 128 experts 354 / 333, 256 experts 2048 tokens 1499 / 1428, Qwen2-MoE shape 512 tokens 234 / 216.
+    // The k loops of such workgroups walk in step, which is where they share most (gate+up of 128 experts of 4096 x 1536, 2048 tokens, one
+    // step apart 599 / in step 534; down projection of 256 experts, 2048 tokens 1487 / 1409; Qwen2-MoE shape 512 tokens two apart 222 /
+    // 218).  Two apart on long loops over streamed weights (down projection of 16 experts, 6400 -> 4096, 1000 tokens 171 / 177 in step).
+    // One apart in gate+up up to 32 rows per expert, where there is little to share and panels a power of two apart are read from one L2
+    // channel (60 experts of 2048 x 1408, 64 tokens 116.5 / 122.9 in step), and for row-major weights, whose rows would be (down
+    // projection of 256 experts, 512 tokens 1233 / 1388).
+    args.chunk = knob(kKnobXcdChunk) >= 0 ? knob(kKnobXcdChunk) : (GATEUP && args.n_tiles_n > 32 ? 0 : 2);
+    args.unit = (HALF ? 2 : 1) * (cus >= 16 ? cus / 16 : 16);
     args.no_nt = knob(kKnobNoNt) > 0;
     args.short_nt = knob(kKnobShortNt) >= 0 ? knob(kKnobShortNt) : (GATEUP ? 64 : 0);
     args.rot_mul_multi = rot_steps(true);
-    args.rot_mul_chunk = knob(kKnobRot) >= 0 ? knob(kKnobRot) : (GATEUP ? 1 : WNT ? 2 : 0);
+    args.rot_mul_chunk = knob(kKnobRot) >= 0 ? knob(kKnobRot) : (GATEUP && args.R <= 32ll * args.E) || args.P == nullptr ? 1 : !GATEUP && WNT && args.K > 4096 ? 2 : 0;
     long long grid = ((long long)max_blocks * args.n_tiles_n + 7) / 8 * 8;   // whole eighths for the per-XCD chunking
     args.slots = 0;
     args.cus = cus;
@@ -1425,7 +1460,7 @@ hipError_t launch_tile_mixed(const GemmArgs& a, int max_blocks, hipStream_t s) {
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     GemmArgs args = a;
-    const long long grid = mixed_launch_shape<IB, GATEUP, WNT>(args, max_blocks, device_cus());
+    const long long grid = mixed_launch_shape<IB, GATEUP, WNT, HALF>(args, max_blocks, device_cus());
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds, s, args);
     return hipGetLastError();
 }

@@ -1,0 +1,51 @@
+"""Runs of consecutive positions per XCD, by the rule: taken where no expert has more than one block (gate+up: up to 32 feature tiles) and, with
+multi-block experts, at feature-tile counts that are no multiple of 8 (or no more than 8) in launches of four rounds (down projection: three);
+not taken otherwise; every row and feature tile covered exactly once either way.  Host arithmetic only."""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+sys.path.insert(0, os.path.dirname(__file__))
+from test_launch_mapping import L, _check_cover, _schedule  # noqa: E402,F401
+
+from paper_2605_23911_amd import binding as B  # noqa: E402
+
+
+def _in_runs(work, unit):
+    """Whether every XCD's workgroups (ids x, x + 8, ..) walk through whole runs of `unit` positions of the tile-major launch."""
+    pos = {}
+    for x in range(8):
+        for q, r in enumerate(work[x::8]):
+            pos.setdefault((x, q // unit), []).append((int(r[2]), int(r[4])) if r[0] else None)
+    order = [t for g in range(max(k[1] for k in pos) + 1) for x in range(8) for t in pos.get((x, g), []) if t is not None]
+    return order == sorted(order)
+
+
+@pytest.mark.parametrize("gateup,ib,wnt,N,few", [(True, 1, True, 2048, True), (True, 1, True, 4096, True), (True, 1, True, 4160, False),
+                                                  (True, 1, True, 1408, True), (False, 2, False, 7168, True), (False, 2, False, 2880, True),
+                                                  (False, 1, True, 2880, True), (False, 2, False, 2048, True)])
+@pytest.mark.parametrize("counts", [[100] * 64, [256, 0, 1, 255] * 24, [200] * 79 + [257], [3, 0, 600, 0, 0, 40] * 20, [300] * 7])
+def test_rule(L, gateup, ib, wnt, N, few, counts):  # noqa: F811
+    offsets, blocks, mix, heavy = _schedule(np.array(counts), 256)
+    work = B.map_launch(gateup, ib, wnt, N, 256, offsets, blocks, None, heavy, cus=256, slack_blocks=5)
+    _check_cover(work, offsets, counts, N, 256, (gateup, ib, wnt, N, counts))
+    tiles = (N + 128 * ib - 1) // (128 * ib)
+    total = len(blocks) * tiles
+    if max(counts) <= 256:                                  # tile-major positions: the runs can be read off
+        if total > 512 or ib == 1:                          # beyond a split last round
+            whole, unit = (total // 128 * 128, 16) if total > 256 else (len(work), len(work) // 8)
+            assert _in_runs(work[:whole], unit) == few
+    # multi-block experts: the order inside an expert differs, coverage is what counts (above)
+
+
+@pytest.mark.parametrize("cus", [8, 24, 64, 256, 304])
+@pytest.mark.parametrize("total_blocks", [1, 2, 7, 33, 64, 65])
+def test_cover_at_every_remainder(L, cus, total_blocks):  # noqa: F811
+    for N in (64, 640, 1408, 2048):
+        counts = [17] * total_blocks
+        offsets, blocks, mix, heavy = _schedule(np.array(counts), 256)
+        for gateup, ib, wnt in ((True, 1, True), (False, 1, True), (False, 2, True), (False, 2, False)):
+            work = B.map_launch(gateup, ib, wnt, N, 256, offsets, blocks, None, heavy, cus=cus, slack_blocks=0)
+            _check_cover(work, offsets, counts, N, 256, (cus, total_blocks, N, gateup, ib, wnt))
