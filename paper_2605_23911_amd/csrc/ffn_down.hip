@@ -39,7 +39,7 @@ int pick(int M, bool packed, const moe_config& c) {
     // experts while the token buffers are small; with many rows per expert on average, the
     // two-weight-block form with cached loads throughout.
     const bool once = (double)R / c.E <= 192.0 && (double)R * c.d * 2.0 <= 128e6;
-    // Row-major: the same line.  9 and 10 differ in the launch order only (10 keeps the row tiles of an
+    // Row-major: 9 and 10 differ in the launch order only (10 keeps the row tiles of an
     // expert side by side: Mixtral shape, 4096 tokens 940 against 1210 us; 9 runs a contiguous eighth
     // of the work per XCD: 0 and 9 at 256 experts, 512 tokens 1330 against 1240 us).  Beyond the line, one weight block
     // (0, three ring buffers or more at any height) against two (10): from 256 rows per expert on 10 is ahead (Mixtral shape 256
@@ -48,7 +48,18 @@ int pick(int M, bool packed, const moe_config& c) {
     // others (16 experts of 6144 x 4096 247 / 230, 4 of 2048 x 8192 94 / 80), but under routing skew, which the host cannot
     // see, it is up to 1.58x behind (8 experts of 6144 x 16384, 200-240 rows: 611-755 / 455-505), so the line stays.
     if (!packed) return once ? (wide ? 9 : 0) : 10;
-    if (once) return wide ? 6 : 5;
+    // Packed.  Two weight blocks also where one block each would make between one and two rounds of workgroups and two make a single
+    // one: us, one / two: Mixtral-8x22B shape (24 tiles of 256 x 8 experts) 64 tokens 266 / 240, 512 tokens 373 / 320, at skew 1 416 / 362; 7
+    // experts, 8192 -> 5120, 300 tokens 155 / 139; 16 experts, 6400 -> 4096, 1000 tokens 174 / 152.  Not where one block each is a
+    // single round (Mixtral-8x7B shape, 700 tokens 212 / 221) or two make a second (24 experts, 4096 -> 3072, 800 tokens 125 / 133).
+    const long long tiles = (long long)((c.d + 127) / 128) * active;
+    const bool one_round = tiles > 256 && tiles <= 512;
+    // Streamed weights up to 240 rows per expert and 256 MB of rows.  us, cached / streamed: Qwen2-MoE shape 1900 tokens (237 rows) 332 / 305, at
+    // skew 1 391 / 359; Mixtral-8x22B shape 900 tokens at skew 1 473 / 440; Mixtral-8x7B shape 900 tokens (225 rows) 270 / 260; 128
+    // experts, 2048 tokens (134 MB) 332 / 323; 256 experts, 2048 tokens (235 MB) 1420 / 1409.  Beyond: 60 experts, 1408 -> 2048, 2400 tokens (240
+    // rows) 138 / 145; 256 experts, 4096 tokens (470 MB) at skew 1, where the cached kernel deals, 1513 / 1561.
+    if ((double)R / c.E < 240.0 && (double)R * c.d * 2.0 <= 256e6)
+        return wide || one_round || (double)R / c.E > 192.0 ? 6 : 5;   // beyond 192 rows many experts have a second block (Mixtral-8x7B shape, 900 tokens, skew 0.3, one / two weight blocks 353 / 312)
     return 7;
 }
 
