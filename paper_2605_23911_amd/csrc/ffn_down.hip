@@ -7,7 +7,7 @@ namespace {
 
 // See the gate+up table for the template parameters; skinny_kernel<JB, gateup, STAGES, SPLITK, packed>.
 const Variant kDown[] = {
-    /*0*/ {256, false, launch_rows<1, false, true>, "tile_kernel<1, false>"},
+    /*0*/ {256, false, launch_rows<1, false>, "tile_kernel<1, false>"},
     /*1*/ {32, false, launch_skinny<1, false, 4, 4, false>, "skinny_kernel<1, false, 4, 4, false>"},
     /*2*/ {64, false, launch_skinny<2, false, 4, 4, false>, "skinny_kernel<2, false, 4, 4, false>"},
     /*3*/ {32, true, launch_skinny<1, false, 4, 4, true>, "skinny_kernel<1, false, 4, 4, true>"},
@@ -16,8 +16,8 @@ const Variant kDown[] = {
     /*6*/ {256, true, launch_down_mixed_wide_nt, "tile_kernel_mixed<2, false, true, true, false>"},
     /*7*/ {256, true, launch_down_mixed_wide, "tile_kernel_mixed<2, false, true, false, false>"},
     /*8*/ {128, true, launch_tile_mixed<1, false, true, true, true>, "tile_kernel_mixed<1, false, true, true, true>"},
-    /*9*/ {256, false, launch_down_rows_wide_chunk, "tile_kernel<2, false>"},
-    /*10*/ {256, false, launch_down_rows_wide, "tile_kernel<2, false>"},
+    /*9*/ {256, false, launch_down_rows_wide, "tile_kernel<2, false>"},
+    /*10*/ {256, false, launch_down_rows_wide, "tile_kernel<2, false>"},   // the same: both numbers stay in use
 };
 constexpr int kNumDown = sizeof(kDown) / sizeof(kDown[0]);
 
@@ -35,13 +35,9 @@ int pick(int M, bool packed, const moe_config& c) {
     if (few_rows && M <= 32) return packed ? 3 : 1;
     if (few_rows && M <= 64) return packed ? 4 : 2;
     if (packed && M <= 128 && two_workgroups_per_cu(c)) return 8;
-    // Per-block regime selection (tile_kernel_mixed, tile_kernel).  Non-temporal weight loads for single-block
-    // experts while the token buffers are small; with many rows per expert on average, the
-    // two-weight-block form with cached loads throughout.
+    // Per-block regime selection (tile_kernel_mixed, tile_kernel).  The line between one weight block and two for row-major weights:
     const bool once = (double)R / c.E <= 192.0 && (double)R * c.d * 2.0 <= 128e6;
-    // Row-major: 9 and 10 differ in the launch order only (10 keeps the row tiles of an
-    // expert side by side: Mixtral shape, 4096 tokens 940 against 1210 us; 9 runs a contiguous eighth
-    // of the work per XCD: 0 and 9 at 256 experts, 512 tokens 1330 against 1240 us).  Beyond the line, one weight block
+    // Row-major, up to the line: 0 and 9 at 256 experts, 512 tokens 1330 against 1240 us.  Beyond the line, one weight block
     // (0, three ring buffers or more at any height) against two (10): from 256 rows per expert on 10 is ahead (Mixtral shape 256
     // rows 432 / 396 us, 320 450 / 370, 512 694 / 545; Qwen2-MoE shape 256 rows 440 / 426).  At 200-248 rows with near-uniform
     // routing 0 is 3-15 % ahead on some shapes (Mixtral 246 / 263, 32 experts of 2880 x 2880 154 / 181) and 0-18 % behind on

@@ -13,12 +13,8 @@ hipError_t launch_down_mixed_wide(const GemmArgs& a, int max_blocks, hipStream_t
     return launch_tile_mixed<2, false, true, false>(a, max_blocks, s);
 }
 
-hipError_t launch_down_rows_wide_chunk(const GemmArgs& a, int max_blocks, hipStream_t s) {
-    return launch_rows<2, false, true>(a, max_blocks, s);
-}
-
 hipError_t launch_down_rows_wide(const GemmArgs& a, int max_blocks, hipStream_t s) {
-    return launch_rows<2, false, false>(a, max_blocks, s);
+    return launch_rows<2, false>(a, max_blocks, s);
 }
 
 }  // namespace moe

@@ -9,7 +9,7 @@ namespace {
 // tile_kernel<IB, gateup>: row-major weights,
 // tile_kernel_mixed<IB, gateup, packed, NT weights for single-block experts, two workgroups per CU>.
 const Variant kGateUp[] = {
-    /*0*/ {256, false, launch_rows<1, true, false>, "tile_kernel<1, true>"},
+    /*0*/ {256, false, launch_rows<1, true>, "tile_kernel<1, true>"},
     /*1*/ {256, true, launch_tile_mixed<1, true, true, true>, "tile_kernel_mixed<1, true, true, true, false>"},
     /*2*/ {128, true, launch_tile_mixed<1, true, true, true, true>, "tile_kernel_mixed<1, true, true, true, true>"},
 };

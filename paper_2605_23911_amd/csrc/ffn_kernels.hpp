@@ -98,7 +98,6 @@ hipError_t launch_routed_mixed_half(const GemmArgs& a, int max_blocks, hipStream
 hipError_t launch_down_mixed_wide_nt(const GemmArgs& a, int max_blocks, hipStream_t s);
 hipError_t launch_down_mixed_wide(const GemmArgs& a, int max_blocks, hipStream_t s);
 hipError_t launch_down_rows_wide(const GemmArgs& a, int max_blocks, hipStream_t s);
-hipError_t launch_down_rows_wide_chunk(const GemmArgs& a, int max_blocks, hipStream_t s);
 
 namespace {
 
@@ -235,7 +234,8 @@ __device__ __forceinline__ bool map_workgroup(const GemmArgs& a, int& tile, int&
 // features q*8 + 4*(lane/32) + 0..3 (q = 0..3) of the block that starts at feature f0.  The two
 // lanes of a row (lane and lane^32) swap halves so that each writes two 16-byte pieces (lane/32
 // = 0: features 0..7 and 16..23, lane/32 = 1: 8..15 and 24..31) instead of four 8-byte ones:
-// half as many store instructions and write requests.  Every lane of the wavefront must call
+// half as many store instructions and write requests.  For few rows, and for results that other workgroups of the launch read
+// (fused_combine); else store_tile.  Every lane of the wavefront must call
 // this (the swap is a cross-lane operation); `live` masks the stores of rows beyond the tile.
 // DEVICE_SCOPE: the 16-byte pieces are written with device-scope (sc1) stores, which go through
 // to the level all XCDs share, so that a workgroup on another XCD can read them after this
@@ -1425,7 +1425,7 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     args.short_nt = knob(kKnobShortNt) >= 0 ? knob(kKnobShortNt) : (GATEUP ? 64 : 0);
     args.rot_mul_multi = rot_steps(true);
     args.rot_mul_chunk = knob(kKnobRot) >= 0 ? knob(kKnobRot) : (GATEUP && args.R <= 32ll * args.E) || args.P == nullptr ? 1 : !GATEUP && WNT && args.K > 4096 ? 2 : 0;
-    long long grid = ((long long)max_blocks * args.n_tiles_n + 7) / 8 * 8;   // whole eighths for the per-XCD chunking
+    long long grid = ((long long)max_blocks * args.n_tiles_n + 7) / 8 * 8;   // as many for every XCD (the runs)
     args.slots = 0;
     args.cus = cus;
     if constexpr (IB == 2 && !GATEUP) {
@@ -1465,7 +1465,7 @@ hipError_t launch_tile_mixed(const GemmArgs& a, int max_blocks, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int IB, bool GATEUP, bool CHUNK>
+template <int IB, bool GATEUP>
 hipError_t launch_rows(const GemmArgs& a, int max_blocks, hipStream_t s) {
     constexpr int NI = IB * (GATEUP ? 2 : 1);
     constexpr int loop = rows_lds(8, NI), staged = store_lds(8, IB), lds = loop > staged ? loop : staged;
@@ -1475,7 +1475,7 @@ hipError_t launch_rows(const GemmArgs& a, int max_blocks, hipStream_t s) {
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     GemmArgs args = a;
-    const long long grid = mixed_launch_shape<IB, GATEUP, CHUNK>(args, max_blocks, device_cus());
+    const long long grid = mixed_launch_shape<IB, GATEUP, false>(args, max_blocks, device_cus());
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds, s, args);
     return hipGetLastError();
 }

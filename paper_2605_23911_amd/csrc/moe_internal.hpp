@@ -45,7 +45,7 @@ enum {
     kKnobDownVariant = 1,     // index into the down-projection variant table
     kKnobSideBySide = 2,      // 0: plain tile-major order inside multi-tile experts
     kKnobEvenRows = 3,        // 0: Algorithm 1's row ranges everywhere, 3: every multi-tile expert dealt evenly
-    kKnobXcdChunk = 4,        // 0/1: per-XCD contiguous chunks off/on for both projections
+    kKnobXcdChunk = 4,        // 0/1: runs of consecutive positions per XCD off/on for both projections
     kKnobRot = 5,             // k-loop rotation between the workgroups of an XCD, in steps
     kKnobShortNt = 6,         // rows up to which a multi-tile expert's last tile streams its weights non-temporally
     kKnobFuseCombine = 7,     // 0: moe_forward always launches the combine kernel, 1: folds it into the down projection whenever the kernel can
