@@ -97,7 +97,7 @@ def lib() -> C.CDLL:
     L.moe_test_knob.restype = C.c_int32       # test hook, not part of include/moe.h
     L.moe_test_knob.argtypes = [C.c_int32, C.c_int32]
     L.moe_test_map_launch.restype = C.c_int32  # test hook (host arithmetic only), not part of include/moe.h
-    L.moe_test_map_launch.argtypes = [C.c_int32] * 5 + [i32p, i32p, C.c_int32, i32p, C.c_int32, C.c_int32, C.c_int32,
+    L.moe_test_map_launch.argtypes = [C.c_int32] * 9 + [i32p, i32p, C.c_int32, i32p, C.c_int32, C.c_int32, C.c_int32,
                                       C.c_int32, i32p]
     _lib = L
     return L
@@ -169,11 +169,11 @@ def test_knob(which: int, value: int) -> int:
 
 
 def map_launch(gateup: bool, ib: int, wnt: bool, N: int, M: int, offsets, blocks, blocks_mix=None, num_heavy: int = 0,
-               cus: int = 256, slack_blocks: int = 0):
+               cus: int = 256, slack_blocks: int = 0, K: int = 4096, packed: bool = True, half: bool = False, runs: bool = False):
     """Test hook: what every workgroup of a per-block-regime GEMM launch would work on, computed on
     the host by the code the kernels run.  offsets [E+1], blocks / blocks_mix [n, 2]: numpy int32
-    (host).  Returns an int32 array [grid, 6] = (has work, expert, first row, rows, feature tile,
-    tile width in units of 128 features)."""
+    (host).  half: the build for two workgroups per CU.  Returns an int32 array [grid, 6] = (has work, expert, first row, rows, feature
+    tile, tile width in units of 128 features); with `runs` a seventh column, whether the launch is dealt in runs of positions per XCD."""
     import numpy as np
     offsets = np.ascontiguousarray(offsets, dtype=np.int32)
     blocks = np.ascontiguousarray(blocks, dtype=np.int32).reshape(-1, 2)
@@ -185,13 +185,13 @@ def map_launch(gateup: bool, ib: int, wnt: bool, N: int, M: int, offsets, blocks
     max_blocks = nb + slack_blocks
     tiles = (N + 128 * ib - 1) // (128 * ib)
     capacity = (max_blocks * tiles + 7) // 8 * 8 + cus
-    out = np.zeros((capacity, 6), dtype=np.int32)
-    grid = lib().moe_test_map_launch(int(gateup), ib, int(wnt), N, M, as_p(offsets), as_p(blocks), nb,
+    out = np.zeros((capacity, 7), dtype=np.int32)
+    grid = lib().moe_test_map_launch(int(gateup), ib, int(wnt), int(half), int(packed), N, K, offsets.size - 1, M, as_p(offsets), as_p(blocks), nb,
                                      as_p(blocks_mix) if blocks_mix is not None else None, num_heavy, cus, max_blocks,
                                      capacity, as_p(out))
     if grid < 0:
         raise MoEError(f"moe_test_map_launch refused (gateup={gateup}, ib={ib})")
-    return out[:grid]
+    return out[:grid, :7 if runs else 6]
 
 
 def forward_workspace_layout(cfg) -> WorkspaceLayout:

@@ -137,17 +137,23 @@ hipError_t launch_down(const moe_config& c, int32_t M, const uint16_t* h, int32_
 
 // Test hook (exported, not declared in include/moe.h): enumerate on the HOST what every workgroup
 // of a per-block-regime GEMM launch would work on, with the launch-order switches and the grid the
-// launcher itself would use.  All array arguments are host memory.  out[w] = {has work, expert,
-// first row, rows, feature tile, feature-tile width in units of 128}; returns the grid size, or -1
+// launcher itself would use.  All array arguments are host memory; E experts hold offsets[E] rows of K elements, `packed` says how
+// the weights are laid out, `half` names the build for two workgroups per CU.  out[w] = {has work, expert,
+// first row, rows, feature tile, feature-tile width in units of 128, in runs of positions per XCD}; returns the grid size, or -1
 // if it exceeds `capacity` or (gateup, ib) names no kernel.  blocks_mix may be null (no dealing).
 extern "C" __attribute__((visibility("default"))) int32_t moe_test_map_launch(
-    int32_t gateup, int32_t ib, int32_t wnt, int32_t N, int32_t M, const int32_t* offsets, const int32_t* blocks,
-    int32_t num_blocks, const int32_t* blocks_mix, int32_t num_heavy, int32_t cus, int32_t max_blocks, int32_t capacity,
+    int32_t gateup, int32_t ib, int32_t wnt, int32_t half, int32_t packed, int32_t N, int32_t K, int32_t E, int32_t M, const int32_t* offsets,
+    const int32_t* blocks, int32_t num_blocks, const int32_t* blocks_mix, int32_t num_heavy, int32_t cus, int32_t max_blocks, int32_t capacity,
     int32_t* out) {
     using namespace moe;
     GemmArgs a{};
     a.N = N;
     a.M = M;
+    a.K = K;
+    a.E = E;
+    a.R = offsets[E];
+    const uint16_t weights = 0;
+    a.P = packed ? &weights : nullptr;   // only whether there is a packed copy is asked
     a.offsets = offsets;
     a.blocks = blocks;
     a.num_blocks = &num_blocks;
@@ -159,26 +165,29 @@ extern "C" __attribute__((visibility("default"))) int32_t moe_test_map_launch(
         a.num_heavy = &num_heavy;
         a.deal_always = knob(kKnobInterleave) > 0;
     }
-    auto run = [&](auto ibc, auto guc, auto wntc) -> int32_t {
+    auto run = [&](auto ibc, auto guc, auto wntc, auto halfc) -> int32_t {
         constexpr int IB = decltype(ibc)::value;
-        constexpr bool GU = decltype(guc)::value, WNT = decltype(wntc)::value;
-        const long long grid = mixed_launch_shape<IB, GU, WNT>(a, max_blocks, cus);
+        constexpr bool GU = decltype(guc)::value, WNT = decltype(wntc)::value, HALF = decltype(halfc)::value;
+        const long long grid = mixed_launch_shape<IB, GU, WNT, HALF>(a, max_blocks, cus);
         if (grid > capacity) return -1;
         for (int w = 0; w < (int)grid; ++w) {
             MixedWork m{};
             const bool has = mixed_assign<IB, GU>(a, w, m);
-            int32_t* o = out + 6 * (size_t)w;
+            int32_t* o = out + 7 * (size_t)w;
             o[0] = has;
             o[1] = m.e; o[2] = m.row0; o[3] = m.rows; o[4] = m.nt;
             o[5] = m.halves ? 1 : IB;
+            o[6] = m.chunked;
         }
         return (int32_t)grid;
     };
-    using std::integral_constant;
     using T_ = std::true_type;
     using F_ = std::false_type;
-    if (gateup && ib == 1) return wnt ? run(integral_constant<int, 1>{}, T_{}, T_{}) : run(integral_constant<int, 1>{}, T_{}, F_{});
-    if (!gateup && ib == 1) return wnt ? run(integral_constant<int, 1>{}, F_{}, T_{}) : run(integral_constant<int, 1>{}, F_{}, F_{});
-    if (!gateup && ib == 2) return wnt ? run(integral_constant<int, 2>{}, F_{}, T_{}) : run(integral_constant<int, 2>{}, F_{}, F_{});
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    if (ib == 1 && half) return gateup ? run(one, T_{}, T_{}, T_{}) : run(one, F_{}, T_{}, T_{});
+    if (gateup && ib == 1) return wnt ? run(one, T_{}, T_{}, F_{}) : run(one, T_{}, F_{}, F_{});
+    if (!gateup && ib == 1) return wnt ? run(one, F_{}, T_{}, F_{}) : run(one, F_{}, F_{}, F_{});
+    if (!gateup && ib == 2) return wnt ? run(two, F_{}, T_{}, F_{}) : run(two, F_{}, F_{}, F_{});
     return -1;
 }

@@ -1409,22 +1409,28 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     // Runs of consecutive positions per XCD (mixed_assign).  The token tile of an expert then comes from beyond L2 once, not once per
     // XCD; with 128 rows of a 256-expert layer that was a fifth of all bytes that the gate+up launch moved.
     //   Gate+up: where the workgroups of a block fit the CUs of an XCD (up to 32 feature tiles).  us, without / with: 128 experts of
-    // 4096 x 1536, 2048 tokens 628 / 540; 256 of 7168 x 2048, 4096 tokens 2567 / 2320, 512 tokens 2165 / 2149; Qwen2-MoE shape 1024
+    // 4096 x 1536, 2048 tokens 628 / 540; 256 of 7168 x 2048, 4096 tokens 2567 / 2320; Qwen2-MoE shape 1024
     // tokens 419 / 398; 16 experts of 6144 x 4096, 1000 tokens 270 / 264; at 112 and 128 feature tiles (Mixtral shapes) 325 / 328 and
-    // 500 / 517.
+    // 500 / 517.  From 64 rows per expert on (uniform routing): below, a token tile is too little to share, and what runs on an XCD at once
+    // reads weight panels that lie a power of two apart at d = 4096 and 2048, out of few L2 channels: 128 experts of 4096 x 1536, 19 rows
+    // 497 / 628, 44 rows 534 / 552, 62 rows 569 / 549; 64 of 4096 x 2048, 31 rows 349 / 404, 62 rows 366 / 356; 32 of 4096 x 4096, 31 rows
+    // 336 / 392, 55 rows 336 / 349; other widths -3 to +2 %.  Row-major weights not at multiples of 16 tiles, whose runs are whole
+    // experts: 64 experts of 2048 x 2048, 8 rows 167 / 178, 62 rows 183 / 190; 32 of 4096 x 4096, 100 rows 367 / 381; ahead at 128 of
+    // 4096 x 1536, 69 rows 562 / 532, 125 rows 619 / 569.
     //   Down: 128 experts 354 / 333, 256 experts 2048 tokens 1499 / 1428, Qwen2-MoE shape 512 tokens 234 / 216.
     // The k loops of such workgroups walk in step, which is where they share most (gate+up of 128 experts of 4096 x 1536, 2048 tokens, one
     // step apart 599 / in step 534; down projection of 256 experts, 2048 tokens 1487 / 1409; Qwen2-MoE shape 512 tokens two apart 222 /
     // 218).  Two apart on long loops over streamed weights (down projection of 16 experts, 6400 -> 4096, 1000 tokens 171 / 177 in step).
-    // One apart in gate+up up to 32 rows per expert, where there is little to share and panels a power of two apart are read from one L2
-    // channel (60 experts of 2048 x 1408, 64 tokens 116.5 / 122.9 in step), and for row-major weights, whose rows would be (down
-    // projection of 256 experts, 512 tokens 1233 / 1388).
-    args.chunk = knob(kKnobXcdChunk) >= 0 ? knob(kKnobXcdChunk) : (GATEUP && args.n_tiles_n > 32 ? 0 : 2);
+    // One apart for row-major weights, whose rows would all be read from one L2 channel (down projection of 256 experts, 512 tokens 1233 / 1388).
+    const bool packed = args.P != nullptr;
+    const bool shares = !GATEUP || (args.n_tiles_n <= 32 && args.R >= 64ll * args.E && (packed || args.n_tiles_n % 16 != 0));
+    args.chunk = knob(kKnobXcdChunk) >= 0 ? knob(kKnobXcdChunk) : shares ? 2 : 0;
     args.unit = (HALF ? 2 : 1) * (cus >= 16 ? cus / 16 : 16);
     args.no_nt = knob(kKnobNoNt) > 0;
     args.short_nt = knob(kKnobShortNt) >= 0 ? knob(kKnobShortNt) : (GATEUP ? 64 : 0);
     args.rot_mul_multi = rot_steps(true);
-    args.rot_mul_chunk = knob(kKnobRot) >= 0 ? knob(kKnobRot) : (GATEUP && args.R <= 32ll * args.E) || args.P == nullptr ? 1 : !GATEUP && WNT && args.K > 4096 ? 2 : 0;
+    const int in_runs = !packed ? 1 : (!GATEUP && WNT && args.K > 4096) ? 2 : 0;
+    args.rot_mul_chunk = knob(kKnobRot) >= 0 ? knob(kKnobRot) : in_runs;
     long long grid = ((long long)max_blocks * args.n_tiles_n + 7) / 8 * 8;   // as many for every XCD (the runs)
     args.slots = 0;
     args.cus = cus;

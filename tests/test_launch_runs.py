@@ -49,3 +49,24 @@ def test_cover_at_every_remainder(L, cus, total_blocks):  # noqa: F811
         for gateup, ib, wnt in ((True, 1, True), (False, 1, True), (False, 2, True), (False, 2, False)):
             work = B.map_launch(gateup, ib, wnt, N, 256, offsets, blocks, None, heavy, cus=cus, slack_blocks=0)
             _check_cover(work, offsets, counts, N, 256, (cus, total_blocks, N, gateup, ib, wnt))
+
+
+def _taken(gateup, ib, wnt, N, counts, M=256, **kw):
+    """Whether the launch is dealt in runs: one answer for all of its workgroups."""
+    offsets, blocks, _, _ = _schedule(np.array(counts), M)
+    work = B.map_launch(gateup, ib, wnt, N, M, offsets, blocks, runs=True, **kw)
+    _check_cover(work[:, :6], offsets, counts, N, M, (gateup, ib, wnt, N, kw))
+    taken = {int(r[6]) for r in work if r[0]}
+    assert len(taken) == 1
+    return bool(taken.pop())
+
+
+@pytest.mark.parametrize("N,rows,packed,runs", [(1536, 63, True, False), (1536, 64, True, True), (1536, 4, True, False), (2048, 64, True, True),
+                                                (4096, 64, True, True), (4160, 100, True, False), (1536, 63, False, False), (1536, 64, False, True),
+                                                (2048, 100, False, False), (4096, 100, False, False), (1408, 100, False, True)])
+def test_gate_up_needs_rows_to_share(L, N, rows, packed, runs):  # noqa: F811
+    """Below 64 rows per expert (and with row-major weights at multiples of 16 feature tiles) there is too little to share, and the weight
+    panels that an XCD reads at once lie in few L2 channels."""
+    assert _taken(True, 1, packed, N, [rows] * 64, packed=packed) == runs
+    if rows < 64:                                          # the build for two workgroups per CU holds at most 32 rows per expert
+        assert not _taken(True, 1, True, N, [min(rows, 32)] * 64, M=128, half=True)
