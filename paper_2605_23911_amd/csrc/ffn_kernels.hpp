@@ -36,6 +36,7 @@
 //                      where there are too few output rows to fill 256 CUs otherwise).
 #pragma once
 
+#include <climits>
 #include <type_traits>
 #include <utility>
 
@@ -68,6 +69,7 @@ struct GemmArgs {
     int sib;                    // tile_kernel_mixed: launch the row tiles of one expert side by side (see there)
     int chunk;                  // tile_kernel_mixed: runs of `unit` positions per XCD: 0 never, 1 always, 2 by the rule (see there)
     int unit;                   // length of a run: half of the workgroups that an XCD runs at once
+    int multi_from;             // chunk 2: workgroups from which on a launch with multi-block experts goes in runs
     int rot_mul_chunk;          // the k-loop rotation of blocks whose feature tiles run on one XCD
     const int32_t* blocks_mix;  // with num_heavy: the same blocks, those of multi-block experts first (the list the dealt order reads)
     int deal_always;            // tile_kernel_mixed with num_heavy: deal the two classes whatever their proportion (tests)
@@ -1049,10 +1051,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
         // by d/128 workgroups and makes up half of what a CU loads), and the row tiles and panels of a multi-block expert meet
         // there whatever the feature-tile count (the order further down needs a multiple of 8).  The positions after the last eight
         // whole runs are cut into eight others.
-        //   By the rule: if no expert has more than one block; with multi-block experts where the feature-tile count is no multiple of 8
-        // or no more than 8, and the launch is four rounds or more, three in the down projection (an XCD's runs may hold more full tiles than another's; in few
-        // rounds that shows: 32 experts of 2880 x 2880, 1001 tokens at skew 1, gate+up 3.6 rounds 219 / 233 us; Mixtral shape, 4096 tokens, down
-        // projection 2.2 rounds 814 / 927, gate+up with 112 tiles 1540 / 1600).
+        //   By the rule: if no expert has more than one block; with multi-block experts from multi_from workgroups on (mixed_launch_shape).
         // Not when heavy and light blocks are dealt (below).  us, without / with: gate+up 60 experts of 2048 x 1408, 4000 tokens
         // (11 tiles) 334 / 296, 128 of 4096 x 1536, 4096 tokens (12) 867 / 823, Qwen2-MoE shape 4096 tokens (20) 1066 / 1023; down
         // projection of the first (8) 193 / 157, 32 experts of 2880 x 2880, 4000 tokens (12) 310 / 286, Qwen2-MoE shape at skew 1 (14) 620 / 596.
@@ -1062,8 +1061,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
         // eighth of the launch per XCD: the same for single-block experts, 6-17 % behind no runs at all where one XCD gets the heavy ones.
         bool runs = !split_round && !deal && a.chunk != 0;
         if (runs && a.chunk == 2)
-            runs = (a.num_multi != nullptr && *a.num_multi == 0) ||
-                   (((a.n_tiles_n & 7) != 0 || a.n_tiles_n <= 8) && total >= (GATEUP ? 64 : 48) * a.unit);
+            runs = (a.num_multi != nullptr && *a.num_multi == 0) || total >= a.multi_from;
         if (runs) {
             const int U = a.unit, q = w >> 3, x = w & 7, group = q / U;
             const int groups = total <= 16 * U ? 0 : total / (8 * U);   // one round: an eighth each
@@ -1426,6 +1424,16 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     const bool shares = !GATEUP || (args.n_tiles_n <= 32 && args.R >= 64ll * args.E && (packed || args.n_tiles_n % 16 != 0));
     args.chunk = knob(kKnobXcdChunk) >= 0 ? knob(kKnobXcdChunk) : shares ? 2 : 0;
     args.unit = (HALF ? 2 : 1) * (cus >= 16 ? cus / 16 : 16);
+    // With multi-block experts: where the feature-tile count is no multiple of 8, or 8 or less (else the side-by-side order has the tiles
+    // that share a panel on one XCD already), and the launch is four rounds or more, three in the down projection, because
+    // an XCD's runs may hold more full tiles than another's (32 experts of 2880 x 2880, 1001 tokens at skew 1, gate+up 3.6 rounds 219 / 233 us; Mixtral
+    // shape, 4096 tokens, down projection 2.2 rounds 814 / 927, gate+up with 112 tiles 1540 / 1600).  In the down projection in launches of any
+    // length where a run holds a whole block: up to 16 feature tiles with streamed weights, up to 8 otherwise.  us, without / with: 64 experts of 896 x
+    // 2048 (7 tiles), 1000 tokens, skew 0.6 87 / 71, skew 2 79 / 65; 60 of 1024 x 1408 (8), 300 tokens, skew 1.2 45 / 44, 128 of 640 x 1024 (5), 2000 tokens,
+    // skew 0.6 55 / 49; 16 of 1792 x 3584 (14), 300 tokens 61 / 58, 700 tokens 84 / 86; cached weights, 16 of 1024 x 4096 (4), 2000 tokens, skew 0.6 100 / 91, but
+    // 8 of 2880 x 2880 (12), 2000 tokens, skew 1.4 76 / 80.  With 23 tiles 101 / 112 (32 of 2880 x 2880, 300 tokens, skew 1.2).
+    const bool scattered = args.n_tiles_n % 8 != 0 || args.n_tiles_n <= 8;
+    args.multi_from = !scattered ? INT_MAX : GATEUP ? 64 * args.unit : args.n_tiles_n <= (WNT ? 16 : 8) ? 0 : 48 * args.unit;
     args.no_nt = knob(kKnobNoNt) > 0;
     args.short_nt = knob(kKnobShortNt) >= 0 ? knob(kKnobShortNt) : (GATEUP ? 64 : 0);
     args.rot_mul_multi = rot_steps(true);

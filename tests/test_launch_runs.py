@@ -1,6 +1,6 @@
-"""Runs of consecutive positions per XCD, by the rule: taken where no expert has more than one block (gate+up: up to 32 feature tiles) and, with
-multi-block experts, at feature-tile counts that are no multiple of 8 (or no more than 8) in launches of four rounds (down projection: three);
-not taken otherwise; every row and feature tile covered exactly once either way.  Host arithmetic only."""
+"""Runs of consecutive positions per XCD: when the rule takes them, on both sides of each of its lines (single-block experts; gate+up by rows
+per expert and feature tiles; with multi-block experts by feature tiles and rounds), and that every row and feature tile is covered exactly once
+either way.  Host arithmetic only."""
 import os
 import sys
 
@@ -70,3 +70,15 @@ def test_gate_up_needs_rows_to_share(L, N, rows, packed, runs):  # noqa: F811
     assert _taken(True, 1, packed, N, [rows] * 64, packed=packed) == runs
     if rows < 64:                                          # the build for two workgroups per CU holds at most 32 rows per expert
         assert not _taken(True, 1, True, N, [min(rows, 32)] * 64, M=128, half=True)
+
+
+@pytest.mark.parametrize("gateup,ib,wnt,N,blocks,runs", [
+    (False, 1, True, 896, 20, True), (False, 1, True, 1024, 20, True), (False, 1, True, 1792, 20, True), (False, 1, True, 2048, 90, False),
+    (False, 1, True, 2880, 33, False), (False, 1, True, 2880, 34, True),          # 23 tiles: 3 rounds are 768 workgroups
+    (False, 2, True, 1408, 32, True), (False, 2, True, 3584, 30, True), (False, 2, False, 2048, 20, True), (False, 2, False, 2880, 63, False),
+    (False, 2, False, 2880, 64, True), (False, 2, False, 4096, 90, False), (True, 1, True, 1408, 93, False), (True, 1, True, 1408, 94, True),
+    (True, 1, True, 1024, 127, False), (True, 1, True, 1024, 128, True), (True, 1, True, 2048, 150, False)])
+def test_with_multi_block_experts(L, gateup, ib, wnt, N, blocks, runs):  # noqa: F811
+    """One expert of two blocks among single-block ones: both sides of every line of the rule."""
+    counts = [257] + [200] * (blocks - 2)
+    assert _taken(gateup, ib, wnt, N, counts) == runs
