@@ -158,7 +158,7 @@ extern "C" __attribute__((visibility("default"))) int32_t moe_test_map_launch(
     a.blocks = blocks;
     a.num_blocks = &num_blocks;
     int32_t multi = 0;
-    for (int i = 0; i < num_blocks; ++i) multi |= blocks[2 * i + 1] > 0;
+    for (int i = 0; i < num_blocks; ++i) multi += blocks[2 * i + 1] > 0 || (i + 1 < num_blocks && blocks[2 * i + 3] > 0);
     a.num_multi = &multi;
     if (blocks_mix != nullptr && knob(kKnobInterleave) != 0) {
         a.blocks_mix = blocks_mix;

@@ -63,13 +63,14 @@ struct GemmArgs {
     const int32_t* blocks;      // [*, 2] (expert, row offset inside the expert)
     const int32_t* num_blocks;  // device scalar
     const int32_t* num_heavy;   // device scalar or null: the first *num_heavy blocks belong to multi-block experts (tile_kernel_mixed)
-    const int32_t* num_multi;   // device scalar or null: 0 if no expert has more than one block
+    const int32_t* num_multi;   // device scalar: the blocks of experts that have more than one
     int R, N, K, n_tiles_n;
     int M;                      // tile height of the block schedule (rows per block <= M)
     int sib;                    // tile_kernel_mixed: launch the row tiles of one expert side by side (see there)
     int chunk;                  // tile_kernel_mixed: runs of `unit` positions per XCD: 0 never, 1 always, 2 by the rule (see there)
     int unit;                   // length of a run: half of the workgroups that an XCD runs at once
-    int multi_from;             // chunk 2: workgroups from which on a launch with multi-block experts goes in runs
+    int multi_from, few_from;   // chunk 2: workgroups from which on a launch with (few) blocks of multi-block experts goes in runs
+    int light;                  // ... if the single-block experts number at most light / 5 of those blocks
     int rot_mul_chunk;          // the k-loop rotation of blocks whose feature tiles run on one XCD
     const int32_t* blocks_mix;  // with num_heavy: the same blocks, those of multi-block experts first (the list the dealt order reads)
     int deal_always;            // tile_kernel_mixed with num_heavy: deal the two classes whatever their proportion (tests)
@@ -363,6 +364,7 @@ __device__ __forceinline__ void permute_inside(const GemmArgs& a, GemmArgs& b, i
     const int G = (a.R + kThreads - 1) / kThreads; // 64-slot groups per wavefront, in slot order
 #pragma unroll
     for (int w = 0; w < W; ++w) wc[w][tid] = 0;
+    if (tid == 0) nblk[1] = 0;
     int e_of[kSmallGroups];
 #pragma unroll
     for (int g = 0; g < kSmallGroups; ++g) {
@@ -410,10 +412,8 @@ __device__ __forceinline__ void permute_inside(const GemmArgs& a, GemmArgs& b, i
         blk[2 * (block0 + q)] = tid;
         blk[2 * (block0 + q) + 1] = q * a.M;
     }
-    const int several = __any(nb > 1);             // an expert of this wavefront with more than one block
-    if (lane == 0) nblk[8 + wave] = several;
+    if (nb > 1) atomicAdd(&nblk[1], nb);           // cleared before the first barrier
     __syncthreads();
-    if (tid == 0) nblk[1] = nblk[8] | nblk[9] | nblk[10] | nblk[11];
     volatile int32_t* next = wc[wave];
 #pragma unroll
     for (int g = 0; g < kSmallGroups; ++g) {
@@ -999,7 +999,8 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
     int tile, nt;
     bool halves = false, dealt = false, units = false;
     const int32_t* blist = a.blocks;   // Algorithm 1's order unless the two classes are dealt (below)
-    const int total = *a.num_blocks * a.n_tiles_n;
+    const int blocks = *a.num_blocks, multi = *a.num_multi;
+    const int total = blocks * a.n_tiles_n;
     int split_from = total;            // first position (in two-block tiles) of a split last round
     {
         int w = wg, sub = 0;
@@ -1038,7 +1039,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
         bool deal = false;
         int dealU = 1, hu = 0, tu = 0;
         if (a.num_heavy != nullptr && !split_round) {
-            const int hb = *a.num_heavy, lb = *a.num_blocks - hb;
+            const int hb = *a.num_heavy, lb = blocks - hb;
             dealU = (a.n_tiles_n & 7) == 0 ? 8 : a.n_tiles_n;
             hu = hb * a.n_tiles_n / dealU;
             tu = total / dealU;
@@ -1051,7 +1052,8 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
         // by d/128 workgroups and makes up half of what a CU loads), and the row tiles and panels of a multi-block expert meet
         // there whatever the feature-tile count (the order further down needs a multiple of 8).  The positions after the last eight
         // whole runs are cut into eight others.
-        //   By the rule: if no expert has more than one block; with multi-block experts from multi_from workgroups on (mixed_launch_shape).
+        //   By the rule: if no expert has more than one block; with blocks of multi-block experts from few_from (they are a sixteenth of all) or
+        // multi_from workgroups on, the latter unless there are too many light blocks beside them (mixed_launch_shape).
         // Not when heavy and light blocks are dealt (below).  us, without / with: gate+up 60 experts of 2048 x 1408, 4000 tokens
         // (11 tiles) 334 / 296, 128 of 4096 x 1536, 4096 tokens (12) 867 / 823, Qwen2-MoE shape 4096 tokens (20) 1066 / 1023; down
         // projection of the first (8) 193 / 157, 32 experts of 2880 x 2880, 4000 tokens (12) 310 / 286, Qwen2-MoE shape at skew 1 (14) 620 / 596.
@@ -1061,7 +1063,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
         // eighth of the launch per XCD: the same for single-block experts, 6-17 % behind no runs at all where one XCD gets the heavy ones.
         bool runs = !split_round && !deal && a.chunk != 0;
         if (runs && a.chunk == 2)
-            runs = (a.num_multi != nullptr && *a.num_multi == 0) || total >= a.multi_from;
+            runs = multi == 0 || (16 * multi <= blocks ? total >= a.few_from : total >= a.multi_from && 5 * (blocks - multi) <= a.light * multi);
         if (runs) {
             const int U = a.unit, q = w >> 3, x = w & 7, group = q / U;
             const int groups = total <= 16 * U ? 0 : total / (8 * U);   // one round: an eighth each
@@ -1105,7 +1107,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
     // The schedule entry is read once: the look-ups (block count, entry, expert offsets, for
     // the gate+up projection the source row) are dependent loads in front of the block's first
     // weight and tile loads, each worth several hundred nanoseconds of a ~100 us block.
-    if (tile >= *a.num_blocks) return false;
+    if (tile >= blocks) return false;
     const int bm = a.M < 256 ? a.M : 256;              // rows per schedule entry
     const int e = blist[2 * tile];
     const int r_in = blist[2 * tile + 1];
@@ -1432,8 +1434,18 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     // 2048 (7 tiles), 1000 tokens, skew 0.6 87 / 71, skew 2 79 / 65; 60 of 1024 x 1408 (8), 300 tokens, skew 1.2 45 / 44, 128 of 640 x 1024 (5), 2000 tokens,
     // skew 0.6 55 / 49; 16 of 1792 x 3584 (14), 300 tokens 61 / 58, 700 tokens 84 / 86; cached weights, 16 of 1024 x 4096 (4), 2000 tokens, skew 0.6 100 / 91, but
     // 8 of 2880 x 2880 (12), 2000 tokens, skew 1.4 76 / 80.  With 23 tiles 101 / 112 (32 of 2880 x 2880, 300 tokens, skew 1.2).
-    const bool scattered = args.n_tiles_n % 8 != 0 || args.n_tiles_n <= 8;
+    //   Gate+up: not beyond 20 tiles, and not where light blocks stand among the heavy ones, whose workgroups of one expert then meet on an XCD in a bunch:
+    // up to 16 tiles as many light ones as heavy ones, beyond, where a block is longer than a run, two fifths.  us, without / with: 23 tiles, 32 experts of 2880 x
+    // 2880, 1500 tokens at skew 1 268 / 277, 4000 tokens at skew 1.6 543 / 552; 20 tiles, Qwen2-MoE shape, 1000 tokens at skew 0.5 475 / 495, at skew
+    // 1 489 / 513, 160 experts of 1536 x 2560, 2000 tokens at skew 1.6 241 / 261, but Qwen2-MoE shape 4096 tokens at skew 1 1141 / 1128, 3000 tokens 898 / 882;
+    // 12 tiles, 128 experts of 4096 x 1536, 1500 tokens at skew 1.6 424 / 442, 4096 tokens at skew 0.5 936 / 887.  The Qwen2-MoE figures with
+    // row-major weights: 1000 tokens at skew 0.5 501 / 532, 4096 tokens 1216 / 1187.
+    //   Down: with a few blocks of multi-block experts, two weight blocks and streamed weights like without (16 tiles, 128 experts of 4096 x 1536, 500 tokens
+    // at skew 0.6 310 / 294; 8 tiles, 60 of 2048 x 1408, 300 tokens 78 / 73); with one weight block rather not (23 tiles, above).
+    const bool scattered = (args.n_tiles_n % 8 != 0 || args.n_tiles_n <= 8) && (!GATEUP || args.n_tiles_n <= 20);
     args.multi_from = !scattered ? INT_MAX : GATEUP ? 64 * args.unit : args.n_tiles_n <= (WNT ? 16 : 8) ? 0 : 48 * args.unit;
+    args.few_from = !GATEUP && IB == 2 && WNT ? 0 : args.multi_from;
+    args.light = !GATEUP ? 5 * 256 : args.n_tiles_n <= 16 ? 5 : 2;   // 256: the most single-block experts that there can be
     args.no_nt = knob(kKnobNoNt) > 0;
     args.short_nt = knob(kKnobShortNt) >= 0 ? knob(kKnobShortNt) : (GATEUP ? 64 : 0);
     args.rot_mul_multi = rot_steps(true);

@@ -93,8 +93,7 @@ hipError_t launch_gate_up(const moe_config& c, int32_t M, const uint16_t* x_rows
                           int32_t ldh, const int32_t* offsets,
                           const int32_t* blocks, const int32_t* num_blocks, const int32_t* num_heavy, const uint16_t* wg,
                           const uint16_t* wu, const uint16_t* packed_gu, uint16_t* h, hipStream_t s);
-// Tables of the permutation and Algorithm 1's block list, as launch_permute_index writes them, except that num_heavy says
-// only whether an expert has more than one block.
+// Tables of the permutation and Algorithm 1's block list, as launch_permute_index writes them (without the second list).
 struct PermuteOut {
     int32_t *counts, *offsets, *row_of, *src_of, *blocks, *num_blocks, *num_heavy;
 };

@@ -72,13 +72,18 @@ def test_gate_up_needs_rows_to_share(L, N, rows, packed, runs):  # noqa: F811
         assert not _taken(True, 1, True, N, [min(rows, 32)] * 64, M=128, half=True)
 
 
-@pytest.mark.parametrize("gateup,ib,wnt,N,blocks,runs", [
-    (False, 1, True, 896, 20, True), (False, 1, True, 1024, 20, True), (False, 1, True, 1792, 20, True), (False, 1, True, 2048, 90, False),
-    (False, 1, True, 2880, 33, False), (False, 1, True, 2880, 34, True),          # 23 tiles: 3 rounds are 768 workgroups
-    (False, 2, True, 1408, 32, True), (False, 2, True, 3584, 30, True), (False, 2, False, 2048, 20, True), (False, 2, False, 2880, 63, False),
-    (False, 2, False, 2880, 64, True), (False, 2, False, 4096, 90, False), (True, 1, True, 1408, 93, False), (True, 1, True, 1408, 94, True),
-    (True, 1, True, 1024, 127, False), (True, 1, True, 1024, 128, True), (True, 1, True, 2048, 150, False)])
-def test_with_multi_block_experts(L, gateup, ib, wnt, N, blocks, runs):  # noqa: F811
-    """One expert of two blocks among single-block ones: both sides of every line of the rule."""
-    counts = [257] + [200] * (blocks - 2)
+# (light blocks, blocks of two-block experts); 896 = 7 tiles, 1024 and 2048 / 2 = 8, 1408 = 11, 1792 = 14, 2560 = 20, 2880 = 23 (12 of 256), 4096 / 2 = 16
+@pytest.mark.parametrize("gateup,ib,wnt,N,light,heavy,runs", [
+    (False, 1, True, 896, 20, 2, True), (False, 1, True, 1024, 20, 2, True), (False, 1, True, 1792, 20, 2, True), (False, 1, True, 2048, 90, 2, False),
+    (False, 1, True, 2880, 31, 2, False), (False, 1, True, 2880, 32, 2, True),     # three rounds are 768 workgroups
+    (False, 2, True, 1408, 28, 4, True), (False, 2, True, 3584, 26, 4, True), (False, 2, False, 2048, 18, 2, True), (False, 2, False, 2880, 59, 4, False),
+    (False, 2, False, 2880, 60, 4, True), (False, 2, False, 4096, 90, 2, False),
+    (False, 2, True, 4096, 30, 2, True), (False, 2, True, 4096, 29, 2, False), (False, 1, True, 4096, 90, 2, False),   # a sixteenth of all blocks
+    (True, 1, True, 1408, 91, 2, False), (True, 1, True, 1408, 92, 2, True), (True, 1, True, 1408, 60, 60, True), (True, 1, True, 1408, 61, 60, False),
+    (True, 1, True, 1024, 64, 64, True), (True, 1, True, 1024, 63, 64, False), (True, 1, True, 2048, 100, 2, False), (True, 1, True, 2048, 10, 100, False),
+    (True, 1, True, 2560, 24, 60, True), (True, 1, True, 2560, 25, 60, False), (True, 1, True, 2560, 80, 4, True), (True, 1, True, 2880, 20, 100, False),
+    (True, 1, True, 2880, 100, 2, False)])
+def test_with_multi_block_experts(L, gateup, ib, wnt, N, light, heavy, runs):  # noqa: F811
+    """Two-block experts among single-block ones: both sides of every line of the rule."""
+    counts = [300] * (heavy // 2) + [200] * light
     assert _taken(gateup, ib, wnt, N, counts) == runs
