@@ -173,7 +173,8 @@ def map_launch(gateup: bool, ib: int, wnt: bool, N: int, M: int, offsets, blocks
     """Test hook: what every workgroup of a per-block-regime GEMM launch would work on, computed on
     the host by the code the kernels run.  offsets [E+1], blocks / blocks_mix [n, 2]: numpy int32
     (host).  half: the build for two workgroups per CU.  Returns an int32 array [grid, 6] = (has work, expert, first row, rows, feature
-    tile, tile width in units of 128 features); with `runs` a seventh column, whether the launch is dealt in runs of positions per XCD."""
+    tile, tile width in units of 128 features); with `runs` two more columns, whether the launch is dealt in runs of positions per XCD and
+    whether the results are stored non-temporally."""
     import numpy as np
     offsets = np.ascontiguousarray(offsets, dtype=np.int32)
     blocks = np.ascontiguousarray(blocks, dtype=np.int32).reshape(-1, 2)
@@ -185,13 +186,13 @@ def map_launch(gateup: bool, ib: int, wnt: bool, N: int, M: int, offsets, blocks
     max_blocks = nb + slack_blocks
     tiles = (N + 128 * ib - 1) // (128 * ib)
     capacity = (max_blocks * tiles + 7) // 8 * 8 + cus
-    out = np.zeros((capacity, 7), dtype=np.int32)
+    out = np.zeros((capacity, 8), dtype=np.int32)
     grid = lib().moe_test_map_launch(int(gateup), ib, int(wnt), int(half), int(packed), N, K, offsets.size - 1, M, as_p(offsets), as_p(blocks), nb,
                                      as_p(blocks_mix) if blocks_mix is not None else None, num_heavy, cus, max_blocks,
                                      capacity, as_p(out))
     if grid < 0:
         raise MoEError(f"moe_test_map_launch refused (gateup={gateup}, ib={ib})")
-    return out[:grid, :7 if runs else 6]
+    return out[:grid, :8 if runs else 6]
 
 
 def forward_workspace_layout(cfg) -> WorkspaceLayout:

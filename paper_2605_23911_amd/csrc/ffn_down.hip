@@ -139,7 +139,8 @@ hipError_t launch_down(const moe_config& c, int32_t M, const uint16_t* h, int32_
 // of a per-block-regime GEMM launch would work on, with the launch-order switches and the grid the
 // launcher itself would use.  All array arguments are host memory; E experts hold offsets[E] rows of K elements, `packed` says how
 // the weights are laid out, `half` names the build for two workgroups per CU.  out[w] = {has work, expert,
-// first row, rows, feature tile, feature-tile width in units of 128, in runs of positions per XCD}; returns the grid size, or -1
+// first row, rows, feature tile, feature-tile width in units of 128, in runs of positions per XCD, results stored
+// non-temporally}; returns the grid size, or -1
 // if it exceeds `capacity` or (gateup, ib) names no kernel.  blocks_mix may be null (no dealing).
 extern "C" __attribute__((visibility("default"))) int32_t moe_test_map_launch(
     int32_t gateup, int32_t ib, int32_t wnt, int32_t half, int32_t packed, int32_t N, int32_t K, int32_t E, int32_t M, const int32_t* offsets,
@@ -173,11 +174,12 @@ extern "C" __attribute__((visibility("default"))) int32_t moe_test_map_launch(
         for (int w = 0; w < (int)grid; ++w) {
             MixedWork m{};
             const bool has = mixed_assign<IB, GU>(a, w, m);
-            int32_t* o = out + 7 * (size_t)w;
+            int32_t* o = out + 8 * (size_t)w;
             o[0] = has;
             o[1] = m.e; o[2] = m.row0; o[3] = m.rows; o[4] = m.nt;
             o[5] = m.halves ? 1 : IB;
             o[6] = m.chunked;
+            o[7] = m.stream;
         }
         return (int32_t)grid;
     };

@@ -71,6 +71,7 @@ struct GemmArgs {
     int unit;                   // length of a run: half of the workgroups that an XCD runs at once
     int multi_from, few_from;   // chunk 2: workgroups from which on a launch with (few) blocks of multi-block experts goes in runs
     int light;                  // ... if the single-block experts number at most light / 5 of those blocks
+    int stream;                 // results of single-block experts may be stored non-temporally (store_tile)
     int rot_mul_chunk;          // the k-loop rotation of blocks whose feature tiles run on one XCD
     const int32_t* blocks_mix;  // with num_heavy: the same blocks, those of multi-block experts first (the list the dealt order reads)
     int deal_always;            // tile_kernel_mixed with num_heavy: deal the two classes whatever their proportion (tests)
@@ -207,6 +208,7 @@ struct Tile {
     int e, row0, rows;
     int n_e;       // rows of the whole expert
     int rot_mul;   // k-loop rotation between workgroups of one XCD, in steps (tile bodies)
+    bool stream;   // the results are stored non-temporally (store_tile)
 };
 __device__ __forceinline__ bool load_tile(const GemmArgs& a, int tile, int BM, Tile& t) {
     BM = a.M < BM ? a.M : BM;   // a kernel may serve a schedule with shorter blocks than it can hold
@@ -280,12 +282,17 @@ __device__ __forceinline__ void store_block(const f32x16& g, const f32x16& u, ui
 // Epilogue of a whole tile (JBE * 32 rows x 128 * IB features): the bf16 results are staged in LDS, which the reduction loop no
 // longer needs, and every row is stored in one piece of 256 * IB bytes.  store_block writes the same row in pieces of 32 bytes,
 // IB * 8 of them; the write path takes the pieces one by one, and while they wait the workgroup holds its CU.
-// Non-temporally where the launch writes 2 MiB or more and the expert is one block: whole lines that go straight through L2 leave it
-// to the weights and token rows.  Cached stores of whole rows gain a fifth of that there, non-temporal pieces lose.  Projection alone,
+// Non-temporally (Tile::stream) where the launch writes 2 MiB or more and its weights do not fit the Infinity Cache beside the results (more than 128 MiB per
+// matrix), and the expert is one block: whole lines that go straight through L2 leave it
+// to the weights and token rows; cached stores of whole rows gain less, non-temporal pieces lose.  Projection alone,
 // us, store_block / staged and cached / staged and non-temporal: down, 64 experts of 128 rows, 2048 -> 7168, 371 / 366 / 332,
-// 144 rows 384 / 376 / 342, 16 rows 317 / 317 / 310; gate+up, 8 experts of 144 rows, 4096 -> 14336, 350 / 348 / 336.  Cached below
-// that size, where the next kernel still finds the results near (layer of 8 experts of 256 x 512, 1000 tokens, 41.3 / 40.7 / 42.9), and
-// for experts of several blocks (32 experts of 2880 x 2880, 1001 tokens at skew 1, down projection 134 / 134 / 139).
+// 144 rows 384 / 376 / 342, 16 rows 317 / 317 / 310; gate+up, 8 experts of 144 rows, 4096 -> 14336, 350 / 348 / 336.  What is streamed is read back from HBM.
+// Cached below those sizes, where the next kernel still finds the results near (us, layer, cached / non-temporal: 24 experts of 512 x 1024, 1000 tokens
+// 56.0 / 57.6; 8 of 1024 x 1024, 1000 tokens 63.9 / 67.5; 16 of 512 x 2048, 600 tokens 65.1 / 68.3; above them 32 of 1408 x 1536, 2045 tokens 114.5 / 109.5), and
+// for experts of several blocks (32 experts of 2880 x 2880, 1001 tokens at skew 1, down projection 134 / 139).
+// The rows of h also under routing skew, where the tall experts are what the down projection ends with and read their rows from HBM then: if an expert has several blocks,
+// or this one more than twice the mean (us, layer, cached / non-temporal: 8 experts of 2048 x 8192, 500 tokens at skew 1 233 / 243; Mixtral shape,
+// 300 tokens at skew 1 549 / 560, 200 tokens at skew 1.6 520 / 526).
 // A single 32-row block with cached stores takes store_block: nothing there pays for two barriers (8 experts of 256 x 512, 64 tokens,
 // layer 20.5 / 20.7; 60 of 2048 x 1408, 64 tokens, 186.4 / 187.2).
 // Every wavefront must call this, with none of its loads into LDS outstanding.
@@ -296,9 +303,8 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[NI][JBE], const G
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const int li = lane & 31, half = lane >> 5;
     char* lds = reinterpret_cast<char*>(xs);
-    const bool stream = t.n_e <= a.M && (long long)a.R * a.N >= (1ll << 20);
     if constexpr (JBE == 1) {
-        if (!stream) {
+        if (!t.stream) {
             const bool live = li < t.rows;
             static_for<IB>([&](auto ib) {
                 store_block<GATEUP>(acc[ib][0], acc[GATEUP ? IB + ib : ib][0], a.Out + (size_t)(t.row0 + (live ? li : 0)) * a.ldo,
@@ -340,7 +346,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[NI][JBE], const G
             }
         }
     };
-    if (stream) rows(std::true_type{});
+    if (t.stream) rows(std::true_type{});
     else rows(std::false_type{});
 }
 // LDS that store_tile needs
@@ -992,6 +998,7 @@ struct MixedWork {
     int nt;                   // feature tile: of IB * 128 features, or of 128 when `halves`
     bool halves;              // IB == 2 down projection: one 128-feature half of a tile of the split last round (IB = 1 body)
     bool chunked;             // the launch is dealt to the XCDs in runs of consecutive positions
+    bool stream;              // results stored non-temporally (store_tile)
     bool deep;                // loads run three steps ahead where the LDS ring holds four (rows_body)
 };
 template <int IB, bool GATEUP>
@@ -1184,6 +1191,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
     m.nt = nt;
     m.halves = halves;
     m.chunked = units;
+    m.stream = a.stream != 0 && n_e <= a.M && (!GATEUP || (multi == 0 && (long long)n_e * a.E <= 2ll * a.R));
     m.deep = a.cus > 0 && (IB * (GATEUP ? 2 : 1) == 1 ? total % a.cus != 0 : 2 * total <= a.cus);   // see rows_body
     return true;
 }
@@ -1206,6 +1214,7 @@ __device__ __forceinline__ void tile_mixed(const GemmArgs& a, uint16_t* xs) {
     t.row0 = m.row0;
     t.rows = m.rows;
     t.n_e = m.n_e;
+    t.stream = m.stream;
     // A short last tile of a multi-tile expert runs through k several times faster than its
     // siblings and shares nothing with them in time: it streams the panel like a single-block
     // expert does (non-temporal, k rotated), so that its stream does not evict the panels the
@@ -1258,6 +1267,7 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const GemmArgs a) {
     t.row0 = m.row0;
     t.rows = m.rows;
     t.n_e = m.n_e;
+    t.stream = m.stream;
     const bool multi = t.n_e > a.M && t.rows > a.short_nt;
     t.rot_mul = rotation(a, m, multi);
     if constexpr (IB == 2 && !GATEUP) {
@@ -1448,6 +1458,7 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     args.light = !GATEUP ? 5 * 256 : args.n_tiles_n <= 16 ? 5 : 2;   // 256: the most single-block experts that there can be
     args.no_nt = knob(kKnobNoNt) > 0;
     args.short_nt = knob(kKnobShortNt) >= 0 ? knob(kKnobShortNt) : (GATEUP ? 64 : 0);
+    args.stream = (long long)args.R * args.N >= (1ll << 20) && (long long)args.E * args.N * args.K > (1ll << 26);
     args.rot_mul_multi = rot_steps(true);
     const int in_runs = !packed ? 1 : (!GATEUP && WNT && args.K > 4096) ? 2 : 0;
     args.rot_mul_chunk = knob(kKnobRot) >= 0 ? knob(kKnobRot) : in_runs;

@@ -87,3 +87,30 @@ def test_with_multi_block_experts(L, gateup, ib, wnt, N, light, heavy, runs):  #
     """Two-block experts among single-block ones: both sides of every line of the rule."""
     counts = [300] * (heavy // 2) + [200] * light
     assert _taken(gateup, ib, wnt, N, counts) == runs
+
+
+def _streamed(gateup, N, K, counts, ib=1):
+    """Experts whose results are stored non-temporally, of those that have rows."""
+    offsets, blocks, _, _ = _schedule(np.array(counts), 256)
+    work = B.map_launch(gateup, ib, True, N, 256, offsets, blocks, K=K, runs=True)
+    per_expert = {}
+    for r in work:
+        if r[0]:
+            per_expert.setdefault(int(r[1]), set()).add(int(r[7]))
+    assert all(len(v) == 1 for v in per_expert.values())
+    return [e for e, v in sorted(per_expert.items()) if v == {1}]
+
+
+def test_what_is_stored_past_the_caches(L):  # noqa: F811
+    """Launches that write 2 MiB or more whose weights do not fit the Infinity Cache; single-block experts; rows of h not where an expert has
+    several blocks, nor those of an expert of more than twice the mean."""
+    every = list(range(8))
+    for gateup in (True, False):
+        assert _streamed(gateup, 4096, 4096, [32] * 8) == every                      # 2^20 values, 2^27 weights
+        assert _streamed(gateup, 4096, 4096, [32] * 7 + [31]) == []                  # 2^20 - 4096 values
+        assert _streamed(gateup, 4096, 2048, [200] * 8) == []                        # 2^26 weights
+        assert _streamed(gateup, 4096, 2112, [200] * 8) == every
+    skewed = [200] + [100] * 3 + [80, 80, 70, 70]                                    # the mean is 100
+    assert _streamed(True, 4096, 4096, skewed) == every and _streamed(True, 4096, 4096, [201] + skewed[1:-1] + [69]) == every[1:]
+    assert _streamed(True, 4096, 4096, [257] + [200] * 7) == [] and _streamed(False, 4096, 4096, [257] + [200] * 7) == every[1:]
+    assert _streamed(False, 4096, 4096, [256, 0, 1] + [200] * 5, ib=2) == [0, 2, 3, 4, 5, 6, 7]
