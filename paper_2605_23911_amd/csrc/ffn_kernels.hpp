@@ -71,6 +71,7 @@ struct GemmArgs {
     int unit;                   // length of a run: half of the workgroups that an XCD runs at once
     int multi_from, few_from;   // chunk 2: workgroups from which on a launch with (few) blocks of multi-block experts goes in runs
     int light;                  // ... if the single-block experts number at most light / 5 of those blocks
+    int eighths;                // without multi-block experts: one run per XCD
     int stream;                 // results of single-block experts may be stored non-temporally (store_tile)
     int rot_mul_chunk;          // the k-loop rotation of blocks whose feature tiles run on one XCD
     const int32_t* blocks_mix;  // with num_heavy: the same blocks, those of multi-block experts first (the list the dealt order reads)
@@ -1072,7 +1073,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
         if (runs && a.chunk == 2)
             runs = multi == 0 || (16 * multi <= blocks ? total >= a.few_from : total >= a.multi_from && 5 * (blocks - multi) <= a.light * multi);
         if (runs) {
-            const int U = a.unit, q = w >> 3, x = w & 7, group = q / U;
+            const int U = a.eighths && multi == 0 ? total : a.unit, q = w >> 3, x = w & 7, group = q / U;
             const int groups = total <= 16 * U ? 0 : total / (8 * U);   // one round: an eighth each
             if (group < groups) {
                 w = (group * 8 + x) * U + (q - group * U);
@@ -1191,7 +1192,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
     m.nt = nt;
     m.halves = halves;
     m.chunked = units;
-    m.stream = a.stream != 0 && n_e <= a.M && (!GATEUP || (multi == 0 && (long long)n_e * a.E <= 2ll * a.R));
+    m.stream = a.stream != 0 && n_e <= a.M && (!GATEUP || (multi == 0 && (long long)n_e * a.E <= 2ll * a.R && (a.P != nullptr || n_e <= 160)));
     m.deep = a.cus > 0 && (IB * (GATEUP ? 2 : 1) == 1 ? total % a.cus != 0 : 2 * total <= a.cus);   // see rows_body
     return true;
 }
@@ -1431,7 +1432,11 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     // The k loops of such workgroups walk in step, which is where they share most (gate+up of 128 experts of 4096 x 1536, 2048 tokens, one
     // step apart 599 / in step 534; down projection of 256 experts, 2048 tokens 1487 / 1409; Qwen2-MoE shape 512 tokens two apart 222 /
     // 218).  Two apart on long loops over streamed weights (down projection of 16 experts, 6400 -> 4096, 1000 tokens 171 / 177 in step).
-    // One apart for row-major weights, whose rows would all be read from one L2 channel (down projection of 256 experts, 512 tokens 1233 / 1388).
+    // Row-major weights, whose rows would all be read from one L2 channel in step (down projection of 256 experts, 512 tokens 1233 / 1388): one apart in gate+up, two
+    // apart in the down projection, and there one contiguous eighth of the launch per XCD where every expert is one block, so that it runs through neighbouring rows.
+    // Down projection, us, plain two apart / runs one apart / runs two apart / eighths: Mixtral-8x22B shape, 60 tokens 275 / 290 / 278 / 278, 300 tokens 325 / 346 / 312 /
+    // 326, 8 tokens 258 / 262 / 249 / 249; 32 experts of 4096 x 4096, 20 tokens 153 / 162 / 159 / 151, 250 tokens 178 / 186 / 183 / 175; 64 of 2048 x 2048, 500 tokens
+    // 106 / 98 / 107 / 97; 32 of 8192 x 1024, 250 tokens 104 / 108 / 102 / 101; 256 experts of DeepSeek-V3's widths, 1000 tokens 1305 / 1279 / 1303 / 1351.
     const bool packed = args.P != nullptr;
     const bool shares = !GATEUP || (args.n_tiles_n <= 32 && args.R >= 64ll * args.E && (packed || args.n_tiles_n % 16 != 0));
     args.chunk = knob(kKnobXcdChunk) >= 0 ? knob(kKnobXcdChunk) : shares ? 2 : 0;
@@ -1458,9 +1463,10 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     args.light = !GATEUP ? 5 * 256 : args.n_tiles_n <= 16 ? 5 : 2;   // 256: the most single-block experts that there can be
     args.no_nt = knob(kKnobNoNt) > 0;
     args.short_nt = knob(kKnobShortNt) >= 0 ? knob(kKnobShortNt) : (GATEUP ? 64 : 0);
+    args.eighths = !GATEUP && !packed;
     args.stream = (long long)args.R * args.N >= (1ll << 20) && (long long)args.E * args.N * args.K > (1ll << 26);
     args.rot_mul_multi = rot_steps(true);
-    const int in_runs = !packed ? 1 : (!GATEUP && WNT && args.K > 4096) ? 2 : 0;
+    const int in_runs = !packed ? (GATEUP ? 1 : 2) : (!GATEUP && WNT && args.K > 4096) ? 2 : 0;
     args.rot_mul_chunk = knob(kKnobRot) >= 0 ? knob(kKnobRot) : in_runs;
     long long grid = ((long long)max_blocks * args.n_tiles_n + 7) / 8 * 8;   // as many for every XCD (the runs)
     args.slots = 0;

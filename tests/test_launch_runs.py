@@ -114,3 +114,17 @@ def test_what_is_stored_past_the_caches(L):  # noqa: F811
     assert _streamed(True, 4096, 4096, skewed) == every and _streamed(True, 4096, 4096, [201] + skewed[1:-1] + [69]) == every[1:]
     assert _streamed(True, 4096, 4096, [257] + [200] * 7) == [] and _streamed(False, 4096, 4096, [257] + [200] * 7) == every[1:]
     assert _streamed(False, 4096, 4096, [256, 0, 1] + [200] * 5, ib=2) == [0, 2, 3, 4, 5, 6, 7]
+
+
+@pytest.mark.parametrize("ib,N,counts", [(1, 6144, [100] * 8), (2, 4096, [200] * 30), (2, 896, [17, 0, 256, 3] * 33)])
+def test_row_major_down_projection_in_eighths(L, ib, N, counts):  # noqa: F811
+    """One contiguous eighth of the launch per XCD where every expert is one block; runs, or none, where one has more."""
+    offsets, blocks, _, _ = _schedule(np.array(counts), 256)
+    work = B.map_launch(False, ib, False, N, 256, offsets, blocks, packed=False)
+    _check_cover(work, offsets, counts, N, 256, (ib, N))
+    assert _in_runs(work, len(work)) and not _in_runs(B.map_launch(False, ib, False, N, 256, offsets, blocks), len(work))
+    counts = counts + [257]
+    offsets, blocks, _, _ = _schedule(np.array(counts), 256)
+    work = B.map_launch(False, ib, False, N, 256, offsets, blocks, packed=False)
+    _check_cover(work, offsets, counts, N, 256, (ib, N))
+    assert not _in_runs(work, len(work))
