@@ -45,14 +45,19 @@ int pick(int M, bool packed, const moe_config& c) {
     // see, it is up to 1.58x behind (8 experts of 6144 x 16384, 200-240 rows: 611-755 / 455-505), so the line stays.
     if (!packed) return once ? (wide ? 9 : 0) : 10;
     // Packed.  Two weight blocks also where one block each would make between one and two rounds of workgroups and two make a single
-    // one: us, one / two: Mixtral-8x22B shape (24 tiles of 256 x 8 experts) 64 tokens 266 / 240, 512 tokens 373 / 320, at skew 1 416 / 362; 7
+    // one: us, one / two: Mixtral-8x22B shape (24 tiles of 256 x 8 experts) 64 tokens 266 / 240, 512 tokens 373 / 320, at skew 1 416 / 366; 7
     // experts, 8192 -> 5120, 300 tokens 155 / 139; 16 experts, 6400 -> 4096, 1000 tokens 174 / 152.  Not where one block each is a
     // single round (Mixtral-8x7B shape, 700 tokens 212 / 221) or two make a second (24 experts, 4096 -> 3072, 800 tokens 125 / 133).
-    const long long tiles = (long long)((c.d + 127) / 128) * active;
-    const bool one_round = tiles > 256 && tiles <= 512;
+    // A last tile of 128 features counts as a whole one of 256: 24 experts at d = 2688 are 504 tiles of 128, but 264 of 256 (800 tokens 90 / 110),
+    // 102 at d = 640 510 and 306 (89 / 102).  256 CUs, not the device's count: kernels can be named without a device.
+    // From 16 tiles of 256 on: below, the second blocks that routing skew makes, which the host cannot see, cost more than a single round gains.
+    // us, one / two, near-uniform and at skew 0.8 (mean of three routings): 9 experts, 4096 -> 3712 67 / 62, 75 / 87; 16 experts, 4096 -> 2176
+    // 67 / 60, 75 / 84; 60 of 1024 x 1024, 1000 tokens 33 / 31, 40 / 44; 85 of 2048 -> 640 46 / 44, 48 / 54; 128 of 3584 -> 512 85 / 86, 88 / 97.
+    const bool one_round = c.d >= 4096 && (c.d + 127) / 128 * active > 256 && (c.d + 255) / 256 * active <= 256;
     // Streamed weights up to 240 rows per expert and 256 MB of rows.  us, cached / streamed: Qwen2-MoE shape 1900 tokens (237 rows) 332 / 305, at
     // skew 1 391 / 359; Mixtral-8x22B shape 900 tokens at skew 1 473 / 440; Mixtral-8x7B shape 900 tokens (225 rows) 270 / 260; 128
-    // experts, 2048 tokens (134 MB) 332 / 323; 256 experts, 2048 tokens (235 MB) 1420 / 1409.  Beyond: 60 experts, 1408 -> 2048, 2400 tokens (240
+    // experts, 2048 tokens (134 MB) 332 / 323; 256 experts, 2048 tokens (235 MB) 1420 / 1409.
+    // Beyond: 60 experts, 1408 -> 2048, 2400 tokens (240
     // rows) 138 / 145; 256 experts, 4096 tokens (470 MB) at skew 1, where the cached kernel deals, 1513 / 1561.
     if ((double)R / c.E < 240.0 && (double)R * c.d * 2.0 <= 256e6)
         return wide || one_round || (double)R / c.E > 192.0 ? 6 : 5;   // beyond 192 rows many experts have a second block (Mixtral-8x7B shape, 900 tokens, skew 0.3, one / two weight blocks 353 / 312)
