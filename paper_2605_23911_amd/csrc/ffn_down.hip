@@ -54,13 +54,15 @@ int pick(int M, bool packed, const moe_config& c) {
     // us, one / two, near-uniform and at skew 0.8 (mean of three routings): 9 experts, 4096 -> 3712 67 / 62, 75 / 87; 16 experts, 4096 -> 2176
     // 67 / 60, 75 / 84; 60 of 1024 x 1024, 1000 tokens 33 / 31, 40 / 44; 85 of 2048 -> 640 46 / 44, 48 / 54; 128 of 3584 -> 512 85 / 86, 88 / 97.
     const bool one_round = c.d >= 4096 && (c.d + 127) / 128 * active > 256 && (c.d + 255) / 256 * active <= 256;
+    // Beyond 192 rows many experts have a second block (Mixtral-8x7B shape, 900 tokens, skew 0.3, one / two weight blocks 353 / 312), unless the
+    // launch is still a single round with those (16 experts, 4096 -> 1024, 1600 tokens 59 / 66, 1800 tokens at skew 0.5 58 / 73).
+    const bool second_blocks = (double)R / c.E > 192.0 && (c.d + 127) / 128 * (active + R / 256) > 256;
     // Streamed weights up to 240 rows per expert and 256 MB of rows.  us, cached / streamed: Qwen2-MoE shape 1900 tokens (237 rows) 332 / 305, at
     // skew 1 391 / 359; Mixtral-8x22B shape 900 tokens at skew 1 473 / 440; Mixtral-8x7B shape 900 tokens (225 rows) 270 / 260; 128
-    // experts, 2048 tokens (134 MB) 332 / 323; 256 experts, 2048 tokens (235 MB) 1420 / 1409.
-    // Beyond: 60 experts, 1408 -> 2048, 2400 tokens (240
+    // experts, 2048 tokens (134 MB) 332 / 323; 256 experts, 2048 tokens (235 MB) 1420 / 1409; 60 experts, 1408 -> 2048, 3300 tokens (220 rows) 117 / 101.
+    // Beyond: 60 experts, 1408 -> 2048, 2400 tokens of 6 (240
     // rows) 138 / 145; 256 experts, 4096 tokens (470 MB) at skew 1, where the cached kernel deals, 1513 / 1561.
-    if ((double)R / c.E < 240.0 && (double)R * c.d * 2.0 <= 256e6)
-        return wide || one_round || (double)R / c.E > 192.0 ? 6 : 5;   // beyond 192 rows many experts have a second block (Mixtral-8x7B shape, 900 tokens, skew 0.3, one / two weight blocks 353 / 312)
+    if ((double)R / c.E < 240.0 && (double)R * c.d * 2.0 <= 256e6) return wide || one_round || second_blocks ? 6 : 5;
     return 7;
 }
 

@@ -1,6 +1,6 @@
 """The down projection's two weight blocks per wavefront, packed weights: where one each would make more than a round of workgroups (256 CUs) and
-two make a single one, counted in the tiles that each form really has, a half-filled last one included, from 16 tiles of 256
-features on.  Host arithmetic only."""
+two make a single one, counted in the tiles that each form really has, a half-filled last one included, from 16 tiles of 256 features on; and beyond
+192 rows per expert unless the launch is a single round of one block each even with the experts' second blocks.  Host arithmetic only."""
 import pytest
 
 import paper_2605_23911_amd as moe
@@ -21,3 +21,10 @@ def _two(T, d, E):
                                      (640, 85, False), (640, 102, False)])
 def test_one_round_of_two_blocks(d, E, two):
     assert _two(40 * E, d, E) == two
+
+
+@pytest.mark.parametrize("T,d,E,two", [(192 * 16, 1024, 16, False), (193 * 16, 1024, 16, False), (239 * 16, 1024, 16, False),   # 8 tiles x (16 + 14)
+                                       (192 * 16, 1280, 16, False), (193 * 16, 1280, 16, True),                                # 10 tiles x (16 + 12)
+                                       (200 * 8, 2048, 8, False), (200 * 8, 2560, 8, True)])                                   # 16 and 20 tiles x (8 + 6)
+def test_many_rows_per_expert(T, d, E, two):
+    assert _two(T, d, E) == two
