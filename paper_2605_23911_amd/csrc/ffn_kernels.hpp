@@ -204,6 +204,16 @@ __device__ __forceinline__ uint32_t token_row_bytes(const GemmArgs& a, int row) 
     return (uint32_t)token_row_index(a, row) * (uint32_t)a.ldx * 2u;
 }
 
+// The thread's number at the start of a body, of which a kernel holds up to sixteen.  Opaque to the compiler: it would work out what the bodies derive
+// from it (places in LDS, rows of the tile) once, in front of them all, and hold it in registers that the tallest body does not have.
+// Scratch, bytes per lane, without / with: tile_kernel_mixed<2, false, true, true, false> 40 / 8, <.., false, false> 12 / 8, tile_kernel<1, true>
+// 8 / 0, routed_tile_kernel_mixed<true> 16 / 0; times the same or up to 1 % shorter.
+__device__ __forceinline__ int body_thread() {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
 // Block schedule entry -> tile geometry (Alg. 1: block = (expert, row offset)).
 struct Tile {
     int e, row0, rows;
@@ -572,7 +582,7 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
     constexpr int BN = 4 * IB * 32;
     constexpr int NBUF = XD + 1;
     constexpr int BUF_BYTES = JBE * 32 * 128;
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int tid = body_thread(), wave = tid / kWave, lane = tid % kWave;
     const int li = lane & 31, half = lane >> 5;
     const int K = a.K, N = a.N;
     const int KT = K / kBK;
@@ -790,7 +800,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
     constexpr int X_BYTES = JBE * 4096;                 // token tile of a step
     constexpr int BUF = X_BYTES + 4 * NI * 4096;
     constexpr int LPS = JBE + 4 * NI;                   // loads per wavefront and step
-    const int tid = threadIdx.x, lane = tid % kWave;
+    const int tid = body_thread(), lane = tid % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int li = lane & 31, half = lane >> 5;
     const int K = a.K, N = a.N;
