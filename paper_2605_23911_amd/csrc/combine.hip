@@ -41,7 +41,7 @@ __device__ __forceinline__ void add_rows(const uint16_t* __restrict__ y_perm, co
 // latency.  Stage inside a layer by events, us, row by row / repeating batches / now: 6 experts, 900 tokens x 2048 8.0 / 8.6 /
 // 7.9, 1200 x 3584 12.5 / 12.8 / 12.4, 4096 x 4096 39.6 / 40.4 / 40.2; 8 experts, 100 tokens x 3584 9.8 / 7.1 / 6.1, 512 x 7168
 // 17.4 / 15.0 / 13.4, 4096 x 7168 110 / 109 / 105 (5.0 TB/s), 1024 x 4096 (64 MiB of rows) 15.3 / 17.8 / 17.6.
-// STREAM: rows and result pass the caches by (launch_combine).
+// STREAM: the rows pass the caches by (launch_combine).
 template <int K, bool STREAM>
 __global__ __launch_bounds__(kThreads) void combine_kernel(const uint16_t* __restrict__ y_perm,
                                                           const int32_t* __restrict__ row_of,
@@ -64,9 +64,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const uint16_t* __res
             if (k & 1) add_rows<1, STREAM>(y_perm, rows, w, i, d, c, acc);
         }
         const u32x4 o = {pack2_bf16(acc[0], acc[1]), pack2_bf16(acc[2], acc[3]), pack2_bf16(acc[4], acc[5]), pack2_bf16(acc[6], acc[7])};
-        u32x4* out = reinterpret_cast<u32x4*>(y + (size_t)t * d + c);
-        if constexpr (STREAM) __builtin_nontemporal_store(o, out);
-        else *out = o;
+        *reinterpret_cast<u32x4*>(y + (size_t)t * d + c) = o;
     }
 }
 
@@ -74,9 +72,10 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const uint16_t* __res
 
 hipError_t launch_combine(const moe_config& c, const uint16_t* y_perm, const int32_t* row_of,
                           const float* topk_w, uint16_t* y, hipStream_t s) {
-    // From 128 MiB of rows on, half of the Infinity Cache, little of them is there and nothing of the rest is worth keeping: non-temporal
-    // loads and stores.  Stage by events, us, cached / non-temporal: 8 experts, 4096 tokens x 3584 49.6 / 44.7, x 7168 105.5 / 99.0 (5.3
-    // TB/s); below the line even or, where the loads alone were tried, slower (6 experts, 4000 x 2048 21.1 / 22.4).
+    // From 128 MiB of rows on, half of the Infinity Cache, little of them is there and none is read again: non-temporal loads.  The result is
+    // stored as usual: what comes next reads it.  Stage by events and a pass over the result after it, us, all cached / rows non-temporal / result
+    // too: 8 experts, 4096 tokens x 3584 48.8 + 12.7 / 43.6 + 12.4 / 42.2 + 13.5, x 7168 104 + 21.2 / 93.6 + 20.3 (5.6 TB/s) / 90.5 + 21.9; 3 experts, 4096 x 7168
+    // 42.0 + 20.3 / 41.6 + 20.2 / 41.6 + 22.3; below the line even or slower (6 experts, 4000 x 2048 21.1 / 22.4).
     const bool stream = (long long)c.T * c.k * c.d >= (1ll << 26);
     auto go = [&](auto k) {
         constexpr int K = decltype(k)::value;
