@@ -16,8 +16,8 @@ const Variant kDown[] = {
     /*6*/ {256, true, launch_down_mixed_wide_nt, "tile_kernel_mixed<2, false, true, true, false>"},
     /*7*/ {256, true, launch_down_mixed_wide, "tile_kernel_mixed<2, false, true, false, false>"},
     /*8*/ {128, true, launch_tile_mixed<1, false, true, true, true>, "tile_kernel_mixed<1, false, true, true, true>"},
-    /*9*/ {256, false, launch_down_rows_wide, "tile_kernel<2, false>"},
-    /*10*/ {256, false, launch_down_rows_wide, "tile_kernel<2, false>"},   // the same: both numbers stay in use
+    /*9*/ {256, false, launch_down_rows_wide, "tile_kernel<2, false>"},    // as 10; only tests force it
+    /*10*/ {256, false, launch_down_rows_wide, "tile_kernel<2, false>"},
 };
 constexpr int kNumDown = sizeof(kDown) / sizeof(kDown[0]);
 
@@ -37,13 +37,13 @@ int pick(int M, bool packed, const moe_config& c) {
     if (packed && M <= 128 && two_workgroups_per_cu(c)) return 8;
     // Per-block regime selection (tile_kernel_mixed, tile_kernel).  The line between one weight block and two for row-major weights:
     const bool once = (double)R / c.E <= 192.0 && (double)R * c.d * 2.0 <= 128e6;
-    // Row-major, up to the line: 0 and 9 at 256 experts, 512 tokens 1330 against 1240 us.  Beyond the line, one weight block
+    // Row-major, up to the line: one block and, where that leaves 512 workgroups, two: 256 experts, 512 tokens 1330 against 1240 us.  Beyond the line, one weight block
     // (0, three ring buffers or more at any height) against two (10): from 256 rows per expert on 10 is ahead (Mixtral shape 256
     // rows 432 / 396 us, 320 450 / 370, 512 694 / 545; Qwen2-MoE shape 256 rows 440 / 426).  At 200-248 rows with near-uniform
     // routing 0 is 3-15 % ahead on some shapes (Mixtral 246 / 263, 32 experts of 2880 x 2880 154 / 181) and 0-18 % behind on
     // others (16 experts of 6144 x 4096 247 / 230, 4 of 2048 x 8192 94 / 80), but under routing skew, which the host cannot
     // see, it is up to 1.58x behind (8 experts of 6144 x 16384, 200-240 rows: 611-755 / 455-505), so the line stays.
-    if (!packed) return once ? (wide ? 9 : 0) : 10;
+    if (!packed) return once && !wide ? 0 : 10;
     // Packed.  Two weight blocks also where one block each would make between one and two rounds of workgroups and two make a single
     // one: us, one / two: Mixtral-8x22B shape (24 tiles of 256 x 8 experts) 64 tokens 266 / 240, 512 tokens 373 / 320, at skew 1 416 / 366; 7
     // experts, 8192 -> 5120, 300 tokens 155 / 139; 16 experts, 6400 -> 4096, 1000 tokens 174 / 152.  Not where one block each is a
