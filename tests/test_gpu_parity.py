@@ -310,7 +310,7 @@ def test_row_tiles_of_an_expert_side_by_side(G, knobs):
 #                with the short tile at the end; the down projection in its two-weight-block form.
 #   skewed16   : 16 experts under skew 2: one of 4 full tiles + a short one, one of three tiles,
 #                one of two, the rest single blocks or empty, in one launch.  down: single-use
-#                weights, one contiguous eighth of the work per XCD.
+#                weights, in the order of the list (16 feature tiles and multi-block experts: no runs per XCD).
 #   mixed8, mixed12 : three multi-tile experts (8, 5 and 2-3 tiles) and five / nine single-block
 #                ones with many rows per expert on average, which is where the down projection
 #                deals its heavy and light blocks evenly over the launch: block by block with

@@ -1,6 +1,7 @@
 """The GEMM epilogue stages a tile in LDS and stores whole rows: every row of an expert is written, none behind the last row of the
-buffer, no feature behind the last one of a ragged tile (which would land in the next row), through both weight layouts and every
-down-projection kernel that stages, with single-block experts (streamed stores) and multi-block ones (cached)."""
+buffer, no feature behind the last one of a ragged tile (which would land in the next row), through both weight layouts and the
+down projections for tiles of 256 rows, with single-block experts and multi-block ones.  Layers this small take cached stores throughout;
+test_gpu_streamed_results.py has the non-temporal ones and the builds for two workgroups per CU."""
 import numpy as np
 import pytest
 import torch
