@@ -1018,6 +1018,7 @@ __host__ __device__ inline bool mixed_assign(const GemmArgs& a, const int wg, Mi
     bool halves = false, dealt = false, units = false;
     const int32_t* blist = a.blocks;   // Algorithm 1's order unless the two classes are dealt (below)
     const int blocks = *a.num_blocks, multi = *a.num_multi;
+    if (blocks == 0) return false;     // no expert has rows: below, a run of the whole launch would have length 0
     const int total = blocks * a.n_tiles_n;
     int split_from = total;            // first position (in two-block tiles) of a split last round
     {

@@ -52,3 +52,27 @@ def test_every_row_in_runs_with_multi_block_experts(packed, dn, ib):
         # bf16 results of fp32 sums, y_perm through a bf16 h: the bound that the parity tests state
         assert float((h[rows].double() - rh).abs().max()) <= 1e-2 * float(rh.abs().max()), f"h of expert {e}"
         assert float((y[rows].double() - ry).abs().max()) <= 1e-2 * float(ry.abs().max()), f"y_perm of expert {e}"
+
+
+@pytest.mark.parametrize("packed", [True, False])
+def test_no_rows_at_all(packed):
+    """Buffers sized for rows of which none came: nothing is written."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_23911_amd as moe
+    moe.lib()
+    dev, E, R, d, F = "cuda:0", 8, 96, 512, 640
+    print(f"[no rows] packed={packed}", flush=True)
+    w = [torch.ones(s, dtype=torch.bfloat16, device=dev) for s in ((E, F, d), (E, F, d), (E, d, F))]
+    cfg = moe.MoEConfig.of(R, d, F, E, 1)
+    p = None
+    if packed:
+        p = torch.empty(moe.packed_weights_size(cfg), dtype=torch.uint8, device=dev)
+        moe.moe_pack_weights(cfg, *w, p)
+    h = torch.full((R, F), 7.0, dtype=torch.bfloat16, device=dev)
+    y = torch.full((R, d), 7.0, dtype=torch.bfloat16, device=dev)
+    ws = torch.empty(moe.ffn_workspace_size(cfg), dtype=torch.uint8, device=dev)
+    moe.moe_grouped_ffn(cfg, torch.ones((R, d), dtype=torch.bfloat16, device=dev), torch.zeros(E + 1, dtype=torch.int32, device=dev),
+                        *((None, None, None) if packed else w), h, y, ws, W_packed=p)
+    torch.cuda.synchronize()
+    assert bool((h == 7.0).all()) and bool((y == 7.0).all())

@@ -128,3 +128,11 @@ def test_row_major_down_projection_in_eighths(L, ib, N, counts):  # noqa: F811
     work = B.map_launch(False, ib, False, N, 256, offsets, blocks, packed=False)
     _check_cover(work, offsets, counts, N, 256, (ib, N))
     assert not _in_runs(work, len(work))
+
+
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("gateup,ib,wnt", [(True, 1, True), (True, 1, False), (False, 1, True), (False, 1, False), (False, 2, True), (False, 2, False)])
+def test_no_rows_at_all(L, gateup, ib, wnt, packed):  # noqa: F811
+    """A launch sized for rows of which none came (a rank none of whose experts was chosen): no workgroup has work, nothing is divided by zero."""
+    work = B.map_launch(gateup, ib, wnt, 512, 256, np.zeros(9, dtype=np.int32), np.zeros((0, 2), dtype=np.int32), packed=packed, slack_blocks=8)
+    assert len(work) and not work[:, 0].any()
