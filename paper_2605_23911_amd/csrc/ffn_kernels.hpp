@@ -1442,7 +1442,8 @@ inline long long mixed_launch_shape(GemmArgs& args, int max_blocks, int cus) {
     //   Down: 128 experts 354 / 333, 256 experts 2048 tokens 1499 / 1428, Qwen2-MoE shape 512 tokens 234 / 216.
     // The k loops of such workgroups walk in step, which is where they share most (gate+up of 128 experts of 4096 x 1536, 2048 tokens, one
     // step apart 599 / in step 534; down projection of 256 experts, 2048 tokens 1487 / 1409; Qwen2-MoE shape 512 tokens two apart 222 /
-    // 218).  Two apart on long loops over streamed weights (down projection of 16 experts, 6400 -> 4096, 1000 tokens 171 / 177 in step).
+    // 218).  Two apart on loops over streamed weights beyond K = 4096, where either is within 3 % (us, two apart / in step: 6144 467 / 473; 6400 144 / 142; 8192
+    // 178 / 172; 11264 129 / 125; 14336, 700 tokens 218 / 222); at 4096 two apart is 102 / 90.
     // Row-major weights, whose rows would all be read from one L2 channel in step (down projection of 256 experts, 512 tokens 1233 / 1388): one apart in gate+up, two
     // apart in the down projection, and there one contiguous eighth of the launch per XCD where every expert is one block, so that it runs through neighbouring rows.
     // Down projection, us, plain two apart / runs one apart / runs two apart / eighths: Mixtral-8x22B shape, 60 tokens 275 / 290 / 278 / 278, 300 tokens 325 / 346 / 312 /
