@@ -626,7 +626,7 @@ __device__ __forceinline__ void tile_body_dma(const GemmArgs& a, const Tile& t, 
     // (d = 4096, F = 14336, ...), so they sit in the same L2 channel; workgroups that run together on
     // an XCD (ids 8 apart) start two steps apart and so spread over the channels.  The sum over k
     // does not care about the order.  Steps past the last are re-reads of it (harmless).
-    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)t.rot_mul) % (unsigned)KT);
+    const int rot = __builtin_amdgcn_readfirstlane((int)(((blockIdx.x >> 3) * (unsigned)t.rot_mul) % (unsigned)KT));
     auto phys = [&](int i) {
         int p = (i < KT ? i : KT - 1) + rot;
         return p >= KT ? p - KT : p;
@@ -847,7 +847,7 @@ __device__ __forceinline__ void rows_body(const GemmArgs& a, const Tile& t, int 
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
         });
     });
-    const int rot = (int)(((blockIdx.x >> 3) * (unsigned)t.rot_mul) % (unsigned)KT);   // see tile_body_dma
+    const int rot = __builtin_amdgcn_readfirstlane((int)(((blockIdx.x >> 3) * (unsigned)t.rot_mul) % (unsigned)KT));   // see tile_body_dma
     auto phys = [&](int i) {
         int p = (i < KT ? i : KT - 1) + rot;
         return p >= KT ? p - KT : p;
